@@ -35,6 +35,11 @@ static int pick_score_chunk(size_t units, int t_max, bool paged) {
   // stripe of the pool, and short chunks keep their workgroups close together in time
   int chunk = paged ? 1024 : kScoreChunk;
   while (chunk > 1024 && units * (size_t)div_up(t_max, chunk) < 2048) chunk /= 2;
+  // a launch that would leave compute units without any workgroup is cut further, down to one 32-key block per
+  // wave: 8 fp32 units of 4096 positions 86.7 us per step with 1024 keys (32 workgroups), 69.2 with 512, 59.9
+  // with 256, 55.0 with 128; 4 bf16 units of 10126 positions 70.5 / 63.5 / 60.2 / 60.2.  From one workgroup per
+  // CU on shorter chunks lose again (8 units of 32768 positions: 96.5 with 1024, 98.0 with 512, 109 with 256)
+  while (chunk > kMinScoreChunk && units * (size_t)div_up(t_max, chunk) < 256) chunk /= 2;
   return chunk;
 }
 
@@ -60,7 +65,7 @@ WsLayout ws_layout(const ams_params* p) {
   w.kbar = o;       o += align256(units * nc_cap * (size_t)p->head_dim * sizeof(double));
   w.park = o;       o += align256(park_score_ws_bytes(w.n_pad));
   w.n_chunks4k = div_up(p->t_max, kChunk);
-  w.vc_part = o;    o += align256(units * (size_t)div_up(p->t_max, 128) * 2 * sizeof(double));  // finest producer: 256 positions per entry
+  w.vc_part = o;    o += align256(units * (size_t)div_up(p->t_max, kMinScoreChunk) * 2 * sizeof(double));  // finest producer: kMinScoreChunk positions per entry
   w.mpart = o;      o += align256(units * w.n_chunks4k * sizeof(double));
   w.cpre = o;       o += align256(units * (size_t)(p->n_segments + 1) * sizeof(double));
   w.n_words = div_up(p->t_max, 32);

@@ -56,6 +56,7 @@ __device__ __forceinline__ int seq_len(const Dims& d, const int32_t* seq_lens, i
 #define AMS_SCORE_CHUNK 4096
 #endif
 constexpr int kScoreChunk = AMS_SCORE_CHUNK;  // most tokens per workgroup of the scoring kernels
+constexpr int kMinScoreChunk = 128;           // fewest: one 32-key block per wave
 constexpr int kChunk = 4096;       // positions per workgroup of the mass / prefix kernels
 
 // Segments the thresholds k*delta (every k >= 1 with k*delta < 1) cut the unit interval into.

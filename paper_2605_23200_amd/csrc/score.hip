@@ -20,7 +20,7 @@ namespace ams {
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// Both sweeps walk a chunk of tokens (256 .. kScoreChunk, chosen on the host so that short caches
+// Both sweeps walk a chunk of tokens (kMinScoreChunk .. kScoreChunk, chosen on the host so that short caches
 // still give the chip enough workgroups) in 32-token blocks per wave.  The keys of the next block are
 // requested before the current block is multiplied (two register buffers, used alternately), and
 // the query columns are processed in groups of kGroup<NB> blocks of 32 so that only that many
