@@ -100,13 +100,14 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS) ? AMS_SCORE
   const int T = TAIL ? T_all : t_end;
   const int c0 = TAIL ? t_end : chunk * a.chunk;
   if (c0 >= T) return;
+  const int t_lim = TAIL ? T : min(T, c0 + a.chunk);  // the tail (at most W + 31 keys) may be longer than a chunk
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5;
   const int t_vis0 = T_all - a.d.W;  // newest key visible to the oldest query of the window
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
   __shared__ int32_t blk_sm[kScoreChunk / 16];
   const int32_t* blk = nullptr;  // paged caches: this chunk's block numbers, staged once
   if (a.k.layout == AMS_LAYOUT_PAGED) {
-    stage_blocks(a, b, c0, min(T, c0 + a.chunk), blk_sm);
+    stage_blocks(a, b, c0, t_lim, blk_sm);
     blk = blk_sm;
   }
   if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
@@ -222,7 +223,6 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS) ? AMS_SCORE
       block_of(av, t0, std::false_type{});
   };
   // this wave's blocks: every fourth block of 32 tokens up to the end of the chunk (or of the cache)
-  const int t_lim = min(T, c0 + a.chunk);
 #pragma unroll 1
   for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 256) {
     if (t0 + 128 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 128, T, lane, av1, blk, c0);
@@ -350,13 +350,14 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
   const int T = TAIL ? T_all : t_end;
   const int c0 = TAIL ? t_end : chunk * a.chunk;
   if (c0 >= T) return;
+  const int t_lim = TAIL ? T : min(T, c0 + a.chunk);  // the tail (at most W + 31 keys) may be longer than a chunk
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5, c = lane & 31;
   const int t_vis0 = T_all - a.d.W;  // newest key visible to the oldest query of the window
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
   __shared__ int32_t blk_sm[kScoreChunk / 16];
   const int32_t* blk = nullptr;  // paged caches: this chunk's block numbers, staged once
   if (a.k.layout == AMS_LAYOUT_PAGED) {
-    stage_blocks(a, b, c0, min(T, c0 + a.chunk), blk_sm);
+    stage_blocks(a, b, c0, t_lim, blk_sm);
     blk = blk_sm;
   }
   if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
@@ -450,7 +451,6 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
     }
   };
   // this wave's blocks: every fourth block of 32 tokens up to the end of the chunk (or of the cache)
-  const int t_lim = min(T, c0 + a.chunk);
 #pragma unroll 1
   for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 256) {
     if (t0 + 128 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 128, T, lane, av1, blk, c0);
