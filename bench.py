@@ -56,8 +56,8 @@ def kernel_bytes(label, w, lens=None):
         "keysum": tok * D * e,                            # K stream (mean key)
         "keydiff": tok * D * e + 4 * tok,                 # K stream + g
         "mass_ema": 4 * tok * 4,                          # u, credit in; credit, m_used out
-        "unit_mass": 4 * tok * 4,                         # the same, with the scan and the quotas in the same launch
-        "segment_scan": 4 * tok,                          # m_used in
+        "vc_sums": 4 * tok * 2,                           # u, credit in (pooled usage out, where it is pooled)
+        "unit_cuts": 0,                                   # the sums of 64 positions, and those that hold a cut
         "quota": 0,
         "select": 4 * tok + 4 * kept,                     # g in, idx out
         "compact": 4 * kept * D * e + 4 * kept * 3,       # K,V rows in + out, idx, credit gather

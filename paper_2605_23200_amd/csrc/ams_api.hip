@@ -66,6 +66,7 @@ WsLayout ws_layout(const ams_params* p) {
   w.park = o;       o += align256(park_score_ws_bytes(w.n_pad));
   w.n_chunks4k = div_up(p->t_max, kChunk);
   w.vc_part = o;    o += align256(units * (size_t)div_up(p->t_max, kMinScoreChunk) * 2 * sizeof(double));  // finest producer: kMinScoreChunk positions per entry
+  w.sub = o;        o += align256(units * (size_t)div_up(p->t_max, 64) * 2 * sizeof(double));
   w.mpart = o;      o += align256(units * w.n_chunks4k * sizeof(double));
   w.cpre = o;       o += align256(units * (size_t)(p->n_segments + 1) * sizeof(double));
   w.n_words = div_up(p->t_max, 32);
@@ -277,7 +278,7 @@ int ams_ema_update(const ams_params* p, const int32_t* seq_lens, const float* u,
   if (!seq_lens || !u || !credit || !m_used || !ws) return AMS_ERR_INVALID_ARG;
   const WsLayout wl = ws_layout(p);
   if (ws_bytes < wl.total) return AMS_ERR_WORKSPACE_TOO_SMALL;
-  return hip_status(launch_ema(p, make_dims(p), seq_lens, u, credit, m_used, VcInfo{false, 0, 0}, (char*)ws, wl,
+  return hip_status(launch_ema(p, make_dims(p), seq_lens, u, credit, m_used, (char*)ws, wl,
                                (hipStream_t)stream), (hipStream_t)stream);
 }
 
@@ -300,15 +301,15 @@ int ams_mass_segment_static(const ams_params* p, const int32_t* seq_lens, const 
   // the chunk totals and the prefix values at the cuts live in the library's own array
   WsLayout wl = ws_layout(p);
   const size_t units = (size_t)p->n_layers * p->batch * p->n_kv_heads;
-  wl.vc_part = 0;  // not touched by the segmentation kernels
+  wl.vc_part = wl.sub = 0;  // not touched by its kernels
   wl.mpart = 0;
   wl.cpre = align256(units * (size_t)wl.n_chunks4k * sizeof(double));
   const size_t need = wl.cpre + align256(units * (size_t)(p->n_segments + 1) * sizeof(double));
   if (need > kStaticScratchBytes) return AMS_ERR_UNSUPPORTED;
   char* scratch_ptr = nullptr;
   if (static_scratch(&scratch_ptr) != hipSuccess) return AMS_ERR_HIP;
-  return hip_status(launch_segment(p, make_dims(p), seq_lens, m_used, bounds, seg_mass, scratch_ptr, wl,
-                                   (hipStream_t)stream), (hipStream_t)stream);
+  return hip_status(launch_segment_static(p, make_dims(p), seq_lens, m_used, bounds, seg_mass, scratch_ptr, wl,
+                                          (hipStream_t)stream), (hipStream_t)stream);
 }
 
 int ams_select(const ams_params* p, const int32_t* seq_lens, const float* g, const int32_t* bounds,

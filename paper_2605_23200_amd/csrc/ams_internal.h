@@ -70,7 +70,7 @@ inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // Workspace carving (offsets in bytes, 256-byte aligned).
 struct WsLayout {
-  size_t part_stats, fin_stats, u, g, m_used, bounds, seg_mass, quota, kbar, park, vc_part, mpart, cpre, flags, csum, total;
+  size_t part_stats, fin_stats, u, g, m_used, bounds, seg_mass, quota, kbar, park, vc_part, sub, mpart, cpre, flags, csum, total;
   int n_chunks, n_pad;
   int score_chunk;  // tokens per workgroup of the scoring kernels for these parameters, dense cache
   int score_chunk_paged, n_chunks_paged;  // the same for a paged cache
@@ -119,14 +119,16 @@ struct ScoreArgs;
 hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, hipStream_t s, bool* ran);
 constexpr int kUnitScorerMinUnits = 128;  // fewer units leave most of the 256 CUs idle: the sweeps win there
 
-// The chunked kernels behind ams_ema_update and ams_mass_segment (the fused step uses launch_unit_mass).
+// ams_ema_update, ams_mass_segment, ams_mass_segment_static (the fused step uses launch_unit_mass).
 hipError_t launch_ema(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* u,
-                      float* credit, float* m_used, const VcInfo& vc, char* ws, const WsLayout& wl,
-                      hipStream_t s);
+                      float* credit, float* m_used, char* ws, const WsLayout& wl, hipStream_t s);
 hipError_t launch_segment(const ams_params* p, const Dims& d, const int32_t* seq_lens,
                           const float* m_used, int32_t* bounds, float* seg_mass, char* ws, const WsLayout& wl,
                           hipStream_t s);
-// The fused step's mass / EMA / segmentation / quota stages in one launch (one workgroup per unit); it also
+hipError_t launch_segment_static(const ams_params* p, const Dims& d, const int32_t* seq_lens,
+                                 const float* m_used, int32_t* bounds, float* seg_mass, char* scratch,
+                                 const WsLayout& wl, hipStream_t s);
+// The fused step's mass / EMA / segmentation / quota stages; it also
 // leaves the -1 tail of idx, the kept counts and the cleared bitmap, so launch_select follows with
 // quota_done = true.  vc: the chunk sums the scorer left, if any.
 hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* u,

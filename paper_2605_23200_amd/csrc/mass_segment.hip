@@ -2,28 +2,32 @@
 // points (Sec. 3.3 "Mass-based adaptive segmentation"; Alg. 1 step 3): thresholds k/S for exactly S
 // segments, or k*Delta followed by the split / merge pass over the segment lengths.
 //
-// Two forms.  The stage calls (ams_ema_update, ams_mass_segment) cut every unit into chunks of 4096
-// positions and make each (chunk, unit) one workgroup:
+// Positions are independent until the prefix sum, so the work is cut over the whole chip first and gathered per unit
+// afterwards:
 //
-//   vc_sums_kernel       partial sums of max(u,0)+eps and of the old credit per chunk
-//   mass_ema_kernel      m = v/Z, c <- lambda c + (1-lambda) m, m_used
+//   vc_sums_kernel       partial sums of max(u,0)+eps and of the old credit (only where the scorer
+//                        has not left them: stage call, causal window, pooled usage); pools the usage on the way
+//   mass_kernel          m = v/Z, c <- lambda c + (1-lambda) m, m_used, and the sum of m_used per 64 positions
+//   sub_totals_kernel    those sums of a given m_used (stage call)
+//   unit_cuts_kernel     one workgroup per unit: prefix over the sums of 64, the 64 positions that hold each cut, the
+//                        split / merge pass, the segment masses and (fused step) the quotas
+//
+// ams_mass_segment_static has no room for the sums of 64 and keeps a form that needs only one total per 4096 positions:
+//
 //   chunk_total_kernel   chunk totals of a given m_used
 //   segment_scan_kernel  inclusive prefix P(j) and the first j with P(j) >= k/S for every k
 //   segment_finalize_kernel  segment masses from the prefix at the cuts
 //   resegment_kernel     (Delta mode) split above L_max / merge below L_min, one pass from the left
 //   segment_mass_kernel  (Delta mode) segment masses by summing m_used over the final segments
 //
-// The fused step runs all of it, and the quotas, in one workgroup per unit (unit_mass_kernel below).
-//
 // Normalisers: Z is the actual sum of max(u,0)+eps.  The credit normaliser sum(c_new) is taken as
 // lambda * sum(c_old) + (1 - lambda) and the outer normaliser as 1: both identities hold exactly in
 // real arithmetic (sum(m) = 1) and to ~1e-8 in floating point, far inside the fp32 tolerance, and
 // they remove two dependent sweeps over T.
 //
-// Prefix: P(j) = C[chunk] + p_local(j) with C[c] the sequential sum of the chunk totals before c and
-// p_local the in-chunk scan; a chunk total IS p_local of the chunk's last position, so
-// P(last of chunk c-1) == C[c] bit for bit and the chain of "first position that reaches k/S"
-// tests is consistent across chunks.  Everything that feeds a comparison is double.
+// Prefix: P(j) = C + p_local(j), C the prefix in front of the piece (64 positions, or a chunk) that holds j and p_local
+// the scan inside it; the total of a piece IS p_local of its last position, so the "first position that reaches k/S"
+// tests agree across pieces.  Everything that feeds a comparison is double.
 #include <type_traits>
 
 #include "ams_internal.h"
@@ -84,23 +88,6 @@ __device__ __forceinline__ void chunk_scan(const float (&x)[kPer], double (&p)[k
 // Sum of p[0..n) in index order (bit-reproducible), same value in every thread of the workgroup.
 // One wave fetches 64 entries at a time in parallel and adds them up through lane broadcasts, so
 // the cost is one memory latency per 64 entries instead of one per entry.
-__device__ __forceinline__ double2 ordered_sum2(const double2* p, int n, double2* sm) {
-  if (threadIdx.x < 64) {
-    double2 acc = make_double2(0.0, 0.0);
-    for (int base = 0; base < n; base += 64) {
-      const int k = min(64, n - base);
-      double2 v = make_double2(0.0, 0.0);
-      if ((int)threadIdx.x < k) v = p[base + threadIdx.x];
-      for (int j = 0; j < k; ++j) {
-        acc.x += __shfl(v.x, j);
-        acc.y += __shfl(v.y, j);
-      }
-    }
-    if (threadIdx.x == 0) *sm = acc;
-  }
-  __syncthreads();
-  return *sm;
-}
 __device__ __forceinline__ double ordered_sum(const double* p, int n, double2* sm) {
   if (threadIdx.x < 64) {
     double acc = 0.0;
@@ -154,6 +141,8 @@ struct MsArgs {
   int pool_r;        // radius of the average pooling of u before Eq. (1) (0 = off)
   double2* vc_part;  // [units][vc_stride] (sum of max(u,0)+eps, sum of old credit) per vc_tokens positions
   int vc_stride, vc_tokens;
+  double* sub;       // [units][n_sub] sum of m_used per kSub positions; stage call: pairs (sum, largest prefix inside)
+  int n_sub;
   double* mpart;     // [units][n_chunks]  chunk totals of m_used
   double* cpre;      // [units][S+1]       prefix at the cuts (negative = threshold never reached)
   int32_t* bounds;   // [units][S+1]
@@ -169,104 +158,202 @@ __device__ __forceinline__ void init_cuts(const MsArgs& a, int unit, int T) {
   }
 }
 
-// Usage as Eq. (1) sees it: with pooling (App. A; Alg. 1 step 1 "optionally smooth") the mean of u
-// over the positions t-r .. t+r that exist, rounded to fp32 like a stored intermediate.  The chunk's
-// scores and r more on either side are staged in LDS once; every thread then reads its windows there.
+// Partial sums of max(u,0)+eps and of the old credit per 1024 * ROUNDS positions, for the normalisers.
+// Usage as Eq. (1) sees it: with pooling (App. A; Alg. 1 step 1 "optionally smooth") the mean of u over the positions
+// t-r .. t+r that exist, rounded to fp32 like a stored intermediate and left in pooled_all for mass_kernel.  The chunk's
+// scores and r more on either side are staged in LDS, from which a thread reads what its four positions see, 16 bytes at
+// a time.
+// Bound: the 8 (pooled: 12) bytes it moves per position.
 constexpr int kMaxPoolR = 31;
-__device__ __forceinline__ void pool_run(const float* u, int chunk0, int j0, int T, int r, float* tile,
-                                         float* pooled, float (&x)[kPer]) {
-  const int first = chunk0 - r;  // position of tile[0]
-  for (int e = threadIdx.x; e < kChunk + 2 * r; e += kBlock) {
-    const int t = first + e;
-    tile[e] = (t >= 0 && t < T) ? u[t] : 0.f;
-  }
-  __syncthreads();
-  // consecutive threads take consecutive positions here (no bank conflicts); the runs of kPer
-  // positions each thread owns afterwards are read back from the pooled copy
-  const double inv_full = 1.0 / (double)(2 * r + 1);
-  for (int e = threadIdx.x; e < kChunk; e += kBlock) {
-    const int t = chunk0 + e;
-    if (t < T) {
-      const int lo = max(0, t - r), hi = min(T - 1, t + r);
-      double sum = 0.0;
-      for (int j = lo; j <= hi; ++j) sum += (double)tile[j - first];
-      const int n = hi - lo + 1;
-      pooled[e] = (float)(n == 2 * r + 1 ? sum * inv_full : sum / (double)n);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kPer; ++i)
-    if (j0 + i < T) x[i] = pooled[j0 - chunk0 + i];
-}
-
+template <int ROUNDS, bool POOL>
 __global__ __launch_bounds__(kBlock) void vc_sums_kernel(MsArgs a, const float* u_all, const float* credit_all,
-                                                          float eps_f) {
+                                                          float eps_f, float* pooled_all) {
+  constexpr int kRun = kBlock * 4 * ROUNDS;
   __shared__ double sm[kWaves];
-  __shared__ float tile[kChunk + 2 * kMaxPoolR], pooled[kChunk];
+  __shared__ __align__(16) float tile[POOL ? kRun + 2 * kMaxPoolR + 4 : 1];
   const int unit = blockIdx.y, chunk = blockIdx.x;
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const int j0 = chunk * kChunk + threadIdx.x * kPer;
-  if (chunk * kChunk >= T) return;
+  const int c0 = chunk * kRun;
+  if (c0 >= T) return;
   const float* u = u_all + (int64_t)unit * a.d.t_stride;
   const float* credit = credit_all + (int64_t)unit * a.d.t_stride;
   double v = 0.0, c = 0.0;
-  float ux[kPer], cx[kPer];
-  load_run(u, j0, T, a.vec, ux, 0.f);
-  load_run(credit, j0, T, a.vec, cx, 0.f);
-  if (a.pool_r > 0) pool_run(u, chunk * kChunk, j0, T, a.pool_r, tile, pooled, ux);
+  float cx[ROUNDS][4], ux[ROUNDS][4];
 #pragma unroll
-  for (int i = 0; i < kPer; ++i)
-    if (j0 + i < T) {
-      v += fmax((double)ux[i], 0.0) + (double)eps_f;
-      c += (double)cx[i];
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int j0 = c0 + (r * kBlock + (int)threadIdx.x) * 4;
+    load_run(credit, j0, T, a.vec, cx[r], 0.f);
+    if (!POOL) load_run(u, j0, T, a.vec, ux[r], 0.f);
+  }
+  if (POOL) {
+    const int r = a.pool_r, first = c0 - r;  // first = position of tile[0]
+#pragma unroll 4
+    for (int e = threadIdx.x; e < kRun + 2 * r; e += kBlock) {
+      const int t = first + e;
+      tile[e] = (t >= 0 && t < T) ? u[t] : 0.f;
+    }
+    __syncthreads();
+    float* out = pooled_all + (int64_t)unit * a.d.t_stride;
+    const double inv_full = 1.0 / (double)(2 * r + 1);
+#pragma unroll
+    for (int rd = 0; rd < ROUNDS; ++rd) {  // four positions per thread from one walk over the scores they see
+      const int e = (rd * kBlock + (int)threadIdx.x) * 4;
+      double sum[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int q = 0; q < 2 * r + 4; q += 4) {
+        const float4 x4 = *reinterpret_cast<const float4*>(&tile[e + q]);  // positions that do not exist hold zeros
+        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (q + j >= i && q + j <= i + 2 * r) sum[i] += (double)x[j];
+      }
+      float pooled[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int t = c0 + e + i;
+        const int n = min(T - 1, t + r) - max(0, t - r) + 1;
+        pooled[i] = (float)(n == 2 * r + 1 ? sum[i] * inv_full : sum[i] / (double)n);
+        if (t < T) v += fmax((double)pooled[i], 0.0) + (double)eps_f;
+      }
+      store_run(out, c0 + e, T, a.vec, pooled);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      c += (double)cx[r][i];
+      if (!POOL && c0 + (r * kBlock + (int)threadIdx.x) * 4 + i < T) v += fmax((double)ux[r][i], 0.0) + (double)eps_f;
     }
   v = block_sum(v, sm);
   c = block_sum(c, sm);
   if (threadIdx.x == 0) a.vc_part[(int64_t)unit * a.vc_stride + chunk] = make_double2(v, c);
 }
 
-__global__ __launch_bounds__(kBlock) void mass_ema_kernel(MsArgs a, const float* u_all, float* credit_all,
-                                                           float* m_used_all, float lambda, float beta,
-                                                           float eps_f) {
-  __shared__ float tile[kChunk + 2 * kMaxPoolR], pooled[kChunk];
-  const int unit = blockIdx.y, chunk = blockIdx.x;
+// ---- pieces of kSub positions: 16 lanes (one DPP row) with four consecutive positions each ----
+constexpr int kSub = 64;
+constexpr int kSubLanes = kSub / 4;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {  // lanes without a source read 0
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Inclusive prefix of the piece at this lane's four positions; lane 15's last entry is the piece's total.
+__device__ __forceinline__ void sub_scan(const float (&x)[4], double (&p)[4]) {
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s += (double)x[i];
+  double incl = s;  // row_shr: 1, 2, 4, 8
+  incl += dpp_f64<0x111>(incl);
+  incl += dpp_f64<0x112>(incl);
+  incl += dpp_f64<0x114>(incl);
+  incl += dpp_f64<0x118>(incl);
+  double run = dpp_f64<0x111>(incl);  // prefix in front of this lane
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    run += (double)x[i];
+    p[i] = run;
+  }
+}
+
+// Eq. (1) and the EMA, position by position.  Bound: the 16 bytes per position it moves: 134 MB in 27 us (5.0 TB/s) for
+// 256 units of 32768 positions, 235 MB in 46 us for 112 of 131072.  One workgroup per unit that also carried the prefix
+// (scan, barrier and the next loads in turn) took 45 and 114 us, and 30 us for 8 units of 32768, where this takes 5 + 7
+// with unit_cuts_kernel.  A workgroup takes ROUNDS runs of 1024 positions, all of their loads in flight before the normalisers are
+// known; every wave adds up the unit's partial sums for itself, so no barrier stands between the loads and the stores.
+template <int ROUNDS, bool TOTALS>
+__global__ __launch_bounds__(kBlock) void mass_kernel(MsArgs a, const float* u_all, float* credit_all, float* m_used_all,
+                                                      float lambda, float beta, float eps_f) {
+  const int unit = blockIdx.y;
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  if (chunk * kChunk >= T) return;
-  __shared__ double2 sums;
+  const int first = blockIdx.x * ROUNDS * kBlock * 4;
+  if (first >= T) return;
   const float* u = u_all + (int64_t)unit * a.d.t_stride;
   float* credit = credit_all + (int64_t)unit * a.d.t_stride;
   float* m_used = m_used_all + (int64_t)unit * a.d.t_stride;
-  const int j0 = chunk * kChunk + threadIdx.x * kPer;
-  float mu[kPer], ux[kPer], cx[kPer];
-  load_run(u, j0, T, a.vec, ux, 0.f);  // in flight while the normalisers are summed
-  load_run(credit, j0, T, a.vec, cx, 0.f);
-  if (a.pool_r > 0) pool_run(u, chunk * kChunk, j0, T, a.pool_r, tile, pooled, ux);
+  const int lane = threadIdx.x & 63;
+  float ux[ROUNDS][4], cx[ROUNDS][4];
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int j0 = first + (r * kBlock + (int)threadIdx.x) * 4;
+    load_run(u, j0, T, a.vec, ux[r], 0.f);
+    load_run(credit, j0, T, a.vec, cx[r], 0.f);
+  }
+  // partial sums of max(u,0)+eps and of the old credit: strided over the lanes, then a fixed tree
   const int nvc = (T + a.vc_tokens - 1) / a.vc_tokens;
-  const double2 zc = ordered_sum2(a.vc_part + (int64_t)unit * a.vc_stride, nvc, &sums);
-  const double Z = zc.x, c_old = zc.y;
+  const double2* vc = a.vc_part + (int64_t)unit * a.vc_stride;
+  double Z = 0.0, c_old = 0.0;
+  for (int i = lane; i < nvc; i += 64) {
+    const double2 p = vc[i];
+    Z += p.x;
+    c_old += p.y;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    Z += __shfl_xor(Z, o);
+    c_old += __shfl_xor(c_old, o);
+  }
   const double lam = (double)lambda, bet = (double)beta, eps = (double)eps_f;
   const double inv_z = 1.0 / Z, inv_csum = 1.0 / (lam * c_old + (1.0 - lam));
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    mu[i] = 0.f;
-    if (j0 + i < T) {
-      const float mc = (float)((fmax((double)ux[i], 0.0) + eps) * inv_z);
-      float cn = mc;
-      mu[i] = mc;  // lambda == 0: credit not used, the mass passes through unchanged
-      if (lambda != 0.f) {
-        cn = (float)(lam * (double)cx[i] + (1.0 - lam) * (double)mc);
-        mu[i] = (float)(bet * (double)mc + (1.0 - bet) * ((double)cn * inv_csum));
+  for (int r = 0; r < ROUNDS; ++r) {
+    const int j0 = first + (r * kBlock + (int)threadIdx.x) * 4;
+    float mu[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      mu[i] = 0.f;
+      if (j0 + i < T) {
+        const float mc = (float)((fmax((double)ux[r][i], 0.0) + eps) * inv_z);
+        float cn = mc;
+        mu[i] = mc;  // lambda == 0: credit not used, the mass passes through unchanged
+        if (lambda != 0.f) {
+          cn = (float)(lam * (double)cx[r][i] + (1.0 - lam) * (double)mc);
+          mu[i] = (float)(bet * (double)mc + (1.0 - bet) * ((double)cn * inv_csum));
+        }
+        cx[r][i] = cn;
       }
-      cx[i] = cn;
+    }
+    store_run(credit, j0, T, a.vec, cx[r]);
+    store_run(m_used, j0, T, a.vec, mu);
+    if (TOTALS) {
+      double p[4];
+      sub_scan(mu, p);
+      if ((lane & (kSubLanes - 1)) == kSubLanes - 1 && j0 - (kSub - 4) < T)
+        a.sub[(int64_t)unit * a.n_sub + j0 / kSub] = p[3];
     }
   }
-  store_run(credit, j0, T, a.vec, cx);
-  store_run(m_used, j0, T, a.vec, mu);
+}
+
+// The sums of 64 positions of a given m_used, each with the largest prefix inside the piece: a caller's values need not
+// be positive, and a threshold may then be reached inside a piece whose end lies below it again.
+__global__ __launch_bounds__(kBlock) void sub_totals_kernel(MsArgs a, const float* m_all) {
+  const int unit = blockIdx.y;
+  int l, b, h;
+  unit_coords(a.d, unit, l, b, h);
+  const int T = seq_len(a.d, a.seq_lens, b);
+  const int j0 = (blockIdx.x * kBlock + (int)threadIdx.x) * 4;
+  if (blockIdx.x * kBlock * 4 >= T) return;
+  float x[4];
+  load_run(m_all + (int64_t)unit * a.d.t_stride, j0, T, a.vec, x, 0.f);
+  double p[4];
+  sub_scan(x, p);
+  double top = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (j0 + i < T) top = fmax(top, p[i]);
+#pragma unroll
+  for (int o = kSubLanes / 2; o >= 1; o >>= 1) top = fmax(top, __shfl_xor(top, o));
+  if ((threadIdx.x & (kSubLanes - 1)) == kSubLanes - 1 && j0 - (kSub - 4) < T)
+    ((double2*)a.sub)[(int64_t)unit * a.n_sub + j0 / kSub] = make_double2(p[3], top);
 }
 
 __global__ __launch_bounds__(kBlock) void chunk_total_kernel(MsArgs a, const float* m_all) {
@@ -365,9 +452,11 @@ __global__ void segment_finalize_kernel(MsArgs a, float* seg_mass_all) {
 // A segment longer than l_max becomes ceil(L / l_max) parts whose lengths differ by at most one, the longer ones
 // first; one shorter than l_min joins the segment to its left, the very first one stays open so that the next
 // initial segment starts where it started; empty initial segments vanish.  Writes the ends of the final segments
-// to out[0 .. n) (at most cap of them) and returns n.  A serial chain of at most K steps: one thread runs it.
+// to out[0 .. n) (at most cap of them) and returns n.  A serial chain of at most K steps that the whole first wave
+// walks together, its lanes writing the parts of a split side by side (10 us by one lane for 10 -> 133 segments).
 template <typename Cut>
 __device__ __forceinline__ int split_merge_pass(Cut cut, int K, int T, int l_min, int l_max, int cap, int32_t* out) {
+  const int lane = threadIdx.x;
   int n = 0, start = 0;
   bool have_left = false;
   for (int i = 1; i <= K; ++i) {
@@ -375,27 +464,31 @@ __device__ __forceinline__ int split_merge_pass(Cut cut, int K, int T, int l_min
     const int L = e - start;
     if (L == 0) continue;
     if (l_max > 0 && L > l_max) {
-      const int parts = (L + l_max - 1) / l_max, base = L / parts, extra = L % parts;
-      int pos = start;
-      for (int j = 0; j < parts && n < cap; ++j) {
-        pos += base + (j < extra ? 1 : 0);
-        out[n++] = pos;
-      }
+      const int parts = (L + l_max - 1) / l_max, base = L / parts, extra = L - base * parts;
+      const int fit = min(parts, cap - n);
+      for (int j = lane; j < fit; j += 64) out[n + j] = start + (j + 1) * base + min(j + 1, extra);
+      n += fit;
       have_left = true;
       start = e;
     } else if (l_min > 0 && L < l_min) {
       if (have_left) {
-        out[n - 1] = e;
+        if (lane == 0) out[n - 1] = e;
         start = e;
       }
     } else {
-      if (n < cap) out[n++] = e;
+      if (n < cap) {
+        if (lane == 0) out[n] = e;
+        ++n;
+      }
       have_left = true;
       start = e;
     }
   }
-  if (start < T && n < cap) out[n++] = T;  // the whole sequence was one too-short segment
-  if (n > 0) out[n - 1] = T;               // (only matters if the capacity cut the list short)
+  if (start < T && n < cap) {  // the whole sequence was one too-short segment
+    if (lane == 0) out[n] = T;
+    ++n;
+  }
+  if (n > 0 && lane == 0) out[n - 1] = T;  // (only matters if the capacity cut the list short)
   return n;
 }
 
@@ -403,23 +496,17 @@ __device__ __forceinline__ int split_merge_pass(Cut cut, int K, int T, int l_min
 // the loop over segments).  Longer than l_max: ceil(L / l_max) parts whose lengths differ by at most
 // one, the longer ones first.  Shorter than l_min: joins the segment to its left; the first one
 // stays open and the next initial segment starts where it started.  Empty initial segments vanish.
-// The pass is a short serial chain (at most K steps) and runs on one lane per unit; the new bounds
-// are staged in LDS because they overwrite the old ones.
+// The new bounds are staged in LDS because they overwrite the old ones.
 __global__ __launch_bounds__(64) void resegment_kernel(MsArgs a) {
   __shared__ int32_t out[kMaxSegments + 1];
-  __shared__ int n_out;
   const int unit = blockIdx.x;
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
   int32_t* bounds = a.bounds + (int64_t)unit * (a.S + 1);
-  if (threadIdx.x == 0) {
-    const int K = a.K;
-    const int n = split_merge_pass([&](int i) { return i == K ? T : bounds[i]; }, K, T, a.l_min, a.l_max, a.S, out);
-    n_out = n;
-  }
+  const int K = a.K;
+  const int n = split_merge_pass([&](int i) { return i == K ? T : bounds[i]; }, K, T, a.l_min, a.l_max, a.S, out);
   __syncthreads();
-  const int n = n_out;
   for (int i = threadIdx.x; i < a.S; i += 64) bounds[i + 1] = i < n ? out[i] : T;
 }
 
@@ -437,312 +524,238 @@ __global__ __launch_bounds__(64) void segment_mass_kernel(MsArgs a, const float*
   if (threadIdx.x == 0) seg_mass_all[(int64_t)unit * a.S + seg] = (float)s;
 }
 
-// Eq. (1), the EMA, the prefix sum with its cuts, the segment masses and the quotas of one unit in ONE
-// workgroup of 1024 threads.  The unit is walked in groups of 1024*PER positions; inside a group thread
-// i owns the PER consecutive positions from i*PER on, so the running prefix is a serial sum per thread,
-// a scan over the lanes, an ordered sum over the 16 waves and the total of the groups before -- no
-// chunk totals through memory, no second read of m_used, and the launches of the chunked kernels above
-// become one.  The next group's usage and credit are requested before the current group is worked on.
-// The arithmetic per position, the thresholds, the split / merge pass and the quotas are those of the
-// kernels above.
-//   GENERAL = false: thresholds k/S, at most 64 segments, no pooling (the headline configuration).
-//   GENERAL = true:  also thresholds k*Delta with the split / merge pass, pooled usage, up to 1024
-//                    segments; needs more LDS (the pooling tile, the quota scratch).
-constexpr int kUnitBlock = 1024;
-constexpr int kUnitMaxSeg = 64;
+// The cuts of one unit from the sums of 64 positions, the masses of its segments and its quotas, in one workgroup.
+// The prefix over the sums (512 of them for 32768 positions) goes to LDS; every threshold finds its piece there by
+// bisection, and 16 lanes scan the 64 positions of that piece for the first one that reaches it.  Only those pieces of
+// m_used are read again: latency bounds this kernel, so nothing in it depends on T beyond the prefix, and all thresholds
+// travel at once (BLOCK / 16 per round).  7 us for 8 units of 32768 positions and 16 segments, 9 for 256, 12 for 112 of
+// 131072 with 32 segments; 20 for 256 units with thresholds k*Delta and 133 final segments (42 with the split / merge pass
+// by one lane and the quotas in LDS).
+//   CUTS_STEP     fused step: thresholds k/S, at most 64 segments
+//   CUTS_GENERAL  fused step: also thresholds k*Delta with the split / merge pass, up to 1024 segments
+//   CUTS_STAGE    ams_mass_segment: no quotas, any sign of m_used (the bisection runs over the largest prefix so far)
+enum { CUTS_STEP = 0, CUTS_GENERAL = 1, CUTS_STAGE = 2 };
+constexpr int kStepMaxSeg = 64;
 
-// Pooled usage of the whole unit (see pool_run), group by group: the group's scores and r more on either
-// side are staged in LDS, consecutive threads then pool consecutive positions (no bank conflicts), store the
-// result (rounded to fp32 like a stored intermediate) to out[] and add max(pooled, 0) + eps to v and the
-// position's old credit to c.  The next group's scores are requested before the current group is pooled.
-template <int GROUP>
-__device__ __forceinline__ void pool_unit(const float* u, const float* credit, float* out, int T, int r,
-                                          float* tile, double eps, double& v, double& c) {
-  constexpr int kStage = (GROUP + 2 * kMaxPoolR + kUnitBlock - 1) / kUnitBlock;
-  const int n_groups = (T + GROUP - 1) / GROUP;
-  const double inv_full = 1.0 / (double)(2 * r + 1);
-  float stage[kStage];
-  auto fetch = [&](int g0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < kStage; ++q) {
-      const int e = q * kUnitBlock + (int)threadIdx.x, t = g0 - r + e;
-      stage[q] = (e < GROUP + 2 * r && t >= 0 && t < T) ? u[t] : 0.f;
-    }
-  };
-  fetch(0);
-#pragma unroll 1
-  for (int g = 0; g < n_groups; ++g) {
-    const int g0 = g * GROUP, first = g0 - r;  // first = position of tile[0]
-#pragma unroll
-    for (int q = 0; q < kStage; ++q) {
-      const int e = q * kUnitBlock + (int)threadIdx.x;
-      if (e < GROUP + 2 * r) tile[e] = stage[q];
-    }
-    __syncthreads();
-    if (g + 1 < n_groups) fetch(g0 + GROUP);
-    for (int e = threadIdx.x; e < GROUP; e += kUnitBlock) {
-      const int t = g0 + e;
-      if (t < T) {
-        const float cr = credit[t];
-        const int lo = max(0, t - r), hi = min(T - 1, t + r);
-        double sum = 0.0;
-        for (int j = lo; j <= hi; ++j) sum += (double)tile[j - first];
-        const int n = hi - lo + 1;
-        const float p = (float)(n == 2 * r + 1 ? sum * inv_full : sum / (double)n);
-        out[t] = p;
-        v += fmax((double)p, 0.0) + eps;
-        c += (double)cr;
-      }
-    }
-    __syncthreads();
-  }
-}
+struct CutsOut {
+  float* seg_mass;
+  int32_t *quota, *idx, *n_kept;
+  uint32_t* flags;
+  int n_words, budget, q_min, n_sink, n_last;
+  const int32_t* status;
+};
 
-template <int PER, bool GENERAL>
-__global__ __launch_bounds__(kUnitBlock) void unit_mass_kernel(MsArgs a, const float* u_all, float* credit_all,
-                                                                float* m_used_all, float lambda, float beta,
-                                                                float eps_f, int budget, int q_min,
-                                                                float* seg_mass_all, int32_t* quota_all,
-                                                                int32_t* idx_all, int32_t* n_kept_all, int n_sink,
-                                                                int n_last, uint32_t* flags_all, int n_words,
-                                                                const int32_t* status) {
-  constexpr int kW = kUnitBlock / 64, kGroup = kUnitBlock * PER;
-  constexpr int kCap = GENERAL ? kMaxSegments : kUnitMaxSeg;
-  __shared__ double wave_tot[2][kW];
-  __shared__ double ends[2][kUnitBlock];
-  __shared__ double thr[kCap + 1], cpre[kCap + 1];
+template <int BLOCK, int KIND>
+__global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel(MsArgs a, const float* m_all, CutsOut o) {
+  constexpr int kW = BLOCK / 64, kPerThread = 4, kCapSub = BLOCK * kPerThread, kGroups16 = BLOCK / kSubLanes;
+  constexpr bool kSigned = KIND == CUTS_STAGE;
+  constexpr int kCap = KIND == CUTS_STEP ? kStepMaxSeg : kMaxSegments;
+  __shared__ double ends[kCapSub];                   // prefix at the end of every piece of the group
+  __shared__ double peak[kSigned ? kCapSub : 1];     // largest prefix up to the end of the piece
+  __shared__ double wave_tot[kW], wave_top[kSigned ? kW : 1];
+  __shared__ double cpre[kCap + 1];
   __shared__ int32_t bounds[kCap + 1];
   __shared__ float mass[kCap];
-  __shared__ double2 sums;
-  __shared__ float tile[GENERAL ? kGroup + 2 * kMaxPoolR : 1];
-  __shared__ int32_t reseg[GENERAL ? kCap + 1 : 1];
+  __shared__ int32_t reseg[KIND == CUTS_STEP ? 1 : kCap + 1];
   __shared__ int n_reseg;
-  // Delta mode on caches of up to kEndGroups groups: the prefix at the end of every thread's run, from which
-  // the mass of a segment that the split / merge pass has moved follows without another sum over its positions
-  constexpr int kEndGroups = 4;
-  __shared__ double ends_all[GENERAL ? kEndGroups * kUnitBlock : 1];
-  __shared__ typename std::conditional<GENERAL, QuotaScratch, int>::type qs;
   const int unit = blockIdx.x, S = a.S;
-  const int K = GENERAL ? a.K : S;  // initial segments: thresholds k = 1 .. K-1
-  const bool delta_mode = GENERAL && a.delta > 0.0;
-  const int pool_r = GENERAL ? a.pool_r : 0;
+  const int K = KIND == CUTS_STEP ? S : a.K;  // initial segments: thresholds k = 1 .. K-1
+  const bool delta_mode = KIND != CUTS_STEP && a.delta > 0.0;
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const float* u = u_all + (int64_t)unit * a.d.t_stride;
-  float* credit = credit_all + (int64_t)unit * a.d.t_stride;
-  float* m_used = m_used_all + (int64_t)unit * a.d.t_stride;
-  const int n_groups = (T + kGroup - 1) / kGroup;
-  // with pooling, the pooled usage passes through the m_used row: written while the normalisers are summed,
-  // read back (and overwritten by m_used proper) in the main walk
-  const float* u_src = pool_r > 0 ? m_used : u;
-  float ux[PER], cx[PER];
-  if (pool_r == 0) load_run(u, (int)threadIdx.x * PER, T, a.vec, ux, 0.f);  // in flight while the normalisers are summed
-  load_run(credit, (int)threadIdx.x * PER, T, a.vec, cx, 0.f);
-  for (int k = threadIdx.x; k <= S; k += kUnitBlock) {
+  const float* m_used = m_all + (int64_t)unit * a.d.t_stride;
+  const int n_sub = (T + kSub - 1) / kSub;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = threadIdx.x & (kSubLanes - 1);
+  for (int k = threadIdx.x; k <= S; k += BLOCK) {
     bounds[k] = (k == 0) ? 0 : T;
     cpre[k] = (k == 0) ? 0.0 : -1.0;
   }
-  for (int k = threadIdx.x; k <= K; k += kUnitBlock) thr[k] = delta_mode ? (double)k * a.delta : (double)k / (double)S;
-  const double lam = (double)lambda, bet = (double)beta, eps = (double)eps_f;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double2 zc;
-  if (a.vc_part && pool_r == 0) {  // the scorer left the sums of max(u,0)+eps and of the old credit per chunk
-    const int nvc = (T + a.vc_tokens - 1) / a.vc_tokens;
-    zc = ordered_sum2(a.vc_part + (int64_t)unit * a.vc_stride, nvc, &sums);
-  } else {
-    // no usable sums from the scorer (causal window, pooled usage): one more walk over the unit, every
-    // thread its positions in order, then the lanes and the waves in a fixed order
-    double v = 0.0, c = 0.0;
-    if (pool_r > 0) {
-      if constexpr (GENERAL) {
-        pool_unit<kGroup>(u, credit, m_used, T, pool_r, tile, eps, v, c);
-      }
-    } else {
-      for (int j = threadIdx.x * 4; j < T; j += kUnitBlock * 4) {
-        float ur[4], cr[4];
-        load_run(u, j, T, a.vec, ur, 0.f);
-        load_run(credit, j, T, a.vec, cr, 0.f);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (j + i < T) {
-            v += fmax((double)ur[i], 0.0) + eps;
-            c += (double)cr[i];
-          }
-      }
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      v += __shfl_xor(v, o);
-      c += __shfl_xor(c, o);
-    }
-    if (lane == 0) ends[0][wave] = v, ends[1][wave] = c;
-    __syncthreads();
-    zc = make_double2(0.0, 0.0);
-    for (int w = 0; w < kW; ++w) {
-      zc.x += ends[0][w];
-      zc.y += ends[1][w];
-    }
-    __syncthreads();  // ends is used again below
-  }
-  if (pool_r > 0) load_run(u_src, (int)threadIdx.x * PER, T, a.vec, ux, 0.f);
-  const double Z = zc.x, c_old = zc.y;
-  const double inv_z = 1.0 / Z, inv_csum = 1.0 / (lam * c_old + (1.0 - lam));
-  const double scale = delta_mode ? 1.0 / a.delta : (double)S;
-  double C = 0.0;  // prefix at the end of the groups before
+  double C = 0.0, top = -INFINITY;  // prefix at the end of the groups before, and the largest one so far
 #pragma unroll 1
-  for (int r = 0; r < n_groups; ++r) {
-    const int j0 = r * kGroup + (int)threadIdx.x * PER, par = r & 1;
-    float un[PER], cn_next[PER];
-    if (r + 1 < n_groups) {
-      load_run(u_src, j0 + kGroup, T, a.vec, un, 0.f);
-      load_run(credit, j0 + kGroup, T, a.vec, cn_next, 0.f);
-    }
-    float mu[PER];
+  for (int base = 0; base < n_sub; base += kCapSub) {
+    const int n = min(kCapSub, n_sub - base);
+    double v[kPerThread], t[kPerThread];
+    const int e0 = (int)threadIdx.x * kPerThread;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      mu[i] = 0.f;
-      if (j0 + i < T) {
-        const float mc = (float)((fmax((double)ux[i], 0.0) + eps) * inv_z);
-        float cn = mc;
-        mu[i] = mc;  // lambda == 0: credit not used, the mass passes through unchanged
-        if (lambda != 0.f) {
-          cn = (float)(lam * (double)cx[i] + (1.0 - lam) * (double)mc);
-          mu[i] = (float)(bet * (double)mc + (1.0 - bet) * ((double)cn * inv_csum));
+    for (int i = 0; i < kPerThread; ++i) {
+      v[i] = 0.0;
+      t[i] = -INFINITY;
+      if (e0 + i < n) {
+        const int64_t at = (int64_t)unit * a.n_sub + base + e0 + i;
+        if (kSigned) {
+          const double2 p = ((const double2*)a.sub)[at];
+          v[i] = p.x;
+          t[i] = p.y;
+        } else {
+          v[i] = a.sub[at];
         }
-        cx[i] = cn;
       }
     }
-    store_run(credit, j0, T, a.vec, cx);
-    store_run(m_used, j0, T, a.vec, mu);
-    // inclusive prefix: serial over the thread's run, scan over the lanes, ordered sum over the waves
-    double ts = 0.0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) ts += (double)mu[i];
+    const double ts = ((v[0] + v[1]) + v[2]) + v[3];
     double incl = ts;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const double v = __shfl_up(incl, o);
-      if (lane >= o) incl += v;
+    for (int d = 1; d < 64; d <<= 1) {
+      const double x = __shfl_up(incl, d);
+      if (lane >= d) incl += x;
     }
-    if (lane == 63) wave_tot[par][wave] = incl;
+    if (lane == 63) wave_tot[wave] = incl;
     __syncthreads();
-    double off = C;
-    for (int w = 0; w < wave; ++w) off += wave_tot[par][w];
-    const double start = off + (incl - ts);  // prefix of the position in front of this thread's run
-    double run = start;
+    double run = C;
+    for (int w = 0; w < wave; ++w) run += wave_tot[w];
+    run += incl - ts;
+    double local_top = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) run += (double)mu[i];
-    ends[par][threadIdx.x] = run;
-    if constexpr (GENERAL)
-      if (delta_mode && n_groups <= kEndGroups) ends_all[r * kUnitBlock + threadIdx.x] = run;
+    for (int i = 0; i < kPerThread; ++i) {
+      t[i] += run;  // the piece's prefixes start where the one before it ends
+      local_top = fmax(local_top, t[i]);
+      t[i] = local_top;
+      run += v[i];
+      ends[e0 + i] = run;
+    }
+    if (kSigned) {
+      double it = local_top;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const double x = __shfl_up(it, d);
+        if (lane >= d) it = fmax(it, x);
+      }
+      double before = __shfl_up(it, 1);
+      if (lane == 0) before = -INFINITY;
+      if (lane == 63) wave_top[wave] = it;
+      __syncthreads();
+      before = fmax(before, top);
+      for (int w = 0; w < wave; ++w) before = fmax(before, wave_top[w]);
+#pragma unroll
+      for (int i = 0; i < kPerThread; ++i) peak[e0 + i] = fmax(before, t[i]);
+    }
     __syncthreads();
-    const double prev_end = threadIdx.x > 0 ? ends[par][threadIdx.x - 1] : C;
-    C = ends[par][kUnitBlock - 1];
-    int f_prev = thresholds_reached(prev_end, K, thr, scale);
-    // most threads see no threshold between their neighbour's prefix and their own last one (the masses
-    // are not negative, so the prefix does not fall)
-    if (thresholds_reached(run, K, thr, scale) > f_prev) {
-      // the walk repeats the additions that gave `run`, so its last value IS the published end of this
-      // run: every threshold in (neighbour's end, run] is met by exactly one position of this thread
-      double P = start;
+    const double* reach = kSigned ? peak : ends;  // never falls (up to a NaN, which ends the search)
+    const double C_end = ends[n - 1], reach0 = kSigned ? top : C, reach1 = reach[n - 1];
+    for (int k = 1 + (int)threadIdx.x / kSubLanes; k < K; k += kGroups16) {
+      const double thr = delta_mode ? (double)k * a.delta : (double)k / (double)S;
+      if (!(thr > reach0) || reach1 < thr) continue;  // in an earlier group, or not in this one
+      int lo = 0, hi = n - 1;  // first piece whose end does not lie below the threshold
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (reach[mid] < thr)
+          lo = mid + 1;
+        else
+          hi = mid;
+      }
+      const int j0 = (base + lo) * kSub + l16 * 4;
+      float x[4];
+      load_run(m_used, j0, T, a.vec, x, 0.f);
+      double p[4];
+      sub_scan(x, p);
+      const double before = lo > 0 ? ends[lo - 1] : C;
+      int j = INT32_MAX;  // first position of this lane that reaches the threshold
+      double P = 0.0;
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        P += (double)mu[i];
-        if (j0 + i < T) {
-          const int f_cur = thresholds_reached(P, K, thr, scale);
-          for (int k = f_prev + 1; k <= f_cur; ++k) {  // position j0+i is the first to reach threshold k
-            atomicMin(&bounds[k], j0 + i + 1);
-            cpre[k] = P;
-          }
-          f_prev = max(f_prev, f_cur);
+      for (int i = 3; i >= 0; --i)
+        if (j0 + i < T && before + p[i] >= thr) {
+          j = j0 + i;
+          P = before + p[i];
         }
+      const uint64_t reached = __ballot(j != INT32_MAX) >> (lane & ~(kSubLanes - 1)) & ((1u << kSubLanes) - 1);
+      if (reached) {
+        if (l16 == __ffsll((long long)reached) - 1) {
+          bounds[k] = j + 1;
+          cpre[k] = P;
+        }
+      } else if (l16 == 0 && reach[lo] >= thr) {  // only the rounding of the last addition lies in between
+        bounds[k] = min(T, (base + lo + 1) * kSub);
+        cpre[k] = ends[lo];
       }
     }
-    if (r + 1 < n_groups) {
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        ux[i] = un[i];
-        cx[i] = cn_next[i];
-      }
-    }
+    C = C_end;
+    top = reach1;
+    if (base + kCapSub < n_sub) __syncthreads();  // the next group overwrites what the searches read
   }
   __syncthreads();
   const double total = C;
-  if constexpr (GENERAL) {
-    if (delta_mode) {
-      // the split / merge pass over the initial segments (see resegment_kernel), then the mass of every
-      // final segment summed from the m_used this workgroup has just written
-      if (threadIdx.x == 0) {
-        const int n = split_merge_pass([&](int i) { return i == K ? T : bounds[i]; }, K, T, a.l_min, a.l_max, S, reseg);
-        n_reseg = n;
-      }
-      __syncthreads();
-      const int n = n_reseg;
-      for (int i = threadIdx.x; i < S; i += kUnitBlock) bounds[i + 1] = i < n ? reseg[i] : T;
-      __syncthreads();
-      if (n_groups <= kEndGroups) {
-        // prefix in front of every bound: the end of the run before the one the bound lies in, plus the
-        // positions of that run in front of it (the scan's own order of additions)
-        for (int i = threadIdx.x; i <= S; i += kUnitBlock) {
-          const int bnd = bounds[i];
-          double P = 0.0;
-          if (bnd > 0) {
-            const int q = (bnd - 1) / PER;  // run of the last position in front of the bound
-            if (q > 0) P = ends_all[q - 1];
-            for (int t = q * PER; t < bnd; ++t) P += (double)m_used[t];
-          }
-          cpre[i] = P;
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < S; i += kUnitBlock) mass[i] = (float)(cpre[i + 1] - cpre[i]);
-      } else {
-        for (int sg = wave; sg < S; sg += kW) {
-          const int lo = bounds[sg], hi = bounds[sg + 1];
-          double sm = 0.0;
-          for (int t = lo + lane; t < hi; t += 64) sm += (double)m_used[t];
-#pragma unroll
-          for (int o = 32; o >= 1; o >>= 1) sm += __shfl_xor(sm, o);
-          if (lane == 0) mass[sg] = (float)sm;
-        }
-      }
-      __syncthreads();
+  if (delta_mode) {
+    if (wave == 0) {
+      const int n = split_merge_pass([&](int i) { return i == K ? T : bounds[i]; }, K, T, a.l_min, a.l_max, S, reseg);
+      if (lane == 0) n_reseg = n;
     }
-  }
-  if (!delta_mode) {
-    for (int i = threadIdx.x; i < S; i += kUnitBlock) {
+    __syncthreads();
+    const int n = n_reseg;
+    for (int i = threadIdx.x; i < S; i += BLOCK) bounds[i + 1] = i < n ? reseg[i] : T;
+    __syncthreads();
+    if (n_sub <= kCapSub) {
+      // prefix in front of every bound: the end of the piece before the one that holds the last position in front of
+      // it, plus the positions of that piece in front of the bound
+      for (int i = (int)threadIdx.x / kSubLanes; i <= S; i += kGroups16) {
+        const int bnd = bounds[i];
+        const int q = (bnd - 1) / kSub;
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        if (bnd > 0) load_run(m_used, q * kSub + l16 * 4, bnd, a.vec, x, 0.f);
+        double p[4];
+        sub_scan(x, p);
+        if (l16 == kSubLanes - 1) cpre[i] = bnd > 0 ? (q > 0 ? ends[q - 1] : 0.0) + p[3] : 0.0;
+      }
+      __syncthreads();
+      for (int i = threadIdx.x; i < S; i += BLOCK) mass[i] = (float)(cpre[i + 1] - cpre[i]);
+    } else {
+      for (int sg = wave; sg < S; sg += kW) {
+        const int lo = bounds[sg], hi = bounds[sg + 1];
+        double sm = 0.0;
+        for (int t = lo + lane; t < hi; t += 64) sm += (double)m_used[t];
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) sm += __shfl_xor(sm, d);
+        if (lane == 0) mass[sg] = (float)sm;
+      }
+    }
+  } else {
+    for (int i = threadIdx.x; i < S; i += BLOCK) {
       const double lo = cpre[i] < 0.0 ? total : cpre[i];
       const double hi = (i + 1 == S || cpre[i + 1] < 0.0) ? total : cpre[i + 1];
       mass[i] = (float)(hi - lo);
     }
-    __syncthreads();
   }
-  for (int i = threadIdx.x; i < S; i += kUnitBlock) seg_mass_all[(int64_t)unit * S + i] = mass[i];
-  for (int i = threadIdx.x; i <= S; i += kUnitBlock) a.bounds[(int64_t)unit * (S + 1) + i] = bounds[i];
-  // what the quota kernels do besides the quotas: the -1 tail of idx, the kept count, the cleared bitmap
-  // of the must-keep path; sinks and the recent suffix come out of the budget first
-  const int kept = min(budget, T);
-  const int sinks = min(n_sink, kept);
-  const int bud = kept - sinks - min(n_last, kept - sinks);
-  int32_t* idx = idx_all + (int64_t)unit * budget;
-  for (int j = kept + threadIdx.x; j < budget; j += kUnitBlock) idx[j] = -1;
-  // a scorer whose bounded wait expired left unfinished scores: no unit reports a kept set then
-  if (threadIdx.x == 0) n_kept_all[unit] = (status && *status != 0) ? -1 : kept;
-  if (flags_all)
-    for (int j = threadIdx.x; j < n_words; j += kUnitBlock) flags_all[(int64_t)unit * n_words + j] = 0u;
-  if (S <= kUnitMaxSeg) {
-    if (threadIdx.x < 64) {
-      const int q = quota_wave(S, bud, q_min, bounds, mass);
-      if ((int)threadIdx.x < S) quota_all[(int64_t)unit * S + threadIdx.x] = q;
-    }
-  } else {
-    if constexpr (GENERAL) {
-      if (threadIdx.x < 64) {  // one wave, no workgroup barriers
-        quota_block<64>(S, bud, q_min, bounds, mass, qs);
-        for (int i = threadIdx.x; i < S; i += 64) quota_all[(int64_t)unit * S + i] = qs.quo[i];
-      }
-    }
+  __syncthreads();
+  if (o.seg_mass)
+    for (int i = threadIdx.x; i < S; i += BLOCK) o.seg_mass[(int64_t)unit * S + i] = mass[i];
+  for (int i = threadIdx.x; i <= S; i += BLOCK) a.bounds[(int64_t)unit * (S + 1) + i] = bounds[i];
+  if constexpr (KIND != CUTS_STAGE) {
+    // what the quota kernels do besides the quotas: the -1 tail of idx, the kept count, the cleared bitmap
+    // of the must-keep path; sinks and the recent suffix come out of the budget first
+    const int kept = min(o.budget, T);
+    const int sinks = min(o.n_sink, kept);
+    const int bud = kept - sinks - min(o.n_last, kept - sinks);
+    int32_t* idx = o.idx + (int64_t)unit * o.budget;
+    for (int j = kept + threadIdx.x; j < o.budget; j += BLOCK) idx[j] = -1;
+    // a scorer whose bounded wait expired left unfinished scores: no unit reports a kept set then
+    if (threadIdx.x == 0) o.n_kept[unit] = (o.status && *o.status != 0) ? -1 : kept;
+    if (o.flags)
+      for (int j = threadIdx.x; j < o.n_words; j += BLOCK) o.flags[(int64_t)unit * o.n_words + j] = 0u;
+    if (threadIdx.x < 64) quota_store<kCap>(S, bud, o.q_min, bounds, mass, o.quota + (int64_t)unit * S);
   }
+}
+
+// 256 threads hold the prefix of 65536 positions and take 16 cuts a round, eight workgroups to a CU; longer caches and
+// more cuts (in Delta mode the masses of all final segments are read off the prefix too) take 1024.
+template <int KIND>
+void launch_cuts(const MsArgs& a, const float* m_used, const CutsOut& o, hipStream_t s) {
+  if (a.n_sub <= 1024 && (a.delta > 0.0 ? a.S : a.K) <= 33)
+    hipLaunchKernelGGL((unit_cuts_kernel<256, KIND>), dim3(a.d.units), dim3(256), 0, s, a, m_used, o);
+  else
+    hipLaunchKernelGGL((unit_cuts_kernel<1024, KIND>), dim3(a.d.units), dim3(1024), 0, s, a, m_used, o);
+}
+
+// Runs of 1024 positions per workgroup of the position-wise kernels: four while that leaves two workgroups for every CU.
+int mass_rounds(const Dims& d) { return (int64_t)d.units * div_up(d.t_max, 4096) >= 512 ? 4 : 1; }
+
+template <bool TOTALS>
+void launch_mass(const MsArgs& a, const ams_params* p, const float* u, float* credit, float* m_used, hipStream_t s) {
+  prof_mark("mass_ema", s);
+  if (mass_rounds(a.d) == 4)
+    hipLaunchKernelGGL((mass_kernel<4, TOTALS>), dim3(div_up(a.d.t_max, 4096), a.d.units), dim3(kBlock), 0, s, a, u, credit,
+                       m_used, p->ema_lambda, p->ema_beta, p->mass_eps);
+  else
+    hipLaunchKernelGGL((mass_kernel<1, TOTALS>), dim3(div_up(a.d.t_max, 1024), a.d.units), dim3(kBlock), 0, s, a, u, credit,
+                       m_used, p->ema_lambda, p->ema_beta, p->mass_eps);
 }
 
 MsArgs make_args(const ams_params* p, const Dims& d, const int32_t* seq_lens, char* ws, const WsLayout& wl,
@@ -758,8 +771,9 @@ MsArgs make_args(const ams_params* p, const Dims& d, const int32_t* seq_lens, ch
   a.l_max = p->l_max;
   a.pool_r = p->pool_kernel > 1 ? p->pool_kernel / 2 : 0;
   a.vc_part = (double2*)(ws + wl.vc_part);
-  a.vc_stride = wl.n_chunks4k;
-  a.vc_tokens = kChunk;
+  a.vc_stride = a.vc_tokens = 0;  // set by the launchers once it is known who leaves the sums
+  a.sub = (double*)(ws + wl.sub);
+  a.n_sub = div_up(p->t_max, kSub);
   a.mpart = (double*)(ws + wl.mpart);
   a.cpre = (double*)(ws + wl.cpre);
   a.bounds = bounds;
@@ -790,26 +804,53 @@ hipError_t static_scratch(char** out) {
   return hipSuccess;
 }
 
+// Partial sums for the normalisers, where the scorer has left none that fit; pooled usage goes to m_used.  Returns the
+// usage that Eq. (1) sees and notes in a where the sums are.
+static const float* own_sums(MsArgs& a, const ams_params* p, const float* u, const float* credit, float* m_used,
+                             hipStream_t s) {
+  const int rounds = mass_rounds(a.d);
+  a.vc_tokens = kBlock * 4 * rounds;
+  a.vc_stride = div_up(a.d.t_max, a.vc_tokens);
+  const dim3 grid(a.vc_stride, a.d.units), blk(kBlock);
+  prof_mark("vc_sums", s);
+#define AMS_VC_SUMS(ROUNDS, POOL) \
+  hipLaunchKernelGGL((vc_sums_kernel<ROUNDS, POOL>), grid, blk, 0, s, a, u, credit, p->mass_eps, m_used)
+  if (a.pool_r > 0) {
+    if (rounds == 4) AMS_VC_SUMS(4, true);
+    else AMS_VC_SUMS(1, true);
+    return m_used;
+  }
+  if (rounds == 4) AMS_VC_SUMS(4, false);
+  else AMS_VC_SUMS(1, false);
+#undef AMS_VC_SUMS
+  return u;
+}
+
 hipError_t launch_ema(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* u,
-                      float* credit, float* m_used, const VcInfo& vc, char* ws, const WsLayout& wl,
-                      hipStream_t s) {
+                      float* credit, float* m_used, char* ws, const WsLayout& wl, hipStream_t s) {
   MsArgs a = make_args(p, d, seq_lens, ws, wl, nullptr);
   a.vec = d.t_stride % 4 == 0 && (((uintptr_t)u | (uintptr_t)credit | (uintptr_t)m_used) & 15) == 0;
-  const dim3 grid(a.n_chunks, d.units);
-  if (vc.have && a.pool_r == 0) {  // left by the scorer (sums of the unsmoothed usage)
-    a.vc_stride = vc.stride;
-    a.vc_tokens = vc.tokens;
-  } else {
-    prof_mark("vc_sums", s);
-    hipLaunchKernelGGL(vc_sums_kernel, grid, dim3(kBlock), 0, s, a, u, (const float*)credit, p->mass_eps);
-  }
-  prof_mark("mass_ema", s);
-  hipLaunchKernelGGL(mass_ema_kernel, grid, dim3(kBlock), 0, s, a, u, credit, m_used, p->ema_lambda,
-                     p->ema_beta, p->mass_eps);
+  const float* usage = own_sums(a, p, u, credit, m_used, s);
+  launch_mass<false>(a, p, usage, credit, m_used, s);
   return hipGetLastError();
 }
 
 hipError_t launch_segment(const ams_params* p, const Dims& d, const int32_t* seq_lens,
+                          const float* m_used, int32_t* bounds, float* seg_mass, char* ws, const WsLayout& wl,
+                          hipStream_t s) {
+  MsArgs a = make_args(p, d, seq_lens, ws, wl, bounds);
+  a.vec = d.t_stride % 4 == 0 && ((uintptr_t)m_used & 15) == 0;
+  prof_mark("sub_totals", s);
+  hipLaunchKernelGGL(sub_totals_kernel, dim3(div_up(d.t_max, kBlock * 4), d.units), dim3(kBlock), 0, s, a, m_used);
+  CutsOut o{};
+  o.seg_mass = seg_mass;
+  prof_mark("unit_cuts", s);
+  launch_cuts<CUTS_STAGE>(a, m_used, o, s);
+  return hipGetLastError();
+}
+
+// The form of ams_mass_segment_static, whose scratch is one total per 4096 positions and one prefix per cut.
+hipError_t launch_segment_static(const ams_params* p, const Dims& d, const int32_t* seq_lens,
                           const float* m_used, int32_t* bounds, float* seg_mass, char* ws, const WsLayout& wl,
                           hipStream_t s) {
   MsArgs a = make_args(p, d, seq_lens, ws, wl, bounds);
@@ -834,7 +875,7 @@ hipError_t launch_segment(const ams_params* p, const Dims& d, const int32_t* seq
   return hipGetLastError();
 }
 
-// The fused step's mass / EMA / segmentation / quota stages in one launch.
+// The fused step's mass / EMA / segmentation / quota stages.
 hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* u,
                             float* credit, float* m_used, int32_t* bounds, float* seg_mass, int32_t* quota,
                             int32_t* idx, int32_t* n_kept, uint32_t* flags, int n_words, const VcInfo& vc,
@@ -842,26 +883,23 @@ hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* s
   if (p->n_segments > kMaxSegments) return hipErrorInvalidValue;
   MsArgs a = make_args(p, d, seq_lens, ws, wl, bounds);
   a.vec = d.t_stride % 4 == 0 && (((uintptr_t)u | (uintptr_t)credit | (uintptr_t)m_used) & 15) == 0;
-  if (vc.have) {  // left by the scorer
+  const bool must = p->n_sink > 0 || p->n_last > 0;
+  if (must && !flags) return hipErrorInvalidValue;
+  const float* usage = u;
+  if (vc.have && a.pool_r == 0) {  // left by the scorer (sums of the unsmoothed usage)
     a.vc_stride = vc.stride;
     a.vc_tokens = vc.tokens;
   } else {
-    a.vc_part = nullptr;  // the kernel sums for itself
+    usage = own_sums(a, p, u, credit, m_used, s);
   }
-  const bool must = p->n_sink > 0 || p->n_last > 0;
-  if (must && !flags) return hipErrorInvalidValue;
-  prof_mark("unit_mass", s);
-  const dim3 grid(d.units), blk(kUnitBlock);
-  const bool general = p->seg_delta > 0.f || a.pool_r > 0 || p->n_segments > kUnitMaxSeg;
-#define AMS_UNIT_MASS_LAUNCH(PER, GEN)                                                                          \
-  hipLaunchKernelGGL((unit_mass_kernel<PER, GEN>), grid, blk, 0, s, a, u, credit, m_used, p->ema_lambda,         \
-                     p->ema_beta, p->mass_eps, p->budget, p->q_min, seg_mass, quota, idx, n_kept, p->n_sink,    \
-                     p->n_last, must ? flags : nullptr, n_words, (const int32_t*)park_status_word(ws, wl))
-  if (general)
-    AMS_UNIT_MASS_LAUNCH(8, true);
+  launch_mass<true>(a, p, usage, credit, m_used, s);
+  const CutsOut o{seg_mass, quota, idx, n_kept, must ? flags : nullptr, n_words, p->budget, p->q_min, p->n_sink,
+                  p->n_last, (const int32_t*)park_status_word(ws, wl)};
+  prof_mark("unit_cuts", s);
+  if (p->seg_delta > 0.f || p->n_segments > kStepMaxSeg)
+    launch_cuts<CUTS_GENERAL>(a, m_used, o, s);
   else
-    AMS_UNIT_MASS_LAUNCH(8, false);
-#undef AMS_UNIT_MASS_LAUNCH
+    launch_cuts<CUTS_STEP>(a, m_used, o, s);
   return hipGetLastError();
 }
 

@@ -1,229 +1,188 @@
-// Quota of every segment of one unit, for up to 64 segments, by one wave (Sec. 3.3 "Segment-wise
-// Quota Allocation"; Alg. 1 step 4).  Shared by the stand-alone quota kernel and the per-unit mass kernel.
+// Quota of every segment of one unit by one wave (Sec. 3.3 "Segment-wise Quota Allocation"; Alg. 1 step 4).
+// Shared by the stand-alone quota kernel and the per-unit kernel of the fused step.
 #ifndef AMS_QUOTA_H
 #define AMS_QUOTA_H
+
+#include <type_traits>
 
 #include "ams_internal.h"
 
 namespace ams {
 
+// Sum over the wave, the same value in every lane: the rows of 16 lanes by DPP, the four rows by scalar reads.
 __device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row_ror:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, true);
+  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
+         (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
 }
 
-// Quotas for S <= 64: lane i owns segment i.  Sums of masses run in index order over the active
-// lanes and every share is rem * M_i / sum, the same operations in the same order as plain C.
-__device__ __forceinline__ int quota_wave(int S, int bud, int q_min, const int32_t* bounds, const float* mass) {
+// Value of lane j, the same j in every lane: two scalar reads instead of a trip through the LDS crossbar.
+__device__ __forceinline__ double lane_f64(double v, int j) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, j);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), j);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Quotas of up to 64 * R segments by one wave: lane i owns the segments i, i + 64, ...; quo[r] is the quota of segment
+// 64 r + lane.  bounds and mass lie in LDS.  Sums of masses run in index order over the open segments and every share is
+// rem * M_i / sum, the same operations in the same order as plain C.  A serial chain: sums and counts travel through
+// scalar lane reads and ballots, and the leftovers go to the largest fractions by bisection on their bit patterns, not
+// by comparing every pair.
+template <int R>
+__device__ __forceinline__ void quota_wave(int S, int bud, int q_min, const int32_t* bounds, const float* mass,
+                                           int (&quo)[R]) {
   const int lane = threadIdx.x;
-  const bool valid = lane < S;
-  const int len = valid ? bounds[lane + 1] - bounds[lane] : 0;
-  const double mass_d = valid ? (double)mass[lane] : 0.0;
-  const int nonempty = __popcll(__ballot(len > 0));
-  int floor_q = q_min;
-  if (wave_sum(min(floor_q, len)) > bud) floor_q = nonempty > 0 ? bud / nonempty : 0;
-  const int lo = min(floor_q, len);
-  const int room = len - lo;
-  bool active = room > 0;
-  int quo = lo;
-  int rem = bud - wave_sum(lo);
-  double raw = 0.0;
-  // proportional shares; a segment whose share reaches its room is filled and leaves the pool
-  for (;;) {
-    const uint64_t act = __ballot(active);
-    const int n_active = __popcll(act);
-    if (n_active == 0 || rem <= 0) break;
-    double msum = 0.0;
-    for (uint64_t m = act; m; m &= m - 1) msum += __shfl(mass_d, __ffsll((long long)m) - 1);
-    if (active) raw = msum > 0.0 ? (double)rem * mass_d / msum : (double)rem / (double)n_active;
-    const bool sat = active && raw >= (double)room;
-    if (!__ballot(sat)) break;
-    rem -= wave_sum(sat ? room : 0);
-    if (sat) {
-      quo = len;
-      active = false;
-    }
-  }
-  if (rem > 0) {
-    double frac = -1.0;
-    int fl_i = 0;
-    if (active) {
-      const double fl = floor(raw);
-      frac = raw - fl;
-      fl_i = (int)fl;
-      quo += fl_i;
-    }
-    int left = rem - wave_sum(fl_i);
-    // one extra each, largest fractional part first, equal parts by lower segment index
-    while (left > 0) {
-      const bool can = active && quo < len;
-      const uint64_t cm = __ballot(can);
-      if (!cm) break;
-      int rank = 0;
-      for (uint64_t m = cm; m; m &= m - 1) {
-        const int j = __ffsll((long long)m) - 1;
-        const double fj = __shfl(frac, j);
-        if (fj > frac || (fj == frac && j < lane)) ++rank;
-      }
-      const bool take = can && rank < left;
-      if (take) ++quo;
-      left -= __popcll(__ballot(take));
-    }
-  }
-  return quo;
-}
-
-// Quotas for up to 1024 segments by the first BLOCK threads of a workgroup (BLOCK == 64: its first wave
-// alone; otherwise BLOCK must be the whole workgroup), the segments in LDS.  Integer
-// sums are order-free; the sum of the masses of the open segments is taken by one thread in index
-// order, the same order as plain C, so that every share is the same double.  The quotas are left in
-// sc.quo (valid after the final barrier inside).
-constexpr int kQuotaMaxSeg = 1024;
-struct QuotaScratch {
-  int32_t len[kQuotaMaxSeg], room[kQuotaMaxSeg], quo[kQuotaMaxSeg];
-  double mass_d[kQuotaMaxSeg], raw[kQuotaMaxSeg];
-  __attribute__((aligned(16))) double key[kQuotaMaxSeg];
-  uint8_t active[kQuotaMaxSeg], can[kQuotaMaxSeg];
-  int red[16];
-  double msum;
-};
-
-// Barrier between the steps of quota_block: a workgroup barrier, or for BLOCK == 64 (one wave runs the whole
-// routine, the other waves of the workgroup do not take part) only the ordering of the wave's own LDS accesses.
-template <int BLOCK>
-__device__ __forceinline__ void quota_sync() {
-  if constexpr (BLOCK == 64) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
-
-template <int BLOCK>
-__device__ __forceinline__ int block_sum_int(int v, int* sm) {
-  v = wave_sum(v);
-  if constexpr (BLOCK == 64) {
-    quota_sync<64>();  // the callers rely on a barrier's ordering of their LDS accesses here
-    return v;
-  }
-  __syncthreads();  // sm may still be read from a previous call
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  int t = 0;
-#pragma unroll
-  for (int w = 0; w < BLOCK / 64; ++w) t += sm[w];
-  return t;
-}
-
-template <int BLOCK>
-__device__ __forceinline__ void quota_block(int S, int bud, int q_min, const int32_t* bounds, const float* mass,
-                                            QuotaScratch& sc) {
+  auto len = [&](int r) __attribute__((always_inline)) {
+    const int i = r * 64 + lane;
+    return i < S ? bounds[i + 1] - bounds[i] : 0;
+  };
   int c_nonempty = 0, c_need = 0;
-  for (int i = threadIdx.x; i < S; i += BLOCK) {
-    sc.len[i] = bounds[i + 1] - bounds[i];
-    sc.mass_d[i] = (double)mass[i];
-    c_nonempty += sc.len[i] > 0;
-    c_need += min(q_min, sc.len[i]);
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    c_nonempty += __popcll(__ballot(len(r) > 0));
+    c_need += min(q_min, len(r));
   }
-  const int nonempty = block_sum_int<BLOCK>(c_nonempty, sc.red);
-  const int need = block_sum_int<BLOCK>(c_need, sc.red);
   int floor_q = q_min;
-  if (need > bud) floor_q = nonempty > 0 ? bud / nonempty : 0;
+  if (wave_sum(c_need) > bud) floor_q = c_nonempty > 0 ? bud / c_nonempty : 0;
+  double raw[R];
+  bool active[R];
   int c_lo = 0;
-  for (int i = threadIdx.x; i < S; i += BLOCK) {
-    const int lo = min(floor_q, sc.len[i]);
-    sc.room[i] = sc.len[i] - lo;
-    sc.active[i] = sc.room[i] > 0;
-    sc.quo[i] = lo;
-    sc.raw[i] = 0.0;
-    c_lo += lo;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int n = len(r);
+    quo[r] = min(floor_q, n);
+    active[r] = n > quo[r];
+    raw[r] = 0.0;
+    c_lo += quo[r];
   }
-  int rem = bud - block_sum_int<BLOCK>(c_lo, sc.red);
+  int rem = bud - wave_sum(c_lo);
   // proportional shares; a segment whose share reaches its room is filled and leaves the pool
   for (;;) {
-    int c_act = 0;
-    for (int i = threadIdx.x; i < S; i += BLOCK) c_act += sc.active[i];
-    const int n_active = block_sum_int<BLOCK>(c_act, sc.red);
+    int n_active = 0;
+    double msum = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) n_active += __popcll(__ballot(active[r]));
     if (n_active == 0 || rem <= 0) break;
-    if (threadIdx.x == 0) {
-      // index order; a closed segment adds an exact zero, so the loads need not wait for the flags
-      double msum = 0.0;
-#pragma unroll 8
-      for (int i = 0; i < S; ++i) {
-        const double md = sc.mass_d[i];
-        const bool open = sc.active[i] != 0;
-        msum += open ? md : 0.0;
-      }
-      sc.msum = msum;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {  // index order; a closed segment adds an exact zero
+      const double open = active[r] ? (double)mass[r * 64 + lane] : 0.0;
+#pragma unroll
+      for (int j0 = 0; j0 < 64; j0 += 16)
+        if (r * 64 + j0 < S) {
+#pragma unroll
+          for (int j = j0; j < j0 + 16; ++j) msum += lane_f64(open, j);
+        }
     }
-    quota_sync<BLOCK>();
-    const double msum = sc.msum;
-    int c_sat = 0, c_taken = 0;
-    for (int i = threadIdx.x; i < S; i += BLOCK)
-      if (sc.active[i]) {
-        sc.raw[i] = msum > 0.0 ? (double)rem * sc.mass_d[i] / msum : (double)rem / (double)n_active;
-        if (sc.raw[i] >= (double)sc.room[i]) {
-          sc.quo[i] = sc.len[i];
-          sc.active[i] = 0;
-          ++c_sat;
-          c_taken += sc.room[i];
+    int c_taken = 0;
+    bool any_sat = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      bool sat = false;
+      if (active[r]) {
+        const int n = len(r), room = n - quo[r];
+        raw[r] = msum > 0.0 ? (double)rem * (double)mass[r * 64 + lane] / msum : (double)rem / (double)n_active;
+        sat = raw[r] >= (double)room;
+        if (sat) {
+          quo[r] = n;
+          active[r] = false;
+          c_taken += room;
         }
       }
-    const int n_sat = block_sum_int<BLOCK>(c_sat, sc.red);
-    rem -= block_sum_int<BLOCK>(c_taken, sc.red);
-    if (n_sat == 0) break;
+      any_sat = any_sat || __ballot(sat) != 0;
+    }
+    if (!any_sat) break;
+    rem -= wave_sum(c_taken);
   }
   if (rem > 0) {
+    // a fraction lies in [0, 1): its bit pattern orders like the number
+    uint64_t key[R];
     int c_given = 0;
-    for (int i = threadIdx.x; i < S; i += BLOCK)
-      if (sc.active[i]) {
-        const double fl = floor(sc.raw[i]);
-        sc.raw[i] -= fl;  // now the fractional part
-        sc.quo[i] += (int)fl;
-        c_given += (int)fl;
-      }
-    int left = rem - block_sum_int<BLOCK>(c_given, sc.red);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const bool real = active[r] && raw[r] == raw[r];  // masses that are no numbers: everybody ranks alike
+      const double fl = real ? floor(raw[r]) : 0.0;
+      key[r] = real ? __builtin_bit_cast(uint64_t, raw[r] - fl) : 0;
+      quo[r] += (int)fl;
+      c_given += (int)fl;
+    }
+    int left = rem - wave_sum(c_given);
     // one extra each, largest fractional part first, equal parts by lower segment index
     while (left > 0) {
-      int c_can = 0;
-      // key = the fractional part of a segment that can still take one, -1 for the others (a fraction
-      // is never negative), padded to a multiple of four entries: the ranking loop then reads one array,
-      // four entries at a time, without waiting for flags
-      const int S4 = (S + 3) & ~3;
-      for (int i = threadIdx.x; i < S4; i += BLOCK) {
-        const bool c = i < S && sc.active[i] && sc.quo[i] < sc.len[i];
-        if (i < S) sc.can[i] = c;
-        sc.key[i] = c ? sc.raw[i] : -1.0;
-        c_can += c;
+      bool can[R];
+      int n_can = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        can[r] = active[r] && quo[r] < len(r);
+        n_can += __popcll(__ballot(can[r]));
       }
-      const int n_can = block_sum_int<BLOCK>(c_can, sc.red);
       if (n_can == 0) break;
-      int c_take = 0;
-      for (int i = threadIdx.x; i < S; i += BLOCK)
-        if (sc.can[i]) {
-          int rank = 0;
-          if (n_can > left) {  // otherwise everybody is served
-            const double fi = sc.key[i];
-            for (int j = 0; j < S4; j += 4) {
-              const double k0 = sc.key[j], k1 = sc.key[j + 1], k2 = sc.key[j + 2], k3 = sc.key[j + 3];
-              rank += (k0 > fi || (k0 == fi && j < i)) ? 1 : 0;
-              rank += (k1 > fi || (k1 == fi && j + 1 < i)) ? 1 : 0;
-              rank += (k2 > fi || (k2 == fi && j + 2 < i)) ? 1 : 0;
-              rank += (k3 > fi || (k3 == fi && j + 3 < i)) ? 1 : 0;
-            }
-          }
-          if (rank < left) {
-            ++sc.quo[i];
-            ++c_take;
-          }
+      if (n_can <= left) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) quo[r] += can[r] ? 1 : 0;
+        left -= n_can;
+        continue;
+      }
+      // the left-th largest fraction, bit by bit from the top, until a bound separates exactly `left` of them
+      auto at_least = [&](uint64_t c) __attribute__((always_inline)) {
+        int n = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) n += __popcll(__ballot(can[r] && key[r] >= c));
+        return n;
+      };
+      constexpr uint64_t kHalf = 0x3FE0000000000000ull;  // 0.5: all fractions from there on share the upper bits
+      uint64_t thr = 0;
+      int bit = 61, n_thr = n_can;
+      if (const int n = at_least(kHalf); n >= left) {
+        thr = kHalf;
+        n_thr = n;
+        bit = 51;
+      }
+      for (; bit >= 0 && n_thr != left; --bit) {
+        const uint64_t c = thr | (1ull << bit);
+        if (const int n = at_least(c); n >= left) {
+          thr = c;
+          n_thr = n;
         }
-      left -= block_sum_int<BLOCK>(c_take, sc.red);
+      }
+      // more than `left` reach the bound only if they are equal to it: of those the lower segments are served
+      int spare = n_thr - left, n_eq = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) n_eq += __popcll(__ballot(can[r] && key[r] == thr));
+      int keep_eq = n_eq - spare;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint64_t eq = __ballot(can[r] && key[r] == thr);
+        const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+        const bool take = can[r] && (key[r] > thr || (key[r] == thr && (int)__popcll(eq & below) < keep_eq));
+        quo[r] += take ? 1 : 0;
+        keep_eq -= (int)__popcll(eq);
+      }
+      left = 0;
     }
   }
-  quota_sync<BLOCK>();
+}
+
+// The quotas of S <= MAX_S segments -> out[0 .. S), by the first wave of the workgroup.
+template <int MAX_S>
+__device__ __forceinline__ void quota_store(int S, int bud, int q_min, const int32_t* bounds, const float* mass,
+                                            int32_t* out) {
+  auto run = [&](auto r_c) __attribute__((always_inline)) {
+    constexpr int R = decltype(r_c)::value;
+    int quo[R];
+    quota_wave<R>(S, bud, q_min, bounds, mass, quo);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r * 64 + (int)threadIdx.x < S) out[r * 64 + threadIdx.x] = quo[r];
+  };
+  if (MAX_S <= 64 || S <= 64) return run(std::integral_constant<int, 1>{});
+  if constexpr (MAX_S > 64) {
+    if (S <= 256) return run(std::integral_constant<int, 4>{});
+    run(std::integral_constant<int, 16>{});
+  }
 }
 
 }  // namespace ams

@@ -1,7 +1,7 @@
 // Segment quotas, in-segment top-k and the kept set (Sec. 3.3 "Segment-wise Quota Allocation",
 // "In-Segment Selection" and the must-keep rules; Alg. 1 steps 4-5).
 //
-// quota_kernel   one wave per unit (up to 64 segments in registers, up to 1024 in LDS); the
+// quota_kernel   one wave per unit, the segments in registers; the
 //                arithmetic is a handful of double operations per segment and is done in index
 //                order so that it is reproducible bit for bit.
 // select_kernel  one workgroup per (segment, unit): radix select (4 x 8 bits, most significant
@@ -21,7 +21,7 @@ namespace {
 
 constexpr int kMaxSeg = 1024;
 
-// What both quota kernels do before the quotas: the -1 tail of idx, the kept count, the cleared bitmap of the
+// What the quota kernel does before the quotas: the -1 tail of idx, the kept count, the cleared bitmap of the
 // must-keep path.  Returns the budget the segments share.
 __device__ __forceinline__ int quota_prologue(const Dims& d, const int32_t* seq_lens, int budget,
                                               int32_t* idx_all, int32_t* n_kept_all, int n_sink, int n_last,
@@ -44,32 +44,22 @@ __device__ __forceinline__ int quota_prologue(const Dims& d, const int32_t* seq_
   return bud;
 }
 
-// Up to 64 segments: one wave per unit.
 __global__ __launch_bounds__(64) void quota_kernel(Dims d, const int32_t* seq_lens, int S, int budget,
                                                    int q_min, const int32_t* bounds_all,
-                                                   float* seg_mass_all, int32_t* quota_all,
+                                                   const float* seg_mass_all, int32_t* quota_all,
                                                    int32_t* idx_all, int32_t* n_kept_all, int n_sink, int n_last,
                                                    uint32_t* flags_all, int n_words) {
+  __shared__ int32_t bounds[kMaxSeg + 1];
+  __shared__ float mass[kMaxSeg];
   const int unit = blockIdx.x;
+  for (int i = threadIdx.x; i < S; i += 64) {
+    bounds[i] = bounds_all[(int64_t)unit * (S + 1) + i];
+    mass[i] = seg_mass_all[(int64_t)unit * S + i];
+  }
+  if (threadIdx.x == 0) bounds[S] = bounds_all[(int64_t)unit * (S + 1) + S];
   const int bud = quota_prologue(d, seq_lens, budget, idx_all, n_kept_all, n_sink, n_last, flags_all, n_words);
-  const int q = quota_wave(S, bud, q_min, bounds_all + (int64_t)unit * (S + 1), seg_mass_all + (int64_t)unit * S);
-  if ((int)threadIdx.x < S) quota_all[(int64_t)unit * S + threadIdx.x] = q;
-}
-
-// More than 64 segments (up to 1024): one wave per unit as well, the segments in LDS.
-constexpr int kQuotaBlock = 64;
-
-__global__ __launch_bounds__(kQuotaBlock) void quota_block_kernel(Dims d, const int32_t* seq_lens, int S,
-                                                                  int budget, int q_min,
-                                                                  const int32_t* bounds_all, float* seg_mass_all,
-                                                                  int32_t* quota_all, int32_t* idx_all,
-                                                                  int32_t* n_kept_all, int n_sink, int n_last,
-                                                                  uint32_t* flags_all, int n_words) {
-  __shared__ QuotaScratch sc;
-  const int unit = blockIdx.x;
-  const int bud = quota_prologue(d, seq_lens, budget, idx_all, n_kept_all, n_sink, n_last, flags_all, n_words);
-  quota_block<kQuotaBlock>(S, bud, q_min, bounds_all + (int64_t)unit * (S + 1), seg_mass_all + (int64_t)unit * S, sc);
-  for (int i = threadIdx.x; i < S; i += kQuotaBlock) quota_all[(int64_t)unit * S + i] = sc.quo[i];
+  __syncthreads();
+  quota_store<kMaxSeg>(S, bud, q_min, bounds, mass, quota_all + (int64_t)unit * S);
 }
 
 // Order-preserving image of a score: larger float <-> larger unsigned; -0 and +0 coincide and
@@ -620,14 +610,11 @@ hipError_t launch_select(const ams_params* p, const Dims& d, const int32_t* seq_
   if (!quota_done) prof_mark("quota", s);
   if (quota_done) {
     // quotas, the tail of idx, the kept count and the cleared bitmap are already in place
-  } else if (S <= 64)
+  } else {
     hipLaunchKernelGGL(quota_kernel, dim3(d.units), dim3(64), 0, s, d, seq_lens, S, p->budget, p->q_min,
                        bounds, seg_mass, quota, idx, n_kept, p->n_sink, p->n_last,
                        must ? flags : nullptr, n_words);
-  else
-    hipLaunchKernelGGL(quota_block_kernel, dim3(d.units), dim3(kQuotaBlock), 0, s, d, seq_lens, S, p->budget,
-                       p->q_min, bounds, seg_mass, quota, idx, n_kept, p->n_sink,
-                       p->n_last, must ? flags : nullptr, n_words);
+  }
   prof_mark("select", s);
   // expected segment length decides the shape of the selection workgroups
   const double expect = p->seg_delta > 0.f

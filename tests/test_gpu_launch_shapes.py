@@ -3,10 +3,12 @@ kernels cut a unit into.  Checked like every step (scores and masses within rela
 stage exact on the GPU's own floats)."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_23200_amd import binding as B
 from paper_2605_23200_amd import inputs
 from paper_2605_23200_amd.harness import Job
+from gpu_util import DEV, to_dev, to_host, workspace
 from test_gpu_step import check_properties_all_units, check_units
 
 pytestmark = pytest.mark.gpu
@@ -34,3 +36,82 @@ def test_few_units_are_cut_into_short_chunks(oracle, dtype, G, W, T, paged, caus
     w = inputs.CONFIGS[1].scaled(L=1, B=2, H=2, G=G, W=W, T=T, T_min=T, dtype=dtype, budget=min(64, T), S=4, n_spans=2,
                                  span_len=(4, 40), paged=paged, causal=causal)
     _run(oracle, w, lens=[T, max(1, T - 1 - (T % 128))])
+
+
+def _stage_params(units, T, S, **kw):
+    return B.make_params(n_layers=1, batch=1, n_kv_heads=units, group=1, window=8, t_max=T, budget=min(64, T),
+                         n_segments=S, **kw)
+
+
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("T,S", [(63, 4), (64, 4), (65, 4), (1023, 33), (1025, 34), (65536, 8), (65537, 8), (262144, 40),
+                                 (262209, 40)])
+def test_cuts_at_the_edges_of_pieces_and_groups(oracle, T, S, signed):
+    """Pieces of 64 positions, the 65536 / 262144 positions whose pieces the two workgroup sizes hold at once, 33 / 34
+    thresholds.  signed: the prefix falls in between, the first position that reaches a threshold still counts."""
+    rng = np.random.default_rng(T + S)
+    m = (rng.random((3, T)) ** 4).astype(np.float32)
+    m[1] *= np.arange(T) % 97 == 0                                     # most pieces hold one or two entries
+    if signed:
+        m[0] -= (rng.random(T) * 0.15).astype(np.float32)
+        m[2] = np.where(np.arange(T) < T // 2, m[2], -m[2] / 2)
+    m /= np.abs(m.astype(np.float64)).sum(1, keepdims=True)
+    m = np.ascontiguousarray(m.astype(np.float32))
+    p = _stage_params(3, T, S)
+    bounds, seg_mass = torch.full((3, S + 1), -3, dtype=torch.int32, device=DEV), torch.full((3, S), -3.0, device=DEV)
+    B.ams_mass_segment(p, to_dev(np.array([T], np.int32)), to_dev(m), bounds, seg_mass, workspace(p))
+    bounds, seg_mass = to_host(bounds), to_host(seg_mass)
+    for i in range(3):
+        b_o, s_o = oracle.segment(m[i], S)
+        np.testing.assert_array_equal(bounds[i], b_o, err_msg=f"unit {i}")
+        # a mass is a difference of two prefixes of at most 1 in magnitude, in double
+        np.testing.assert_allclose(seg_mass[i], s_o, rtol=1e-6, atol=1e-12)
+
+
+@pytest.mark.parametrize("T,S,pool", [(1023, 64, 5), (1025, 65, 0), (4097, 16, 63), (65600, 256, 3), (9000, 257, 0)])
+def test_mass_step_at_the_edges_of_its_runs(oracle, T, S, pool):
+    """Runs of 1024 positions, 64 / 65 and 256 / 257 segments (registers per lane of the quota wave), the widest pool."""
+    w = inputs.CONFIGS[0].scaled(H=2, T=T, S=S, budget=min(700, T), n_spans=3, span_len=(8, 60), pool_kernel=pool)
+    _run(oracle, w)
+
+
+def test_many_chunks_take_four_runs_per_workgroup(oracle):
+    """512 chunks of 4096 positions: four runs per workgroup, the last chunk ragged, pooled and not."""
+    for pool in (0, 5):
+        w = inputs.CONFIGS[0].scaled(L=16, H=8, T=12289 + 17, W=4, D=64, dtype="bf16", budget=100, n_spans=3,
+                                     span_len=(8, 60), pool_kernel=pool)
+        _run(oracle, w, units=[0, 63, 127])
+
+
+@pytest.mark.parametrize("T,delta,l_min,l_max", [(70001, 0.01, 8, 200), (270000, 0.05, 16, 1024)])
+def test_split_and_merge_on_long_caches(oracle, T, delta, l_min, l_max):
+    """Masses of moved segments from the prefix (up to 262144 positions) and by summing (beyond)."""
+    cap = int(np.ceil(1 / delta)) + 1 + T // l_max
+    rng = np.random.default_rng(T)
+    m = np.stack([oracle.mass((rng.random(T) ** e).astype(np.float32)) for e in (1, 8)])
+    p = _stage_params(2, T, cap, seg_delta=delta, l_min=l_min, l_max=l_max)
+    bounds, seg_mass = torch.full((2, cap + 1), -3, dtype=torch.int32, device=DEV), torch.full((2, cap), -3.0, device=DEV)
+    B.ams_mass_segment(p, to_dev(np.array([T], np.int32)), to_dev(m), bounds, seg_mass, workspace(p))
+    for i in range(2):
+        b_o, s_o, _ = oracle.segment_adaptive(m[i], delta, l_min, l_max, cap)
+        np.testing.assert_array_equal(to_host(bounds)[i], b_o)
+        np.testing.assert_allclose(to_host(seg_mass)[i], s_o, rtol=1e-5, atol=1e-12)
+
+
+@pytest.mark.parametrize("S", [64, 65, 128, 256, 257, 1024])
+def test_quota_ties_at_every_register_count(oracle, S):
+    """Equal fractions, empty and full segments: the leftovers go to the lower segments, the sum is the budget."""
+    rng = np.random.default_rng(S)
+    for budget, levels in ((S // 3 + 1, 2), (2 * S + 1, 3), (7 * S // 2, 1), (20 * S, 1000)):
+        lens = rng.integers(0, 30, size=S)
+        lens[S // 2] += 9
+        bounds = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)[None]
+        mass = np.where(lens > 0, (1 + rng.integers(0, levels, size=S)) / 8, 0).astype(np.float32)[None]
+        T = int(bounds[0, -1])
+        p = _stage_params(1, T, S)
+        p.budget = budget
+        quota = torch.zeros((1, S), dtype=torch.int32, device=DEV)
+        idx, n_kept = torch.zeros((1, budget), dtype=torch.int32, device=DEV), torch.zeros(1, dtype=torch.int32, device=DEV)
+        B.ams_select(p, to_dev(np.array([T], np.int32)), torch.zeros((1, T), device=DEV), to_dev(bounds), to_dev(mass),
+                     quota, idx, n_kept)
+        np.testing.assert_array_equal(to_host(quota)[0], oracle.quota(bounds[0], mass[0], budget, 1), err_msg=f"{budget}")
