@@ -84,16 +84,11 @@ struct Emit {
   }
 };
 
-// 3968 keys + the four histograms come to 19.6 KB: eight workgroups fit the LDS of a CU (4096 keys: seven,
-// and the 4096 workgroups of the headline workload then need three rounds instead of two)
-constexpr int kSelectCap = 3968;
+// The selection kernel holds the keys of a segment in registers: BLOCK threads with PER keys each.  One wave takes the
+// many short segments (no barriers between waves), 256, 512 and 1024 threads the longer ones; a segment that is longer
+// than its shape's BLOCK * PER is selected from memory.
 
-// The selection kernel comes in two shapes: 256 threads with room for 3968 keys in LDS (segments of
-// thousands of positions) and one wave with room for 1024 keys (many short segments: more workgroups
-// per compute unit and no barriers between waves).  BLOCK = threads, CAP = segment lengths up to
-// which the keys are selected from a copy in LDS.
-
-// Segment longer than the LDS staging area: the scores are re-read from memory for every pass.
+// Segment longer than the registers hold: the scores are re-read from memory for every pass.
 template <bool FLAGS, int BLOCK>
 __device__ void select_from_memory(const float* g, int a, int b, int q, const Emit<FLAGS>& emit, int* hist,
                                    uint32_t* sel_prefix, int* sel_rem, int2* wave_cnt) {
@@ -168,159 +163,240 @@ __device__ void select_from_memory(const float* g, int a, int b, int q, const Em
   }
 }
 
-template <bool FLAGS, int BLOCK, int CAP>
+// Inclusive sum over the lanes of a wave (DPP: inside the rows of 16, then the rows' ends into the rows after them).
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+
+// Lowest and highest key of the wave, the same in every lane.
+__device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
+#define AMS_ROR(X, CTRL) (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(X), CTRL, 0xf, 0xf, true)
+  lo = min(lo, AMS_ROR(lo, 0x128)), hi = max(hi, AMS_ROR(hi, 0x128));
+  lo = min(lo, AMS_ROR(lo, 0x124)), hi = max(hi, AMS_ROR(hi, 0x124));
+  lo = min(lo, AMS_ROR(lo, 0x122)), hi = max(hi, AMS_ROR(hi, 0x122));
+  lo = min(lo, AMS_ROR(lo, 0x121)), hi = max(hi, AMS_ROR(hi, 0x121));
+#undef AMS_ROR
+  uint32_t l = 0xFFFFFFFFu, h = 0;
+#pragma unroll
+  for (int r = 0; r < 64; r += 16) {
+    l = min(l, (uint32_t)__builtin_amdgcn_readlane((int)lo, r));
+    h = max(h, (uint32_t)__builtin_amdgcn_readlane((int)hi, r));
+  }
+  lo = l;
+  hi = h;
+}
+
+// The q largest keys of a segment.  Latency and LDS atomics bound this kernel (a few thousand keys per workgroup), so the
+// steps that need all threads are few: the keys stay in registers, 256 bins cut the range between the lowest and the
+// highest key, and once the bin with the q-th largest holds no more than 64 keys, those are listed and one wave counts for
+// each the ones in front of it (higher, or equal at a lower position).  A bin that is too full is cut into 256 again;
+// keys that are all equal are taken in position order.  (Ranking up to 256 listed keys through LDS instead of one more
+// pass took 16 us longer for 72 segments of 1457 normal scores.)  The picks are bits of a map of the segment, whose
+// running count gives every pick its place in the ascending list.
+template <bool FLAGS, int BLOCK, int PER>
 __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget, const float* g_all,
-                                                           const int32_t* bounds_all,
-                                                           const int32_t* quota_all, int32_t* idx_all,
-                                                           uint32_t* flags_all, int n_words) {
-  __shared__ uint32_t keys[CAP];
-  __shared__ int hist[(BLOCK / 64)][256];
-  __shared__ uint32_t sel_prefix;
-  __shared__ int sel_rem;
-  __shared__ int2 wave_cnt[(BLOCK / 64)];
-  __shared__ uint32_t red_and[(BLOCK / 64)], red_or[(BLOCK / 64)];
+                                                       const int32_t* bounds_all,
+                                                       const int32_t* quota_all, int32_t* idx_all,
+                                                       uint32_t* flags_all, int n_words) {
+  constexpr int kW = BLOCK / 64, kCap = BLOCK * PER, kWords = kCap / 64, kPerLane = (kWords + 63) / 64;
+  constexpr int kList = 64;  // keys that one wave ranks
+  __shared__ __align__(16) int hist[2][256];
+  __shared__ uint2 list[kList];          // (key, position in the segment) of the keys in the bin
+  __shared__ __align__(8) uint64_t picked[kWords], equal[kWords];
+  __shared__ int before[kWords];         // picks in front of each word
+  __shared__ int n_list;
+  __shared__ uint2 red[kW];
+  __shared__ int2 wave_cnt[kW];
+  __shared__ uint32_t mem_prefix;
+  __shared__ int mem_rem;
   const int unit = blockIdx.y, seg = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int32_t* bounds = bounds_all + (int64_t)unit * (S + 1);
   const int32_t* quota = quota_all + (int64_t)unit * S;
   const int a = bounds[seg], b = bounds[seg + 1], q = quota[seg];
   if (q <= 0) return;
+  const int L = b - a;
+  const float* g = g_all + (int64_t)unit * d.t_stride;
+  uint32_t key[PER];
+  const bool from_memory = L > kCap;
+  if (q < L && !from_memory) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int e = i * BLOCK + (int)threadIdx.x;
+      key[i] = e < L ? __float_as_uint(g[a + e]) : 0u;
+    }
+  }
   int out0 = 0;  // place of this segment's picks in the index list: the quotas before it
   if (!FLAGS) {
-    for (int i = threadIdx.x; i < seg; i += BLOCK) out0 += quota[i];
+    for (int i = lane; i < seg; i += 64) out0 += quota[i];
     out0 = wave_sum(out0);
-    if ((threadIdx.x & 63) == 0) wave_cnt[threadIdx.x >> 6].x = out0;
-    __syncthreads();
-    out0 = 0;
-#pragma unroll
-    for (int w = 0; w < BLOCK / 64; ++w) out0 += wave_cnt[w].x;
-    __syncthreads();
   }
-  const float* g = g_all + (int64_t)unit * d.t_stride;
   const Emit<FLAGS> emit{idx_all + (int64_t)unit * budget + out0,
                          FLAGS ? flags_all + (int64_t)unit * n_words : nullptr};
-  const int L = b - a;
   if (q >= L) {  // whole segment kept
     for (int j = threadIdx.x; j < L; j += BLOCK) emit(j, a + j);
     return;
   }
-  if (L > CAP) {
-    select_from_memory<FLAGS, BLOCK>(g, a, b, q, emit, &hist[0][0], &sel_prefix, &sel_rem, wave_cnt);
+  if (from_memory) {
+    select_from_memory<FLAGS, BLOCK>(g, a, b, q, emit, &hist[0][0], &mem_prefix, &mem_rem, wave_cnt);
     return;
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
-  // keys of the segment -> LDS; bits that are the same in every key need no radix pass
-  uint32_t k_and = 0xFFFFFFFFu, k_or = 0;
-  for (int e = threadIdx.x; e < L; e += BLOCK) {
-    const uint32_t k = score_key(g[a + e]);
-    keys[e] = k;
-    k_and &= k;
-    k_or |= k;
-  }
+  // range of the keys
+  uint32_t lo = 0xFFFFFFFFu, hi = 0;
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    k_and &= __shfl_xor(k_and, o);
-    k_or |= __shfl_xor(k_or, o);
-  }
-  if (lane == 0) {
-    red_and[wave] = k_and;
-    red_or[wave] = k_or;
-  }
-  __syncthreads();
-  k_and = red_and[0];
-  k_or = red_or[0];
-#pragma unroll
-  for (int w = 1; w < BLOCK / 64; ++w) {
-    k_and &= red_and[w];
-    k_or |= red_or[w];
-  }
-  const uint32_t diff = k_and ^ k_or;
-  uint32_t thr = k_and;  // all keys equal: the threshold is that key
-  int rem = q;
-  if (diff != 0) {
-    const int hb = 31 - __clz(diff);  // highest bit in which two keys differ
-    uint32_t mask = hb == 31 ? 0u : ~((2u << hb) - 1u);  // bits known so far
-    uint32_t prefix = k_and & mask;
-    int shift = max(hb - 7, 0);
-    for (;;) {
-      for (int i = threadIdx.x; i < (BLOCK / 64) * 256; i += BLOCK) (&hist[0][0])[i] = 0;
-      __syncthreads();
-      for (int e = threadIdx.x; e < L; e += BLOCK) {
-        const uint32_t k = keys[e];
-        if ((k & mask) == prefix) atomicAdd(&hist[wave][(k >> shift) & 255], 1);
-      }
-      __syncthreads();
-      if (wave == 0) {
-        int hbin[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          hbin[i] = 0;
-#pragma unroll
-          for (int w = 0; w < (BLOCK / 64); ++w) hbin[i] += hist[w][lane * 4 + i];
-        }
-        const int s = hbin[0] + hbin[1] + hbin[2] + hbin[3];
-        int incl = s;  // sum over lanes >= this one
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int v = __shfl_down(incl, o);
-          if (lane + o < 64) incl += v;
-        }
-        int cum = incl - s;  // keys in bins above this lane's
-#pragma unroll
-        for (int i = 3; i >= 0; --i) {
-          if (cum < rem && rem <= cum + hbin[i]) {
-            sel_prefix = (uint32_t)(lane * 4 + i);
-            sel_rem = rem - cum;
-          }
-          cum += hbin[i];
-        }
-      }
-      __syncthreads();
-      // the digit may overlap bits that are already known; OR-ing it in is then a no-op for those bits
-      prefix |= sel_prefix << shift;
-      rem = sel_rem;
-      mask = shift == 0 ? 0xFFFFFFFFu : ~((1u << shift) - 1u);
-      __syncthreads();
-      if (shift == 0) break;
-      shift = max(shift - 8, 0);
-    }
-    thr = prefix;
-  }
-  // thr = key of the q-th largest score; rem = how many of the keys equal to it are kept (the first
-  // rem in position order).  Every thread takes a contiguous run of positions, so one workgroup scan
-  // of the per-thread counts gives every kept position its place in the ascending output.
-  const int per = (L + BLOCK - 1) / BLOCK;
-  const int e0 = min(L, (int)threadIdx.x * per), e1 = min(L, e0 + per);
-  int c_gt = 0, c_eq = 0;
-  for (int e = e0; e < e1; ++e) {
-    const uint32_t k = keys[e];
-    c_gt += k > thr;
-    c_eq += k == thr;
-  }
-  int i_gt = c_gt, i_eq = c_eq;  // inclusive scans within the wave
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int vg = __shfl_up(i_gt, o), ve = __shfl_up(i_eq, o);
-    if (lane >= o) {
-      i_gt += vg;
-      i_eq += ve;
+  for (int i = 0; i < PER; ++i) {
+    const int e = i * BLOCK + (int)threadIdx.x;
+    key[i] = score_key(__uint_as_float(key[i]));
+    if (e < L) {
+      lo = min(lo, key[i]);
+      hi = max(hi, key[i]);
     }
   }
-  if (lane == 63) wave_cnt[wave] = make_int2(i_gt, i_eq);
+  for (int i = threadIdx.x; i < 512; i += BLOCK) (&hist[0][0])[i] = 0;
+  if (threadIdx.x == 0) n_list = 0;
+  wave_min_max(lo, hi);
+  if (lane == 0) red[wave] = make_uint2(lo, hi);
   __syncthreads();
-  int n_gt = i_gt - c_gt, n_eq = i_eq - c_eq;
-  for (int w = 0; w < wave; ++w) {
-    n_gt += wave_cnt[w].x;
-    n_eq += wave_cnt[w].y;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) {
+    lo = min(lo, red[w].x);
+    hi = max(hi, red[w].y);
   }
-  for (int e = e0; e < e1; ++e) {
-    const uint32_t k = keys[e];
-    if (k > thr) {
-      emit(n_gt + min(n_eq, rem), a + e);
-      ++n_gt;
-    } else if (k == thr) {
-      if (n_eq < rem) emit(n_gt + n_eq, a + e);
-      ++n_eq;
+
+  // keys in [lo, lo + 2^(sh + 8)) are cut into 256 bins of 2^sh; rem of them are still to be picked
+  int sh = max(0, 24 - (int)__clz((int)((hi - lo) | 1u)));
+  uint32_t span = hi - lo;  // highest offset that still belongs to the window
+  int rem = q, n_bin = 0;
+  for (int pass = 0;; ++pass) {
+    int* h = hist[pass & 1];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint32_t off = key[i] - lo;
+      if (i * BLOCK + (int)threadIdx.x < L && key[i] >= lo && off <= span) atomicAdd(&h[off >> sh], 1);
+    }
+    __syncthreads();
+    // every wave for itself, lane 0 the highest bins: the bin in which the count from the top reaches rem
+    const int4 c = *reinterpret_cast<const int4*>(&h[252 - 4 * lane]);
+    const int s = (c.x + c.y) + (c.z + c.w);
+    const int above = wave_scan(s) - s;
+    const bool mine = above < rem && rem <= above + s;
+    const int c3 = above + c.w, c2 = c3 + c.z, c1 = c2 + c.y;
+    int bin = 252 - 4 * lane, cum = c1, in = c.x;
+    if (rem <= c3) {
+      bin += 3, cum = above, in = c.w;
+    } else if (rem <= c2) {
+      bin += 2, cum = c3, in = c.z;
+    } else if (rem <= c1) {
+      bin += 1, cum = c2, in = c.y;
+    }
+    const int src = __ffsll((long long)__ballot(mine)) - 1;
+    bin = __builtin_amdgcn_readlane(bin, src);
+    rem -= __builtin_amdgcn_readlane(cum, src);
+    n_bin = __builtin_amdgcn_readlane(in, src);
+    lo += (uint32_t)bin << sh;
+    span = (1u << sh) - 1u;
+    if (n_bin <= kList || n_bin == rem || sh == 0) break;
+    sh = max(0, sh - 8);
+    int* next = hist[(pass + 1) & 1];
+    if (pass > 0) {  // the bins of two passes ago (every wave has read them: they were read before the last barrier)
+      for (int i = threadIdx.x; i < 256; i += BLOCK) next[i] = 0;
+      __syncthreads();
+    }
+  }
+  // keys above lo + span are in, keys below lo are out, of the n_bin keys in between rem are to be picked
+  const bool all = n_bin == rem, ranked = !all && n_bin <= kList;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    if (i * BLOCK >= L) break;
+    const int e = i * BLOCK + (int)threadIdx.x;
+    const bool valid = e < L && key[i] >= lo;
+    const bool inside = valid && key[i] - lo <= span;
+    const uint64_t top = __ballot(valid && (all || !inside)), mid = __ballot(inside);
+    if (lane == 0) {
+      picked[i * kW + wave] = top;
+      if (!ranked) equal[i * kW + wave] = mid;
+    }
+    if (ranked && inside) list[atomicAdd(&n_list, 1)] = make_uint2(key[i], (uint32_t)e);
+  }
+  __syncthreads();
+  const int words = (L + 63) / 64;
+  if (ranked) {
+    if (wave == 0) {
+      const uint2 me = lane < n_bin ? list[lane] : make_uint2(0u, 0xFFFFFFFFu);
+      int rank = 0;
+      for (int j = 0; j < n_bin; ++j) {
+        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)me.x, j), e = (uint32_t)__builtin_amdgcn_readlane((int)me.y, j);
+        rank += k > me.x || (k == me.x && e < me.y);
+      }
+      if (lane < n_bin && rank < rem) atomicOr((unsigned long long*)&picked[me.y >> 6], 1ull << (me.y & 63));
+    }
+    __syncthreads();
+  } else if (!all) {  // equal keys: the first rem in position order
+    if (wave == 0) {
+      int c[kPerLane], t = 0;
+#pragma unroll
+      for (int i = 0; i < kPerLane; ++i) {
+        const int w = lane * kPerLane + i;
+        c[i] = w < words ? __popcll(equal[w]) : 0;
+        t += c[i];
+      }
+      int seen = wave_scan(t) - t;
+#pragma unroll
+      for (int i = 0; i < kPerLane; ++i) {
+        const int w = lane * kPerLane + i;
+        if (w < words) {
+          uint64_t m = equal[w];
+          for (int drop = seen + c[i] - max(rem, seen); drop > 0; --drop) m &= ~(1ull << (63 - __clzll((long long)m)));
+          picked[w] |= m;
+        }
+        seen += c[i];
+      }
+    }
+    __syncthreads();
+  }
+  if (FLAGS) {  // the segment's map goes into the unit's, shifted to where the segment starts
+    const uint32_t* map = (const uint32_t*)picked;
+    const int s = a & 31;
+    for (int w = threadIdx.x; w < 2 * words; w += BLOCK) {
+      const uint32_t v = map[w];
+      const int at = (a >> 5) + w;
+      if (v << s) atomicOr(&emit.flags[at], v << s);
+      if (s && v >> (32 - s)) atomicOr(&emit.flags[at + 1], v >> (32 - s));
+    }
+    return;
+  }
+  if (wave == 0) {
+    int c[kPerLane], t = 0;
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) {
+      const int w = lane * kPerLane + i;
+      c[i] = w < words ? __popcll(picked[w]) : 0;
+      t += c[i];
+    }
+    int run = wave_scan(t) - t;
+#pragma unroll
+    for (int i = 0; i < kPerLane; ++i) {
+      const int w = lane * kPerLane + i;
+      if (w < words) before[w] = run;
+      run += c[i];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    if (i * BLOCK >= L) break;
+    const int w = i * kW + wave;
+    if (w < words) {
+      const uint64_t m = picked[w];
+      if ((m >> lane) & 1ull)
+        emit.out[before[w] + __popcll(m & ((1ull << lane) - 1ull))] = a + i * BLOCK + (int)threadIdx.x;
     }
   }
 }
@@ -616,27 +692,34 @@ hipError_t launch_select(const ams_params* p, const Dims& d, const int32_t* seq_
                        must ? flags : nullptr, n_words);
   }
   prof_mark("select", s);
-  // expected segment length decides the shape of the selection workgroups
+  // The expected segment length decides the shape of the selection workgroups (one wave: 1024 keys, 256 threads: 4096,
+  // 512: 8192, 1024: 32768).  Segments differ by a factor of two or so, so a shape is left where longer ones would start
+  // to miss the registers: 4096 expected takes 2272 us per step with 512 threads and 2328 with 1024 (2286 with 256, many
+  // of whose segments go through memory); 2048 expected 998 with 256 and 1007 with 512; 512 expected 45.3 with 256 and
+  // 46.7 with one wave; 136 expected 176.5 with one wave and 178.2 with 256.
   const double expect = p->seg_delta > 0.f
                             ? (p->l_max > 0 ? (double)p->l_max : (double)p->t_max * (double)p->seg_delta)
                             : (double)p->t_max / (double)S;
-  const bool small = expect <= 512.0;
   const dim3 grid(S, d.units);
+#define AMS_SELECT(FLAGS, BLOCK, PER)                                                                               \
+  hipLaunchKernelGGL((select_kernel<FLAGS, BLOCK, PER>), grid, dim3(BLOCK), 0, s, d, S, p->budget, g, bounds, quota, \
+                     idx, flags, n_words)
+#define AMS_SELECT_SHAPE(FLAGS)             \
+  if (expect <= 256.0)                     \
+    AMS_SELECT(FLAGS, 64, 16);              \
+  else if (expect <= 2560.0)               \
+    AMS_SELECT(FLAGS, 256, 16);             \
+  else if (expect <= 5120.0)               \
+    AMS_SELECT(FLAGS, 512, 16);             \
+  else                                      \
+    AMS_SELECT(FLAGS, 1024, 32)
   if (!must) {
-    if (small)
-      hipLaunchKernelGGL((select_kernel<false, 64, 1024>), grid, dim3(64), 0, s, d, S, p->budget, g, bounds, quota,
-                         idx, nullptr, 0);
-    else
-      hipLaunchKernelGGL((select_kernel<false, 256, kSelectCap>), grid, dim3(256), 0, s, d, S, p->budget, g, bounds,
-                         quota, idx, nullptr, 0);
+    AMS_SELECT_SHAPE(false);
     return hipGetLastError();
   }
-  if (small)
-    hipLaunchKernelGGL((select_kernel<true, 64, 1024>), grid, dim3(64), 0, s, d, S, p->budget, g, bounds, quota,
-                       idx, flags, n_words);
-  else
-    hipLaunchKernelGGL((select_kernel<true, 256, kSelectCap>), grid, dim3(256), 0, s, d, S, p->budget, g, bounds, quota,
-                       idx, flags, n_words);
+  AMS_SELECT_SHAPE(true);
+#undef AMS_SELECT_SHAPE
+#undef AMS_SELECT
   prof_mark("finalize", s);
   hipLaunchKernelGGL(finalize_kernel, dim3(d.units), dim3(kFinBlock), 0, s, d, seq_lens, p->budget, p->n_sink,
                      p->n_last, g, flags, n_words, idx);

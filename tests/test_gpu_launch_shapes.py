@@ -115,3 +115,40 @@ def test_quota_ties_at_every_register_count(oracle, S):
         B.ams_select(p, to_dev(np.array([T], np.int32)), torch.zeros((1, T), device=DEV), to_dev(bounds), to_dev(mass),
                      quota, idx, n_kept)
         np.testing.assert_array_equal(to_host(quota)[0], oracle.quota(bounds[0], mass[0], budget, 1), err_msg=f"{budget}")
+
+
+@pytest.mark.parametrize("must", [False, True])
+@pytest.mark.parametrize("lens", [[1024, 1025, 63, 64, 65, 1, 0, 130, 200, 2, 40, 7, 250, 90],   # one wave: 1024 keys
+                                  [4096, 4097, 1000, 255, 256, 257],                              # 256 threads
+                                  [8192, 8193, 100, 5000],                                        # 512 threads
+                                  [32768], [32769]])                                              # 1024 threads
+def test_select_at_the_edges_of_its_shapes(oracle, lens, must):
+    """Segments that just fit a shape's registers and that do not; scores that fill one bin over several passes (an
+    outlier and neighbouring floats), ties by the hundred, signed zeros, infinities and NaN."""
+    S, T = len(lens), sum(lens)
+    bounds = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    rng = np.random.default_rng(T + S)
+    g = rng.standard_normal((6, T)).astype(np.float32)
+    g[1] = (1 + rng.integers(0, 70, T) * 2.0 ** -23).astype(np.float32)
+    g[1, ::501] = 3e38
+    g[1, 3::701] = -3e38
+    g[2] = np.round(g[2])
+    g[3] = -1.5
+    g[4] = np.float32(1e-40) * rng.integers(0, 3, T).astype(np.float32)
+    g[5, ::3], g[5, 1::5], g[5, 2::7], g[5, 4::11] = np.nan, -np.inf, np.inf, -0.0
+    for budget in (max(1, T // 16), T // 2, T - 1):
+        p = _stage_params(6, T, S)
+        p.budget = budget
+        if must:
+            p.n_sink, p.n_last = 3, 33
+        mass = np.tile(np.array(lens, np.float32) / T, (6, 1))
+        quota = torch.zeros((6, S), dtype=torch.int32, device=DEV)
+        idx, n_kept = torch.zeros((6, budget), dtype=torch.int32, device=DEV), torch.zeros(6, dtype=torch.int32, device=DEV)
+        B.ams_select(p, to_dev(np.array([T], np.int32)), to_dev(g), to_dev(np.tile(bounds, (6, 1))), to_dev(mass), quota,
+                     idx, n_kept, workspace(p))
+        sinks, last, seg_budget = oracle.must_keep(T, budget, p.n_sink, p.n_last)
+        for i in range(6):
+            q = oracle.quota(bounds, mass[i], seg_budget, 1)
+            np.testing.assert_array_equal(to_host(quota)[i], q)
+            want = oracle.finalize(g[i], oracle.select(g[i], bounds, q), sinks, last, budget)
+            np.testing.assert_array_equal(to_host(idx)[i], want, err_msg=f"row {i} budget {budget}")
