@@ -152,3 +152,11 @@ def test_select_at_the_edges_of_its_shapes(oracle, lens, must):
             np.testing.assert_array_equal(to_host(quota)[i], q)
             want = oracle.finalize(g[i], oracle.select(g[i], bounds, q), sinks, last, budget)
             np.testing.assert_array_equal(to_host(idx)[i], want, err_msg=f"row {i} budget {budget}")
+
+
+@pytest.mark.parametrize("H", [1, 2, 3, 8])
+def test_paged_heads_move_over_the_workgroups(oracle, H):
+    """Paged sweeps give the heads of a chunk to workgroups in an order that moves on: every (unit, chunk) once, for head
+    counts that do and do not divide the period; ragged lengths end chunks early."""
+    w = inputs.CONFIGS[2].scaled(L=2, B=5, H=H, T=2100, T_min=900, D=64, W=4, budget=100, S=4, n_spans=2, span_len=(8, 90))
+    _run(oracle, w)
