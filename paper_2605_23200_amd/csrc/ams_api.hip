@@ -26,14 +26,14 @@ static int padded_queries(int n, bool bf16) {
 
 // Tokens per workgroup of the scoring sweeps: as many as possible (the query window is loaded once per
 // workgroup), but few enough that the launch has a couple of thousand workgroups to fill 256 CUs.
-static int pick_score_chunk(size_t units, int t_max, bool paged) {
+static int pick_score_chunk(size_t units, int t_max, bool paged, int most) {
   // measured on 256 units: 4096 tokens at 32k positions (1.060 ms per step against 1.077 with 2048 and
   // 1.13 with 1024), 1024 at 2176 positions (0.208 against 0.229 with 2048); 512 and 256 lose to the
   // per-workgroup load of the query window
   // paged pools (16384 ragged units of up to 16384 positions): 26.4 ms per step with 1024 against 27.3 with
   // 2048, 30.8 with 4096 and 28.0 with 512 -- the eight heads of a (layer, sequence, chunk) share each 2 KB
   // stripe of the pool, and short chunks keep their workgroups close together in time
-  int chunk = paged ? 1024 : kScoreChunk;
+  int chunk = paged ? 1024 : most;
   while (chunk > 1024 && units * (size_t)div_up(t_max, chunk) < 2048) chunk /= 2;
   // a launch that would leave compute units without any workgroup is cut further, down to one 32-key block per
   // wave: 8 fp32 units of 4096 positions 86.7 us per step with 1024 keys (32 workgroups), 69.2 with 512, 59.9
@@ -46,8 +46,11 @@ static int pick_score_chunk(size_t units, int t_max, bool paged) {
 WsLayout ws_layout(const ams_params* p) {
   WsLayout w;
   const size_t units = (size_t)p->n_layers * p->batch * p->n_kv_heads;
-  w.score_chunk = pick_score_chunk(units, p->t_max, false);
-  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true);
+  // the key-based scores collect their g in LDS next to u, next to a larger query window: half the chunk keeps three
+  // workgroups on a CU
+  const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY ? kKeysChunk : kScoreChunk;
+  w.score_chunk = pick_score_chunk(units, p->t_max, false, most);
+  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most);
   w.n_chunks = div_up(p->t_max, w.score_chunk);
   w.n_chunks_paged = div_up(p->t_max, w.score_chunk_paged);
   const size_t nc_cap = (size_t)max(w.n_chunks, w.n_chunks_paged);  // the parameters do not say which layout comes

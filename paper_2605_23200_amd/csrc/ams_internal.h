@@ -56,6 +56,7 @@ __device__ __forceinline__ int seq_len(const Dims& d, const int32_t* seq_lens, i
 #define AMS_SCORE_CHUNK 4096
 #endif
 constexpr int kScoreChunk = AMS_SCORE_CHUNK;  // most tokens per workgroup of the scoring kernels
+constexpr int kKeysChunk = kScoreChunk < 2048 ? kScoreChunk : 2048;  // most, for the key-based scorers
 constexpr int kMinScoreChunk = 128;           // fewest: one 32-key block per wave
 constexpr int kChunk = 4096;       // positions per workgroup of the mass / prefix kernels
 
@@ -117,6 +118,9 @@ hipError_t launch_score_oneread(const ams_params* p, const Dims& d, const KvDev&
 // one (sum of max(u,0)+eps, sum of old credit) entry per unit at a.vc_part[unit] when a.vc_part is set.
 struct ScoreArgs;
 hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, hipStream_t s, bool* ran);
+// The two sweeps with the key-diversity score, or the mean cosines of the redundancy-aware one, left in a.g (bf16 caches,
+// no causal window; score_keys.hip).
+hipError_t launch_key_sweeps(const ScoreArgs& a, int nb, int head_dim, bool cosines, hipStream_t s);
 constexpr int kUnitScorerMinUnits = 128;  // fewer units leave most of the 256 CUs idle: the sweeps win there
 
 // ams_ema_update, ams_mass_segment, ams_mass_segment_static (the fused step uses launch_unit_mass).

@@ -178,3 +178,22 @@ def test_first_reference_and_its_second_walk(oracle, G, W):
     job.step()
     check_properties_all_units(job)
     check_units(oracle, job, host, np.zeros((w.units, w.T), np.float32), units + [1, 2])
+
+
+@pytest.mark.parametrize("scorer", [B.SCORER_KEYDIFF, B.SCORER_REDUNDANCY])
+@pytest.mark.parametrize("D,G,W,T,paged", [(128, 4, 32, 2049, False), (128, 1, 32, 4100, False), (64, 2, 32, 127, False),
+                                            (64, 7, 32, 2048, True), (128, 8, 32, 2500, True), (128, 7, 32, 3333, False),
+                                            (64, 4, 32, 31, False), (128, 4, 32, 1, False)])
+def test_key_scores_ride_along_with_the_sweeps(oracle, scorer, D, G, W, T, paged):
+    """Every number of column blocks, chunk edges, ragged last blocks, single keys; a sequence with zero keys among the
+    others.  (The sum of a shorter second sequence must not see the rows past its end.)"""
+    w = inputs.CONFIGS[1].scaled(L=1, B=2, H=2, D=D, G=G, W=W, T=T, T_min=T, budget=min(128, T), S=4, n_spans=2,
+                                 span_len=(1, 60), paged=paged)
+    host = inputs.dense_cache(w, n_threads=4)
+    host["seq_lens"][:] = [T, max(1, T - 5)]
+    host["K"][0, 0, 1, ::3] = 0
+    host["K"][0, 1, :, max(1, T - 5):] = inputs.to_bf16_bits(np.full(1, 1e4, np.float32))[0]
+    job = Job(w, host, scorer=scorer)
+    job.step()
+    check_properties_all_units(job)
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), list(range(w.units)), scorer=scorer)
