@@ -197,3 +197,11 @@ def test_key_scores_ride_along_with_the_sweeps(oracle, scorer, D, G, W, T, paged
     job.step()
     check_properties_all_units(job)
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), list(range(w.units)), scorer=scorer)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("budget", [1, 15, 16, 17, 31, 33, 65])
+def test_compaction_at_the_edges_of_its_row_groups(oracle, dtype, D, budget):
+    """16, 32 or 64 rows per workgroup: kept counts around them, rows of 128 to 512 bytes."""
+    w = inputs.CONFIGS[1].scaled(L=1, H=2, G=1, W=8, D=D, dtype=dtype, T=300, budget=budget, S=2, n_spans=1, span_len=(8, 40))
+    _run(oracle, w)
