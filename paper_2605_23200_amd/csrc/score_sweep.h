@@ -179,15 +179,10 @@ __device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
   return a.causal ? max(0, (T - a.d.W + 1) / 32 * 32) : T;
 }
 
-//
-// First reference (five or more column blocks, where the vector instructions bound the sweep): the exponentials are taken
-// relative to each lane's largest logit of the wave's FIRST block, and later blocks do not look for the maximum.  A sum in
-// floating point has the same relative error at any scale, so a later, larger logit only matters when it makes the
-// exponents large: a wave whose sums pass 2^24 walks its blocks again with the maximum tracked.  112 units of 131072
-// positions, 224 queries: 2239 -> 2167 us per step.  With four column blocks and less the sweep waits for memory
-// (982 -> 977 for 256 units of 32768) and short chunks lose by it (161 -> 165 us for ragged caches of up to 9001
-// positions, 45.6 -> 46.8 for 8 fp32 units of 4096), so they track; so does the sweep that adds up the keys, which spills
-// otherwise (2550 against 2665 us for 112 units of 131072 positions; with unit vectors it is 3347 against 3823).
+// The reference of the exponentials follows the running maximum, so that the largest logit of a wave has the exponent 0.  A
+// reference taken from the wave's first block alone saves the maxima (2239 -> 2167 us per step for 112 units of 131072
+// positions, 224 queries), but a later, dominant key then has an exponent of up to 24 in fp32, which costs its share 1e-6;
+// larger ones need the wave's blocks again, and the moment sweep next to it took 1949 us instead of 1858 (65536 positions).
 //
 // KEYS (key-diversity and redundancy-aware scores, bf16 caches): the sums of the keys, or of the unit vectors, that those
 // scores need ride along with the first sweep, and their dot products with the keys along with the second, so that K is
@@ -203,7 +198,6 @@ template <bool BF16, int NB, bool TAIL, bool MOMENTS, int HD, int KEYS = KEYS_NO
 __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
   constexpr int NG = kGroup<NB>, QS = Tr<BF16, HD>::kQStride;
-  constexpr bool kFirstRef = kPipe<BF16, NB, TAIL> && !MOMENTS && KEYS != KEYS_MEAN;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch[4][NB * 32];
   int unit, chunk;
@@ -248,12 +242,10 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
     z[nb] = 0.f;
   }
   const float c2 = a.c2;
-  bool recount = false;  // a second walk over the blocks: the keys have been added already
   float* g_row = MOMENTS ? a.g + (int64_t)unit * a.d.t_stride : nullptr;
   __shared__ float g_sm[MOMENTS ? kScoreChunk : 1];  // the chunk's moment scores, written once at the end
-  auto block_of = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0, auto ragged_c, auto track_c) __attribute__((always_inline)) {
+  auto block_of = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0, auto ragged_c) __attribute__((always_inline)) {
     constexpr bool ragged = decltype(ragged_c)::value;  // the block reaches past the end of the cache
-    constexpr bool track = decltype(track_c)::value;    // the reference follows the running maximum
     // the query fragments are re-read from LDS for every block: keeping them in registers across
     // blocks would cost more registers than the reads cost time, so their address is made opaque
     int qoff = 0;
@@ -288,20 +280,17 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = (t0 + acc_row(i, hf) >= T) ? -INFINITY : acc[i];
       }
-      float mx = m[nb];
-      if (track) {
-        float mr = acc[0];
+      float mr = acc[0];
 #pragma unroll
-        for (int i = 1; i < 16; ++i) mr = fmaxf(mr, acc[i]);
-        mx = fmaxf(mx, mr * c2);  // c2 > 0: the maximum commutes with the scale
-      }
+      for (int i = 1; i < 16; ++i) mr = fmaxf(mr, acc[i]);
+      const float mx = fmaxf(m[nb], mr * c2);  // c2 > 0: the maximum commutes with the scale
       float sum = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i], c2, -mx));
-      z[nb] = track ? __builtin_fmaf(z[nb], __builtin_amdgcn_exp2f(m[nb] - mx), sum) : z[nb] + sum;
+      z[nb] = __builtin_fmaf(z[nb], __builtin_amdgcn_exp2f(m[nb] - mx), sum);
       m[nb] = mx;
     };
-    if constexpr (kPipe<BF16, NB, TAIL> && (!ragged || kFirstRef)) {
+    if constexpr (kPipe<BF16, NB, TAIL> && !ragged) {
       constexpr int NV = Tr<BF16, HD>::kAVecs;
       const char* qb = qlds + qoff + (lane & 31) * QS + (lane >> 5) * (Tr<BF16, HD>::kRowBytes / 2);
       uint4 bq[2][NV];
@@ -336,7 +325,7 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
       }
     }
     if constexpr (KEYS != KEYS_NONE)
-      if (!kFirstRef || !recount) add_keys<HD, KEYS == KEYS_COS>(av, ident, inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
+      add_keys<HD, KEYS == KEYS_COS>(av, ident, inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
     if (MOMENTS) {
       const int c = lane & 31;
       float rr[16];
@@ -353,53 +342,18 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
   };
   auto block = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0) __attribute__((always_inline)) {
     if (t0 + 32 > T)
-      block_of(av, t0, std::true_type{}, std::bool_constant<!kFirstRef>{});
+      block_of(av, t0, std::true_type{});
     else
-      block_of(av, t0, std::false_type{}, std::bool_constant<!kFirstRef>{});
+      block_of(av, t0, std::false_type{});
   };
   // this wave's blocks: every fourth block of 32 tokens up to the end of the chunk (or of the cache)
-  auto walk = [&](int t0, uint4 (&cur)[Tr<BF16, HD>::kAVecs], uint4 (&next)[Tr<BF16, HD>::kAVecs]) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (; t0 < t_lim; t0 += 256) {
-      if (t0 + 128 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 128, T, lane, next, blk, c0);
-      block(cur, t0);
-      if (t0 + 128 >= t_lim) break;
-      if (t0 + 256 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 256, T, lane, cur, blk, c0);
-      block(next, t0 + 128);
-    }
-  };
-  const int t_first = c0 + wave * 32;
-  if constexpr (!kFirstRef) {
-    walk(t_first, av0, av1);
-  } else {
-    constexpr float kSumLimit = 16777216.f;  // 2^24
-#pragma unroll 1
-    for (bool again = false; t_first < t_lim; again = true) {
-      // tracked: the first block, or (again) all of them; on the way out av1 holds the block after the last
-      int t0 = t_first;
-#pragma unroll 1
-      for (;;) {
-        if (t0 + 128 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 128, T, lane, av1, blk, c0);
-        block_of(av0, t0, std::true_type{}, std::true_type{});
-        t0 += 128;
-        if (!again || t0 >= t_lim) break;
-#pragma unroll
-        for (int i = 0; i < Tr<BF16, HD>::kAVecs; ++i) av0[i] = av1[i];
-      }
-      if (again) break;
-      walk(t0, av1, av0);
-      bool high = false;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) high = high || !(z[nb] <= kSumLimit);
-      if (!__ballot(high)) break;
-      recount = true;
-      load_a<BF16, HD>(a, l, b, h, t_first, T, lane, av0, blk, c0);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        m[nb] = kNegInit;
-        z[nb] = 0.f;
-      }
-    }
+  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 256) {
+    if (t0 + 128 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 128, T, lane, av1, blk, c0);
+    block(av0, t0);
+    if (t0 + 128 >= t_lim) break;
+    if (t0 + 256 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 256, T, lane, av0, blk, c0);
+    block(av1, t0 + 128);
   }
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {

@@ -1,0 +1,43 @@
+"""Inputs on which a result hangs on the precision of what it is formed from.  Each bound is derived from the roundings that
+a result may carry."""
+import numpy as np
+import pytest
+
+from paper_2605_23200_amd import binding as B
+from paper_2605_23200_amd import inputs
+from paper_2605_23200_amd.harness import Job
+from gpu_util import assert_close_rel, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("G", [4, 5, 7, 8])
+def test_two_dominant_keys_share_the_mass(oracle, G):
+    """Two keys with the same logit, 20 to 23 powers of two above the first keys their waves see, in blocks of different
+    waves.  All queries are ones and every key is one repeated number, so the logits are exact and the two keys hold nearly
+    half of the mass each.  What is left: the exponential of each key's own maximum and its rounded argument, the weight, at
+    most eight column sums (of equal terms: the inexact ones are 3, 5, 6 and 7) and the store, 6 roundings of 2^-24 = 3.6e-7.
+    An exponent of 20 carried in fp32 adds up to 1.3e-6 of the share on its own."""
+    w = inputs.CONFIGS[1].scaled(L=8, H=8, G=G, W=32, T=4200, budget=300, S=4, n_spans=0)
+    host = inputs.dense_cache(w, n_threads=8)
+    rng = np.random.default_rng(G)
+    one = lambda x: inputs.to_bf16_bits(np.float32(x))
+    host["Q"][:] = one(1.0)
+    host["K"][:] = one(-1.0)
+    t1, t2 = 130, 200                         # second blocks of waves 0 and 2 (blocks of 32 keys, four waves)
+    for l in range(8):
+        for h in range(8):
+            k = host["K"][l, 0, h]
+            r1, r2 = rng.integers(1, 128, 2) / 1024.0      # raw logits -16 .. 0 of the waves' first blocks
+            k[0:32], k[64:96] = one(-r1), one(-r2)
+            k[t1], k[t2] = one(1.25), one(1.25)            # raw logit 160
+    job = Job(w, host)
+    job.step()
+    u = to_host(job.intermediates().u)
+    worst = 0.0
+    for i in range(0, 64, 3):
+        l, h = i // 8, i % 8
+        want, _ = oracle.score(host["Q"][l, 0, h * G:(h + 1) * G].reshape(-1, w.D), host["K"][l, 0, h], G, 32)
+        assert_close_rel(u[i, :w.T], want, what=f"u unit {i}")
+        worst = max(worst, np.abs(u[i, [t1, t2]].astype(np.float64) / want[[t1, t2]] - 1).max())
+    assert worst < 3.6e-7, f"{worst:.2e}"

@@ -162,11 +162,11 @@ def test_paged_heads_move_over_the_workgroups(oracle, H):
     _run(oracle, w)
 
 
+@pytest.mark.parametrize("scorer", [B.SCORER_MEAN_WINDOW, B.SCORER_KEYDIFF, B.SCORER_REDUNDANCY])
 @pytest.mark.parametrize("G,W", [(5, 32), (7, 32), (8, 32)])
-def test_first_reference_and_its_second_walk(oracle, G, W):
-    """Five or more column blocks: exponentials relative to a wave's first block.  One key of each unit, in a wave's first,
-    second, middle or last (ragged) block, lies 6 to 100 units above the others: below and above the limit at which the
-    wave walks its blocks again."""
+def test_one_dominant_key_in_any_block(oracle, G, W, scorer):
+    """Five or more column blocks.  One key of each unit, in a wave's first, second, middle or last (ragged) block, lies 6 to
+    100 units above the others: the running maximum rises late or early, and the key sums see every key once."""
     w = inputs.CONFIGS[1].scaled(L=8, H=8, G=G, W=W, T=4200, budget=300, S=4, n_spans=3, span_len=(8, 90))
     host = inputs.dense_cache(w, n_threads=8)
     units, where = list(range(0, 64, 7)), (0, 40, 128, 150, 700, 1023, 1024, 3000, 4199)
@@ -174,10 +174,10 @@ def test_first_reference_and_its_second_walk(oracle, G, W):
         l, h = i // 8, i % 8
         q = inputs.bf16_bits_to_f32(host["Q"][l, 0, h * G + n % G, n % W])
         host["K"][l, 0, h, where[n % len(where)]] = inputs.to_bf16_bits(((0.5, 1.5, 4.0, 8.0)[n % 4] * q).astype(np.float32))
-    job = Job(w, host)
+    job = Job(w, host, scorer=scorer)
     job.step()
     check_properties_all_units(job)
-    check_units(oracle, job, host, np.zeros((w.units, w.T), np.float32), units + [1, 2])
+    check_units(oracle, job, host, np.zeros((w.units, w.T), np.float32), units + [1, 2], scorer=scorer)
 
 
 @pytest.mark.parametrize("scorer", [B.SCORER_KEYDIFF, B.SCORER_REDUNDANCY])
