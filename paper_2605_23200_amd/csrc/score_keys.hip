@@ -5,10 +5,13 @@
 // 0.41 ms of sweeps for 256 units of 32768 keys), while the sweeps leave the matrix cores idle for two thirds of the time.
 // Here a tile times the identity turns it into one channel per lane for the sums (8 more matrix instructions per block of
 // 32 keys, next to 32 for 128 queries), the diagonal of the tile times itself gives the squared lengths (8), and the mean
-// key joins the query columns as three bf16 terms (8): fp32 products and sums as before, the ratio in double.  The sweeps
-// then take 0.52 + 0.52 ms (key diversity; 1770 -> 1145 us per step) and 0.60 + 0.49 ms (mean cosines; 1891 -> 1281 with
-// the softmax partials of the cosines taken where they are formed).  fp32 caches, the causal window (whose newest keys go
-// through the tail kernels) and the one-launch path of short caches keep the streaming kernels.
+// key joins the query columns as three bf16 terms (8).  The precision is that of the streaming kernels: the sums of the keys,
+// and of the unit vectors with their lengths' reciprocals, in double; the squared lengths and the products with the mean key
+// in fp32; the ratio in double.  (Sums of 16 keys in fp32 first took 2 % less, 1166 against 1193 us per step and 1299 against
+// 1326, but lose a mean key far below the size of its keys.)  256 units of 32768 keys: 1734 -> 1193 us per step for the key
+// diversity, 1927 -> 1326 for the mean cosines with the softmax partials of the cosines taken where they are formed.  fp32
+// caches, the causal window (whose newest keys go through the tail kernels) and the one-launch path of short caches keep
+// the streaming kernels.
 #include "score_sweep.h"
 
 namespace ams {

@@ -94,16 +94,16 @@ __device__ __forceinline__ float key_norm2(const floatx16& gram, int c) {
 }
 
 // Adds a block's keys to this lane's running sums.  A key tile times the identity is the tile itself with one channel per
-// lane and 16 tokens in its registers (exact), which are then added up: in fp32 inside the block (16 numbers of 8
-// significant bits), in double across blocks.  ident: the two halves of the identity, one per 8 columns.
+// lane and 16 tokens in its registers (exact), which are then added up in double like in the streaming kernels: keys that
+// cancel leave a sum far below their size.  ident: the two halves of the identity, one per 8 columns.
 template <int HD, bool COS>
-__device__ __forceinline__ void add_keys(const uint4 (&av)[Tr<true, HD>::kAVecs], const uint4 (*ident)[64], float* inv_len,
+__device__ __forceinline__ void add_keys(const uint4 (&av)[Tr<true, HD>::kAVecs], const uint4 (*ident)[64], double* inv_len,
                                          int lane, int rows, double (&sum)[HD / 32]) {
   const int hf = lane >> 5;
   if (COS) {  // 1 / length of the block's tokens (0 for a zero key and for rows past the end), through LDS
     const int c = lane & 31;
     const float n2 = key_norm2(key_gram<HD>(av), c);
-    if (((c >> 2) & 1) == hf) inv_len[c] = (n2 > 0.f && c < rows) ? rsqrtf(n2) : 0.f;
+    if (((c >> 2) & 1) == hf) inv_len[c] = (n2 > 0.f && c < rows) ? rsqrt((double)n2) : 0.0;
     // the wave's own LDS accesses stay in order; the compiler must keep them so
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -119,21 +119,15 @@ __device__ __forceinline__ void add_keys(const uint4 (&av)[Tr<true, HD>::kAVecs]
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[2 * cb]), I0, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[2 * cb + 1]), I1, acc, 0, 0, 0);
-    float t[4];  // four independent chains
+    double t[2] = {sum[cb], 0.0};  // two independent chains
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (COS) {
-        const float4 w = *(const float4*)(inv_len + 8 * q + 4 * hf + off);
-        t[q] = __builtin_fmaf(acc[4 * q + 3], w.w,
-                              __builtin_fmaf(acc[4 * q + 2], w.z, __builtin_fmaf(acc[4 * q + 1], w.y, acc[4 * q] * w.x)));
-      } else {
-        float x[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = acc_row(4 * q + i, hf) < rows ? acc[4 * q + i] : 0.f;
-        t[q] = (x[0] + x[1]) + (x[2] + x[3]);
-      }
+    for (int i = 0; i < 16; ++i) {
+      if (COS)
+        t[i & 1] = __builtin_fma((double)acc[i], inv_len[acc_row(i, hf) + off], t[i & 1]);
+      else
+        t[i & 1] += acc_row(i, hf) < rows ? (double)acc[i] : 0.0;
     }
-    sum[cb] += (double)((t[0] + t[1]) + (t[2] + t[3]));
+    sum[cb] = t[0] + t[1];
   }
 }
 // Channel whose sum lane n of a half wave holds in sum[cb].
@@ -221,7 +215,7 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
   if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
   load_q<BF16, NB, HD>(a, l, b, h, qlds);
   __shared__ uint4 ident[KEYS ? 2 : 1][64];
-  __shared__ __align__(16) float inv_len[KEYS == KEYS_COS ? 4 : 1][32];
+  __shared__ __align__(16) double inv_len[KEYS == KEYS_COS ? 4 : 1][32];
   double ksum[KEYS ? HD / 32 : 1];
   if constexpr (KEYS != KEYS_NONE) {
     if (threadIdx.x < 128) {

@@ -1,12 +1,12 @@
-"""Inputs on which a result hangs on the precision of what it is formed from.  Each bound is derived from the roundings that
-a result may carry."""
+"""Inputs on which a result hangs on the precision of its intermediate sums: dominant keys, keys that nearly cancel.
+Each bound is derived from the roundings that a result may carry."""
 import numpy as np
 import pytest
 
 from paper_2605_23200_amd import binding as B
 from paper_2605_23200_amd import inputs
 from paper_2605_23200_amd.harness import Job
-from gpu_util import assert_close_rel, to_host
+from gpu_util import assert_close_rel, assert_close_terms, score_term_magnitudes, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -41,3 +41,25 @@ def test_two_dominant_keys_share_the_mass(oracle, G):
         assert_close_rel(u[i, :w.T], want, what=f"u unit {i}")
         worst = max(worst, np.abs(u[i, [t1, t2]].astype(np.float64) / want[[t1, t2]] - 1).max())
     assert worst < 3.6e-7, f"{worst:.2e}"
+
+
+@pytest.mark.parametrize("dtype,D,G,W", [("bf16", 128, 4, 32), ("bf16", 128, 1, 8), ("bf16", 64, 7, 32), ("bf16", 128, 8, 32),
+                                         ("f32", 128, 2, 16)])
+def test_mean_key_of_keys_that_cancel(oracle, dtype, D, G, W):
+    """Two of every four keys cancel and leave a mean key 2^-22 of their size, which only sums in double keep (the oracle
+    sums in double; the products with the mean key are fp32, 1e-5 of their terms as everywhere)."""
+    T = 1500
+    w = inputs.CONFIGS[1].scaled(L=1, H=2, D=D, G=G, W=W, T=T, dtype=dtype, budget=100, S=4, n_spans=0)
+    host = inputs.dense_cache(w, n_threads=4)
+    k = inputs.as_f32(host["K"]).copy()
+    k[..., 1::2, :] *= np.float32(2.0 ** -22)
+    k[..., 2::4, :] = -k[..., 0::4, :][..., :k[..., 2::4, :].shape[-2], :]
+    k[..., T // 4 * 4:, :] *= np.float32(2.0 ** -22)
+    host["K"] = inputs._store(k, dtype)
+    job = Job(w, host, scorer=B.SCORER_KEYDIFF)
+    job.step()
+    g = to_host(job.intermediates().g)
+    for h in range(2):
+        q = host["Q"][0, 0, h * G:(h + 1) * G].reshape(-1, D)
+        _, want = oracle.score(q, host["K"][0, 0, h], G, W, B.SCORER_KEYDIFF)
+        assert_close_terms(g[h, :T], want, score_term_magnitudes(B.SCORER_KEYDIFF, q, host["K"][0, 0, h]), what=f"g unit {h}")
