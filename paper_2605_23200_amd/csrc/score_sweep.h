@@ -181,7 +181,10 @@ __device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
 // KEYS (key-diversity and redundancy-aware scores, bf16 caches): the sums of the keys, or of the unit vectors, that those
 // scores need ride along with the first sweep, and their dot products with the keys along with the second, so that K is
 // streamed twice and not four times (score_keys.hip).  The unit vectors take two waves per SIMD: with the registers of
-// three the first sweep spills (1281 against 1415 us per step for 256 units of 32768 positions).
+// three the first sweep spills (1281 against 1415 us per step for 256 units of 32768 positions).  With seven or eight column
+// blocks of 128 channels the pipeline over them spills at two waves as well (52 and 56 registers): there the blocks are taken
+// in two groups of accumulator tiles (none and 13; 1894 -> 1451 us for 112 units of 65536 positions and 224 queries, 894 ->
+// 791 for 256 units of 8192 and 256 queries, where the streaming kernels take 790).
 //
 // MOMENTS (expected-attention score, Sec. 3.3 plug-in scorer): the log of the Gaussian moment of the
 // window's queries is mean_n s + var_n s / 2 over the N logits of a token.  It needs no softmax
@@ -191,7 +194,8 @@ __device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
 template <bool BF16, int NB, bool TAIL, bool MOMENTS, int HD, int KEYS = KEYS_NONE>
 __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
-  constexpr int NG = kGroup<NB>, QS = Tr<BF16, HD>::kQStride;
+  constexpr bool kSpare = KEYS == KEYS_COS && HD == 128 && NB >= 7;  // see KEYS above
+  constexpr int NG = kSpare ? 4 : kGroup<NB>, QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch[4][NB * 32];
   int unit, chunk;
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
       z[nb] = __builtin_fmaf(z[nb], __builtin_amdgcn_exp2f(m[nb] - mx), sum);
       m[nb] = mx;
     };
-    if constexpr (kPipe<BF16, NB, TAIL> && !ragged) {
+    if constexpr (kPipe<BF16, NB, TAIL> && !kSpare && !ragged) {
       constexpr int NV = Tr<BF16, HD>::kAVecs;
       const char* qb = qlds + qoff + (lane & 31) * QS + (lane >> 5) * (Tr<BF16, HD>::kRowBytes / 2);
       uint4 bq[2][NV];
@@ -306,17 +310,22 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
           col_hints<NV, MOMENTS ? 10 : 6, 2, false>();
       }
     } else {
-#pragma unroll
-      for (int g0 = 0; g0 < NB; g0 += NG) {
-        floatx16 acc[NG];
-        tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+      auto group = [&](auto g0_c) __attribute__((always_inline)) {
+        constexpr int g0 = decltype(g0_c)::value, n = NB - g0 < NG ? NB - g0 : NG;
+        floatx16 acc[n];
+        tile_mma<BF16, n, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
         if (MOMENTS) {
 #pragma unroll
-          for (int k = 0; k < NG; ++k) col_moments(acc[k], g0 + k);
+          for (int k = 0; k < n; ++k) col_moments(acc[k], g0 + k);
         }
 #pragma unroll
-        for (int k = 0; k < NG; ++k) col_stats(acc[k], g0 + k);
-      }
+        for (int k = 0; k < n; ++k) col_stats(acc[k], g0 + k);
+      };
+      group(std::integral_constant<int, 0>{});
+      if constexpr (NB > NG) group(std::integral_constant<int, NG>{});
+      if constexpr (NB > 2 * NG) group(std::integral_constant<int, 2 * NG>{});
+      if constexpr (NB > 3 * NG) group(std::integral_constant<int, 3 * NG>{});
+      static_assert(NB <= 4 * NG, "four groups at most");
     }
     if constexpr (KEYS != KEYS_NONE)
       add_keys<HD, KEYS == KEYS_COS>(av, ident, inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
