@@ -195,7 +195,7 @@ template <bool BF16, int NB, bool TAIL, bool MOMENTS, int HD, int KEYS = KEYS_NO
 __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
   constexpr bool kSpare = KEYS == KEYS_COS && HD == 128 && NB >= 7;  // see KEYS above
-  constexpr int NG = kSpare ? 4 : kGroup<NB>, QS = Tr<BF16, HD>::kQStride;
+  constexpr int NG = kGroup<NB>, QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch[4][NB * 32];
   int unit, chunk;
@@ -309,23 +309,28 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
         else if (nb + 1 < NB)
           col_hints<NV, MOMENTS ? 10 : 6, 2, false>();
       }
-    } else {
+    } else if constexpr (kSpare) {
       auto group = [&](auto g0_c) __attribute__((always_inline)) {
-        constexpr int g0 = decltype(g0_c)::value, n = NB - g0 < NG ? NB - g0 : NG;
+        constexpr int g0 = decltype(g0_c)::value, n = NB - g0 < 4 ? NB - g0 : 4;
         floatx16 acc[n];
         tile_mma<BF16, n, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
-        if (MOMENTS) {
-#pragma unroll
-          for (int k = 0; k < n; ++k) col_moments(acc[k], g0 + k);
-        }
 #pragma unroll
         for (int k = 0; k < n; ++k) col_stats(acc[k], g0 + k);
       };
       group(std::integral_constant<int, 0>{});
-      if constexpr (NB > NG) group(std::integral_constant<int, NG>{});
-      if constexpr (NB > 2 * NG) group(std::integral_constant<int, 2 * NG>{});
-      if constexpr (NB > 3 * NG) group(std::integral_constant<int, 3 * NG>{});
-      static_assert(NB <= 4 * NG, "four groups at most");
+      group(std::integral_constant<int, 4>{});
+    } else {
+#pragma unroll
+      for (int g0 = 0; g0 < NB; g0 += NG) {
+        floatx16 acc[NG];
+        tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+        if (MOMENTS) {
+#pragma unroll
+          for (int k = 0; k < NG; ++k) col_moments(acc[k], g0 + k);
+        }
+#pragma unroll
+        for (int k = 0; k < NG; ++k) col_stats(acc[k], g0 + k);
+      }
     }
     if constexpr (KEYS != KEYS_NONE)
       add_keys<HD, KEYS == KEYS_COS>(av, ident, inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
