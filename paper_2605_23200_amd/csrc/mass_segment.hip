@@ -683,29 +683,27 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
     const int n = n_reseg;
     for (int i = threadIdx.x; i < S; i += BLOCK) bounds[i + 1] = i < n ? reseg[i] : T;
     __syncthreads();
-    if (n_sub <= kCapSub) {
-      // prefix in front of every bound: the end of the piece before the one that holds the last position in front of
-      // it, plus the positions of that piece in front of the bound
-      for (int i = (int)threadIdx.x / kSubLanes; i <= S; i += kGroups16) {
-        const int bnd = bounds[i];
-        const int q = (bnd - 1) / kSub;
-        float x[4] = {0.f, 0.f, 0.f, 0.f};
-        if (bnd > 0) load_run(m_used, q * kSub + l16 * 4, bnd, a.vec, x, 0.f);
-        double p[4];
-        sub_scan(x, p);
-        if (l16 == kSubLanes - 1) cpre[i] = bnd > 0 ? (q > 0 ? ends[q - 1] : 0.0) + p[3] : 0.0;
-      }
-      __syncthreads();
-      for (int i = threadIdx.x; i < S; i += BLOCK) mass[i] = (float)(cpre[i + 1] - cpre[i]);
-    } else {
-      for (int sg = wave; sg < S; sg += kW) {
-        const int lo = bounds[sg], hi = bounds[sg + 1];
-        double sm = 0.0;
-        for (int t = lo + lane; t < hi; t += 64) sm += (double)m_used[t];
+    // the masses of the final segments: each the sum of its own positions (the whole pieces inside and the rest of the
+    // pieces at its ends), because a segment may hold far less than the last bit of the prefix in front of it
+    for (int sg = (int)threadIdx.x / kSubLanes; sg < S; sg += kGroups16) {
+      const int lo = bounds[sg], hi = bounds[sg + 1], q0 = lo / kSub, q1 = (hi - 1) / kSub;
+      double sum = 0.0;
+      if (hi > lo) {
+        const int t0 = q0 * kSub + l16 * 4, t1 = q1 * kSub + l16 * 4;
+        float x0[4], x1[4] = {0.f, 0.f, 0.f, 0.f};
+        load_run(m_used, t0, hi, a.vec, x0, 0.f);
+        if (q1 > q0) load_run(m_used, t1, hi, a.vec, x1, 0.f);
+#pragma unroll 4
+        for (int q = q0 + 1 + l16; q < q1; q += kSubLanes) {
+          const int64_t at = (int64_t)unit * a.n_sub + q;
+          sum += kSigned ? ((const double2*)a.sub)[at].x : a.sub[at];
+        }
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) sm += __shfl_xor(sm, d);
-        if (lane == 0) mass[sg] = (float)sm;
+        for (int i = 0; i < 4; ++i) sum += (t0 + i >= lo ? (double)x0[i] : 0.0) + (double)x1[i];
       }
+#pragma unroll
+      for (int d = kSubLanes / 2; d >= 1; d >>= 1) sum += __shfl_xor(sum, d);
+      if (l16 == 0) mass[sg] = (float)sum;
     }
   } else {
     for (int i = threadIdx.x; i < S; i += BLOCK) {
@@ -735,7 +733,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
 }
 
 // 256 threads hold the prefix of 65536 positions and take 16 cuts a round, eight workgroups to a CU; longer caches and
-// more cuts (in Delta mode the masses of all final segments are read off the prefix too) take 1024.
+// more cuts (in Delta mode all final segments are summed, 16 lanes to a segment) take 1024.
 template <int KIND>
 void launch_cuts(const MsArgs& a, const float* m_used, const CutsOut& o, hipStream_t s) {
   if (a.n_sub <= 1024 && (a.delta > 0.0 ? a.S : a.K) <= 33)

@@ -1,12 +1,13 @@
-"""Inputs on which a result hangs on the precision of its intermediate sums: dominant keys, keys that nearly cancel.
-Each bound is derived from the roundings that a result may carry."""
+"""Inputs on which a result hangs on the precision of its intermediate sums: dominant keys, keys that nearly cancel,
+segments whose mass is a tiny part of the prefix.  Each bound is derived from the roundings that a result may carry."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_23200_amd import binding as B
 from paper_2605_23200_amd import inputs
 from paper_2605_23200_amd.harness import Job
-from gpu_util import assert_close_rel, assert_close_terms, score_term_magnitudes, to_host
+from gpu_util import DEV, assert_close_rel, assert_close_terms, score_term_magnitudes, to_dev, to_host, workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +64,28 @@ def test_mean_key_of_keys_that_cancel(oracle, dtype, D, G, W):
         q = host["Q"][0, 0, h * G:(h + 1) * G].reshape(-1, D)
         _, want = oracle.score(q, host["K"][0, 0, h], G, W, B.SCORER_KEYDIFF)
         assert_close_terms(g[h, :T], want, score_term_magnitudes(B.SCORER_KEYDIFF, q, host["K"][0, 0, h]), what=f"g unit {h}")
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("T,l_max", [(9000, 256), (70001, 1024), (300000, 2048)])
+def test_segment_masses_far_below_the_prefix(oracle, T, l_max, static):
+    """Final segments with 1e-12 of the mass and less, behind positions that hold nearly all of it: a mass is a sum of its
+    own positions (double, stored as fp32: 1e-6), not a difference of prefixes near one."""
+    delta, l_min, cap = 0.1, 16, 12 + T // l_max
+    rng = np.random.default_rng(T)
+    m = rng.random((2, T)) * 1e-17
+    m[:, : T // 8] = rng.random((2, T // 8))
+    m[1, -40:] = rng.random(40)
+    m = (m / m.sum(1, keepdims=True)).astype(np.float32)
+    p = B.make_params(n_layers=1, batch=1, n_kv_heads=2, group=1, window=8, t_max=T, budget=64, n_segments=cap,
+                      seg_delta=delta, l_min=l_min, l_max=l_max)
+    bounds, mass = torch.full((2, cap + 1), -3, dtype=torch.int32, device=DEV), torch.full((2, cap), -3.0, device=DEV)
+    args = (p, to_dev(np.array([T], np.int32)), to_dev(m), bounds, mass)
+    if static:
+        B.ams_mass_segment_static(*args)
+    else:
+        B.ams_mass_segment(*args, workspace(p))
+    for i in range(2):
+        b_o, s_o, _ = oracle.segment_adaptive(m[i], delta, l_min, l_max, cap)
+        np.testing.assert_array_equal(to_host(bounds)[i], b_o)
+        assert_close_rel(to_host(mass)[i], s_o, rtol=1e-6, atol=0.0, what=f"seg_mass unit {i}")
