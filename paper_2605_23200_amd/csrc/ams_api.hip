@@ -67,11 +67,8 @@ WsLayout ws_layout(const ams_params* p) {
   w.quota = o;      o += align256(units * (size_t)p->n_segments * sizeof(int32_t));
   w.kbar = o;       o += align256(units * nc_cap * (size_t)p->head_dim * sizeof(double));
   w.park = o;       o += align256(park_score_ws_bytes(w.n_pad));
-  w.n_chunks4k = div_up(p->t_max, kChunk);
   w.vc_part = o;    o += align256(units * (size_t)div_up(p->t_max, kMinScoreChunk) * 2 * sizeof(double));  // finest producer: kMinScoreChunk positions per entry
   w.sub = o;        o += align256(units * (size_t)div_up(p->t_max, 64) * 2 * sizeof(double));
-  w.mpart = o;      o += align256(units * w.n_chunks4k * sizeof(double));
-  w.cpre = o;       o += align256(units * (size_t)(p->n_segments + 1) * sizeof(double));
   w.n_words = div_up(p->t_max, 32);
   w.flags = o;      o += align256(units * (size_t)w.n_words * sizeof(uint32_t));
   w.csum = o;       o += align256(units * sizeof(double));
@@ -301,17 +298,12 @@ int ams_mass_segment_static(const ams_params* p, const int32_t* seq_lens, const 
   const int rc = check_params(p);
   if (rc) return rc;
   if (!seq_lens || !m_used || !bounds || !seg_mass) return AMS_ERR_INVALID_ARG;
-  // the chunk totals and the prefix values at the cuts live in the library's own array
-  WsLayout wl = ws_layout(p);
   const size_t units = (size_t)p->n_layers * p->batch * p->n_kv_heads;
-  wl.vc_part = wl.sub = 0;  // not touched by its kernels
-  wl.mpart = 0;
-  wl.cpre = align256(units * (size_t)wl.n_chunks4k * sizeof(double));
-  const size_t need = wl.cpre + align256(units * (size_t)(p->n_segments + 1) * sizeof(double));
-  if (need > kStaticScratchBytes) return AMS_ERR_UNSUPPORTED;
+  const size_t limit = align256(units * (size_t)div_up(p->t_max, 4096) * 8) + align256(units * (size_t)(p->n_segments + 1) * 8);
+  if (limit > kStaticScratchBytes) return AMS_ERR_UNSUPPORTED;  // the range that the header states
   char* scratch_ptr = nullptr;
   if (static_scratch(&scratch_ptr) != hipSuccess) return AMS_ERR_HIP;
-  return hip_status(launch_segment_static(p, make_dims(p), seq_lens, m_used, bounds, seg_mass, scratch_ptr, wl,
+  return hip_status(launch_segment_static(p, make_dims(p), seq_lens, m_used, bounds, seg_mass, scratch_ptr, ws_layout(p),
                                           (hipStream_t)stream), (hipStream_t)stream);
 }
 

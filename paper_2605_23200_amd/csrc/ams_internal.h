@@ -58,7 +58,6 @@ __device__ __forceinline__ int seq_len(const Dims& d, const int32_t* seq_lens, i
 constexpr int kScoreChunk = AMS_SCORE_CHUNK;  // most tokens per workgroup of the scoring kernels
 constexpr int kKeysChunk = kScoreChunk < 2048 ? kScoreChunk : 2048;  // most, for the key-based scorers
 constexpr int kMinScoreChunk = 128;           // fewest: one 32-key block per wave
-constexpr int kChunk = 4096;       // positions per workgroup of the mass / prefix kernels
 
 // Segments the thresholds k*delta (every k >= 1 with k*delta < 1) cut the unit interval into.
 inline int initial_segments(float delta) {
@@ -71,11 +70,10 @@ inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 // Workspace carving (offsets in bytes, 256-byte aligned).
 struct WsLayout {
-  size_t part_stats, fin_stats, u, g, m_used, bounds, seg_mass, quota, kbar, park, vc_part, sub, mpart, cpre, flags, csum, total;
+  size_t part_stats, fin_stats, u, g, m_used, bounds, seg_mass, quota, kbar, park, vc_part, sub, flags, csum, total;
   int n_chunks, n_pad;
   int score_chunk;  // tokens per workgroup of the scoring kernels for these parameters, dense cache
   int score_chunk_paged, n_chunks_paged;  // the same for a paged cache
-  int n_chunks4k;  // chunks of kChunk positions per unit
   int n_words;     // 32-position words of the kept-set bitmap per unit
 };
 WsLayout ws_layout(const ams_params* p);
@@ -131,7 +129,7 @@ hipError_t launch_segment(const ams_params* p, const Dims& d, const int32_t* seq
                           hipStream_t s);
 hipError_t launch_segment_static(const ams_params* p, const Dims& d, const int32_t* seq_lens,
                                  const float* m_used, int32_t* bounds, float* seg_mass, char* scratch,
-                                 const WsLayout& wl, hipStream_t s);
+                                 WsLayout wl, hipStream_t s);
 // The fused step's mass / EMA / segmentation / quota stages; it also
 // leaves the -1 tail of idx, the kept counts and the cleared bitmap, so launch_select follows with
 // quota_done = true.  vc: the chunk sums the scorer left, if any.

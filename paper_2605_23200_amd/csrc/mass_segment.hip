@@ -12,20 +12,15 @@
 //   unit_cuts_kernel     one workgroup per unit: prefix over the sums of 64, the 64 positions that hold each cut, the
 //                        split / merge pass, the segment masses and (fused step) the quotas
 //
-// ams_mass_segment_static has no room for the sums of 64 and keeps a form that needs only one total per 4096 positions:
-//
-//   chunk_total_kernel   chunk totals of a given m_used
-//   segment_scan_kernel  inclusive prefix P(j) and the first j with P(j) >= k/S for every k
-//   segment_finalize_kernel  segment masses from the prefix at the cuts
-//   resegment_kernel     (Delta mode) split above L_max / merge below L_min, one pass from the left
-//   segment_mass_kernel  (Delta mode) segment masses by summing m_used over the final segments
+// ams_mass_segment_static runs the same kernels on the library's own scratch while the sums of 64 fit there; beyond that
+// unit_cuts_kernel forms them itself, by the same additions in the same order.
 //
 // Normalisers: Z is the actual sum of max(u,0)+eps.  The credit normaliser sum(c_new) is taken as
 // lambda * sum(c_old) + (1 - lambda) and the outer normaliser as 1: both identities hold exactly in
 // real arithmetic (sum(m) = 1) and to ~1e-8 in floating point, far inside the fp32 tolerance, and
 // they remove two dependent sweeps over T.
 //
-// Prefix: P(j) = C + p_local(j), C the prefix in front of the piece (64 positions, or a chunk) that holds j and p_local
+// Prefix: P(j) = C + p_local(j), C the prefix in front of the piece of 64 positions that holds j and p_local
 // the scan inside it; the total of a piece IS p_local of its last position, so the "first position that reaches k/S"
 // tests agree across pieces.  Everything that feeds a comparison is double.
 #include <type_traits>
@@ -38,9 +33,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
-constexpr int kPer = 16;  // consecutive positions per thread
 constexpr int kMaxSegments = 1024;
-static_assert(kBlock * kPer == kChunk, "one workgroup covers one chunk");
 
 // Sum over the workgroup, same value in every thread, fixed order.
 __device__ __forceinline__ double block_sum(double v, double* sm) {
@@ -55,55 +48,7 @@ __device__ __forceinline__ double block_sum(double v, double* sm) {
   return t;
 }
 
-// In-chunk inclusive prefix of the kPer consecutive positions each thread owns, and the chunk
-// total (= prefix of the very last position).  The association is fixed by the thread layout.
-__device__ __forceinline__ void chunk_scan(const float (&x)[kPer], double (&p)[kPer], double& total,
-                                           double* wave_tot, double* bcast) {
-  double ts = 0.0;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) ts += (double)x[i];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double incl = ts;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double v = __shfl_up(incl, o);
-    if (lane >= o) incl += v;
-  }
-  __syncthreads();
-  if (lane == 63) wave_tot[wave] = incl;
-  __syncthreads();
-  double off = 0.0;
-  for (int w = 0; w < wave; ++w) off += wave_tot[w];
-  double run = off + (incl - ts);
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    run += (double)x[i];
-    p[i] = run;
-  }
-  if (threadIdx.x == kBlock - 1) *bcast = run;
-  __syncthreads();
-  total = *bcast;
-}
-
-// Sum of p[0..n) in index order (bit-reproducible), same value in every thread of the workgroup.
-// One wave fetches 64 entries at a time in parallel and adds them up through lane broadcasts, so
-// the cost is one memory latency per 64 entries instead of one per entry.
-__device__ __forceinline__ double ordered_sum(const double* p, int n, double2* sm) {
-  if (threadIdx.x < 64) {
-    double acc = 0.0;
-    for (int base = 0; base < n; base += 64) {
-      const int k = min(64, n - base);
-      double v = 0.0;
-      if ((int)threadIdx.x < k) v = p[base + threadIdx.x];
-      for (int j = 0; j < k; ++j) acc += __shfl(v, j);
-    }
-    if (threadIdx.x == 0) sm->x = acc;
-  }
-  __syncthreads();
-  return sm->x;
-}
-
-// kPer consecutive fp32 of a row: 16-byte accesses when the row allows it.
+// N consecutive fp32 of a row: 16-byte accesses when the row allows it.
 template <int N>
 __device__ __forceinline__ void load_run(const float* row, int j0, int T, bool vec, float (&x)[N], float fill) {
   if (vec && j0 + N <= T) {
@@ -133,7 +78,6 @@ __device__ __forceinline__ void store_run(float* row, int j0, int T, bool vec, c
 struct MsArgs {
   Dims d;
   const int32_t* seq_lens;
-  int n_chunks;      // chunks per unit (stride of the per-chunk arrays)
   int S;             // entries of the per-unit segment arrays
   int K;             // initial segments: thresholds k = 1..K-1 (K == S unless delta > 0)
   double delta;      // > 0: thresholds k*delta; 0: thresholds k/S
@@ -143,20 +87,9 @@ struct MsArgs {
   int vc_stride, vc_tokens;
   double* sub;       // [units][n_sub] sum of m_used per kSub positions; stage call: pairs (sum, largest prefix inside)
   int n_sub;
-  double* mpart;     // [units][n_chunks]  chunk totals of m_used
-  double* cpre;      // [units][S+1]       prefix at the cuts (negative = threshold never reached)
   int32_t* bounds;   // [units][S+1]
   bool vec;          // rows of the fp32 vectors are 16-byte aligned
 };
-
-__device__ __forceinline__ void init_cuts(const MsArgs& a, int unit, int T) {
-  int32_t* bounds = a.bounds + (int64_t)unit * (a.S + 1);
-  double* cpre = a.cpre + (int64_t)unit * (a.S + 1);
-  for (int k = threadIdx.x; k <= a.S; k += kBlock) {
-    bounds[k] = (k == 0) ? 0 : T;
-    cpre[k] = (k == 0) ? 0.0 : -1.0;
-  }
-}
 
 // Partial sums of max(u,0)+eps and of the old credit per 1024 * ROUNDS positions, for the normalisers.
 // Usage as Eq. (1) sees it: with pooling (App. A; Alg. 1 step 1 "optionally smooth") the mean of u over the positions
@@ -333,8 +266,20 @@ __global__ __launch_bounds__(kBlock) void mass_kernel(MsArgs a, const float* u_a
   }
 }
 
-// The sums of 64 positions of a given m_used, each with the largest prefix inside the piece: a caller's values need not
-// be positive, and a threshold may then be reached inside a piece whose end lies below it again.
+// A given m_used, four positions per lane: prefixes p inside the piece and the largest of them over the piece (the same in its
+// 16 lanes).  A caller's values need not be positive: a threshold may be reached inside a piece whose end lies below it again.
+__device__ __forceinline__ double piece_scan(const float (&x)[4], int j0, int T, double (&p)[4]) {
+  sub_scan(x, p);
+  double top = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (j0 + i < T) top = fmax(top, p[i]);
+#pragma unroll
+  for (int o = kSubLanes / 2; o >= 1; o >>= 1) top = fmax(top, __shfl_xor(top, o));
+  return top;
+}
+
+// The sums of 64 positions of a given m_used, each with the largest prefix inside the piece.
 __global__ __launch_bounds__(kBlock) void sub_totals_kernel(MsArgs a, const float* m_all) {
   const int unit = blockIdx.y;
   int l, b, h;
@@ -345,106 +290,9 @@ __global__ __launch_bounds__(kBlock) void sub_totals_kernel(MsArgs a, const floa
   float x[4];
   load_run(m_all + (int64_t)unit * a.d.t_stride, j0, T, a.vec, x, 0.f);
   double p[4];
-  sub_scan(x, p);
-  double top = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (j0 + i < T) top = fmax(top, p[i]);
-#pragma unroll
-  for (int o = kSubLanes / 2; o >= 1; o >>= 1) top = fmax(top, __shfl_xor(top, o));
+  const double top = piece_scan(x, j0, T, p);
   if ((threadIdx.x & (kSubLanes - 1)) == kSubLanes - 1 && j0 - (kSub - 4) < T)
     ((double2*)a.sub)[(int64_t)unit * a.n_sub + j0 / kSub] = make_double2(p[3], top);
-}
-
-__global__ __launch_bounds__(kBlock) void chunk_total_kernel(MsArgs a, const float* m_all) {
-  __shared__ double wave_tot[kWaves];
-  __shared__ double bcast;
-  const int unit = blockIdx.y, chunk = blockIdx.x;
-  int l, b, h;
-  unit_coords(a.d, unit, l, b, h);
-  const int T = seq_len(a.d, a.seq_lens, b);
-  if (chunk * kChunk >= T) return;
-  if (chunk == 0) init_cuts(a, unit, T);
-  const float* m = m_all + (int64_t)unit * a.d.t_stride;
-  const int j0 = chunk * kChunk + threadIdx.x * kPer;
-  float x[kPer];
-  load_run(m, j0, T, a.vec, x, 0.f);
-  double p[kPer], total;
-  chunk_scan(x, p, total, wave_tot, &bcast);
-  if (threadIdx.x == 0) a.mpart[(int64_t)unit * a.n_chunks + chunk] = total;
-}
-
-// Number of thresholds thr[k], k = 1..S-1, that are <= c.  thr[k] holds (double)k / (double)S (or
-// (double)k * delta), the exact value the comparison is defined with; the table keeps divisions out
-// of the per-thread path.  scale (S or 1/delta) only gives the first guess.
-__device__ __forceinline__ int thresholds_reached(double c, int S, const double* thr, double scale) {
-  int f = (int)floor(c * scale);
-  f = max(0, min(S - 1, f));
-  while (f < S - 1 && c >= thr[f + 1]) ++f;
-  while (f > 0 && c < thr[f]) --f;
-  return f;
-}
-
-__global__ __launch_bounds__(kBlock) void segment_scan_kernel(MsArgs a, const float* m_all) {
-  __shared__ double wave_tot[kWaves];
-  __shared__ double bcast;
-  __shared__ double ends[kBlock];
-  __shared__ double thr[kMaxSegments + 1];
-  const int unit = blockIdx.y, chunk = blockIdx.x;
-  int l, b, h;
-  unit_coords(a.d, unit, l, b, h);
-  const int T = seq_len(a.d, a.seq_lens, b);
-  if (chunk * kChunk >= T) return;
-  const float* m = m_all + (int64_t)unit * a.d.t_stride;
-  __shared__ double2 sums;
-  const int K = a.K;
-  const double scale = a.delta > 0.0 ? 1.0 / a.delta : (double)a.S;
-  for (int k = threadIdx.x; k <= K; k += kBlock) thr[k] = a.delta > 0.0 ? (double)k * a.delta : (double)k / (double)a.S;
-  const int j0 = chunk * kChunk + threadIdx.x * kPer;
-  float x[kPer];
-  load_run(m, j0, T, a.vec, x, 0.f);
-  const double C = ordered_sum(a.mpart + (int64_t)unit * a.n_chunks, chunk, &sums);  // prefix before this chunk
-  double p[kPer], total;
-  chunk_scan(x, p, total, wave_tot, &bcast);
-  ends[threadIdx.x] = C + p[kPer - 1];
-  __syncthreads();
-  const double prev_end = threadIdx.x > 0 ? ends[threadIdx.x - 1] : C;
-  int f_prev = thresholds_reached(prev_end, K, thr, scale);
-  int32_t* bounds = a.bounds + (int64_t)unit * (a.S + 1);
-  double* cpre = a.cpre + (int64_t)unit * (a.S + 1);
-  // most threads see no threshold between their neighbour's prefix and their own largest one
-  double p_max = p[0];
-#pragma unroll
-  for (int i = 1; i < kPer; ++i) p_max = fmax(p_max, p[i]);
-  if (thresholds_reached(C + p_max, K, thr, scale) <= f_prev) return;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    if (j0 + i < T) {
-      const double P = C + p[i];
-      const int f_cur = thresholds_reached(P, K, thr, scale);
-      for (int k = f_prev + 1; k <= f_cur; ++k) {  // position j0+i is the first to reach k/S
-        atomicMin(&bounds[k], j0 + i + 1);
-        cpre[k] = P;
-      }
-      f_prev = max(f_prev, f_cur);
-    }
-  }
-}
-
-__global__ void segment_finalize_kernel(MsArgs a, float* seg_mass_all) {
-  const int unit = blockIdx.x;
-  int l, b, h;
-  unit_coords(a.d, unit, l, b, h);
-  const int T = seq_len(a.d, a.seq_lens, b);
-  const int nch = (T + kChunk - 1) / kChunk;
-  double total = 0.0;
-  for (int c = 0; c < nch; ++c) total += a.mpart[(int64_t)unit * a.n_chunks + c];
-  const double* cpre = a.cpre + (int64_t)unit * (a.S + 1);
-  for (int i = threadIdx.x; i < a.S; i += blockDim.x) {
-    const double lo = cpre[i] < 0.0 ? total : cpre[i];
-    const double hi = (i + 1 == a.S || cpre[i + 1] < 0.0) ? total : cpre[i + 1];
-    seg_mass_all[(int64_t)unit * a.S + i] = (float)(hi - lo);
-  }
 }
 
 // Split / merge pass over the initial segments, one pass from the left (Alg. 1 step 3, the loop over segments;
@@ -492,49 +340,18 @@ __device__ __forceinline__ int split_merge_pass(Cut cut, int K, int T, int l_min
   return n;
 }
 
-// Delta mode, after the cut points: one pass over the initial segments from the left (Alg. 1 step 3,
-// the loop over segments).  Longer than l_max: ceil(L / l_max) parts whose lengths differ by at most
-// one, the longer ones first.  Shorter than l_min: joins the segment to its left; the first one
-// stays open and the next initial segment starts where it started.  Empty initial segments vanish.
-// The new bounds are staged in LDS because they overwrite the old ones.
-__global__ __launch_bounds__(64) void resegment_kernel(MsArgs a) {
-  __shared__ int32_t out[kMaxSegments + 1];
-  const int unit = blockIdx.x;
-  int l, b, h;
-  unit_coords(a.d, unit, l, b, h);
-  const int T = seq_len(a.d, a.seq_lens, b);
-  int32_t* bounds = a.bounds + (int64_t)unit * (a.S + 1);
-  const int K = a.K;
-  const int n = split_merge_pass([&](int i) { return i == K ? T : bounds[i]; }, K, T, a.l_min, a.l_max, a.S, out);
-  __syncthreads();
-  for (int i = threadIdx.x; i < a.S; i += 64) bounds[i + 1] = i < n ? out[i] : T;
-}
-
-// Mass of every final segment: one wave per (segment, unit), strided partial sums in double, then
-// a fixed tree over the lanes.
-__global__ __launch_bounds__(64) void segment_mass_kernel(MsArgs a, const float* m_all, float* seg_mass_all) {
-  const int unit = blockIdx.y, seg = blockIdx.x;
-  const int32_t* bounds = a.bounds + (int64_t)unit * (a.S + 1);
-  const int lo = bounds[seg], hi = bounds[seg + 1];
-  const float* m = m_all + (int64_t)unit * a.d.t_stride;
-  double s = 0.0;
-  for (int t = lo + threadIdx.x; t < hi; t += 64) s += (double)m[t];
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-  if (threadIdx.x == 0) seg_mass_all[(int64_t)unit * a.S + seg] = (float)s;
-}
-
 // The cuts of one unit from the sums of 64 positions, the masses of its segments and its quotas, in one workgroup.
 // The prefix over the sums (512 of them for 32768 positions) goes to LDS; every threshold finds its piece there by
 // bisection, and 16 lanes scan the 64 positions of that piece for the first one that reaches it.  Only those pieces of
 // m_used are read again: latency bounds this kernel, so nothing in it depends on T beyond the prefix, and all thresholds
 // travel at once (BLOCK / 16 per round).  7 us for 8 units of 32768 positions and 16 segments, 9 for 256, 12 for 112 of
-// 131072 with 32 segments; 20 for 256 units with thresholds k*Delta and 133 final segments (42 with the split / merge pass
-// by one lane and the quotas in LDS).
+// 131072 with 32 segments; 21 for 256 units with thresholds k*Delta and 133 final segments (42 with the split / merge pass
+// by one lane and the quotas in LDS; with the masses as differences of prefixes, which lose those below 1e-10, 20).
 //   CUTS_STEP     fused step: thresholds k/S, at most 64 segments
 //   CUTS_GENERAL  fused step: also thresholds k*Delta with the split / merge pass, up to 1024 segments
 //   CUTS_STAGE    ams_mass_segment: no quotas, any sign of m_used (the bisection runs over the largest prefix so far)
-enum { CUTS_STEP = 0, CUTS_GENERAL = 1, CUTS_STAGE = 2 };
+//   CUTS_OWN      the same without the sums of 64 in memory: the workgroup forms them from m_used, in the same order
+enum { CUTS_STEP = 0, CUTS_GENERAL = 1, CUTS_STAGE = 2, CUTS_OWN = 3 };
 constexpr int kStepMaxSeg = 64;
 
 struct CutsOut {
@@ -548,7 +365,7 @@ struct CutsOut {
 template <int BLOCK, int KIND>
 __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel(MsArgs a, const float* m_all, CutsOut o) {
   constexpr int kW = BLOCK / 64, kPerThread = 4, kCapSub = BLOCK * kPerThread, kGroups16 = BLOCK / kSubLanes;
-  constexpr bool kSigned = KIND == CUTS_STAGE;
+  constexpr bool kOwn = KIND == CUTS_OWN, kSigned = KIND == CUTS_STAGE || kOwn;
   constexpr int kCap = KIND == CUTS_STEP ? kStepMaxSeg : kMaxSegments;
   __shared__ double ends[kCapSub];                   // prefix at the end of every piece of the group
   __shared__ double peak[kSigned ? kCapSub : 1];     // largest prefix up to the end of the piece
@@ -577,13 +394,31 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
     const int n = min(kCapSub, n_sub - base);
     double v[kPerThread], t[kPerThread];
     const int e0 = (int)threadIdx.x * kPerThread;
+    if constexpr (kOwn) {
+      for (int first = 0; first < n; first += 4 * kGroups16) {  // four pieces per 16 lanes in flight
+        const int e = first + (int)threadIdx.x / kSubLanes;
+        float x[4][4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) load_run(m_used, (base + e + r * kGroups16) * kSub + l16 * 4, T, a.vec, x[r], 0.f);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double p[4];
+          const double t16 = piece_scan(x[r], (base + e + r * kGroups16) * kSub + l16 * 4, T, p);
+          if (l16 == kSubLanes - 1 && e + r * kGroups16 < n) ends[e + r * kGroups16] = p[3], peak[e + r * kGroups16] = t16;
+        }
+      }
+      __syncthreads();
+    }
 #pragma unroll
     for (int i = 0; i < kPerThread; ++i) {
       v[i] = 0.0;
       t[i] = -INFINITY;
       if (e0 + i < n) {
         const int64_t at = (int64_t)unit * a.n_sub + base + e0 + i;
-        if (kSigned) {
+        if (kOwn) {  // this thread's four entries, which it replaces by the prefixes below
+          v[i] = ends[e0 + i];
+          t[i] = peak[e0 + i];
+        } else if (kSigned) {
           const double2 p = ((const double2*)a.sub)[at];
           v[i] = p.x;
           t[i] = p.y;
@@ -671,6 +506,11 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
     C = C_end;
     top = reach1;
     if (base + kCapSub < n_sub) __syncthreads();  // the next group overwrites what the searches read
+    if (kOwn && delta_mode && n_sub <= kCapSub) {  // the sums of 64 once more, for the masses below
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < kPerThread; ++i) peak[e0 + i] = v[i];
+    }
   }
   __syncthreads();
   const double total = C;
@@ -693,10 +533,25 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
         float x0[4], x1[4] = {0.f, 0.f, 0.f, 0.f};
         load_run(m_used, t0, hi, a.vec, x0, 0.f);
         if (q1 > q0) load_run(m_used, t1, hi, a.vec, x1, 0.f);
+        if (kOwn && n_sub > kCapSub) {
+          for (int q = q0 + 1; q < q1; q += 4) {
+            float x[4][4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) load_run(m_used, (q + r) * kSub + l16 * 4, q1 * kSub, a.vec, x[r], 0.f);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              double p[4];
+              sub_scan(x[r], p);
+              const double v = __shfl(p[3], lane | (kSubLanes - 1));
+              if (q + r < q1 && ((q + r - q0 - 1) & (kSubLanes - 1)) == l16) sum += v;
+            }
+          }
+        } else {
 #pragma unroll 4
-        for (int q = q0 + 1 + l16; q < q1; q += kSubLanes) {
-          const int64_t at = (int64_t)unit * a.n_sub + q;
-          sum += kSigned ? ((const double2*)a.sub)[at].x : a.sub[at];
+          for (int q = q0 + 1 + l16; q < q1; q += kSubLanes) {
+            const int64_t at = (int64_t)unit * a.n_sub + q;
+            sum += kOwn ? peak[q] : kSigned ? ((const double2*)a.sub)[at].x : a.sub[at];
+          }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) sum += (t0 + i >= lo ? (double)x0[i] : 0.0) + (double)x1[i];
@@ -716,7 +571,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
   if (o.seg_mass)
     for (int i = threadIdx.x; i < S; i += BLOCK) o.seg_mass[(int64_t)unit * S + i] = mass[i];
   for (int i = threadIdx.x; i <= S; i += BLOCK) a.bounds[(int64_t)unit * (S + 1) + i] = bounds[i];
-  if constexpr (KIND != CUTS_STAGE) {
+  if constexpr (!kSigned) {
     // what the quota kernels do besides the quotas: the -1 tail of idx, the kept count, the cleared bitmap
     // of the must-keep path; sinks and the recent suffix come out of the budget first
     const int kept = min(o.budget, T);
@@ -761,7 +616,6 @@ MsArgs make_args(const ams_params* p, const Dims& d, const int32_t* seq_lens, ch
   MsArgs a;
   a.d = d;
   a.seq_lens = seq_lens;
-  a.n_chunks = wl.n_chunks4k;
   a.S = p->n_segments;
   a.delta = (double)p->seg_delta;
   a.K = p->seg_delta > 0.f ? initial_segments(p->seg_delta) : p->n_segments;
@@ -772,8 +626,6 @@ MsArgs make_args(const ams_params* p, const Dims& d, const int32_t* seq_lens, ch
   a.vc_stride = a.vc_tokens = 0;  // set by the launchers once it is known who leaves the sums
   a.sub = (double*)(ws + wl.sub);
   a.n_sub = div_up(p->t_max, kSub);
-  a.mpart = (double*)(ws + wl.mpart);
-  a.cpre = (double*)(ws + wl.cpre);
   a.bounds = bounds;
   a.vec = false;  // set by the launchers once the pointers are known
   return a;
@@ -847,29 +699,25 @@ hipError_t launch_segment(const ams_params* p, const Dims& d, const int32_t* seq
   return hipGetLastError();
 }
 
-// The form of ams_mass_segment_static, whose scratch is one total per 4096 positions and one prefix per cut.
+// ams_mass_segment_static.  The cuts do not depend on the workgroup's size (it only says how many pieces are held at once, and
+// up to 1024 of them the first four waves of either size do the same), so the outputs are those of launch_segment bit for bit.
 hipError_t launch_segment_static(const ams_params* p, const Dims& d, const int32_t* seq_lens,
-                          const float* m_used, int32_t* bounds, float* seg_mass, char* ws, const WsLayout& wl,
-                          hipStream_t s) {
-  MsArgs a = make_args(p, d, seq_lens, ws, wl, bounds);
+                                 const float* m_used, int32_t* bounds, float* seg_mass, char* scratch, WsLayout wl,
+                                 hipStream_t s) {
+  wl.vc_part = wl.sub = 0;  // the sums of 64 are all that the scratch holds
+  if ((int64_t)d.units * div_up(d.t_max, kSub) * (int64_t)sizeof(double2) <= (int64_t)kStaticScratchBytes)
+    return launch_segment(p, d, seq_lens, m_used, bounds, seg_mass, scratch, wl, s);
+  MsArgs a = make_args(p, d, seq_lens, scratch, wl, bounds);
   a.vec = d.t_stride % 4 == 0 && ((uintptr_t)m_used & 15) == 0;
-  const dim3 grid(a.n_chunks, d.units);
-  prof_mark("chunk_total", s);
-  hipLaunchKernelGGL(chunk_total_kernel, grid, dim3(kBlock), 0, s, a, m_used);
-  prof_mark("segment_scan", s);
-  hipLaunchKernelGGL(segment_scan_kernel, grid, dim3(kBlock), 0, s, a, m_used);
-  if (a.delta > 0.0) {  // the cuts move, so the masses cannot come from the prefix at the cuts
-    if (!seg_mass) return hipErrorInvalidValue;
-    prof_mark("resegment", s);
-    hipLaunchKernelGGL(resegment_kernel, dim3(d.units), dim3(64), 0, s, a);
-    prof_mark("segment_mass", s);
-    hipLaunchKernelGGL(segment_mass_kernel, dim3(a.S, d.units), dim3(64), 0, s, a, m_used, seg_mass);
-    return hipGetLastError();
-  }
-  if (seg_mass) {
-    prof_mark("segment_finalize", s);
-    hipLaunchKernelGGL(segment_finalize_kernel, dim3(d.units), dim3(64), 0, s, a, seg_mass);
-  }
+  CutsOut o{};
+  o.seg_mass = seg_mass;
+  prof_mark("unit_cuts", s);
+  // the reads of m_used bound this form: many units take the small workgroups, of which four fit a CU (1024 units of 8192
+  // positions: 32 us per call with 1024 threads)
+  if (a.n_sub <= 1024 && d.units >= 512)
+    hipLaunchKernelGGL((unit_cuts_kernel<256, CUTS_OWN>), dim3(d.units), dim3(256), 0, s, a, m_used, o);
+  else
+    hipLaunchKernelGGL((unit_cuts_kernel<1024, CUTS_OWN>), dim3(d.units), dim3(1024), 0, s, a, m_used, o);
   return hipGetLastError();
 }
 

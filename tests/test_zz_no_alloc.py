@@ -1,6 +1,6 @@
 """The entry point that allocates nothing (ams_mass_segment_static: scratch in the library's own device
 array) against ams_mass_segment with a caller's workspace, through the C ABI: two calls in a row, the
-second on a smaller input, bounds bit-exact and segment masses bit-exact (same kernels, same order)."""
+second on a smaller input, bounds bit-exact and segment masses bit-exact (same additions in the same order)."""
 import numpy as np
 import pytest
 import torch
@@ -46,6 +46,27 @@ def test_static_scratch_entry_matches_the_workspace_entry():
         np.testing.assert_array_equal(b_st, b_ws)
         np.testing.assert_array_equal(m_st.view(np.uint32), m_ws.view(np.uint32))
         assert (b_st[:, 0] == 0).all() and (np.diff(b_st, axis=1) >= 0).all()
+
+
+@pytest.mark.parametrize("units,T,S,kw", [
+    (32, 20000, 1000, {}),                                                        # sums of 64 in the library's array
+    (256, 20000, 450, {}), (100, 70001, 40, {}), (9, 600001, 700, {}),            # formed by the cutting kernel
+    (600, 8200, 16, {}),                                                          # the same with small workgroups
+    (32, 9000, 152, dict(delta=0.1, l_min=16, l_max=64)), (70, 70001, 85, dict(delta=0.1, l_min=16, l_max=1024)),
+    (256, 20001, 12, dict(delta=0.1)), (600, 8200, 60, dict(delta=0.1, l_min=8, l_max=300)),
+    (8, 600001, 1024, dict(delta=0.1, l_min=16, l_max=600))])
+def test_both_entries_add_in_the_same_order(units, T, S, kw):
+    """Masses down to 1e-12 of the largest, in which another order of additions shows (2 of 160000 masses of the first shape
+    differed between two orders in double); scratch that holds the sums of 64 positions and scratch that does not."""
+    for seed in range(3 if units * T < 2e6 else 1):
+        p, lens, m = _case((units, 1, 1), T, S, seed, **kw)
+        m = m ** 2
+        m /= m.sum(1, keepdim=True)
+        m[-1, : T // 2] *= -0.5                                                   # a prefix that falls
+        b_ws, m_ws = _run(p, lens, m, static=False)
+        b_st, m_st = _run(p, lens, m, static=True)
+        np.testing.assert_array_equal(b_st, b_ws)
+        np.testing.assert_array_equal(m_st.view(np.uint32), m_ws.view(np.uint32))
 
 
 def test_static_scratch_entry_rejects_what_does_not_fit():
