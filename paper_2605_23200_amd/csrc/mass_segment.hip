@@ -498,9 +498,27 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
           bounds[k] = j + 1;
           cpre[k] = P;
         }
-      } else if (l16 == 0 && reach[lo] >= thr) {  // only the rounding of the last addition lies in between
-        bounds[k] = min(T, (base + lo + 1) * kSub);
-        cpre[k] = ends[lo];
+      } else if (reach[lo] >= thr) {  // only the rounding of the start of the piece lies in between: where it is highest
+        P = -INFINITY;
+#pragma unroll
+        for (int i = 3; i >= 0; --i)
+          if (j0 + i < T && before + p[i] >= P) {
+            j = j0 + i;
+            P = before + p[i];
+          }
+#pragma unroll
+        for (int d = 1; d < kSubLanes; d <<= 1) {
+          const double P2 = __shfl_xor(P, d);
+          const int j2 = __shfl_xor(j, d);
+          if (P2 > P || (P2 == P && j2 < j)) {
+            P = P2;
+            j = j2;
+          }
+        }
+        if (l16 == 0) {
+          bounds[k] = j + 1;
+          cpre[k] = P;
+        }
       }
     }
     C = C_end;

@@ -83,6 +83,27 @@ def test_many_chunks_take_four_runs_per_workgroup(oracle):
         _run(oracle, w, units=[0, 63, 127])
 
 
+def test_a_peak_on_the_threshold_is_the_cut(oracle):
+    """The prefix rises to a threshold within its last bit, at the peak of a piece of 64, and falls from there: the cut is
+    at the peak also where only one of two orders of additions reaches the threshold (found by a search over seeds)."""
+    T, S, rows = 2560, 4, []
+    for seed in (16, 68, 146, 152):
+        rng = np.random.default_rng(seed)
+        m = (rng.random(T) ** 12 * 1e-3).astype(np.float32)
+        pos = int(rng.integers(1, 10)) * 256 + int(rng.integers(4, 40))
+        left = 0.25 - m[:pos - 3].astype(np.float64).sum()
+        for q in range(pos - 3, pos + 1):
+            m[q] = np.float32(left)
+            left -= float(m[q])
+        m[pos + 1:] = -m[pos + 1:]
+        rows.append(m)
+    p = _stage_params(4, T, S)
+    bounds, seg_mass = torch.full((4, S + 1), -3, dtype=torch.int32, device=DEV), torch.full((4, S), -3.0, device=DEV)
+    B.ams_mass_segment(p, to_dev(np.array([T], np.int32)), to_dev(np.stack(rows)), bounds, seg_mass, workspace(p))
+    for i in range(4):
+        np.testing.assert_array_equal(to_host(bounds)[i], oracle.segment(rows[i], S)[0], err_msg=f"unit {i}")
+
+
 @pytest.mark.parametrize("T,delta,l_min,l_max", [(70001, 0.01, 8, 200), (270000, 0.05, 16, 1024)])
 def test_split_and_merge_on_long_caches(oracle, T, delta, l_min, l_max):
     """Masses of moved segments from the prefix (up to 262144 positions) and by summing (beyond)."""
