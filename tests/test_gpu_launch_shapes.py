@@ -106,7 +106,7 @@ def test_a_peak_on_the_threshold_is_the_cut(oracle):
 
 @pytest.mark.parametrize("T,delta,l_min,l_max", [(70001, 0.01, 8, 200), (270000, 0.05, 16, 1024)])
 def test_split_and_merge_on_long_caches(oracle, T, delta, l_min, l_max):
-    """Masses of moved segments from the prefix (up to 262144 positions) and by summing (beyond)."""
+    """Prefixes held whole (up to 262144 positions) and in groups (beyond), segments that the length rules have moved."""
     cap = int(np.ceil(1 / delta)) + 1 + T // l_max
     rng = np.random.default_rng(T)
     m = np.stack([oracle.mass((rng.random(T) ** e).astype(np.float32)) for e in (1, 8)])
@@ -139,14 +139,18 @@ def test_quota_ties_at_every_register_count(oracle, S):
 
 
 @pytest.mark.parametrize("must", [False, True])
-@pytest.mark.parametrize("lens", [[1024, 1025, 63, 64, 65, 1, 0, 130, 200, 2, 40, 7, 250, 90],   # one wave: 1024 keys
-                                  [4096, 4097, 1000, 255, 256, 257],                              # 256 threads
-                                  [8192, 8193, 100, 5000],                                        # 512 threads
-                                  [32768], [32769]])                                              # 1024 threads
-def test_select_at_the_edges_of_its_shapes(oracle, lens, must):
+@pytest.mark.parametrize("threads,lens", [(64, [1024, 1025, 63, 64, 65, 1, 0, 130, 200, 2, 40, 7, 250, 90]),   # 1024 keys
+                                          (256, [4096, 4097, 1000, 255, 256, 257]),
+                                          (512, [8192, 8193, 100, 2000, 1000]),
+                                          (1024, [32768]), (1024, [32769])])
+def test_select_at_the_edges_of_its_shapes(oracle, threads, lens, must):
     """Segments that just fit a shape's registers and that do not; scores that fill one bin over several passes (an
     outlier and neighbouring floats), ties by the hundred, signed zeros, infinities and NaN."""
     S, T = len(lens), sum(lens)
+    # the rule that picks the shape: the expected length, T / S, against 256, 2560 and 5120
+    assert threads == (64 if T <= 256 * S else 256 if T <= 2560 * S else 512 if T <= 5120 * S else 1024)
+    cap = 32 * threads if threads == 1024 else 16 * threads
+    assert cap in lens or cap + 1 in lens
     bounds = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     rng = np.random.default_rng(T + S)
     g = rng.standard_normal((6, T)).astype(np.float32)
