@@ -538,11 +538,15 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
       double k2 = k * k;
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) k2 += __shfl_xor(k2, o);
+      // an infinite key: the identity product spreads NaN to the channels next to it, where the sum is none
+      if (__ballot(isinf(k))) k2 = INFINITY;
       if (lane == 0) k2_sm[wave] = k2;
     }
   }
   __syncthreads();
-  const double kbar2 = KEYS == KEYS_MEAN ? k2_sm[0] + k2_sm[1] : 0.0;  // squared length of the mean key
+  const double kbar2 = KEYS != KEYS_MEAN                            ? 0.0
+                       : isinf(k2_sm[0]) || isinf(k2_sm[1]) ? INFINITY
+                                                            : k2_sm[0] + k2_sm[1];  // squared length of the mean key
   const double inv_others = KEYS == KEYS_COS && T > 1 ? 1.0 / (double)(T - 1) : 0.0;
   float4 f[NB];
 #pragma unroll

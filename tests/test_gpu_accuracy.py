@@ -66,6 +66,27 @@ def test_mean_key_of_keys_that_cancel(oracle, dtype, D, G, W):
         assert_close_terms(g[h, :T], want, score_term_magnitudes(B.SCORER_KEYDIFF, q, host["K"][0, 0, h]), what=f"g unit {h}")
 
 
+@pytest.mark.parametrize("scorer", [B.SCORER_KEYDIFF, B.SCORER_REDUNDANCY])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_a_key_that_is_no_number(scorer, bad):
+    """One entry of one key is infinite or NaN: the scores that a bf16 cache gets from the sweeps are numbers, zeros and NaN
+    where those of an fp32 cache with the same values are, which come from the streaming kernels."""
+    got = []
+    for dtype in ("f32", "bf16"):
+        w = inputs.CONFIGS[1].scaled(L=1, H=3, G=2, W=8, T=700, dtype=dtype, budget=100, S=4, n_spans=0)
+        host = inputs.dense_cache(w, n_threads=2)
+        if dtype == "f32":      # the values of the bf16 cache
+            host["K"] = inputs.bf16_bits_to_f32(inputs.to_bf16_bits(host["K"])).reshape(host["K"].shape)
+        host["K"][0, 0, 1, 300, 77] = bad if dtype == "f32" else np.array([bad], np.float32).view(np.uint32)[0] >> 16
+        host["K"][0, 0, 2, 40] = 0
+        job = Job(w, host, scorer=scorer)
+        job.step()
+        got.append(to_host(job.intermediates().g)[:, :700])
+    for i in range(3):
+        np.testing.assert_array_equal(np.isnan(got[1][i]), np.isnan(got[0][i]), err_msg=f"unit {i}")
+        np.testing.assert_array_equal(got[1][i] == 0, got[0][i] == 0, err_msg=f"unit {i}")
+
+
 @pytest.mark.parametrize("static", [False, True])
 @pytest.mark.parametrize("T,l_max", [(9000, 256), (70001, 1024), (300000, 2048)])
 def test_segment_masses_far_below_the_prefix(oracle, T, l_max, static):
