@@ -152,6 +152,8 @@ __device__ __forceinline__ int key_channel(int cb, int n) {
 // consecutive XCDs, so without more each XCD would read one head, the same 256 of every 2048 bytes, all through the
 // launch; the heads therefore move on by one every eighth (layer, sequence, chunk).  4096 ragged units, 8 heads: 6025 us
 // per step against 6447; moving on every time, or every second time, gives 6490 and 6267, every 16th or 64th 6007 to 6008.
+// 4 heads gain as well (2048 units, 3396 -> 3080); with 1, 2 or 3 heads, or rows of 128 bytes, it makes no difference (3537
+// and 3571, 3727 and 3700, 2333 and 2344; 3581 and 3559 for 8 heads).
 __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool reversed, int& unit, int& chunk) {
   int bx = blockIdx.x, by = blockIdx.y;
   if (reversed) {
