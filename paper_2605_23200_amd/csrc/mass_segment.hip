@@ -344,9 +344,9 @@ __device__ __forceinline__ int split_merge_pass(Cut cut, int K, int T, int l_min
 // The prefix over the sums (512 of them for 32768 positions) goes to LDS; every threshold finds its piece there by
 // bisection, and 16 lanes scan the 64 positions of that piece for the first one that reaches it.  Only those pieces of
 // m_used are read again: latency bounds this kernel, so nothing in it depends on T beyond the prefix, and all thresholds
-// travel at once (BLOCK / 16 per round).  7 us for 8 units of 32768 positions and 16 segments, 9 for 256, 12 for 112 of
-// 131072 with 32 segments; 21 for 256 units with thresholds k*Delta and 133 final segments (42 with the split / merge pass
-// by one lane and the quotas in LDS; with the masses as differences of prefixes, which lose those below 1e-10, 20).
+// travel at once (BLOCK / 16 per round).  6 us for 8 units of 32768 positions and 16 segments, 8 for 256, 9 for 112 of
+// 131072 with 32 segments; 23 for 256 units with thresholds k*Delta and 133 final segments (42 with the split / merge pass
+// by one lane and the quotas in LDS; with the masses as differences of prefixes, which lose those below 1e-10, 22).
 //   CUTS_STEP     fused step: thresholds k/S, at most 64 segments
 //   CUTS_GENERAL  fused step: also thresholds k*Delta with the split / merge pass, up to 1024 segments
 //   CUTS_STAGE    ams_mass_segment: no quotas, any sign of m_used (the bisection runs over the largest prefix so far)
