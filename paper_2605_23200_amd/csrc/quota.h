@@ -31,7 +31,8 @@ __device__ __forceinline__ double lane_f64(double v, int j) {
 // 64 r + lane.  bounds and mass lie in LDS.  Sums of masses run in index order over the open segments and every share is
 // rem * M_i / sum, the same operations in the same order as plain C.  A serial chain: sums and counts travel through
 // scalar lane reads and ballots, and the leftovers go to the largest fractions by bisection on their bit patterns, not
-// by comparing every pair.
+// by comparing every pair.  With R = 16 the lane reads want more scalar registers than there are: 683 of them live in lanes of
+// vector registers (no memory is touched), 3 us for 139 segments.
 template <int R>
 __device__ __forceinline__ void quota_wave(int S, int bud, int q_min, const int32_t* bounds, const float* mass,
                                            int (&quo)[R]) {
