@@ -345,8 +345,9 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   a.credit = credit;
   a.csum = (vc && credit) ? (double*)(ws + wl.csum) : nullptr;
   a.ksum = nullptr;
-  // softmax partials of a score that a sweep forms: the chunk statistics of the queries have been merged by the time the
-  // second sweep writes them there; the first one (moment scores) takes the key sums' place, which nobody uses then
+  // softmax partials of a score that a sweep forms: the second sweep (mean cosines) leaves them where the sums of 64 positions
+  // go later (it reads the statistics and the key sums itself), the first one (moment scores) takes the key sums' place,
+  // which nobody uses then
   a.soft = nullptr;
   a.eps = p->mass_eps;
   a.k = k;
@@ -361,6 +362,12 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   a.n_chunks = paged ? wl.n_chunks_paged : wl.n_chunks;
   a.chunk = paged ? wl.score_chunk_paged : wl.score_chunk;
   a.n_pad = wl.n_pad;
+  // The second sweep merges the statistics itself where that is cheaper than a launch between the sweeps (1.2 us of gap and
+  // 5 of its own): every workgroup reads its unit's partial statistics once more.  us per step, with the kernel and without:
+  // 44.5 and 41.0 (8 fp32 units of 4096), 33.7 and 32.4 (9 units of 2105), 95.5 and 92 (24 fp32 units of 9804, 240
+  // workgroups), 147.8 and 143.6 (32 units of 27209, 864 workgroups), 99.8 and 97.3 (48 units of 1376, 224 queries).  With up
+  // to 2048 workgroups or 128 chunks there is no gain any more (828 units of 12608: 822 and 827).
+  a.fold = !causal && (int64_t)d.units * a.n_chunks <= 1024 && a.n_chunks <= 64;
   a.inv_sqrt_d = (float)(1.0 / sqrt((double)d.D));
   a.c2 = (float)(1.4426950408889634 / sqrt((double)d.D));
   const bool bf16 = p->kv_dtype == AMS_BF16;
@@ -400,7 +407,7 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   if (!oneread && key_score && bf16 && !causal) {
     a.g = g;
     a.ksum = (double*)(ws + wl.kbar);
-    a.soft = (double2*)(ws + wl.part_stats);
+    a.soft = (double2*)(ws + wl.sub);
     e = launch_key_sweeps(a, nb, d.D, p->scorer == AMS_SCORER_REDUNDANCY, s);
     a.ksum = nullptr;
     vc_stride = a.n_chunks;

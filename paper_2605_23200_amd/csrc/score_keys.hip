@@ -17,13 +17,18 @@
 namespace ams {
 namespace {
 
+template <int NB, int HD, int KEYS>
+hipError_t by_fold(const ScoreArgs& a, hipStream_t s) {
+  return a.fold ? run_key_sweeps<NB, HD, KEYS, true>(a, s) : run_key_sweeps<NB, HD, KEYS, false>(a, s);
+}
+
 template <int HD, int KEYS>
 hipError_t by_nb(const ScoreArgs& a, int nb, hipStream_t s) {
-  if (nb <= 1) return run_key_sweeps<1, HD, KEYS>(a, s);
-  if (nb <= 2) return run_key_sweeps<2, HD, KEYS>(a, s);
-  if (nb <= 4) return run_key_sweeps<4, HD, KEYS>(a, s);
-  if (nb <= 7) return run_key_sweeps<7, HD, KEYS>(a, s);
-  if (nb <= 8) return run_key_sweeps<8, HD, KEYS>(a, s);
+  if (nb <= 1) return by_fold<1, HD, KEYS>(a, s);
+  if (nb <= 2) return by_fold<2, HD, KEYS>(a, s);
+  if (nb <= 4) return by_fold<4, HD, KEYS>(a, s);
+  if (nb <= 7) return by_fold<7, HD, KEYS>(a, s);
+  if (nb <= 8) return by_fold<8, HD, KEYS>(a, s);
   return hipErrorInvalidValue;
 }
 

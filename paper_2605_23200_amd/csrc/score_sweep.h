@@ -403,6 +403,16 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
   }
 }
 
+// What the second sweep needs of query n: reference, weight of its shares in u and in the last-query g, whether it exists.
+__device__ __forceinline__ float4 query_weights(const ScoreArgs& a, int n, int T, float M, double Z) {
+  const bool real = n < a.d.N;
+  // causal window on a cache shorter than the window: a query before position 0 does not exist
+  const bool exists = real && (!a.causal || T - a.d.W + (n % a.d.W) >= 0);
+  const bool newest = exists && (n % a.d.W) == a.d.W - 1;
+  return make_float4(M, exists ? (float)(1.0 / ((double)a.d.N * Z)) : 0.f, newest ? (float)(1.0 / ((double)a.d.G * Z)) : 0.f,
+                     real ? 1.f : 0.f);
+}
+
 // Chunk statistics merged per query: the 1024 threads split into (query, contiguous range of
 // chunks) pairs, the ranges are then combined in ascending order (fixed association) -> M_n and
 // the per-query weights of the column sums.
@@ -438,16 +448,7 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
     for (int q = 0; q < parts; ++q) M = fmaxf(M, pm[q * a.n_pad + n]);
     double Z = 0.0;
     for (int q = 0; q < parts; ++q) Z += pz[q * a.n_pad + n] * (double)__builtin_amdgcn_exp2f(pm[q * a.n_pad + n] - M);
-    const bool real = n < a.d.N;
-    // causal window on a cache shorter than the window: a query before position 0 does not exist
-    const bool exists = real && (!a.causal || T - a.d.W + (n % a.d.W) >= 0);
-    const bool newest = exists && (n % a.d.W) == a.d.W - 1;
-    float4 f;
-    f.x = M;
-    f.y = exists ? (float)(1.0 / ((double)a.d.N * Z)) : 0.f;
-    f.z = newest ? (float)(1.0 / ((double)a.d.G * Z)) : 0.f;
-    f.w = real ? 1.f : 0.f;
-    a.fin[(int64_t)unit * a.n_pad + n] = f;
+    a.fin[(int64_t)unit * a.n_pad + n] = query_weights(a, n, T, M, Z);
   }
   if (a.ksum && (int)threadIdx.x < a.d.D) {  // the unit's key sum takes the place of its first chunk's, for the second sweep
     double* k = a.ksum + (int64_t)unit * a.n_chunks * a.d.D + threadIdx.x;
@@ -487,13 +488,65 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
 // ---------------------------------------------------------------------------------------------
 // Sweep 2: u[t] = sum_n exp2(x[n][t] - M_n) / (N Z_n), and g for the softmax-based scorers.
 // ---------------------------------------------------------------------------------------------
+// Merges a unit's chunk statistics inside the second sweep (launches of few workgroups, where a reduction kernel of its own
+// costs more than every workgroup reading them again): weights of query n -> ((float4*)sm)[n], sm of 4 KB; and the sums of
+// the chunk's credit before the update, per wave -> c_sm.
+__device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0, int t_lim, int T, char* sm, double* c_sm) {
+  double* pz = (double*)sm;
+  float* pm = (float*)(sm + kThreads * sizeof(double));
+  double cs = 0.0;
+  if (a.vc_part && a.credit) {
+    const float* c_row = a.credit + (int64_t)unit * a.d.t_stride;
+#pragma unroll 4
+    for (int t = c0 + threadIdx.x; t < t_lim; t += kThreads) cs += (double)c_row[t];
+  }
+  const int nch = (T + a.chunk - 1) / a.chunk;
+  const int parts = kThreads / a.n_pad, n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
+  if (part < parts) {
+    const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
+    float M = kNegInit;
+    double Z = 0.0;
+    for (int first = part; first < nch; first += 8 * parts) {  // eight entries in flight
+      float2 s[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        s[i] = first + i * parts < nch ? p[(int64_t)(first + i * parts) * a.n_pad] : make_float2(kNegInit, 0.f);
+      float mx = M;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) mx = fmaxf(mx, s[i].x);
+      Z *= (double)__builtin_amdgcn_exp2f(M - mx);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) Z += (double)s[i].y * (double)__builtin_amdgcn_exp2f(s[i].x - mx);
+      M = mx;
+    }
+    pm[threadIdx.x] = M;
+    pz[threadIdx.x] = Z;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) cs += __shfl_xor(cs, o);
+  if ((threadIdx.x & 63) == 0) c_sm[threadIdx.x >> 6] = cs;
+  __syncthreads();
+  float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+  if ((int)threadIdx.x < a.n_pad) {
+    float M = kNegInit;
+    for (int q = 0; q < parts; ++q) M = fmaxf(M, pm[q * a.n_pad + n]);
+    double Z = 0.0;
+    for (int q = 0; q < parts; ++q) Z += pz[q * a.n_pad + n] * (double)__builtin_amdgcn_exp2f(pm[q * a.n_pad + n] - M);
+    f = query_weights(a, n, T, M, Z);
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < a.n_pad) ((float4*)sm)[threadIdx.x] = f;
+  __syncthreads();
+}
+
 // TAIL (causal window, blocks from t_end on): a (query, key) pair the mask hides adds nothing, and
 // every observation a key is missing counts as the largest share it got.
-template <bool BF16, int NB, int MODE, bool TAIL, int HD, int KEYS = KEYS_NONE>
+template <bool BF16, int NB, int MODE, bool TAIL, int HD, int KEYS = KEYS_NONE, bool FOLD = false>
 __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES : 2) void score_usage_kernel(ScoreArgs a) {
   constexpr int NG = kGroup<NB>;
   constexpr int QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
+  if (FOLD && a.status && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *a.status = 0;  // no bounded wait on this path
   // the second sweep walks the cache backwards: what the first sweep read last is still in the
   // memory-side cache (about a tenth of the keys at the headline size)
   int unit, chunk;
@@ -524,7 +577,14 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
     if (threadIdx.x < 128) {
       double k = 0.0;
       if (threadIdx.x < HD) {
-        k = a.ksum[(int64_t)unit * a.n_chunks * HD + threadIdx.x];
+        const double* ks = a.ksum + (int64_t)unit * a.n_chunks * HD + threadIdx.x;
+        if (FOLD) {
+          const int nch = (T + a.chunk - 1) / a.chunk;
+#pragma unroll 8
+          for (int i = 0; i < nch; ++i) k += ks[(int64_t)i * HD];
+        } else {
+          k = *ks;
+        }
         if (KEYS == KEYS_MEAN) k /= (double)T;
         const float x = (float)k;
         const uint32_t hi = __float_as_uint(x) & 0xFFFF0000u;
@@ -550,9 +610,6 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
                        : isinf(k2_sm[0]) || isinf(k2_sm[1]) ? INFINITY
                                                             : k2_sm[0] + k2_sm[1];  // squared length of the mean key
   const double inv_others = KEYS == KEYS_COS && T > 1 ? 1.0 / (double)(T - 1) : 0.0;
-  float4 f[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) f[nb] = a.fin[(int64_t)unit * a.n_pad + nb * 32 + c];
   float* u_row = a.u + (int64_t)unit * a.d.t_stride;
   float* g_row = a.g ? a.g + (int64_t)unit * a.d.t_stride : nullptr;
   const float c2 = a.c2;
@@ -563,6 +620,17 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
   constexpr int kBuf = KEYS != KEYS_NONE ? kKeysChunk : kScoreChunk;
   __shared__ float u_sm[kBuf];
   __shared__ float g_sm[kBufG ? kBuf : 1];
+  __shared__ double c_sm[FOLD ? 4 : 1];
+  float4 f[NB];
+  if constexpr (FOLD) {
+    fold_stats(a, unit, c0, t_lim, T_all, (char*)u_sm, c_sm);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) f[nb] = ((const float4*)u_sm)[nb * 32 + c];
+    __syncthreads();
+  } else {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) f[nb] = a.fin[(int64_t)unit * a.n_pad + nb * 32 + c];
+  }
   float v_part = 0.f;  // this lane's share of sum(max(u,0)+eps): one term per block of 32 keys of this wave (32 blocks per chunk)
   auto block = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0) __attribute__((always_inline)) {
     float pu[16], pg[16], pm[16];
@@ -677,16 +745,17 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
   }
   if (KEYS == KEYS_COS) softmax_part(g_sm, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
   if (a.vc_part) {  // chunk sums of max(u,0)+eps in a fixed order: lanes, then waves
-    __shared__ double vc_sm[4];
+    __shared__ double v_sm[4];
     double v_acc = (double)v_part;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v_acc += __shfl_xor(v_acc, o);
-    if (lane == 0) vc_sm[wave] = v_acc;
+    if (lane == 0) v_sm[wave] = v_acc;
     __syncthreads();
     if (threadIdx.x == 0) {
       // the unit's credit sum (formed between the sweeps) rides in the first chunk's entry
-      const double c = (chunk == 0 && a.csum) ? a.csum[unit] : 0.0;
-      a.vc_part[(int64_t)unit * a.n_chunks + chunk] = make_double2((vc_sm[0] + vc_sm[1]) + (vc_sm[2] + vc_sm[3]), c);
+      double c = (!FOLD && chunk == 0 && a.csum) ? a.csum[unit] : 0.0;
+      if (FOLD) c = (c_sm[0] + c_sm[1]) + (c_sm[2] + c_sm[3]);
+      a.vc_part[(int64_t)unit * a.n_chunks + chunk] = make_double2((v_sm[0] + v_sm[1]) + (v_sm[2] + v_sm[3]), c);
     }
   }
 }
@@ -708,32 +777,39 @@ template <bool BF16, int NB, bool TAIL, int HD>
 hipError_t launch_usage(const ScoreArgs& a, int mode, dim3 grid, int lds, hipStream_t s) {
   const dim3 blk(kThreads);
   hipError_t e;
-  switch (mode) {
-    case MODE_LAST:
-      if ((e = ensure_lds<score_usage_kernel<BF16, NB, MODE_LAST, TAIL, HD>>(lds)) != hipSuccess) return e;
-      hipLaunchKernelGGL((score_usage_kernel<BF16, NB, MODE_LAST, TAIL, HD>), grid, blk, lds, s, a);
-      break;
-    default:
-      if ((e = ensure_lds<score_usage_kernel<BF16, NB, MODE_MEAN, TAIL, HD>>(lds)) != hipSuccess) return e;
-      hipLaunchKernelGGL((score_usage_kernel<BF16, NB, MODE_MEAN, TAIL, HD>), grid, blk, lds, s, a);
-  }
-  return hipGetLastError();
+  auto launch = [&](auto mode_c, auto fold_c) {
+    constexpr int M = decltype(mode_c)::value;
+    constexpr bool F = decltype(fold_c)::value;
+    if ((e = ensure_lds<score_usage_kernel<BF16, NB, M, TAIL, HD, KEYS_NONE, F>>(lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL((score_usage_kernel<BF16, NB, M, TAIL, HD, KEYS_NONE, F>), grid, blk, lds, s, a);
+    return hipGetLastError();
+  };
+  auto by_fold = [&](auto mode_c) {
+    if constexpr (!TAIL)
+      if (a.fold) return launch(mode_c, std::true_type{});
+    return launch(mode_c, std::false_type{});
+  };
+  return mode == MODE_LAST ? by_fold(std::integral_constant<int, MODE_LAST>{})
+                           : by_fold(std::integral_constant<int, MODE_MEAN>{});
 }
 
 // The two plain sweeps with the keys riding along.
-template <int NB, int HD, int KEYS>
+template <int NB, int HD, int KEYS, bool FOLD>
 hipError_t run_key_sweeps(const ScoreArgs& a, hipStream_t s) {
+  constexpr auto usage = score_usage_kernel<true, NB, MODE_MEAN, false, HD, KEYS, FOLD>;
   const int lds = NB * 32 * Tr<true, HD>::kQStride, lds_k = lds + 4 * Tr<true, HD>::kQStride;
   const dim3 grid(a.n_chunks, a.d.units), blk(kThreads);
   hipError_t e;
   if ((e = ensure_lds<score_stats_kernel<true, NB, false, false, HD, KEYS>>(lds)) != hipSuccess) return e;
-  if ((e = ensure_lds<score_usage_kernel<true, NB, MODE_MEAN, false, HD, KEYS>>(lds_k)) != hipSuccess) return e;
+  if ((e = ensure_lds<usage>(lds_k)) != hipSuccess) return e;
   prof_mark("score_stats", s);
   hipLaunchKernelGGL((score_stats_kernel<true, NB, false, false, HD, KEYS>), grid, blk, lds, s, a);
-  prof_mark("score_reduce", s);
-  hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
+  if (!FOLD) {
+    prof_mark("score_reduce", s);
+    hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
+  }
   prof_mark("score_usage", s);
-  hipLaunchKernelGGL((score_usage_kernel<true, NB, MODE_MEAN, false, HD, KEYS>), grid, blk, lds_k, s, a);
+  hipLaunchKernelGGL(usage, grid, blk, lds_k, s, a);
   return hipGetLastError();
 }
 
@@ -748,8 +824,10 @@ hipError_t run_softmax_sweeps(const ScoreArgs& a, int mode, hipStream_t s) {
     prof_mark("score_stats_tail", s);
     if ((e = launch_stats<BF16, NB, true, HD>(a, mode == MODE_EXPECTED, dim3(1, a.d.units), lds, s)) != hipSuccess) return e;
   }
-  prof_mark("score_reduce", s);
-  hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
+  if (!a.fold) {
+    prof_mark("score_reduce", s);
+    hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
+  }
   // the moment-based score has been written by the first sweep: the second one leaves g alone
   ScoreArgs a2 = a;
   if (mode == MODE_EXPECTED) a2.g = nullptr;

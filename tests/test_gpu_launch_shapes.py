@@ -230,3 +230,29 @@ def test_compaction_at_the_edges_of_its_row_groups(oracle, dtype, D, budget):
     """16, 32 or 64 rows per workgroup: kept counts around them, rows of 128 to 512 bytes."""
     w = inputs.CONFIGS[1].scaled(L=1, H=2, G=1, W=8, D=D, dtype=dtype, T=300, budget=budget, S=2, n_spans=1, span_len=(8, 40))
     _run(oracle, w)
+
+
+def _labels(job):
+    B.ams_profile_begin()
+    job.step()
+    return [k for k, _ in B.ams_profile_end()]
+
+
+@pytest.mark.parametrize("scorer", [B.SCORER_MEAN_WINDOW, B.SCORER_LAST_QUERY, B.SCORER_KEYDIFF, B.SCORER_REDUNDANCY,
+                                    B.SCORER_EXPECTED_VNORM])
+@pytest.mark.parametrize("T,dtype,G,W,D,folded", [(8192, "bf16", 7, 32, 128, True), (8193, "bf16", 4, 32, 64, False),
+                                                  (5000, "f32", 2, 20, 128, True), (130, "bf16", 1, 8, 128, True),
+                                                  (1, "bf16", 4, 8, 128, True)])
+def test_second_sweep_merges_the_statistics_of_small_launches(oracle, T, dtype, G, W, D, folded, scorer):
+    """64 and 65 chunks of one unit; the empty first sequence has no workgroup that gets as far as its merge, and the scratch
+    holds garbage (a status word that nobody cleared would void the event)."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=2, H=1, G=G, W=W, D=D, T=T, T_min=T, dtype=dtype, budget=max(1, min(96, T // 3)), S=4,
+                                 n_spans=2, span_len=(1, 40))
+    host = inputs.dense_cache(w, n_threads=4)
+    if T > 1:
+        host["seq_lens"][:] = [0, T]
+    job = Job(w, host, scorer=scorer)
+    job.ws.fill_(255)
+    assert ("score_reduce" not in _labels(job)) == folded
+    assert to_host(job.n_kept).tolist() == [min(w.budget, int(t)) for t in host["seq_lens"]]
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [1] if T > 1 else [0, 1], scorer=scorer)
