@@ -58,6 +58,7 @@ def kernel_bytes(label, w, lens=None):
         "mass_ema": 4 * tok * 4,                          # u, credit in; credit, m_used out
         "vc_sums": 4 * tok * 2,                           # u, credit in (pooled usage out, where it is pooled)
         "unit_cuts": 0,                                   # the sums of 64 positions, and those that hold a cut
+        "unit_mass_cuts": 4 * tok * 4,                    # short caches: both in one launch
         "quota": 0,
         "select": 4 * tok + 4 * kept,                     # g in, idx out
         "compact": 4 * kept * D * e + 4 * kept * 3,       # K,V rows in + out, idx, credit gather

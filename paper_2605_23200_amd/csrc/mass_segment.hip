@@ -196,6 +196,42 @@ __device__ __forceinline__ void sub_scan(const float (&x)[4], double (&p)[4]) {
   }
 }
 
+// Normalisers of one unit: its partial sums of max(u,0)+eps and of the old credit, added up by every wave for itself (strided
+// over the lanes, then a fixed tree).
+struct MassOf {
+  double lam, bet, eps, inv_z, inv_csum;
+  bool ema;
+  __device__ __forceinline__ MassOf(const MsArgs& a, int unit, int T, float lambda, float beta, float eps_f)
+      : lam((double)lambda), bet((double)beta), eps((double)eps_f), ema(lambda != 0.f) {
+    const int nvc = (T + a.vc_tokens - 1) / a.vc_tokens;
+    const double2* vc = a.vc_part + (int64_t)unit * a.vc_stride;
+    double Z = 0.0, c_old = 0.0;
+    for (int i = threadIdx.x & 63; i < nvc; i += 64) {
+      const double2 p = vc[i];
+      Z += p.x;
+      c_old += p.y;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      Z += __shfl_xor(Z, o);
+      c_old += __shfl_xor(c_old, o);
+    }
+    inv_z = 1.0 / Z;
+    inv_csum = 1.0 / (lam * c_old + (1.0 - lam));
+  }
+  // m_used of a position with usage u; its credit is replaced by the new one
+  __device__ __forceinline__ float operator()(float u, float& credit) const {
+    const float mc = (float)((fmax((double)u, 0.0) + eps) * inv_z);
+    float cn = mc, mu = mc;  // lambda == 0: credit not used, the mass passes through unchanged
+    if (ema) {
+      cn = (float)(lam * (double)credit + (1.0 - lam) * (double)mc);
+      mu = (float)(bet * (double)mc + (1.0 - bet) * ((double)cn * inv_csum));
+    }
+    credit = cn;
+    return mu;
+  }
+};
+
 // Eq. (1) and the EMA, position by position.  Bound: the 16 bytes per position it moves: 134 MB in 27 us (5.0 TB/s) for
 // 256 units of 32768 positions, 235 MB in 46 us for 112 of 131072.  One workgroup per unit that also carried the prefix
 // (scan, barrier and the next loads in turn) took 45 and 114 us, and 30 us for 8 units of 32768, where this takes 5 + 7
@@ -221,22 +257,7 @@ __global__ __launch_bounds__(kBlock) void mass_kernel(MsArgs a, const float* u_a
     load_run(u, j0, T, a.vec, ux[r], 0.f);
     load_run(credit, j0, T, a.vec, cx[r], 0.f);
   }
-  // partial sums of max(u,0)+eps and of the old credit: strided over the lanes, then a fixed tree
-  const int nvc = (T + a.vc_tokens - 1) / a.vc_tokens;
-  const double2* vc = a.vc_part + (int64_t)unit * a.vc_stride;
-  double Z = 0.0, c_old = 0.0;
-  for (int i = lane; i < nvc; i += 64) {
-    const double2 p = vc[i];
-    Z += p.x;
-    c_old += p.y;
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    Z += __shfl_xor(Z, o);
-    c_old += __shfl_xor(c_old, o);
-  }
-  const double lam = (double)lambda, bet = (double)beta, eps = (double)eps_f;
-  const double inv_z = 1.0 / Z, inv_csum = 1.0 / (lam * c_old + (1.0 - lam));
+  const MassOf mass(a, unit, T, lambda, beta, eps_f);
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
     const int j0 = first + (r * kBlock + (int)threadIdx.x) * 4;
@@ -244,16 +265,7 @@ __global__ __launch_bounds__(kBlock) void mass_kernel(MsArgs a, const float* u_a
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       mu[i] = 0.f;
-      if (j0 + i < T) {
-        const float mc = (float)((fmax((double)ux[r][i], 0.0) + eps) * inv_z);
-        float cn = mc;
-        mu[i] = mc;  // lambda == 0: credit not used, the mass passes through unchanged
-        if (lambda != 0.f) {
-          cn = (float)(lam * (double)cx[r][i] + (1.0 - lam) * (double)mc);
-          mu[i] = (float)(bet * (double)mc + (1.0 - bet) * ((double)cn * inv_csum));
-        }
-        cx[r][i] = cn;
-      }
+      if (j0 + i < T) mu[i] = mass(ux[r][i], cx[r][i]);
     }
     store_run(credit, j0, T, a.vec, cx[r]);
     store_run(m_used, j0, T, a.vec, mu);
@@ -351,7 +363,8 @@ __device__ __forceinline__ int split_merge_pass(Cut cut, int K, int T, int l_min
 //   CUTS_GENERAL  fused step: also thresholds k*Delta with the split / merge pass, up to 1024 segments
 //   CUTS_STAGE    ams_mass_segment: no quotas, any sign of m_used (the bisection runs over the largest prefix so far)
 //   CUTS_OWN      the same without the sums of 64 in memory: the workgroup forms them from m_used, in the same order
-enum { CUTS_STEP = 0, CUTS_GENERAL = 1, CUTS_STAGE = 2, CUTS_OWN = 3 };
+//   CUTS_MASS     CUTS_STEP for caches of up to 8 * BLOCK positions, which forms the masses itself (mass_kernel's arithmetic)
+enum { CUTS_STEP = 0, CUTS_GENERAL = 1, CUTS_STAGE = 2, CUTS_OWN = 3, CUTS_MASS = 4 };
 constexpr int kStepMaxSeg = 64;
 
 struct CutsOut {
@@ -360,24 +373,31 @@ struct CutsOut {
   uint32_t* flags;
   int n_words, budget, q_min, n_sink, n_last;
   const int32_t* status;
+  // CUTS_MASS: the usage, the credit (updated in place), where the masses go, and the parameters of Eq. (1) and the EMA
+  const float* u;
+  float *credit, *m_used;
+  float lambda, beta, eps;
 };
 
 template <int BLOCK, int KIND>
 __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel(MsArgs a, const float* m_all, CutsOut o) {
   constexpr int kW = BLOCK / 64, kPerThread = 4, kCapSub = BLOCK * kPerThread, kGroups16 = BLOCK / kSubLanes;
-  constexpr bool kOwn = KIND == CUTS_OWN, kSigned = KIND == CUTS_STAGE || kOwn;
-  constexpr int kCap = KIND == CUTS_STEP ? kStepMaxSeg : kMaxSegments;
+  constexpr bool kOwn = KIND == CUTS_OWN, kSigned = KIND == CUTS_STAGE || kOwn, kMass = KIND == CUTS_MASS;
+  constexpr bool kStep = KIND == CUTS_STEP || kMass;  // thresholds k/S, few of them
+  constexpr int kCap = kStep ? kStepMaxSeg : kMaxSegments;
+  constexpr int ROUNDS = 2;  // CUTS_MASS: runs of four positions per thread
+  __shared__ __align__(16) float m_sm[kMass ? BLOCK * 4 * ROUNDS : 4];
   __shared__ double ends[kCapSub];                   // prefix at the end of every piece of the group
   __shared__ double peak[kSigned ? kCapSub : 1];     // largest prefix up to the end of the piece
   __shared__ double wave_tot[kW], wave_top[kSigned ? kW : 1];
   __shared__ double cpre[kCap + 1];
   __shared__ int32_t bounds[kCap + 1];
   __shared__ float mass[kCap];
-  __shared__ int32_t reseg[KIND == CUTS_STEP ? 1 : kCap + 1];
+  __shared__ int32_t reseg[kStep ? 1 : kCap + 1];
   __shared__ int n_reseg;
   const int unit = blockIdx.x, S = a.S;
-  const int K = KIND == CUTS_STEP ? S : a.K;  // initial segments: thresholds k = 1 .. K-1
-  const bool delta_mode = KIND != CUTS_STEP && a.delta > 0.0;
+  const int K = kStep ? S : a.K;  // initial segments: thresholds k = 1 .. K-1
+  const bool delta_mode = !kStep && a.delta > 0.0;
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
@@ -394,6 +414,32 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
     const int n = min(kCapSub, n_sub - base);
     double v[kPerThread], t[kPerThread];
     const int e0 = (int)threadIdx.x * kPerThread;
+    if constexpr (kMass) {  // (one group)
+      const float* u = o.u + (int64_t)unit * a.d.t_stride;
+      float *credit = o.credit + (int64_t)unit * a.d.t_stride, *out = o.m_used + (int64_t)unit * a.d.t_stride;
+      float ux[ROUNDS][4], cx[ROUNDS][4];
+#pragma unroll
+      for (int r = 0; r < ROUNDS; ++r) {
+        const int j0 = (r * BLOCK + (int)threadIdx.x) * 4;
+        load_run(u, j0, T, a.vec, ux[r], 0.f);
+        load_run(credit, j0, T, a.vec, cx[r], 0.f);
+      }
+      const MassOf mass(a, unit, T, o.lambda, o.beta, o.eps);
+#pragma unroll
+      for (int r = 0; r < ROUNDS; ++r) {
+        const int j0 = (r * BLOCK + (int)threadIdx.x) * 4;
+        float mu[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mu[i] = j0 + i < T ? mass(ux[r][i], cx[r][i]) : 0.f;
+        *reinterpret_cast<float4*>(&m_sm[j0]) = make_float4(mu[0], mu[1], mu[2], mu[3]);
+        double p[4];
+        sub_scan(mu, p);
+        if (l16 == kSubLanes - 1 && j0 - (kSub - 4) < T) ends[j0 / kSub] = p[3];
+        store_run(credit, j0, T, a.vec, cx[r]);
+        store_run(out, j0, T, a.vec, mu);
+      }
+      __syncthreads();
+    }
     if constexpr (kOwn) {
       for (int first = 0; first < n; first += 4 * kGroups16) {  // four pieces per 16 lanes in flight
         const int e = first + (int)threadIdx.x / kSubLanes;
@@ -415,7 +461,9 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
       t[i] = -INFINITY;
       if (e0 + i < n) {
         const int64_t at = (int64_t)unit * a.n_sub + base + e0 + i;
-        if (kOwn) {  // this thread's four entries, which it replaces by the prefixes below
+        if (kMass) {  // this thread's four entries, which it replaces by the prefixes below
+          v[i] = ends[e0 + i];
+        } else if (kOwn) {
           v[i] = ends[e0 + i];
           t[i] = peak[e0 + i];
         } else if (kSigned) {
@@ -480,7 +528,12 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
       }
       const int j0 = (base + lo) * kSub + l16 * 4;
       float x[4];
-      load_run(m_used, j0, T, a.vec, x, 0.f);
+      if constexpr (kMass) {
+        const float4 x4 = *reinterpret_cast<const float4*>(&m_sm[j0]);
+        x[0] = x4.x, x[1] = x4.y, x[2] = x4.z, x[3] = x4.w;
+      } else {
+        load_run(m_used, j0, T, a.vec, x, 0.f);
+      }
       double p[4];
       sub_scan(x, p);
       const double before = lo > 0 ? ends[lo - 1] : C;
@@ -756,9 +809,25 @@ hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* s
   } else {
     usage = own_sums(a, p, u, credit, m_used, s);
   }
-  launch_mass<true>(a, p, usage, credit, m_used, s);
   const CutsOut o{seg_mass, quota, idx, n_kept, must ? flags : nullptr, n_words, p->budget, p->q_min, p->n_sink,
-                  p->n_last, (const int32_t*)park_status_word(ws, wl)};
+                  p->n_last, (const int32_t*)park_status_word(ws, wl), usage, credit, m_used, p->ema_lambda, p->ema_beta,
+                  p->mass_eps};
+  // Short caches: a workgroup holds all masses of its unit, eight positions per thread, and finds the cuts on chip; one launch
+  // and one trip of the masses through memory less: 41.0 -> 39.2 us per step for 8 units of 4096, 32.4 -> 30.6 for 9 of 2105,
+  // 172.2 -> 170.8 for 256 of 2176.  Up to 512 units; more of them keep the whole chip busy with the position-wise kernel
+  // (1152 ragged units of 2435: 230.7 without and 235.3 with, 768 of 5384: 548 and 573).  At 16384 positions there is no gain
+  // any more (24 units of 9804: 91 without and 97 with).
+  if (p->seg_delta == 0.f && p->n_segments <= kStepMaxSeg && d.t_max <= 8192 && d.units <= 512) {
+    prof_mark("unit_mass_cuts", s);
+    if (d.t_max <= 2048)
+      hipLaunchKernelGGL((unit_cuts_kernel<256, CUTS_MASS>), dim3(d.units), dim3(256), 0, s, a, m_used, o);
+    else if (d.t_max <= 4096)
+      hipLaunchKernelGGL((unit_cuts_kernel<512, CUTS_MASS>), dim3(d.units), dim3(512), 0, s, a, m_used, o);
+    else
+      hipLaunchKernelGGL((unit_cuts_kernel<1024, CUTS_MASS>), dim3(d.units), dim3(1024), 0, s, a, m_used, o);
+    return hipGetLastError();
+  }
+  launch_mass<true>(a, p, usage, credit, m_used, s);
   prof_mark("unit_cuts", s);
   if (p->seg_delta > 0.f || p->n_segments > kStepMaxSeg)
     launch_cuts<CUTS_GENERAL>(a, m_used, o, s);

@@ -256,3 +256,24 @@ def test_second_sweep_merges_the_statistics_of_small_launches(oracle, T, dtype, 
     assert ("score_reduce" not in _labels(job)) == folded
     assert to_host(job.n_kept).tolist() == [min(w.budget, int(t)) for t in host["seq_lens"]]
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [1] if T > 1 else [0, 1], scorer=scorer)
+
+
+@pytest.mark.parametrize("vec", [True, False])
+@pytest.mark.parametrize("T,S,fused", [(2048, 64, True), (2049, 5, True), (4096, 64, True), (4097, 7, True), (8192, 64, True),
+                                       (8193, 16, False), (3000, 65, False), (63, 3, True)])
+def test_short_caches_form_masses_and_cuts_in_one_launch(oracle, T, S, fused, vec):
+    """The three workgroup sizes and their edges, ragged and empty sequences, 64 / 65 segments, rows of odd stride."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=3, H=2, G=1, W=8, T=T, T_min=T, budget=max(1, T // 5), S=S, n_spans=3,
+                                 span_len=(1, 30))
+    host = inputs.dense_cache(w, n_threads=4)
+    host["seq_lens"][:] = [T, 0, max(1, T // 2 - 1)]
+    job = Job(w, host)
+    if not vec:
+        job.t_stride = job.p.t_stride = T | 1
+        job.credit = torch.zeros((job.units, job.t_stride), device=DEV)
+        job.ws = torch.zeros(B.ams_workspace_bytes(job.p), dtype=torch.uint8, device=DEV)
+    labels = _labels(job)
+    assert ("unit_mass_cuts" in labels) == fused and ("mass_ema" in labels) != fused
+    assert to_host(job.n_kept).tolist() == [min(w.budget, int(t)) for t in host["seq_lens"] for _ in range(2)]
+    assert (to_host(job.idx)[2:4] == -1).all() and (to_host(job.intermediates().bounds)[2:4] == 0).all()
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, 1, 4, 5])
