@@ -62,6 +62,7 @@ def kernel_bytes(label, w, lens=None):
         "quota": 0,
         "select": 4 * tok + 4 * kept,                     # g in, idx out
         "compact": 4 * kept * D * e + 4 * kept * 3,       # K,V rows in + out, idx, credit gather
+        "select_gather": 4 * tok + 4 * kept + 4 * kept * D * e + 4 * kept * 2,  # both in one launch
     }.get(label, 0)
     return per_layer_head * w.L * w.H
 

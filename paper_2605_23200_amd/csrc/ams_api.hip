@@ -377,11 +377,12 @@ int ams_compress_step(const ams_params* p, const ams_kv_view* src, const int32_t
   if ((e = launch_unit_mass(p, d, seq_lens, u, credit, m_used, bounds, seg_mass, quota, idx, n_kept,
                             (uint32_t*)(w + wl.flags), wl.n_words, vc, w, wl, s)) != hipSuccess)
     return AMS_ERR_HIP;
+  const Gather ga{make_kv(p, src, src->k), vdev, make_kv(p, dst, dst->k), make_kv(p, dst, dst->v), credit, credit_dst};
+  const bool fused = select_gathers(p);
   if ((e = launch_select(p, d, seq_lens, g, bounds, seg_mass, quota, idx, n_kept, (uint32_t*)(w + wl.flags),
-                         wl.n_words, s, true)) != hipSuccess)
+                         wl.n_words, s, true, fused ? &ga : nullptr)) != hipSuccess)
     return AMS_ERR_HIP;
-  if ((e = launch_compact(p, d, make_kv(p, src, src->k), make_kv(p, src, src->v), make_kv(p, dst, dst->k),
-                          make_kv(p, dst, dst->v), idx, n_kept, credit, credit_dst, s)) != hipSuccess)
+  if (!fused && (e = launch_compact(p, d, ga.ks, ga.vs, ga.kd, ga.vd, idx, n_kept, credit, credit_dst, s)) != hipSuccess)
     return AMS_ERR_HIP;
   prof_mark("end", s);
   return AMS_OK;

@@ -139,9 +139,17 @@ hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* s
                             char* ws, const WsLayout& wl, hipStream_t s);
 // flags (n_words words per unit): bitmap of the kept set, needed when a must-keep set is configured, else
 // may be null.  quota_done: the quotas (and what the quota kernels do besides) are already in place.
+// gather: the compaction that follows, done by the workgroups that select (no must-keep set only).
+struct Gather {
+  KvDev ks, vs, kd, vd;
+  const float* credit_src;
+  float* credit_dst;
+};
+bool select_gathers(const ams_params* p);
 hipError_t launch_select(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* g,
                          const int32_t* bounds, float* seg_mass, int32_t* quota, int32_t* idx,
-                         int32_t* n_kept, uint32_t* flags, int n_words, hipStream_t s, bool quota_done = false);
+                         int32_t* n_kept, uint32_t* flags, int n_words, hipStream_t s, bool quota_done = false,
+                         const Gather* gather = nullptr);
 hipError_t launch_compact(const ams_params* p, const Dims& d, const KvDev& ks, const KvDev& vs,
                           const KvDev& kd, const KvDev& vd, const int32_t* idx, const int32_t* n_kept,
                           const float* credit_src, float* credit_dst, hipStream_t s);

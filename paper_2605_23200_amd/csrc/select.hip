@@ -4,10 +4,11 @@
 // quota_kernel   one wave per unit, the segments in registers; the
 //                arithmetic is a handful of double operations per segment and is done in index
 //                order so that it is reproducible bit for bit.
-// select_kernel  one workgroup per (segment, unit): radix select (4 x 8 bits, most significant
-//                digit first) of the quota-th largest score on an order-preserving integer image
-//                of the floats, then an ordered compaction that keeps everything above the
-//                threshold and the first few positions equal to it, ascending.
+// select_kernel  one workgroup per (segment, unit): the quota-th largest score on an order-preserving integer
+//                image of the floats, then an ordered compaction that keeps everything above the
+//                threshold and the first few positions equal to it, ascending.  In the fused step it
+//                may gather the kept rows too (Alg. 1 step 6), several workgroups to a segment where
+//                the launch is small.
 // finalize_kernel  (only with a must-keep set) one workgroup per unit.  The segment picks arrive as
 //                bits of a per-unit bitmap, so the union with the must-keep positions and the removal
 //                of duplicates are one OR; what the duplicates leave open is filled with the best
@@ -71,18 +72,65 @@ __device__ __forceinline__ uint32_t score_key(float x) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// Where a selected position goes: slot `slot` of the ascending index list, or its bit of the bitmap.
+// Where a selected position goes: slot `slot` of the ascending index list (if it lies in the workgroup's share [r0, r1)),
+// or its bit of the bitmap.
 template <bool FLAGS>
 struct Emit {
   int32_t* out;
   uint32_t* flags;
+  int r0, r1;
   __device__ __forceinline__ void operator()(int slot, int t) const {
     if (FLAGS)
       atomicOr(&flags[t >> 5], 1u << (t & 31));
-    else
+    else if (slot >= r0 && slot < r1)
       out[slot] = t;
   }
 };
+
+// What a selection workgroup does with its picks: index list, bits of the unit's map, or index list and gather.
+enum { SELECT_LIST = 0, SELECT_FLAGS = 1, SELECT_GATHER = 2 };
+constexpr int kGatherList = 512;  // picks kept in LDS for the gather; later ones are read back from the index list
+
+struct GatherArgs {
+  KvDev ks, vs, kd, vd;
+  const float* credit_src;
+  float* credit_dst;
+  const int32_t* n_kept;
+  int budget, parts;
+};
+
+// The kept rows of one segment, picks [r0, r1) of it (pick j sits in row out0 + j of the compacted cache): K' = K[idx],
+// V' = V[idx] and the credit (Alg. 1 step 6; App. E for a paged destination).
+template <int BLOCK, typename Pos>
+__device__ __forceinline__ void gather_rows(const Dims& d, const GatherArgs& ga, int unit, int out0, int r0, int r1, Pos pos) {
+  int l, b, h;
+  unit_coords(d, unit, l, b, h);
+  const int lanes = ga.ks.row_bytes / 16, per = BLOCK / lanes;
+  const int sub = threadIdx.x % lanes, r = threadIdx.x / lanes;
+  const float* c_src = ga.credit_src + (int64_t)unit * d.t_stride;
+  float* c_dst = ga.credit_dst ? ga.credit_dst + (int64_t)unit * ga.budget + out0 : nullptr;
+  int jc = r0 + (int)threadIdx.x;
+  float c = 0.f;  // travels with the first rows
+  if (c_dst && jc < r1) c = c_src[pos(jc)];
+  for (int j = r0 + r; j < r1; j += 2 * per) {
+    const bool two = j + per < r1;
+    const int t0 = pos(j), t1 = two ? pos(j + per) : t0;
+    const uint4 k0 = *(const uint4*)(kv_row(ga.ks, l, b, h, t0) + sub * 16);
+    const uint4 v0 = *(const uint4*)(kv_row(ga.vs, l, b, h, t0) + sub * 16);
+    const uint4 k1 = *(const uint4*)(kv_row(ga.ks, l, b, h, t1) + sub * 16);
+    const uint4 v1 = *(const uint4*)(kv_row(ga.vs, l, b, h, t1) + sub * 16);
+    *(uint4*)(kv_row(ga.kd, l, b, h, out0 + j) + sub * 16) = k0;
+    *(uint4*)(kv_row(ga.vd, l, b, h, out0 + j) + sub * 16) = v0;
+    if (two) {
+      *(uint4*)(kv_row(ga.kd, l, b, h, out0 + j + per) + sub * 16) = k1;
+      *(uint4*)(kv_row(ga.vd, l, b, h, out0 + j + per) + sub * 16) = v1;
+    }
+  }
+  if (c_dst && jc < r1) {
+    c_dst[jc] = c;
+    for (jc += BLOCK; jc < r1; jc += BLOCK) c_dst[jc] = c_src[pos(jc)];
+  }
+}
 
 // The selection kernel holds the keys of a segment in registers: BLOCK threads with PER keys each.  One wave takes the
 // many short segments (no barriers between waves), 256, 512 and 1024 threads the longer ones; a segment that is longer
@@ -199,11 +247,12 @@ __device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
 // keys that are all equal are taken in position order.  (Ranking up to 256 listed keys through LDS instead of one more
 // pass took 16 us longer for 72 segments of 1457 normal scores.)  The picks are bits of a map of the segment, whose
 // running count gives every pick its place in the ascending list.
-template <bool FLAGS, int BLOCK, int PER>
+template <int MODE, int BLOCK, int PER>
 __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget, const float* g_all,
                                                        const int32_t* bounds_all,
                                                        const int32_t* quota_all, int32_t* idx_all,
-                                                       uint32_t* flags_all, int n_words) {
+                                                       uint32_t* flags_all, int n_words, GatherArgs ga) {
+  constexpr bool FLAGS = MODE == SELECT_FLAGS, GATHER = MODE == SELECT_GATHER;
   constexpr int kW = BLOCK / 64, kCap = BLOCK * PER, kWords = kCap / 64, kPerLane = (kWords + 63) / 64;
   constexpr int kList = 64;  // keys that one wave ranks
   __shared__ __align__(16) int hist[2][256];
@@ -215,12 +264,21 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget
   __shared__ int2 wave_cnt[kW];
   __shared__ uint32_t mem_prefix;
   __shared__ int mem_rem;
-  const int unit = blockIdx.y, seg = blockIdx.x;
+  __shared__ int32_t rows[GATHER ? kGatherList : 1];
+  const int unit = blockIdx.y, seg = GATHER ? (int)blockIdx.x / ga.parts : (int)blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int32_t* bounds = bounds_all + (int64_t)unit * (S + 1);
   const int32_t* quota = quota_all + (int64_t)unit * S;
   const int a = bounds[seg], b = bounds[seg + 1], q = quota[seg];
-  if (q <= 0) return;
+  if (GATHER && ga.n_kept[unit] < 0) return;  // a scorer's bounded wait expired: nothing is kept
+  // this workgroup's share of the segment's picks, by their place in ascending order
+  int r0 = 0, r1 = q;
+  if (GATHER && ga.parts > 1) {
+    const int part = (int)blockIdx.x - seg * ga.parts;
+    r0 = (int)((int64_t)q * part / ga.parts);
+    r1 = (int)((int64_t)q * (part + 1) / ga.parts);
+  }
+  if (r0 >= r1) return;
   const int L = b - a;
   const float* g = g_all + (int64_t)unit * d.t_stride;
   uint32_t key[PER];
@@ -238,13 +296,18 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget
     out0 = wave_sum(out0);
   }
   const Emit<FLAGS> emit{idx_all + (int64_t)unit * budget + out0,
-                         FLAGS ? flags_all + (int64_t)unit * n_words : nullptr};
+                         FLAGS ? flags_all + (int64_t)unit * n_words : nullptr, r0, r1};
   if (q >= L) {  // whole segment kept
     for (int j = threadIdx.x; j < L; j += BLOCK) emit(j, a + j);
+    if (GATHER) gather_rows<BLOCK>(d, ga, unit, out0, r0, r1, [&](int j) { return a + j; });
     return;
   }
   if (from_memory) {
     select_from_memory<FLAGS, BLOCK>(g, a, b, q, emit, &hist[0][0], &mem_prefix, &mem_rem, wave_cnt);
+    if (GATHER) {
+      __syncthreads();
+      gather_rows<BLOCK>(d, ga, unit, out0, r0, r1, [&](int j) { return emit.out[j]; });
+    }
     return;
   }
 
@@ -395,9 +458,17 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget
     const int w = i * kW + wave;
     if (w < words) {
       const uint64_t m = picked[w];
-      if ((m >> lane) & 1ull)
-        emit.out[before[w] + __popcll(m & ((1ull << lane) - 1ull))] = a + i * BLOCK + (int)threadIdx.x;
+      if ((m >> lane) & 1ull) {
+        const int j = before[w] + __popcll(m & ((1ull << lane) - 1ull)), t = a + i * BLOCK + (int)threadIdx.x;
+        emit(j, t);
+        if (GATHER && j >= r0 && j - r0 < kGatherList) rows[j - r0] = t;
+      }
     }
+  }
+  if (GATHER) {
+    __syncthreads();
+    gather_rows<BLOCK>(d, ga, unit, out0, r0, r1,
+                       [&](int j) { return j - r0 < kGatherList ? rows[j - r0] : emit.out[j]; });
   }
 }
 
@@ -676,22 +747,34 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
 
 }  // namespace
 
+// The workgroups that select gather the rows as well: one launch less, and the latency of the selections that are still
+// running hides behind the rows of the others.  us per step, with a gather kernel and without: 39.2 and 37.2 (8 fp32 units
+// of 4096 positions, 1024 kept), 995 and 983 (256 units of 32768, 2048 kept), 167 and 162.5 (192 ragged units of up to 9001,
+// 512 kept), 410 and 397 (1708 units of 1933, 144 kept), 141 and 136.5 (32 units of 27209, 3100 kept in 64 segments).  The gather
+// kernel stays where the picks of a workgroup are many or few: long segments (8780 expected: 315 and 331 with short shares),
+// most of the cache kept (256 units, 2048 of 2176: 171 and 177), a couple of rows per segment (93.5 and 94.8); and where
+// the kept set is only known after finalize_kernel.
+bool select_gathers(const ams_params* p) {
+  const int S = p->n_segments, keep = p->budget < p->t_max ? p->budget : p->t_max;
+  return p->n_sink == 0 && p->n_last == 0 && p->seg_delta == 0.f && (int64_t)p->t_max <= (int64_t)2560 * S &&
+         (int64_t)keep * 2 < p->t_max && keep >= 8 * S;
+}
+
 hipError_t launch_select(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* g,
                          const int32_t* bounds, float* seg_mass, int32_t* quota, int32_t* idx,
-                         int32_t* n_kept, uint32_t* flags, int n_words, hipStream_t s, bool quota_done) {
+                         int32_t* n_kept, uint32_t* flags, int n_words, hipStream_t s, bool quota_done,
+                         const Gather* gather) {
   const int S = p->n_segments;
   if (S > kMaxSeg) return hipErrorInvalidValue;
   const bool must = p->n_sink > 0 || p->n_last > 0;
-  if (must && !flags) return hipErrorInvalidValue;
-  if (!quota_done) prof_mark("quota", s);
-  if (quota_done) {
-    // quotas, the tail of idx, the kept count and the cleared bitmap are already in place
-  } else {
+  if (must && (!flags || gather)) return hipErrorInvalidValue;
+  if (!quota_done) {  // else the quotas, the tail of idx, the kept count and the cleared bitmap are already in place
+    prof_mark("quota", s);
     hipLaunchKernelGGL(quota_kernel, dim3(d.units), dim3(64), 0, s, d, seq_lens, S, p->budget, p->q_min,
                        bounds, seg_mass, quota, idx, n_kept, p->n_sink, p->n_last,
                        must ? flags : nullptr, n_words);
   }
-  prof_mark("select", s);
+  prof_mark(gather ? "select_gather" : "select", s);
   // The expected segment length decides the shape of the selection workgroups (one wave: 1024 keys, 256 threads: 4096,
   // 512: 8192, 1024: 32768).  Segments differ by a factor of two or so, so a shape is left where longer ones would start
   // to miss the registers: 4096 expected takes 2272 us per step with 512 threads and 2328 with 1024 (2286 with 256, many
@@ -700,29 +783,39 @@ hipError_t launch_select(const ams_params* p, const Dims& d, const int32_t* seq_
   const double expect = p->seg_delta > 0.f
                             ? (p->l_max > 0 ? (double)p->l_max : (double)p->t_max * (double)p->seg_delta)
                             : (double)p->t_max / (double)S;
-  const dim3 grid(S, d.units);
-#define AMS_SELECT(FLAGS, BLOCK, PER)                                                                               \
-  hipLaunchKernelGGL((select_kernel<FLAGS, BLOCK, PER>), grid, dim3(BLOCK), 0, s, d, S, p->budget, g, bounds, quota, \
-                     idx, flags, n_words)
-#define AMS_SELECT_SHAPE(FLAGS)             \
-  if (expect <= 256.0)                     \
-    AMS_SELECT(FLAGS, 64, 16);              \
-  else if (expect <= 2560.0)               \
-    AMS_SELECT(FLAGS, 256, 16);             \
-  else if (expect <= 5120.0)               \
-    AMS_SELECT(FLAGS, 512, 16);             \
-  else                                      \
-    AMS_SELECT(FLAGS, 1024, 32)
-  if (!must) {
-    AMS_SELECT_SHAPE(false);
-    return hipGetLastError();
+  GatherArgs ga{};
+  if (gather) {
+    ga = GatherArgs{gather->ks, gather->vs, gather->kd, gather->vd, gather->credit_src, gather->credit_dst, n_kept, p->budget, 1};
+    // a small launch gives a segment's rows to several workgroups, which all select: 42.4 us per step for 8 fp32 units of 8
+    // segments with one workgroup each, 37.2 with four (1024 rows of 512 bytes kept per unit); 59 and 52 for 6 units of 8
+    const int rows = min(p->budget, d.t_max) / S;
+    while ((int64_t)S * d.units * ga.parts < 512 && rows / (2 * ga.parts) >= 32) ga.parts *= 2;
   }
-  AMS_SELECT_SHAPE(true);
+  const dim3 grid(S * (gather ? ga.parts : 1), d.units);
+#define AMS_SELECT(MODE, BLOCK, PER)                                                                               \
+  hipLaunchKernelGGL((select_kernel<MODE, BLOCK, PER>), grid, dim3(BLOCK), 0, s, d, S, p->budget, g, bounds, quota, \
+                     idx, flags, n_words, ga)
+#define AMS_SELECT_SHAPE(MODE)             \
+  if (expect <= 256.0)                     \
+    AMS_SELECT(MODE, 64, 16);              \
+  else if (expect <= 2560.0)               \
+    AMS_SELECT(MODE, 256, 16);             \
+  else if (expect <= 5120.0)               \
+    AMS_SELECT(MODE, 512, 16);             \
+  else                                     \
+    AMS_SELECT(MODE, 1024, 32)
+  if (must) {
+    AMS_SELECT_SHAPE(SELECT_FLAGS);
+    prof_mark("finalize", s);
+    hipLaunchKernelGGL(finalize_kernel, dim3(d.units), dim3(kFinBlock), 0, s, d, seq_lens, p->budget, p->n_sink,
+                       p->n_last, g, flags, n_words, idx);
+  } else if (gather) {
+    AMS_SELECT_SHAPE(SELECT_GATHER);
+  } else {
+    AMS_SELECT_SHAPE(SELECT_LIST);
+  }
 #undef AMS_SELECT_SHAPE
 #undef AMS_SELECT
-  prof_mark("finalize", s);
-  hipLaunchKernelGGL(finalize_kernel, dim3(d.units), dim3(kFinBlock), 0, s, d, seq_lens, p->budget, p->n_sink,
-                     p->n_last, g, flags, n_words, idx);
   return hipGetLastError();
 }
 

@@ -277,3 +277,27 @@ def test_short_caches_form_masses_and_cuts_in_one_launch(oracle, T, S, fused, ve
     assert to_host(job.n_kept).tolist() == [min(w.budget, int(t)) for t in host["seq_lens"] for _ in range(2)]
     assert (to_host(job.idx)[2:4] == -1).all() and (to_host(job.intermediates().bounds)[2:4] == 0).all()
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, 1, 4, 5])
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("bf16", 128), ("f32", 128)])
+@pytest.mark.parametrize("T,S,budget,gathers", [(9000, 4, 3000, True), (10240, 4, 4000, True), (10241, 4, 1000, False),
+                                                (5000, 16, 128, True), (5000, 16, 127, False), (700, 4, 349, True),
+                                                (700, 4, 350, False), (2000, 1, 900, True)])
+def test_selection_gathers_its_rows(oracle, T, S, budget, gathers, dtype, D, paged):
+    """Shares of a segment's picks over one to sixteen workgroups; picks beyond the list in LDS; a segment longer than the
+    registers hold (half of the mass lies in a few positions in front of it); segments kept whole; both layouts."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=2, H=2, G=1, W=8, D=D, T=T, T_min=T, dtype=dtype, budget=budget, S=S, n_spans=0,
+                                 paged=paged)
+    host = inputs.dense_cache(w, n_threads=4)
+    host["seq_lens"][:] = [T, T - 3]
+    k, q = inputs.as_f32(host["K"]).copy(), inputs.as_f32(host["Q"])
+    for h in range(2):
+        qbar = q[0, 0, h].mean(0)
+        k[0, 0, h, 5:9] += 9 * qbar / np.linalg.norm(qbar)     # the first sequence: most thresholds fall on four positions
+    host["K"] = inputs._store(k, dtype)
+    job = Job(w, host)
+    labels = _labels(job)
+    assert ("select_gather" in labels) == gathers and ("compact" in labels) != gathers
+    check_properties_all_units(job)
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), list(range(w.units)))
