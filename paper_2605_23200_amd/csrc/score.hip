@@ -366,8 +366,9 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   // 5 of its own): every workgroup reads its unit's partial statistics once more.  us per step, with the kernel and without:
   // 44.5 and 41.0 (8 fp32 units of 4096), 33.7 and 32.4 (9 units of 2105), 95.5 and 92 (24 fp32 units of 9804, 240
   // workgroups), 147.8 and 143.6 (32 units of 27209, 864 workgroups), 99.8 and 97.3 (48 units of 1376, 224 queries).  With up
-  // to 2048 workgroups or 128 chunks there is no gain any more (828 units of 12608: 822 and 827).
-  a.fold = !causal && (int64_t)d.units * a.n_chunks <= 1024 && a.n_chunks <= 64;
+  // to 2048 workgroups or 128 chunks there is no gain any more (828 units of 12608: 822 and 827), and with more than 32 KB of
+  // partial statistics per unit every workgroup takes as long as the kernel (4 fp32 units of 7328, 112 queries: 61.6 and 63.9).
+  a.fold = !causal && (int64_t)d.units * a.n_chunks <= 1024 && a.n_chunks * a.n_pad <= 4096;
   a.inv_sqrt_d = (float)(1.0 / sqrt((double)d.D));
   a.c2 = (float)(1.4426950408889634 / sqrt((double)d.D));
   const bool bf16 = p->kv_dtype == AMS_BF16;

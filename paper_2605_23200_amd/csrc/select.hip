@@ -788,8 +788,9 @@ hipError_t launch_select(const ams_params* p, const Dims& d, const int32_t* seq_
     ga = GatherArgs{gather->ks, gather->vs, gather->kd, gather->vd, gather->credit_src, gather->credit_dst, n_kept, p->budget, 1};
     // a small launch gives a segment's rows to several workgroups, which all select: 42.4 us per step for 8 fp32 units of 8
     // segments with one workgroup each, 37.2 with four (1024 rows of 512 bytes kept per unit); 59 and 52 for 6 units of 8
+    // (at least 8 KB of keys to a share: what 256 threads move in two steps)
     const int rows = min(p->budget, d.t_max) / S;
-    while ((int64_t)S * d.units * ga.parts < 512 && rows / (2 * ga.parts) >= 32) ga.parts *= 2;
+    while ((int64_t)S * d.units * ga.parts < 512 && rows / (2 * ga.parts) * ga.ks.row_bytes >= 8192) ga.parts *= 2;
   }
   const dim3 grid(S * (gather ? ga.parts : 1), d.units);
 #define AMS_SELECT(MODE, BLOCK, PER)                                                                               \

@@ -240,11 +240,12 @@ def _labels(job):
 
 @pytest.mark.parametrize("scorer", [B.SCORER_MEAN_WINDOW, B.SCORER_LAST_QUERY, B.SCORER_KEYDIFF, B.SCORER_REDUNDANCY,
                                     B.SCORER_EXPECTED_VNORM])
-@pytest.mark.parametrize("T,dtype,G,W,D,folded", [(8192, "bf16", 7, 32, 128, True), (8193, "bf16", 4, 32, 64, False),
+@pytest.mark.parametrize("T,dtype,G,W,D,folded", [(8192, "bf16", 2, 32, 128, True), (8193, "bf16", 2, 32, 64, False),
+                                                  (2304, "bf16", 7, 32, 128, True), (4097, "bf16", 4, 32, 128, False),
                                                   (5000, "f32", 2, 20, 128, True), (130, "bf16", 1, 8, 128, True),
                                                   (1, "bf16", 4, 8, 128, True)])
 def test_second_sweep_merges_the_statistics_of_small_launches(oracle, T, dtype, G, W, D, folded, scorer):
-    """64 and 65 chunks of one unit; the empty first sequence has no workgroup that gets as far as its merge, and the scratch
+    """64 chunks of 64 columns and one more, 18 of 224, 33 of 128 (32 KB of statistics is the limit); the empty first sequence has no workgroup that gets as far as its merge, and the scratch
     holds garbage (a status word that nobody cleared would void the event)."""
     w = inputs.CONFIGS[1].scaled(L=1, B=2, H=1, G=G, W=W, D=D, T=T, T_min=T, dtype=dtype, budget=max(1, min(96, T // 3)), S=4,
                                  n_spans=2, span_len=(1, 40))
