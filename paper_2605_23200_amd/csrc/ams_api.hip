@@ -25,8 +25,9 @@ static int padded_queries(int n, bool bf16) {
 }
 
 // Tokens per workgroup of the scoring sweeps: as many as possible (the query window is loaded once per
-// workgroup), but few enough that the launch has a couple of thousand workgroups to fill 256 CUs.
-static int pick_score_chunk(size_t units, int t_max, bool paged, int most) {
+// workgroup), but few enough that the launch has a couple of thousand workgroups to fill 256 CUs.  even: all sequences have
+// t_max positions as far as the host can tell; small_tiles: the sweeps' tiles leave room for four workgroups on a CU.
+static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool even, bool small_tiles) {
   // measured on 256 units: 4096 tokens at 32k positions (1.060 ms per step against 1.077 with 2048 and
   // 1.13 with 1024), 1024 at 2176 positions (0.208 against 0.229 with 2048); 512 and 256 lose to the
   // per-workgroup load of the query window
@@ -44,6 +45,23 @@ static int pick_score_chunk(size_t units, int t_max, bool paged, int most) {
   // per step with the value-weighted score where it took 129 with chunks of 1024, and 123 where it took 168 with the fp32 key
   // diversity; 1 to 8 units of 8192 to 131072 positions take 0.44 to 0.88 of what they took)
   while (chunk > kMinScoreChunk && units * (size_t)div_up(t_max, chunk) < 256) chunk /= 2;
+  // Units of one length whose keys fit one round of workgroups: chunks that give every compute unit the same number of
+  // workgroups, two of them (three where a tile takes few registers, one where there is not enough work), if they come out
+  // at least 85 % full.  Chunks of a power of two leave a second round of workgroups to a part of the chip; us per step with
+  // them and with this rule, bf16, 128 channels: 182 and 172 (64 units of 16384, 128 queries), 269 and 263 (90 of 20000), 61.0
+  // and 57.1 (8 of 20000), 181 and 141 (20 of 30000, 224 queries); 111 and 99 (57 of 20000, 64 channels); 215 and 180 (20 of
+  // 30000, fp32).  One workgroup per CU where two would do, or three large tiles, lose: 84 and 92 (40 of 11000), 316 and 333
+  // (128 of 16384).  Ragged sequences keep the power of two: their workgroups end at different times whatever the cut (209
+  // against 229 for 2 sequences of 11003 and 20011 positions in chunks of 2304).
+  if (!paged && even) {
+    const bool few = chunk < 1024;
+    for (int per_cu = few ? 1 : small_tiles ? 3 : 2; per_cu >= (few ? 1 : 2); --per_cu) {
+      const size_t n = (size_t)per_cu * 256 / units;
+      if (n == 0) break;
+      const int c = div_up(div_up(t_max, (int64_t)n), kMinScoreChunk) * kMinScoreChunk;
+      if (c <= most && (few || c > 512) && (double)units * t_max >= 0.85 * 256.0 * per_cu * c) return c;
+    }
+  }
   return chunk;
 }
 
@@ -53,8 +71,9 @@ WsLayout ws_layout(const ams_params* p) {
   // the key-based scores collect their g in LDS next to u, next to a larger query window: half the chunk keeps three
   // workgroups on a CU
   const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY ? kKeysChunk : kScoreChunk;
-  w.score_chunk = pick_score_chunk(units, p->t_max, false, most);
-  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most);
+  const bool small_tiles = p->kv_dtype == AMS_BF16 && (p->group * p->window <= 64 || p->head_dim == 64);
+  w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles);
+  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false);
   w.n_chunks = div_up(p->t_max, w.score_chunk);
   w.n_chunks_paged = div_up(p->t_max, w.score_chunk_paged);
   const size_t nc_cap = (size_t)max(w.n_chunks, w.n_chunks_paged);  // the parameters do not say which layout comes

@@ -302,3 +302,19 @@ def test_selection_gathers_its_rows(oracle, T, S, budget, gathers, dtype, D, pag
     assert ("select_gather" in labels) == gathers and ("compact" in labels) != gathers
     check_properties_all_units(job)
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), list(range(w.units)))
+
+
+@pytest.mark.parametrize("scorer,causal", [(B.SCORER_MEAN_WINDOW, False), (B.SCORER_LAST_QUERY, True), (B.SCORER_KEYDIFF, False),
+                                           (B.SCORER_REDUNDANCY, False), (B.SCORER_EXPECTED_VNORM, True)])
+@pytest.mark.parametrize("units,T,dtype,G,W,D", [(5, 30000, "bf16", 7, 32, 128),    # one workgroup per CU, chunks of 640
+                                                 (64, 6000, "bf16", 4, 32, 128),    # two, 768
+                                                 (64, 7001, "bf16", 2, 8, 128),     # three, 640
+                                                 (20, 16001, "f32", 1, 8, 128),     # two, 640
+                                                 (12, 22001, "bf16", 4, 32, 64)])   # three, 384 is too short: two, 640
+def test_chunks_that_fill_one_round(oracle, units, T, dtype, G, W, D, scorer, causal):
+    """Chunks that are no power of two: every part of a step that counts in chunks, ragged last chunks."""
+    w = inputs.CONFIGS[1].scaled(L=units // 4 if units % 4 == 0 else 1, H=4 if units % 4 == 0 else units, D=D, G=G, W=W, T=T,
+                                 T_min=T, dtype=dtype, budget=200, S=8, n_spans=4, span_len=(8, 200), causal=causal)
+    if scorer == B.SCORER_REDUNDANCY and T > 7000:
+        pytest.skip("the oracle evaluates the T^2 definition: minutes at this length")
+    _run(oracle, w, scorer=scorer, units=[0, units // 2, units - 1] if scorer != B.SCORER_REDUNDANCY else [units - 1])
