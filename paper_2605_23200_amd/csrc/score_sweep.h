@@ -35,6 +35,9 @@ constexpr int kGroup = (NB % AMS_SCORE_GROUP_DIV == 0 && NB >= 4) ? NB / AMS_SCO
 #ifndef AMS_SCORE_PIPE_MIN_NB
 #define AMS_SCORE_PIPE_MIN_NB 5
 #endif
+// Column blocks without padding, whatever the number of queries that NB column blocks are taken for (NB of 1, 2, 4, 7, 8).
+template <int NB>
+constexpr int kFullBlocks = NB == 8 ? 7 : NB == 7 ? 4 : NB / 2;
 template <bool BF16, int NB, bool TAIL>
 constexpr bool kPipe = BF16 && !TAIL && NB >= AMS_SCORE_PIPE_MIN_NB;
 
@@ -190,16 +193,27 @@ __device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
 //
 // MOMENTS (expected-attention score, Sec. 3.3 plug-in scorer): the log of the Gaussian moment of the
 // window's queries is mean_n s + var_n s / 2 over the N logits of a token.  It needs no softmax
-// statistics, so it is formed here, where few registers are live, from sums of (s - r) and (s - r)^2
-// with r the token's logit against the unit's first query (a reference close to the mean keeps the
-// subtraction of the squares harmless).  Raw logits are used: the causal mask does not apply.
+// statistics, so it is formed here, where few registers are live.  Raw logits are used: the causal mask does not apply.
+// Centred form (bf16): the mean logit of a token is its product with the mean query, which takes part as three bf16 terms
+// that add up to its fp32 value, the same in all columns of a tile; the products with the queries then start from minus
+// that tile, so that the accumulators are s - mean and the variance is one multiply-add per logit (24 more matrix
+// instructions per block of 32 keys, one vector instruction per logit for the variance and one for s itself instead of four,
+// one reduction over the lanes instead of three).  256 units of 32768 positions, 128 queries: 1195 -> 1157 us per step, 454 ->
+// 428 with 64 channels and 16384 positions.  With seven or eight column blocks of 128 channels it spills (1835 -> 1933, 659 ->
+// 958): there, in the causal tail and for fp32 caches, where the extra products are not hidden, the sums are those of
+// (s - r) and (s - r)^2 with r the token's logit against the unit's first query (a reference close to the mean keeps
+// the subtraction of the squares harmless).
 template <bool BF16, int NB, bool TAIL, bool MOMENTS, int HD, int KEYS = KEYS_NONE>
 __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
   constexpr bool kSpare = KEYS == KEYS_COS && HD == 128 && NB >= 7;  // see KEYS above
+  constexpr bool kCentred = MOMENTS && BF16 && !TAIL && (NB <= 4 || HD == 64);  // see MOMENTS above
   constexpr int NG = kGroup<NB>, QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
-  __shared__ float2 xch[4][NB * 32];
+  __shared__ float2 xch_own[kCentred ? 1 : 4][NB * 32];
+  // the centred sweep needs the room: its exchange takes the place of the query window, which is used up by then
+  float2(*xch)[NB * 32] = kCentred ? (float2(*)[NB * 32])qlds : xch_own;
+  __shared__ __align__(16) char mean_sm[kCentred ? 3 * HD * 2 : 16];  // minus the mean query in three bf16 terms
   int unit, chunk;
   sweep_tile(a, TAIL, false, unit, chunk);
   int l, b, h;
@@ -243,7 +257,42 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
   }
   const float c2 = a.c2;
   float* g_row = MOMENTS ? a.g + (int64_t)unit * a.d.t_stride : nullptr;
-  __shared__ float g_sm[MOMENTS ? kScoreChunk : 1];  // the chunk's moment scores, written once at the end
+  __shared__ __align__(16) float g_sm[MOMENTS ? kScoreChunk : 4];  // the chunk's moment scores, written once at the end
+  if constexpr (kCentred) {
+    constexpr int PAIRS = HD / 2, PARTS = kThreads / PAIRS;
+    double2* sums = (double2*)g_sm;
+    const int pair = threadIdx.x % PAIRS;
+    double2 t = make_double2(0.0, 0.0);
+#pragma unroll 8
+    for (int n = threadIdx.x / PAIRS; n < a.d.N; n += PARTS) {
+      const uint32_t v = *(const uint32_t*)(qlds + n * QS + pair * 4);
+      t.x += (double)__uint_as_float(v << 16);
+      t.y += (double)__uint_as_float(v & 0xFFFF0000u);
+    }
+    sums[threadIdx.x] = t;
+    __syncthreads();
+    if (threadIdx.x < PAIRS) {
+      for (int p = 1; p < PARTS; ++p) {
+        t.x += sums[p * PAIRS + pair].x;
+        t.y += sums[p * PAIRS + pair].y;
+      }
+      const float x[2] = {(float)(-t.x / (double)a.d.N), (float)(-t.y / (double)a.d.N)};
+      uint32_t term[3] = {0, 0, 0};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        float r = x[e];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const uint32_t h = __float_as_uint(r) & 0xFFFF0000u;
+          term[j] |= e ? h : h >> 16;
+          r -= __uint_as_float(h);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 3; ++j) *(uint32_t*)(mean_sm + j * HD * 2 + pair * 4) = term[j];
+    }
+    __syncthreads();
+  }
   auto block_of = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0, auto ragged_c) __attribute__((always_inline)) {
     constexpr bool ragged = decltype(ragged_c)::value;  // the block reaches past the end of the cache
     // the query fragments are re-read from LDS for every block: keeping them in registers across
@@ -251,8 +300,30 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
     int qoff = 0;
     asm volatile("" : "+s"(qoff));
     float ref[16], s1[16], s2[16];
+    floatx16 centre;  // minus the mean logit of every token
+    if constexpr (kCentred) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) centre[i] = s2[i] = 0.f;
+      const char* mb = mean_sm + qoff + hf * HD;
+#pragma unroll
+      for (int j = 2; j >= 0; --j)  // smallest terms first
+#pragma unroll
+        for (int ks = 0; ks < Tr<BF16, HD>::kAVecs; ++ks)
+          centre = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[ks]),
+                                                           __builtin_bit_cast(bf16x8, *(const uint4*)(mb + j * HD * 2 + ks * 16)),
+                                                           centre, 0, 0, 0);
+    }
     // the vector work on one column block of logits
-    auto col_moments = [&](const floatx16& acc, int nb) __attribute__((always_inline)) {
+    auto col_moments = [&](floatx16& acc, int nb) __attribute__((always_inline)) {
+      if constexpr (kCentred) {
+        // padded query columns do not count; the first ones are real with every N that takes NB column blocks
+        const bool real = nb < kFullBlocks<NB> || nb * 32 + (lane & 31) < a.d.N;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s2[i] = __builtin_fmaf(real ? acc[i] : 0.f, acc[i], s2[i]);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] -= centre[i];  // the logit itself
+        return;
+      }
       if (nb == 0) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -298,12 +369,16 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
       col_frags<BF16, HD>(qb, bq[0]);
       col_frags<BF16, HD>(qb + 32 * QS, bq[1]);
       __builtin_amdgcn_sched_barrier(0);
-      col_mma<BF16, HD>(av, bq[0], acc2[0]);
+      if constexpr (kCentred) acc2[0] = centre;
+      col_mma<BF16, HD, !kCentred>(av, bq[0], acc2[0]);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         __builtin_amdgcn_sched_barrier(0);
         if (nb + 2 < NB) col_frags<BF16, HD>(qb + (nb + 2) * 32 * QS, bq[nb & 1]);
-        if (nb + 1 < NB) col_mma<BF16, HD>(av, bq[(nb + 1) & 1], acc2[(nb + 1) & 1]);
+        if (nb + 1 < NB) {
+          if constexpr (kCentred) acc2[(nb + 1) & 1] = centre;
+          col_mma<BF16, HD, !kCentred>(av, bq[(nb + 1) & 1], acc2[(nb + 1) & 1]);
+        }
         if (MOMENTS) col_moments(acc2[nb & 1], nb);
         col_stats(acc2[nb & 1], nb);
         if (nb + 2 < NB)
@@ -325,7 +400,11 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
 #pragma unroll
       for (int g0 = 0; g0 < NB; g0 += NG) {
         floatx16 acc[NG];
-        tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+        if constexpr (kCentred) {
+#pragma unroll
+          for (int k = 0; k < NG; ++k) acc[k] = centre;
+        }
+        tile_mma<BF16, NG, HD, !kCentred>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
         if (MOMENTS) {
 #pragma unroll
           for (int k = 0; k < NG; ++k) col_moments(acc[k], g0 + k);
@@ -336,7 +415,15 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
     }
     if constexpr (KEYS != KEYS_NONE)
       add_keys<HD, KEYS == KEYS_COS>(av, ident, inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
-    if (MOMENTS) {
+    if constexpr (kCentred) {
+      const int c = lane & 31, t = t0 + acc_row(c >> 1, hf);
+      // the variance's share of every lane, and the mean (the same in all of them) from the first one
+      const float k_var = 0.5f * a.inv_sqrt_d * a.inv_sqrt_d / (float)a.d.N, k_mean = c == 0 ? -a.inv_sqrt_d / k_var : 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s2[i] = __builtin_fmaf(centre[i], k_mean, s2[i]);
+      const float e = reduce16_over32(s2, c) * k_var;
+      if ((c & 1) == 0 && t < T_all) g_sm[t - c0] = e;
+    } else if (MOMENTS) {
       const int c = lane & 31;
       float rr[16];
 #pragma unroll
@@ -365,6 +452,7 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
     if (t0 + 256 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 256, T, lane, av0, blk, c0);
     block(av1, t0 + 128);
   }
+  if (kCentred) __syncthreads();
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const float m2 = __shfl_xor(m[nb], 32), z2 = __shfl_xor(z[nb], 32);

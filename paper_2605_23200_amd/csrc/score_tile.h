@@ -114,13 +114,14 @@ __device__ __forceinline__ void stage_blocks(const ScoreArgs& a, int b, int c0, 
 }
 
 // acc[nb][i] = s_raw[token 8*(i/4) + 4*hf + i%4][query nb*32 + lane%32]
-template <bool BF16, int NB, int HD = 128>
+// (CLEAR = false: acc starts from what it holds)
+template <bool BF16, int NB, int HD = 128, bool CLEAR = true>
 __device__ __forceinline__ void tile_mma(const uint4 (&av)[Tr<BF16, HD>::kAVecs], const char* qlds,
                                          int lane, floatx16 (&acc)[NB]) {
   constexpr int QS = Tr<BF16, HD>::kQStride, NV = Tr<BF16, HD>::kAVecs;
   const char* qb = qlds + (lane & 31) * QS + (lane >> 5) * (Tr<BF16, HD>::kRowBytes / 2);
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
+  for (int nb = 0; nb < NB && CLEAR; ++nb)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[nb][i] = 0.f;
   if constexpr (BF16) {
@@ -165,12 +166,12 @@ __device__ __forceinline__ void col_frags(const char* qb, uint4 (&bq)[Tr<BF16, H
 #pragma unroll
   for (int ks = 0; ks < Tr<BF16, HD>::kAVecs; ++ks) bq[ks] = *(const uint4*)(qb + ks * 16);
 }
-template <bool BF16, int HD = 128>
+template <bool BF16, int HD = 128, bool CLEAR = true>
 __device__ __forceinline__ void col_mma(const uint4 (&av)[Tr<BF16, HD>::kAVecs],
                                         const uint4 (&bq)[Tr<BF16, HD>::kAVecs], floatx16& acc) {
   static_assert(BF16, "the pipelined walk is written for bf16 caches");
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  for (int i = 0; i < 16 && CLEAR; ++i) acc[i] = 0.f;
 #pragma unroll
   for (int ks = 0; ks < Tr<BF16, HD>::kAVecs; ++ks)
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av[ks]), __builtin_bit_cast(bf16x8, bq[ks]),
