@@ -70,7 +70,8 @@ WsLayout ws_layout(const ams_params* p) {
   const size_t units = (size_t)p->n_layers * p->batch * p->n_kv_heads;
   // the key-based scores collect their g in LDS next to u, next to a larger query window: half the chunk keeps three
   // workgroups on a CU
-  const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY ? kKeysChunk : kScoreChunk;
+  // (fp32: the three terms of the query window take the room)
+  const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY || p->kv_dtype == AMS_F32 ? kKeysChunk : kScoreChunk;
   const bool small_tiles = p->kv_dtype == AMS_BF16 && (p->group * p->window <= 64 || p->head_dim == 64);
   w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles);
   w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false);

@@ -43,13 +43,14 @@ constexpr bool kPipe = BF16 && !TAIL && NB >= AMS_SCORE_PIPE_MIN_NB;
 
 // (maximum, sum of exp relative to it) of n scores -> *out, in double, by the whole workgroup; lanes, then waves,
 // combined in a fixed order.  An empty partial is (-inf, 0).
+template <int THREADS = kThreads>
 __device__ __forceinline__ void softmax_part(const float* e, int n, double2* out) {
-  __shared__ double2 sm[4];
+  __shared__ double2 sm[THREADS / 64];
   float mf = -INFINITY;
-  for (int t = threadIdx.x; t < n; t += kThreads) mf = fmaxf(mf, e[t]);
+  for (int t = threadIdx.x; t < n; t += THREADS) mf = fmaxf(mf, e[t]);
   double m = (double)mf, z = 0.0;
   if (mf != -INFINITY)
-    for (int t = threadIdx.x; t < n; t += kThreads) z += exp((double)e[t] - m);
+    for (int t = threadIdx.x; t < n; t += THREADS) z += exp((double)e[t] - m);
   auto merge = [](double& m1, double& z1, double m2, double z2) __attribute__((always_inline)) {
     const double mx = fmax(m1, m2);
     if (mx == -INFINITY) return;
@@ -70,7 +71,7 @@ __device__ __forceinline__ void softmax_part(const float* e, int n, double2* out
   __syncthreads();
   if (threadIdx.x == 0) {
     double M = sm[0].x, Z = sm[0].y;
-    for (int w = 1; w < 4; ++w) merge(M, Z, sm[w].x, sm[w].y);
+    for (int w = 1; w < THREADS / 64; ++w) merge(M, Z, sm[w].x, sm[w].y);
     *out = make_double2(M, Z);
   }
 }
@@ -139,6 +140,10 @@ __device__ __forceinline__ int key_channel(int cb, int n) {
   return (n >> 4) * (HD / 2) + cb * 16 + (n & 15);
 }
 
+// Threads of a sweep workgroup: eight waves where the query window leaves room for one workgroup on a CU only.
+template <bool BF16, int NB, int HD>
+constexpr int kSweepThreads = !BF16 && NB == 4 && HD == 128 ? 2 * kThreads : kThreads;
+
 // ---------------------------------------------------------------------------------------------
 // Sweep 1: per chunk, per query (max, sum exp2) of the scaled logits.
 // ---------------------------------------------------------------------------------------------
@@ -204,13 +209,14 @@ __device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
 // (s - r) and (s - r)^2 with r the token's logit against the unit's first query (a reference close to the mean keeps
 // the subtraction of the squares harmless).
 template <bool BF16, int NB, bool TAIL, bool MOMENTS, int HD, int KEYS = KEYS_NONE>
-__global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
+__global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
   constexpr bool kSpare = KEYS == KEYS_COS && HD == 128 && NB >= 7;  // see KEYS above
+  constexpr int THREADS = kSweepThreads<BF16, NB, HD>, WAVES = THREADS / 64, STEP = THREADS / 2;  // STEP: tokens between two blocks of a wave
   constexpr bool kCentred = MOMENTS && BF16 && !TAIL && (NB <= 4 || HD == 64);  // see MOMENTS above
-  constexpr int NG = kGroup<NB>, QS = Tr<BF16, HD>::kQStride;
+  constexpr int NG = BF16 || MOMENTS ? kGroup<NB> : NB, QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
-  __shared__ float2 xch_own[kCentred ? 1 : 4][NB * 32];
+  __shared__ float2 xch_own[kCentred ? 1 : WAVES][NB * 32];
   // the centred sweep needs the room: its exchange takes the place of the query window, which is used up by then
   float2(*xch)[NB * 32] = kCentred ? (float2(*)[NB * 32])qlds : xch_own;
   __shared__ __align__(16) char mean_sm[kCentred ? 3 * HD * 2 : 16];  // minus the mean query in three bf16 terms
@@ -229,11 +235,11 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
   __shared__ int32_t blk_sm[kScoreChunk / 16];
   const int32_t* blk = nullptr;  // paged caches: this chunk's block numbers, staged once
   if (a.k.layout == AMS_LAYOUT_PAGED) {
-    stage_blocks(a, b, c0, t_lim, blk_sm);
+    stage_blocks<THREADS>(a, b, c0, t_lim, blk_sm);
     blk = blk_sm;
   }
   if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
-  load_q<BF16, NB, HD>(a, l, b, h, qlds);
+  load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
   __shared__ uint4 ident[KEYS ? 2 : 1][64];
   __shared__ __align__(16) double inv_len[KEYS == KEYS_COS ? 4 : 1][32];
   double ksum[KEYS ? HD / 32 : 1];
@@ -404,7 +410,8 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
 #pragma unroll
           for (int k = 0; k < NG; ++k) acc[k] = centre;
         }
-        tile_mma<BF16, NG, HD, !kCentred>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+        if (!BF16 && g0 > 0) forget_terms(av);
+        tile_mma<BF16, NG, HD, !kCentred, !MOMENTS>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
         if (MOMENTS) {
 #pragma unroll
           for (int k = 0; k < NG; ++k) col_moments(acc[k], g0 + k);
@@ -443,14 +450,14 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
     else
       block_of(av, t0, std::false_type{});
   };
-  // this wave's blocks: every fourth block of 32 tokens up to the end of the chunk (or of the cache)
+  // this wave's blocks: every WAVES-th block of 32 tokens up to the end of the chunk (or of the cache)
 #pragma unroll 1
-  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 256) {
-    if (t0 + 128 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 128, T, lane, av1, blk, c0);
+  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 2 * STEP) {
+    if (t0 + STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + STEP, T, lane, av1, blk, c0);
     block(av0, t0);
-    if (t0 + 128 >= t_lim) break;
-    if (t0 + 256 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 256, T, lane, av0, blk, c0);
-    block(av1, t0 + 128);
+    if (t0 + STEP >= t_lim) break;
+    if (t0 + 2 * STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 2 * STEP, T, lane, av0, blk, c0);
+    block(av1, t0 + STEP);
   }
   if (kCentred) __syncthreads();
 #pragma unroll
@@ -476,15 +483,15 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4 && !MOMENTS && KEYS != K
   }
   __syncthreads();
   if (MOMENTS)
-    for (int t = c0 + threadIdx.x; t < t_lim; t += kThreads) g_row[t] = g_sm[t - c0];
-  if (MOMENTS && !TAIL && a.soft) softmax_part(g_sm, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
-  for (int n = threadIdx.x; n < NB * 32; n += kThreads) {
+    for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) g_row[t] = g_sm[t - c0];
+  if (MOMENTS && !TAIL && a.soft) softmax_part<THREADS>(g_sm, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
+  for (int n = threadIdx.x; n < NB * 32; n += THREADS) {
     float M = kNegInit;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, xch[w][n].x);
+    for (int w = 0; w < WAVES; ++w) M = fmaxf(M, xch[w][n].x);
     float Z = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) Z += xch[w][n].y * __builtin_amdgcn_exp2f(xch[w][n].x - M);
+    for (int w = 0; w < WAVES; ++w) Z += xch[w][n].y * __builtin_amdgcn_exp2f(xch[w][n].x - M);
     // the tail's entry follows those of the chunks
     const int slot = TAIL ? (t_end + a.chunk - 1) / a.chunk : chunk;
     a.part[((int64_t)unit * (a.n_chunks + 1) + slot) * a.n_pad + n] = make_float2(M, Z);
@@ -579,17 +586,18 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
 // Merges a unit's chunk statistics inside the second sweep (launches of few workgroups, where a reduction kernel of its own
 // costs more than every workgroup reading them again): weights of query n -> ((float4*)sm)[n], sm of 4 KB; and the sums of
 // the chunk's credit before the update, per wave -> c_sm.
+template <int THREADS>
 __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0, int t_lim, int T, char* sm, double* c_sm) {
   double* pz = (double*)sm;
-  float* pm = (float*)(sm + kThreads * sizeof(double));
+  float* pm = (float*)(sm + THREADS * sizeof(double));
   double cs = 0.0;
   if (a.vc_part && a.credit) {
     const float* c_row = a.credit + (int64_t)unit * a.d.t_stride;
 #pragma unroll 4
-    for (int t = c0 + threadIdx.x; t < t_lim; t += kThreads) cs += (double)c_row[t];
+    for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) cs += (double)c_row[t];
   }
   const int nch = (T + a.chunk - 1) / a.chunk;
-  const int parts = kThreads / a.n_pad, n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
+  const int parts = THREADS / a.n_pad, n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
   if (part < parts) {
     const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
     float M = kNegInit;
@@ -630,8 +638,9 @@ __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0,
 // TAIL (causal window, blocks from t_end on): a (query, key) pair the mask hides adds nothing, and
 // every observation a key is missing counts as the largest share it got.
 template <bool BF16, int NB, int MODE, bool TAIL, int HD, int KEYS = KEYS_NONE, bool FOLD = false>
-__global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES : 2) void score_usage_kernel(ScoreArgs a) {
-  constexpr int NG = kGroup<NB>;
+__global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES : 2) void score_usage_kernel(ScoreArgs a) {
+  constexpr int THREADS = kSweepThreads<BF16, NB, HD>, WAVES = THREADS / 64, STEP = THREADS / 2;  // STEP: tokens between two blocks of a wave
+  constexpr int NG = BF16 ? kGroup<NB> : NB;
   constexpr int QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
   if (FOLD && a.status && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *a.status = 0;  // no bounded wait on this path
@@ -652,11 +661,11 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
   __shared__ int32_t blk_sm[kScoreChunk / 16];
   const int32_t* blk = nullptr;  // paged caches: this chunk's block numbers, staged once
   if (a.k.layout == AMS_LAYOUT_PAGED) {
-    stage_blocks(a, b, c0, t_lim, blk_sm);
+    stage_blocks<THREADS>(a, b, c0, t_lim, blk_sm);
     blk = blk_sm;
   }
   if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
-  load_q<BF16, NB, HD>(a, l, b, h, qlds);
+  load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
   // KEYS: the mean key (or the sum of the unit vectors) as three bf16 terms that add up to its fp32 value, and a row of
   // zeros, behind the query window
   char* krow = qlds + NB * 32 * QS;
@@ -705,13 +714,13 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
   // scattered through the sweep cost the key stream 7 % of its rate
   // (last query with 8 column blocks: LDS is needed for the query window)
   constexpr bool kBufG = KEYS != KEYS_NONE || (MODE == MODE_LAST && NB <= 7);
-  constexpr int kBuf = KEYS != KEYS_NONE ? kKeysChunk : kScoreChunk;
+  constexpr int kBuf = KEYS != KEYS_NONE || !BF16 ? kKeysChunk : kScoreChunk;
   __shared__ float u_sm[kBuf];
   __shared__ float g_sm[kBufG ? kBuf : 1];
-  __shared__ double c_sm[FOLD ? 4 : 1];
+  __shared__ double c_sm[FOLD ? WAVES : 1];
   float4 f[NB];
   if constexpr (FOLD) {
-    fold_stats(a, unit, c0, t_lim, T_all, (char*)u_sm, c_sm);
+    fold_stats<THREADS>(a, unit, c0, t_lim, T_all, (char*)u_sm, c_sm);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) f[nb] = ((const float4*)u_sm)[nb * 32 + c];
     __syncthreads();
@@ -817,23 +826,23 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
       v_part += fmaxf(ru, 0.f) + a.eps;
     }
   };
-  // this wave's blocks: every fourth block of 32 tokens up to the end of the chunk (or of the cache)
+  // this wave's blocks: every WAVES-th block of 32 tokens up to the end of the chunk (or of the cache)
 #pragma unroll 1
-  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 256) {
-    if (t0 + 128 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 128, T, lane, av1, blk, c0);
+  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 2 * STEP) {
+    if (t0 + STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + STEP, T, lane, av1, blk, c0);
     block(av0, t0);
-    if (t0 + 128 >= t_lim) break;
-    if (t0 + 256 < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 256, T, lane, av0, blk, c0);
-    block(av1, t0 + 128);
+    if (t0 + STEP >= t_lim) break;
+    if (t0 + 2 * STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 2 * STEP, T, lane, av0, blk, c0);
+    block(av1, t0 + STEP);
   }
   __syncthreads();
-  for (int t = c0 + threadIdx.x; t < t_lim; t += kThreads) {
+  for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) {
     u_row[t] = u_sm[t - c0];
     if (kBufG) g_row[t] = g_sm[t - c0];
   }
   if (KEYS == KEYS_COS) softmax_part(g_sm, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
   if (a.vc_part) {  // chunk sums of max(u,0)+eps in a fixed order: lanes, then waves
-    __shared__ double v_sm[4];
+    __shared__ double v_sm[WAVES];
     double v_acc = (double)v_part;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v_acc += __shfl_xor(v_acc, o);
@@ -842,8 +851,13 @@ __global__ __launch_bounds__(kThreads, (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES :
     if (threadIdx.x == 0) {
       // the unit's credit sum (formed between the sweeps) rides in the first chunk's entry
       double c = (!FOLD && chunk == 0 && a.csum) ? a.csum[unit] : 0.0;
-      if (FOLD) c = (c_sm[0] + c_sm[1]) + (c_sm[2] + c_sm[3]);
-      a.vc_part[(int64_t)unit * a.n_chunks + chunk] = make_double2((v_sm[0] + v_sm[1]) + (v_sm[2] + v_sm[3]), c);
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < WAVES; w += 2) {
+        v += v_sm[w] + v_sm[w + 1];
+        if (FOLD) c += c_sm[w] + c_sm[w + 1];
+      }
+      a.vc_part[(int64_t)unit * a.n_chunks + chunk] = make_double2(v, c);
     }
   }
 }
@@ -853,17 +867,17 @@ hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hi
   hipError_t e;
   if (moments) {
     if ((e = ensure_lds<score_stats_kernel<BF16, NB, TAIL, true, HD>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, true, HD>), grid, dim3(kThreads), lds, s, a);
+    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, true, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
   } else {
     if ((e = ensure_lds<score_stats_kernel<BF16, NB, TAIL, false, HD>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, false, HD>), grid, dim3(kThreads), lds, s, a);
+    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, false, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
   }
   return hipGetLastError();
 }
 
 template <bool BF16, int NB, bool TAIL, int HD>
 hipError_t launch_usage(const ScoreArgs& a, int mode, dim3 grid, int lds, hipStream_t s) {
-  const dim3 blk(kThreads);
+  const dim3 blk(kSweepThreads<BF16, NB, HD>);
   hipError_t e;
   auto launch = [&](auto mode_c, auto fold_c) {
     constexpr int M = decltype(mode_c)::value;

@@ -4,6 +4,8 @@
 #ifndef AMS_SCORE_TILE_H
 #define AMS_SCORE_TILE_H
 
+#include <type_traits>
+
 #include "ams_internal.h"
 
 namespace ams {
@@ -59,24 +61,73 @@ inline hipError_t ensure_lds(int bytes) {
   return e;
 }
 
-// Row geometry of a cache of HD channels: bytes per row, stride of a query row in LDS (padded by
-// 16 bytes against bank conflicts), 16-byte vectors per half row (what one lane feeds the MFMA).
+// Row geometry of a cache of HD channels: bytes per row, stride of a query row in LDS (bf16, or the three bf16 terms of an
+// fp32 row one behind the other; padded by 16 bytes against bank conflicts), 16-byte vectors per half row (what one lane
+// feeds the MFMA).
 template <bool BF16, int HD = 128>
 struct Tr {
   static_assert(HD == 64 || HD == 128, "head dimensions the tiles are written for");
-  static constexpr int kRowBytes = HD * (BF16 ? 2 : 4), kQStride = kRowBytes + 16, kAVecs = kRowBytes / 32;
+  static constexpr int kRowBytes = HD * (BF16 ? 2 : 4), kAVecs = kRowBytes / 32;
+  static constexpr int kQTerm = HD * 2, kQStride = kQTerm * (BF16 ? 1 : 3) + 16;
 };
 
+// fp32 values as sums of three bf16 terms, each the rest rounded to nearest: 24 bits hold exactly.  A value that is no
+// number, infinite or rounds to infinity has SAFE's terms: itself (truncated) alone.
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t round2_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2){a, b}, bf16x2));
+}
+__device__ __forceinline__ bool infinite_or_nan(uint32_t bits) { return (bits & 0x7F800000u) == 0x7F800000u; }
+template <bool SAFE>
+__device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  hi = round2_bf16(a, b);
+  if (SAFE) {
+    if (infinite_or_nan(hi << 16)) hi = (hi & 0xFFFF0000u) | (__float_as_uint(a) >> 16);
+    if (infinite_or_nan(hi)) hi = (hi & 0xFFFFu) | (__float_as_uint(b) & 0xFFFF0000u);
+  }
+  float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xFFFF0000u);
+  if (SAFE) {
+    if (infinite_or_nan(hi << 16)) ra = 0.f;
+    if (infinite_or_nan(hi)) rb = 0.f;
+  }
+  mid = round2_bf16(ra, rb);
+  lo = round2_bf16(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xFFFF0000u));
+}
+
+// Makes the keys opaque where they are, so that terms formed from them before are formed again instead of being kept.
+template <int N>
+__device__ __forceinline__ void forget_terms(const uint4 (&av)[N]) {
+  auto& v = const_cast<uint4(&)[N]>(av);
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i].x), "+v"(v[i].y), "+v"(v[i].z), "+v"(v[i].w));
+}
+
+// 16 bytes (column col) of a query row -> its place in LDS.
+template <bool BF16, int HD>
+__device__ __forceinline__ void store_q(char* row, int col, const uint4& v) {
+  if constexpr (BF16) {
+    *(uint4*)(row + col * 16) = v;
+  } else {
+    const float4 x = __builtin_bit_cast(float4, v);
+    uint2 t[3];
+    split2<true>(x.x, x.y, t[0].x, t[1].x, t[2].x);
+    split2<true>(x.z, x.w, t[0].y, t[1].y, t[2].y);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) *(uint2*)(row + j * Tr<BF16, HD>::kQTerm + col * 8) = t[j];
+  }
+}
+
 // Query window of the unit -> LDS, rows padded against bank conflicts, rows >= N zero.
-template <bool BF16, int NB, int HD = 128>
+template <bool BF16, int NB, int HD = 128, int THREADS = kThreads>
 __device__ __forceinline__ void load_q(const ScoreArgs& a, int l, int b, int h, char* qlds) {
   constexpr int RB = Tr<BF16, HD>::kRowBytes, QS = Tr<BF16, HD>::kQStride, CPR = RB / 16;
   const char* src = a.q + ((((int64_t)l * a.d.B + b) * a.d.H + h) * a.d.G) * (int64_t)a.d.W * RB;
-  for (int ch = threadIdx.x; ch < NB * 32 * CPR; ch += kThreads) {
+  for (int ch = threadIdx.x; ch < NB * 32 * CPR; ch += THREADS) {
     const int n = ch / CPR, col = ch % CPR;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (n < a.d.N) v = *(const uint4*)(src + (int64_t)n * RB + col * 16);
-    *(uint4*)(qlds + n * QS + col * 16) = v;
+    store_q<BF16, HD>(qlds + n * QS, col, v);
   }
 }
 
@@ -106,25 +157,95 @@ __device__ __forceinline__ void load_a(const ScoreArgs& a, int l, int b, int h, 
 }
 
 // Paged cache: block numbers of the positions [c0, t_lim) of sequence b -> LDS (c0 a multiple of 16).
+template <int THREADS = kThreads>
 __device__ __forceinline__ void stage_blocks(const ScoreArgs& a, int b, int c0, int t_lim, int32_t* blk_lds) {
   const int n = (t_lim - c0 + 15) >> 4;
-  for (int i = threadIdx.x; i < n; i += kThreads)
+  for (int i = threadIdx.x; i < n; i += THREADS)
     blk_lds[i] = a.k.block_table[(int64_t)b * a.k.max_blocks + (c0 >> 4) + i];
   __syncthreads();
 }
 
-// acc[nb][i] = s_raw[token 8*(i/4) + 4*hf + i%4][query nb*32 + lane%32]
-// (CLEAR = false: acc starts from what it holds)
-template <bool BF16, int NB, int HD = 128, bool CLEAR = true>
-__device__ __forceinline__ void tile_mma(const uint4 (&av)[Tr<BF16, HD>::kAVecs], const char* qlds,
-                                         int lane, floatx16 (&acc)[NB]) {
-  constexpr int QS = Tr<BF16, HD>::kQStride, NV = Tr<BF16, HD>::kAVecs;
-  const char* qb = qlds + (lane & 31) * QS + (lane >> 5) * (Tr<BF16, HD>::kRowBytes / 2);
+// fp32 tile by bf16 matrix instructions: with K = K1 + K2 + K3 and Q = Q1 + Q2 + Q3 (bf16 terms, each 2^-9 of the one before)
+// the six products down to 2^-18 are kept, K3 Q1 + K1 Q3 + K2 Q2 + K2 Q1 + K1 Q2 + K1 Q1; what is left out is 2^-26 of a
+// product.  One v_mfma_f32_32x32x16_bf16 takes half the time of a v_mfma_f32_32x32x2_f32 and does eight times its work, so
+// that six of them cost 3/8; the terms of K take 5.5 vector instructions per value.  Products are exact and 16 of them are
+// added per step, where the fp32 instruction rounds after two: against 64 bits the usage is off by 1.9e-7 (2-norm, 8 units of
+// 4096 positions), 2.4e-7 with the fp32 instruction.  us per step, with it and with this: 408 and 290 (20 units of 30000, 128
+// queries), 419 and 239 (130 of 3000), 238 and 194 (20 of 30000, 64 queries), 175 and 165 (8 queries: memory bound), 240 and
+// 170 (176 ragged units of up to 2772, 64 queries).
+// SAFE: keys that are infinite or no number (K1 holds them, and the products with Q2 and Q3, which may be zero, leave them out).
+template <int NB, int HD, bool SAFE, bool AHEAD>
+__device__ __forceinline__ void tile_split(const uint4 (&av)[Tr<false, HD>::kAVecs], const char* qb, floatx16 (&acc)[NB]) {
+  constexpr int QS = Tr<false, HD>::kQStride, QT = Tr<false, HD>::kQTerm;
 #pragma unroll
-  for (int nb = 0; nb < NB && CLEAR; ++nb)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[nb][i] = 0.f;
+  struct Terms {
+    uint32_t h[4], m[4], l[4], f[4];  // K1, K2, K3, and K1 without what is infinite or no number
+  };
+  auto split = [&](int ks) __attribute__((always_inline)) {
+    const float4 x0 = __builtin_bit_cast(float4, av[2 * ks]), x1 = __builtin_bit_cast(float4, av[2 * ks + 1]);
+    Terms t;
+    split2<SAFE>(x0.x, x0.y, t.h[0], t.m[0], t.l[0]);
+    split2<SAFE>(x0.z, x0.w, t.h[1], t.m[1], t.l[1]);
+    split2<SAFE>(x1.x, x1.y, t.h[2], t.m[2], t.l[2]);
+    split2<SAFE>(x1.z, x1.w, t.h[3], t.m[3], t.l[3]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      t.f[i] = t.h[i];
+      if (SAFE)
+        t.f[i] = (infinite_or_nan(t.h[i] << 16) ? 0u : t.h[i] & 0xFFFFu) | (infinite_or_nan(t.h[i]) ? 0u : t.h[i] & 0xFFFF0000u);
+    }
+    return t;
+  };
+  auto frag = [](const uint32_t (&t)[4]) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8, make_uint4(t[0], t[1], t[2], t[3]));
+  };
+  constexpr int NK = HD / 16, kBuf = AHEAD ? 2 : 1;  // AHEAD: the next step's terms are formed and read a step ahead
+  Terms t[kBuf];
+  uint4 q[kBuf][NB][3];
+  auto fetch = [&](int ks) __attribute__((always_inline)) {
+    t[ks % kBuf] = split(ks);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) q[ks % kBuf][nb][j] = *(const uint4*)(qb + nb * 32 * QS + ks * 16 + j * QT);
+  };
+  if (kBuf == 2) fetch(0);
+#pragma unroll
+  for (int ks = 0; ks < NK; ++ks) {
+    if (kBuf == 1) fetch(ks);
+    if (kBuf == 2 && ks + 1 < NK) fetch(ks + 1);
+    const Terms& k = t[ks % kBuf];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const bf16x8 Q1 = __builtin_bit_cast(bf16x8, q[ks % kBuf][nb][0]), Q2 = __builtin_bit_cast(bf16x8, q[ks % kBuf][nb][1]),
+                   Q3 = __builtin_bit_cast(bf16x8, q[ks % kBuf][nb][2]);
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(k.l), Q1, acc[nb], 0, 0, 0);
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(k.f), Q3, acc[nb], 0, 0, 0);
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(k.m), Q2, acc[nb], 0, 0, 0);
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(k.m), Q1, acc[nb], 0, 0, 0);
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(k.f), Q2, acc[nb], 0, 0, 0);
+      acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(k.h), Q1, acc[nb], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // a step's terms at a time: hoisted further, they do not fit the registers
+  }
+}
+
+// acc[nb][i] = s_raw[token 8*(i/4) + 4*hf + i%4][query nb*32 + lane%32]
+// (CLEAR = false: acc starts from what it holds; AHEAD: registers to spare, see tile_split)
+template <bool BF16, int NB, int HD = 128, bool CLEAR = true, bool AHEAD = true>
+__device__ __forceinline__ void tile_mma(const uint4 (&av)[Tr<BF16, HD>::kAVecs], const char* qlds,
+                                         int lane, floatx16 (&acc)[NB]) {
+  constexpr int QS = Tr<BF16, HD>::kQStride;
+  [[maybe_unused]] constexpr int NV = Tr<BF16, HD>::kAVecs;
+  const char* qb = qlds + (lane & 31) * QS + (lane >> 5) * (Tr<BF16, HD>::kQTerm / 2);
   if constexpr (BF16) {
+#pragma unroll
+    for (int nb = 0; nb < NB && CLEAR; ++nb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[nb][i] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < NV; ++ks) {
       const bf16x8 A = __builtin_bit_cast(bf16x8, av[ks]);
@@ -135,17 +256,15 @@ __device__ __forceinline__ void tile_mma(const uint4 (&av)[Tr<BF16, HD>::kAVecs]
       }
     }
   } else {
+    tile_split<NB, HD, false, AHEAD && NB <= 2>(av, qb, acc);
+    float t = 0.f;  // a key that is infinite or no number shows in every column
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const float4 A = __builtin_bit_cast(float4, av[j]);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const float4 bv = *(const float4*)(qb + nb * 32 * QS + j * 16);
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(A.x, bv.x, acc[nb], 0, 0, 0);
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(A.y, bv.y, acc[nb], 0, 0, 0);
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(A.z, bv.z, acc[nb], 0, 0, 0);
-        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(A.w, bv.w, acc[nb], 0, 0, 0);
-      }
+    for (int i = 0; i < 16; ++i) t = __builtin_fmaf(acc[0][i], 0.f, t);
+    if (__builtin_expect(__any(t != 0.f), 0)) {
+      forget_terms(av);
+      int off = 0;
+      asm volatile("" : "+s"(off));
+      tile_split<NB, HD, true, false>(av, qb + off, acc);
     }
   }
 }

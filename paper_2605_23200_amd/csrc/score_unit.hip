@@ -17,7 +17,7 @@ constexpr int kUnitThreads = 512, kUnitWaves = kUnitThreads / 64;
 
 template <bool BF16, int NB, int MODE, int HD>
 __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a) {
-  constexpr int NG = (NB % 2 == 0 && NB >= 4) ? NB / 2 : NB, QS = Tr<BF16, HD>::kQStride, NQ = NB * 32;
+  constexpr int NG = (BF16 && NB % 2 == 0 && NB >= 4) ? NB / 2 : NB, QS = Tr<BF16, HD>::kQStride, NQ = NB * 32;
   constexpr int RB = Tr<BF16, HD>::kRowBytes, CPR = RB / 16;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch[kUnitWaves][NQ];
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
       const int n = ch / CPR, col = ch % CPR;
       uint4 v = make_uint4(0, 0, 0, 0);
       if (n < a.d.N) v = *(const uint4*)(src + (int64_t)n * RB + col * 16);
-      *(uint4*)(qlds + n * QS + col * 16) = v;
+      store_q<BF16, HD>(qlds + n * QS, col, v);
     }
   }
   // the old credit of the unit (for the EMA normaliser): at most 8 positions per thread, in flight during the walks
