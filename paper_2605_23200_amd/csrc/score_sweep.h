@@ -162,7 +162,55 @@ constexpr int kSweepThreads = !BF16 && NB == 4 && HD == 128 ? 2 * kThreads : kTh
 // per step against 6447; moving on every time, or every second time, gives 6490 and 6267, every 16th or 64th 6007 to 6008.
 // 4 heads gain as well (2048 units, 3396 -> 3080); with 1, 2 or 3 heads, or rows of 128 bytes, it makes no difference (3537
 // and 3571, 3727 and 3700, 2333 and 2344; 3581 and 3559 for 8 heads).
+//
+// Ragged batches (compact): the chunks past the end of a sequence are left out of the count, so that the workgroups that have
+// work are the first ones of the launch, without gaps.  With a grid of (chunk, unit) the gaps repeat with the batch and leave
+// some XCDs more work than others: 192 units of 700 to 9001 positions 161 -> 145 us per step, 768 paged units of 2354 to 5384
+// 560 -> 509, 4096 paged ones of 4096 to 16384 5655 -> 5557.  A sequence per lane, so at most 64 of them.
+__device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
+  return a.causal ? max(0, (T - a.d.W + 1) / 32 * 32) : T;
+}
 __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool reversed, int& unit, int& chunk) {
+  if (a.compact && !tail) {
+    const int lane = threadIdx.x & 63, B = a.d.B, H = a.d.H;
+    const int len = lane < B ? max(0, min(a.seq_lens[lane], a.d.t_max)) : 0;
+    const int n = (causal_t_end(a, len) + a.chunk - 1) / a.chunk;  // chunks of this lane's sequence
+    int incl = n;
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);  // row_shr: 1, 2, 4, 8
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast: 15, 31
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);
+    const int per_layer = __builtin_amdgcn_readlane(incl, 63), total = per_layer * H * a.d.L;
+    int lin = blockIdx.y * gridDim.x + blockIdx.x;
+    unit = 0;
+    chunk = a.n_chunks;  // past every sequence: nothing to do
+    if (lin >= total) return;
+    if (reversed) lin = total - 1 - lin;
+    int rest, h = 0;  // (sequence, chunk) of the layer, counted over what there is
+    int l;
+    if (a.k.layout == AMS_LAYOUT_PAGED) {
+      const int r = lin / H;
+      h = (lin + r / 8) % H;
+      l = r / per_layer;
+      rest = r - l * per_layer;
+    } else {
+      l = lin / (per_layer * H);
+      rest = lin - l * per_layer * H;
+    }
+    const int scale = a.k.layout == AMS_LAYOUT_PAGED ? 1 : H;
+    const int b = __popcll(__ballot(lane < B && incl * scale <= rest));  // sequences that end before it
+    const int nb = __builtin_amdgcn_readlane(n, b);
+    rest -= (__builtin_amdgcn_readlane(incl, b) - nb) * scale;
+    if (scale > 1) {
+      h = rest / nb;
+      rest -= h * nb;
+    }
+    chunk = rest;
+    unit = (l * B + b) * H + h;
+    return;
+  }
   int bx = blockIdx.x, by = blockIdx.y;
   if (reversed) {
     bx = gridDim.x - 1 - bx;
@@ -177,10 +225,6 @@ __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool r
   const int rest = lin / a.d.H, h = (lin + rest / 8) % a.d.H;
   chunk = rest % (int)gridDim.x;
   unit = (rest / (int)gridDim.x) * a.d.H + h;
-}
-
-__device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
-  return a.causal ? max(0, (T - a.d.W + 1) / 32 * 32) : T;
 }
 
 // The reference of the exponentials follows the running maximum, so that the largest logit of a wave has the exponent 0.  A

@@ -41,6 +41,7 @@ struct ScoreArgs {
   double* ksum;         // [units][n_chunks][D]: sums of the keys (or of the unit vectors); NULL: nobody wants them here
   double2* soft;        // [units][n_chunks]: (max, sum of exp) of the scores in g, left by the sweep that forms them; may be NULL
   float eps;
+  bool compact; // ragged batch: the workgroups of the sweeps count only the chunks that exist
   bool fold;    // the second sweep merges the first one's statistics itself (no reduction kernel between them)
   bool causal;  // causal window (App. A): query w of the window sees keys 0 .. T-W+w
   int32_t* status;  // word the one-read scorer raises when a bounded wait expires; the two-sweep path clears it

@@ -336,3 +336,31 @@ def test_centred_moments_at_every_number_of_columns(oracle, D, G, W, common):
     job = Job(w, host, scorer=B.SCORER_EXPECTED)
     job.step()
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), list(range(w.units)), scorer=B.SCORER_EXPECTED)
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("L,N,H", [(16, 33, 2), (5, 64, 3), (18, 2, 16), (4, 65, 3), (23, 3, 8)])
+def test_ragged_batches_count_the_chunks_that_exist(oracle, L, N, H, paged, causal):
+    """Launches of more than 1024 workgroups, up to 64 sequences and one more: empty sequences first, in the middle and last,
+    lengths around the chunk's edges; every (unit, chunk) once in both sweeps."""
+    T = 2100
+    w = inputs.CONFIGS[1].scaled(L=L, B=N, H=H, G=1, W=4, D=64, T=T, T_min=T, budget=40, S=2, n_spans=2, span_len=(8, 90),
+                                 paged=paged, causal=causal)
+    host = inputs.dense_cache(w, n_threads=8)
+    lens = np.random.default_rng(N).choice([0, 1, 31, 1023, 1024, 1025, 1030, 2048, 2049, T], size=N)
+    lens[0], lens[-1] = 0, 0
+    lens[N // 2] = T
+    host["seq_lens"][:] = lens
+    job = Job(w, host, score_path=B.SCORE_PATH_TWO_SWEEPS)
+    assert w.units * ((T + 1023) // 1024) >= 1024
+    job.intermediates().u.fill_(-1.0)
+    job.step()
+    u = job.intermediates().u.double()
+    seen = torch.arange(job.t_stride, device=DEV)[None, :] < job.lens.long().repeat_interleave(H).repeat(L)[:, None]
+    total = (u * seen).sum(1)
+    assert bool(((u >= 0) | ~seen).all()) and bool((u[~seen] == -1).all())
+    if not causal:
+        assert float((total[seen[:, 0]] - 1).abs().max()) < 1e-4
+    live = [i for i in range(w.units) if lens[i // H % N] > 0]
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), live[::max(1, len(live) // 12)])
