@@ -12,8 +12,8 @@
 // finalize_kernel  (only with a must-keep set) one workgroup per unit.  The segment picks arrive as
 //                bits of a per-unit bitmap, so the union with the must-keep positions and the removal
 //                of duplicates are one OR; what the duplicates leave open is filled with the best
-//                scores outside the set (another radix select, over the unset positions), and the
-//                ascending index list is read off the bitmap.
+//                scores outside the set (the same selection over the unset positions; radix passes where the
+//                sequence is too long for registers), and the ascending index list is read off the bitmap.
 #include "ams_internal.h"
 #include "quota.h"
 
@@ -240,6 +240,29 @@ __device__ __forceinline__ void wave_min_max(uint32_t& lo, uint32_t& hi) {
   hi = h;
 }
 
+// Of 256 bins over the keys from lo on, 2^sh keys wide: the one in which the count from the top reaches rem, found by every
+// wave for itself, lane 0 the highest bins.  lo and rem move on to that bin, n_bin is what it holds.
+__device__ __forceinline__ void top_bin(const int* h, int lane, int& rem, uint32_t& lo, int sh, int& n_bin) {
+  const int4 c = *reinterpret_cast<const int4*>(&h[252 - 4 * lane]);
+  const int s = (c.x + c.y) + (c.z + c.w);
+  const int above = wave_scan(s) - s;
+  const bool mine = above < rem && rem <= above + s;
+  const int c3 = above + c.w, c2 = c3 + c.z, c1 = c2 + c.y;
+  int bin = 252 - 4 * lane, cum = c1, in = c.x;
+  if (rem <= c3) {
+    bin += 3, cum = above, in = c.w;
+  } else if (rem <= c2) {
+    bin += 2, cum = c3, in = c.z;
+  } else if (rem <= c1) {
+    bin += 1, cum = c2, in = c.y;
+  }
+  const int src = __ffsll((long long)__ballot(mine)) - 1;
+  bin = __builtin_amdgcn_readlane(bin, src);
+  rem -= __builtin_amdgcn_readlane(cum, src);
+  n_bin = __builtin_amdgcn_readlane(in, src);
+  lo += (uint32_t)bin << sh;
+}
+
 // The q largest keys of a segment.  Latency and LDS atomics bound this kernel (a few thousand keys per workgroup), so the
 // steps that need all threads are few: the keys stay in registers, 256 bins cut the range between the lowest and the
 // highest key, and once the bin with the q-th largest holds no more than 64 keys, those are listed and one wave counts for
@@ -345,25 +368,7 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget
       if (i * BLOCK + (int)threadIdx.x < L && key[i] >= lo && off <= span) atomicAdd(&h[off >> sh], 1);
     }
     __syncthreads();
-    // every wave for itself, lane 0 the highest bins: the bin in which the count from the top reaches rem
-    const int4 c = *reinterpret_cast<const int4*>(&h[252 - 4 * lane]);
-    const int s = (c.x + c.y) + (c.z + c.w);
-    const int above = wave_scan(s) - s;
-    const bool mine = above < rem && rem <= above + s;
-    const int c3 = above + c.w, c2 = c3 + c.z, c1 = c2 + c.y;
-    int bin = 252 - 4 * lane, cum = c1, in = c.x;
-    if (rem <= c3) {
-      bin += 3, cum = above, in = c.w;
-    } else if (rem <= c2) {
-      bin += 2, cum = c3, in = c.z;
-    } else if (rem <= c1) {
-      bin += 1, cum = c2, in = c.y;
-    }
-    const int src = __ffsll((long long)__ballot(mine)) - 1;
-    bin = __builtin_amdgcn_readlane(bin, src);
-    rem -= __builtin_amdgcn_readlane(cum, src);
-    n_bin = __builtin_amdgcn_readlane(in, src);
-    lo += (uint32_t)bin << sh;
+    top_bin(h, lane, rem, lo, sh, n_bin);
     span = (1u << sh) - 1u;
     if (n_bin <= kList || n_bin == rem || sh == 0) break;
     sh = max(0, sh - 8);
@@ -488,13 +493,15 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
                                                              int n_sink, int n_last, const float* g_all,
                                                              uint32_t* flags_all, int n_words,
                                                              int32_t* idx_all) {
-  __shared__ int hist[kFinWaves][256];
+  __shared__ __align__(16) int hist[kFinWaves][256];
   __shared__ uint32_t sel_digit;
   __shared__ int sel_rem;
   __shared__ int red[kFinWaves];
   __shared__ uint32_t red_and[kFinWaves], red_or[kFinWaves];
   __shared__ int2 wave_cnt[kFinWaves];
   __shared__ uint32_t bm[kFinBlock];  // the bitmap of a sequence of up to 32768 positions
+  __shared__ uint2 list[64];          // (key, position) of the keys of the last bin
+  __shared__ int n_list;
   const int unit = blockIdx.x;
   int l, b, h;
   unit_coords(d, unit, l, b, h);
@@ -546,23 +553,14 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
   // key of the deficit-th largest score among the positions outside the set
   uint32_t thr = 0xFFFFFFFFu;
   int rem = 0;
-  if (fill) {
+  if (fill && !inreg) {
     // bits that are the same in every key need no radix pass
     uint32_t k_and = 0xFFFFFFFFu, k_or = 0u;
-    if (inreg) {
-#pragma unroll
-      for (int j = 0; j < kFinPer; ++j)
-        if (kreg[j]) {
-          k_and &= kreg[j];
-          k_or |= kreg[j];
-        }
-    } else {
-      for (int t = threadIdx.x; t < T; t += kFinBlock) {
-        const uint32_t k = key_at(t);
-        if (k) {
-          k_and &= k;
-          k_or |= k;
-        }
+    for (int t = threadIdx.x; t < T; t += kFinBlock) {
+      const uint32_t k = key_at(t);
+      if (k) {
+        k_and &= k;
+        k_or |= k;
       }
     }
 #pragma unroll
@@ -593,17 +591,9 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
       for (;;) {
         for (int i = threadIdx.x; i < kFinWaves * 256; i += kFinBlock) (&hist[0][0])[i] = 0;
         __syncthreads();
-        if (inreg) {
-#pragma unroll
-          for (int j = 0; j < kFinPer; ++j) {
-            const uint32_t k = kreg[j];
-            if (k && (k & mask) == prefix) atomicAdd(&hist[wave][(k >> shift) & 255], 1);
-          }
-        } else {
-          for (int t = threadIdx.x; t < T; t += kFinBlock) {
-            const uint32_t k = key_at(t);
-            if (k && (k & mask) == prefix) atomicAdd(&hist[wave][(k >> shift) & 255], 1);
-          }
+        for (int t = threadIdx.x; t < T; t += kFinBlock) {
+          const uint32_t k = key_at(t);
+          if (k && (k & mask) == prefix) atomicAdd(&hist[wave][(k >> shift) & 255], 1);
         }
         __syncthreads();
         if (wave == 0) {
@@ -646,32 +636,85 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
 
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   if (inreg) {
-    // the positions that fill the gap get their bits: everything above the threshold, and of the
-    // positions equal to it the first rem in index order
+    // The positions that fill the gap get their bits.  As in select_kernel: 256 bins over the range of the keys, the bin that
+    // holds the deficit-th largest, a wave that ranks its keys, another 256 bins where they are too many.  93 -> 85 us per step
+    // for 32 units of 6007 positions, 265 -> 246 for 504 ragged ones of up to 1617 (radix passes of 8 bits over a histogram per
+    // wave before, three or four of them).
     if (fill) {
-      int c_eq = 0;
-#pragma unroll
-      for (int j = 0; j < kFinPer; ++j) c_eq += kreg[j] == thr;
-      c_eq = wave_sum(c_eq);
-      if (lane == 0) red[wave] = c_eq;
-      __syncthreads();
-      c_eq = 0;
-#pragma unroll
-      for (int w = 0; w < kFinWaves; ++w) c_eq += red[w];
-      __syncthreads();  // red[] is written again below: every wave has read it first
-      const bool all_eq = c_eq == rem;  // no choice to make among equal scores
+      uint32_t lo = 0xFFFFFFFFu, hi = 0;
 #pragma unroll
       for (int j = 0; j < kFinPer; ++j) {
-        const int t = threadIdx.x + j * kFinBlock;
-        if (kreg[j] > thr || (all_eq && kreg[j] == thr)) atomicOr(&bm[t >> 5], 1u << (t & 31));
+        if (j * kFinBlock < T && kreg[j]) {
+          lo = min(lo, kreg[j]);
+          hi = max(hi, kreg[j]);
+        }
       }
-      if (!all_eq) {
-        int base_eq = 0;  // equal scores met so far, in index order (round j covers 1024 consecutive positions)
+      for (int i = threadIdx.x; i < 512; i += kFinBlock) (&hist[0][0])[i] = 0;
+      if (threadIdx.x == 0) n_list = 0;
+      wave_min_max(lo, hi);
+      if (lane == 0) {
+        red_and[wave] = lo;
+        red_or[wave] = hi;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kFinWaves; ++w) {
+        lo = min(lo, red_and[w]);
+        hi = max(hi, red_or[w]);
+      }
+      int sh = max(0, 24 - (int)__clz((int)((hi - lo) | 1u)));
+      uint32_t span = hi - lo;
+      int n_bin = 0;
+      rem = deficit;
+      for (int pass = 0;; ++pass) {
+        int* h = hist[pass & 1];
+#pragma unroll
+        for (int j = 0; j < kFinPer; ++j) {
+          const uint32_t k = kreg[j];
+          if (j * kFinBlock < T && k >= lo && k - lo <= span) atomicAdd(&h[(k - lo) >> sh], 1);  // (no key is 0, lo is at least 1)
+        }
+        __syncthreads();
+        top_bin(h, lane, rem, lo, sh, n_bin);
+        span = (1u << sh) - 1u;
+        if (n_bin <= 64 || n_bin == rem || sh == 0) break;
+        sh = max(0, sh - 8);
+        int* next = hist[(pass + 1) & 1];
+        if (pass > 0) {  // the bins of two passes ago
+          for (int i = threadIdx.x; i < 256; i += kFinBlock) next[i] = 0;
+          __syncthreads();
+        }
+      }
+      // keys above lo + span fill the gap, and of the n_bin keys from lo to there rem
+      const bool all = n_bin == rem, ranked = !all && n_bin <= 64;
+#pragma unroll
+      for (int j = 0; j < kFinPer; ++j) {
+        const uint32_t k = kreg[j];
+        const int t = threadIdx.x + j * kFinBlock;
+        if (j * kFinBlock < T && k >= lo) {
+          if (all || k - lo > span)
+            atomicOr(&bm[t >> 5], 1u << (t & 31));
+          else if (ranked)
+            list[atomicAdd(&n_list, 1)] = make_uint2(k, (uint32_t)t);
+        }
+      }
+      if (ranked) {
+        __syncthreads();
+        if (wave == 0) {
+          const uint2 me = lane < n_bin ? list[lane] : make_uint2(0u, 0xFFFFFFFFu);
+          int rank = 0;
+          for (int q = 0; q < n_bin; ++q) {
+            const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)me.x, q), e = (uint32_t)__builtin_amdgcn_readlane((int)me.y, q);
+            rank += k > me.x || (k == me.x && e < me.y);
+          }
+          if (lane < n_bin && rank < rem) atomicOr(&bm[me.y >> 5], 1u << (me.y & 31));
+        }
+      } else if (!all) {  // the keys of the bin are equal: the first rem in index order
+        int base_eq = 0;  // equal scores met so far (round j covers 1024 consecutive positions)
 #pragma unroll
         for (int j = 0; j < kFinPer; ++j) {
           if (j * kFinBlock < T && base_eq < rem) {
             const int t = threadIdx.x + j * kFinBlock;
-            const bool eq = kreg[j] == thr;
+            const bool eq = kreg[j] == lo;
             const uint64_t be = __ballot(eq);
             if (lane == 0) red[wave] = __popcll(be);
             __syncthreads();

@@ -364,3 +364,34 @@ def test_ragged_batches_count_the_chunks_that_exist(oracle, L, N, H, paged, caus
         assert float((total[seen[:, 0]] - 1).abs().max()) < 1e-4
     live = [i for i in range(w.units) if lens[i // H % N] > 0]
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), live[::max(1, len(live) // 12)])
+
+
+@pytest.mark.parametrize("n_sink,n_last", [(40, 900), (1, 0), (0, 64)])
+@pytest.mark.parametrize("T", [1023, 1025, 6007, 32768, 32769])
+def test_gap_of_a_must_keep_set_is_filled(oracle, T, n_sink, n_last):
+    """More than 64 positions to fill, and few; keys that share a bin over several passes, ties by the hundred, infinities
+    and NaN; the last length whose keys stay in registers and the first that does not."""
+    S, rng = 5, np.random.default_rng(T + n_last)
+    bounds = np.array([0, 7, T // 5, T // 2, T - 100, T], np.int32)
+    g = rng.standard_normal((5, T)).astype(np.float32)
+    g[1] = (1 + rng.integers(0, 70, T) * 2.0 ** -23).astype(np.float32)
+    g[1, ::501] = 3e38
+    g[2] = -1.5
+    g[3] = np.round(g[3] * 2)
+    g[4, ::3], g[4, 1::5], g[4, 2::7], g[4, 4::11] = np.nan, -np.inf, np.inf, -0.0
+    g[:, :40] += 2.0                                                # the segments pick must-keep positions
+    g[:, -900:] += 2.0
+    mass = np.tile(np.diff(bounds).astype(np.float32) / T, (5, 1))
+    for budget in (n_sink + n_last + 3, T // 2 + 500):
+        p = _stage_params(5, T, S)
+        p.budget, p.n_sink, p.n_last = budget, n_sink, n_last
+        quota = torch.zeros((5, S), dtype=torch.int32, device=DEV)
+        idx, n_kept = torch.zeros((5, budget), dtype=torch.int32, device=DEV), torch.zeros(5, dtype=torch.int32, device=DEV)
+        B.ams_select(p, to_dev(np.array([T], np.int32)), to_dev(g), to_dev(np.tile(bounds, (5, 1))), to_dev(mass), quota,
+                     idx, n_kept, workspace(p))
+        sinks, last, seg_budget = oracle.must_keep(T, budget, n_sink, n_last)
+        n = min(budget, T)
+        for i in range(5):
+            q = oracle.quota(bounds, mass[i], seg_budget, 1)
+            want = oracle.finalize(g[i], oracle.select(g[i], bounds, q), sinks, last, n)
+            np.testing.assert_array_equal(to_host(idx)[i, :n], want, err_msg=f"row {i} budget {budget}")
