@@ -83,7 +83,8 @@ typedef enum {
   AMS_SCORE_PATH_ONE_LAUNCH = 3  /* short caches (t_max <= 4096): one workgroup walks a unit's keys
                                     twice in one launch; at most 128 queries per KV head, no causal
                                     window, no moment-based scorer; AMS_ERR_UNSUPPORTED otherwise.
-                                    AUTO takes it when it applies and there are >= 128 units        */
+                                    AUTO takes it when it applies, there are >= 128 units (> 176
+                                    beyond 2816 positions), not for key-based scores of bf16 caches */
 } ams_score_path;
 
 typedef enum {

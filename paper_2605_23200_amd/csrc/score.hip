@@ -394,10 +394,17 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
                              &oneread);
   if (e != hipSuccess) return e;
   if (!oneread && p->score_path == AMS_SCORE_PATH_ONE_READ) return hipErrorNotSupported;
+  // the key-based scores ride along with the sweeps where these run plain over a bf16 cache
+  const bool keys_ride = (p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY) && bf16 && !causal;
   if (!oneread) {
-    // short caches with enough units to fill the chip: one workgroup per unit, one launch
+    // Short caches with enough units to fill the chip: one workgroup per unit, one launch.  Not for the key-based scores, which
+    // would have to stream K twice more (us per event with and without: 103 and 89 for 142 units of 1836 positions with the key
+    // diversity, 164 and 114 for 128 of 4096, 358 and 249 for 300 of 3500 with the mean cosines), and not for longer ones of
+    // these caches whose single round leaves three CUs in ten idle (90 and 79 for 128 of 3000, 113 and 98 for 128 of 4096,
+    // 122 and 118 for 160 of 4096; but 127 and 131 for 180 of 4096, 156 and 169 for 256, 52 and 53 for 128 of 2600, D = 64).
+    const bool thin = d.t_max > 2816 && d.units <= 176;
     const bool want_unit = p->score_path == AMS_SCORE_PATH_ONE_LAUNCH ||
-                           (p->score_path == AMS_SCORE_PATH_AUTO && d.units >= kUnitScorerMinUnits);
+                           (p->score_path == AMS_SCORE_PATH_AUTO && d.units >= kUnitScorerMinUnits && !keys_ride && !thin);
     if (want_unit) {
       e = launch_score_unit(a, bf16, d.D, mode, s, &oneread);
       if (e != hipSuccess) return e;
@@ -406,10 +413,8 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     }
     if (!oneread && p->score_path == AMS_SCORE_PATH_ONE_LAUNCH) return hipErrorNotSupported;
   }
-  // the key-based scores ride along with the sweeps where these run plain over a bf16 cache
-  const bool key_score = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY;
   bool keys_done = false;
-  if (!oneread && key_score && bf16 && !causal) {
+  if (!oneread && keys_ride) {
     a.g = g;
     a.ksum = (double*)(ws + wl.kbar);
     a.soft = (double2*)(ws + wl.sub);

@@ -395,3 +395,16 @@ def test_gap_of_a_must_keep_set_is_filled(oracle, T, n_sink, n_last):
             q = oracle.quota(bounds, mass[i], seg_budget, 1)
             want = oracle.finalize(g[i], oracle.select(g[i], bounds, q), sinks, last, n)
             np.testing.assert_array_equal(to_host(idx)[i, :n], want, err_msg=f"row {i} budget {budget}")
+
+
+@pytest.mark.parametrize("scorer,units,T,one_launch", [(B.SCORER_MEAN_WINDOW, 128, 2816, True), (B.SCORER_MEAN_WINDOW, 128, 2817, False),
+                                                       (B.SCORER_LAST_QUERY, 178, 4096, True), (B.SCORER_LAST_QUERY, 176, 3500, False),
+                                                       (B.SCORER_KEYDIFF, 128, 900, False), (B.SCORER_REDUNDANCY, 130, 300, False)])
+def test_short_caches_choose_their_scorer(oracle, scorer, units, T, one_launch):
+    """Where the one-launch scorer ends: a round with three CUs in ten idle beyond 2816 positions, scores that need the keys."""
+    w = inputs.CONFIGS[1].scaled(L=units // 2, H=2, G=2, W=4, D=64, T=T, T_min=T, budget=60, S=4, n_spans=2, span_len=(8, 90))
+    host = inputs.dense_cache(w, n_threads=8)
+    job = Job(w, host, scorer=scorer)
+    assert ("score_unit" in _labels(job)) == one_launch
+    check_properties_all_units(job)
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, units // 2, units - 1], scorer=scorer)
