@@ -364,8 +364,9 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   a.n_pad = wl.n_pad;
   // Batches whose sequences may differ in length: the workgroups count the chunks that exist (sweep_tile), where the launch has
   // more of them than run at once.  Below that the count's 0.5 us per workgroup is all it does (93.5 and 95.2 us per step for
-  // 48 x 3 units of up to 1376, 52.3 and 53.3 for 2 x 3 of up to 20068).
-  a.compact = d.B > 1 && d.B <= 64 && (int64_t)d.units * a.n_chunks >= 1024;
+  // 48 x 3 units of up to 1376, 52.3 and 53.3 for 2 x 3 of up to 20068,
+  // 207.2 and 208.3 for the stage calls of 64 units of up to 20011, 1280 workgroups; but 162 and 143 for 192 of up to 9001).
+  a.compact = d.B > 1 && d.B <= 64 && (int64_t)d.units * a.n_chunks >= 1536;
   // The second sweep merges the statistics itself where that is cheaper than a launch between the sweeps (1.2 us of gap and
   // 5 of its own): every workgroup reads its unit's partial statistics once more.  us per step, with the kernel and without:
   // 44.5 and 41.0 (8 fp32 units of 4096), 33.7 and 32.4 (9 units of 2105), 95.5 and 92 (24 fp32 units of 9804, 240

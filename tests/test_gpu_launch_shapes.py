@@ -342,7 +342,7 @@ def test_centred_moments_at_every_number_of_columns(oracle, D, G, W, common):
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("L,N,H", [(16, 33, 2), (5, 64, 3), (18, 2, 16), (4, 65, 3), (23, 3, 8)])
 def test_ragged_batches_count_the_chunks_that_exist(oracle, L, N, H, paged, causal):
-    """Launches of more than 1024 workgroups, up to 64 sequences and one more: empty sequences first, in the middle and last,
+    """Launches of more than 1536 workgroups, up to 64 sequences and one more: empty sequences first, in the middle and last,
     lengths around the chunk's edges; every (unit, chunk) once in both sweeps."""
     T = 2100
     w = inputs.CONFIGS[1].scaled(L=L, B=N, H=H, G=1, W=4, D=64, T=T, T_min=T, budget=40, S=2, n_spans=2, span_len=(8, 90),
@@ -353,7 +353,7 @@ def test_ragged_batches_count_the_chunks_that_exist(oracle, L, N, H, paged, caus
     lens[N // 2] = T
     host["seq_lens"][:] = lens
     job = Job(w, host, score_path=B.SCORE_PATH_TWO_SWEEPS)
-    assert w.units * ((T + 1023) // 1024) >= 1024
+    assert w.units * ((T + 1023) // 1024) >= 1536
     job.intermediates().u.fill_(-1.0)
     job.step()
     u = job.intermediates().u.double()
