@@ -47,7 +47,7 @@ def assert_close_rel(got, want, rtol=1e-5, atol=1e-12, what=""):
     want = np.asarray(want, np.float64)
     err = np.abs(got - want)
     tol = atol + rtol * np.abs(want)
-    bad = err > tol
+    bad = ~(err <= tol)                                # a result that is no number is beyond every bound
     assert not bad.any(), (f"{what}: {bad.sum()} of {bad.size} beyond rtol={rtol}; worst rel "
                            f"{(err / np.maximum(np.abs(want), 1e-300)).max():.3e} at {np.argmax(err / np.maximum(tol, 1e-300))}")
 
@@ -81,6 +81,6 @@ def assert_close_terms(got, want, magnitude, rtol=1e-5, atol=1e-12, what=""):
     want = np.asarray(want, np.float64)
     err = np.abs(got - want)
     tol = atol + rtol * np.asarray(magnitude, np.float64)
-    bad = err > tol
+    bad = ~(err <= tol)                                # a result that is no number is beyond every bound
     assert not bad.any(), (f"{what}: {bad.sum()} of {bad.size} beyond rtol={rtol} of their terms; worst ratio "
                            f"{(err / np.maximum(tol, 1e-300)).max():.3f} at {np.argmax(err / np.maximum(tol, 1e-300))}")
