@@ -249,9 +249,9 @@ __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool r
 // instructions per block of 32 keys, one vector instruction per logit for the variance and one for s itself instead of four,
 // one reduction over the lanes instead of three).  256 units of 32768 positions, 128 queries: 1195 -> 1157 us per step, 454 ->
 // 428 with 64 channels and 16384 positions.  With seven or eight column blocks of 128 channels it spills (1835 -> 1933, 659 ->
-// 958): there, in the causal tail and for fp32 caches, where the extra products are not hidden, the sums are those of
-// (s - r) and (s - r)^2 with r the token's logit against the unit's first query (a reference close to the mean keeps
-// the subtraction of the squares harmless).
+// 958): there, in the causal tail and for fp32 caches, where the extra products are not hidden, and for a wave whose
+// statistics come out as no numbers, the sums are those of (s - r) and (s - r)^2 with r the token's logit against the unit's
+// first query (a reference close to the mean keeps the subtraction of the squares harmless).
 template <bool BF16, int NB, bool TAIL, bool MOMENTS, int HD, int KEYS = KEYS_NONE>
 __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
@@ -343,15 +343,16 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     }
     __syncthreads();
   }
-  auto block_of = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0, auto ragged_c) __attribute__((always_inline)) {
+  auto block_of = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0, auto ragged_c, auto centred_c) __attribute__((always_inline)) {
     constexpr bool ragged = decltype(ragged_c)::value;  // the block reaches past the end of the cache
+    constexpr bool centred = kCentred && decltype(centred_c)::value;
     // the query fragments are re-read from LDS for every block: keeping them in registers across
     // blocks would cost more registers than the reads cost time, so their address is made opaque
     int qoff = 0;
     asm volatile("" : "+s"(qoff));
     float ref[16], s1[16], s2[16];
     floatx16 centre;  // minus the mean logit of every token
-    if constexpr (kCentred) {
+    if constexpr (centred) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) centre[i] = s2[i] = 0.f;
       const char* mb = mean_sm + qoff + hf * HD;
@@ -365,7 +366,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     }
     // the vector work on one column block of logits
     auto col_moments = [&](floatx16& acc, int nb) __attribute__((always_inline)) {
-      if constexpr (kCentred) {
+      if constexpr (centred) {
         // padded query columns do not count; the first ones are real with every N that takes NB column blocks
         const bool real = nb < kFullBlocks<NB> || nb * 32 + (lane & 31) < a.d.N;
 #pragma unroll
@@ -419,15 +420,15 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
       col_frags<BF16, HD>(qb, bq[0]);
       col_frags<BF16, HD>(qb + 32 * QS, bq[1]);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (kCentred) acc2[0] = centre;
-      col_mma<BF16, HD, !kCentred>(av, bq[0], acc2[0]);
+      if constexpr (centred) acc2[0] = centre;
+      col_mma<BF16, HD, !centred>(av, bq[0], acc2[0]);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         __builtin_amdgcn_sched_barrier(0);
         if (nb + 2 < NB) col_frags<BF16, HD>(qb + (nb + 2) * 32 * QS, bq[nb & 1]);
         if (nb + 1 < NB) {
-          if constexpr (kCentred) acc2[(nb + 1) & 1] = centre;
-          col_mma<BF16, HD, !kCentred>(av, bq[(nb + 1) & 1], acc2[(nb + 1) & 1]);
+          if constexpr (centred) acc2[(nb + 1) & 1] = centre;
+          col_mma<BF16, HD, !centred>(av, bq[(nb + 1) & 1], acc2[(nb + 1) & 1]);
         }
         if (MOMENTS) col_moments(acc2[nb & 1], nb);
         col_stats(acc2[nb & 1], nb);
@@ -447,26 +448,27 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
       group(std::integral_constant<int, 0>{});
       group(std::integral_constant<int, 4>{});
     } else {
+      constexpr int n = kCentred && !centred ? 1 : NG;  // the rare second walk takes as few registers as it can
 #pragma unroll
-      for (int g0 = 0; g0 < NB; g0 += NG) {
-        floatx16 acc[NG];
-        if constexpr (kCentred) {
+      for (int g0 = 0; g0 < NB; g0 += n) {
+        floatx16 acc[n];
+        if constexpr (centred) {
 #pragma unroll
-          for (int k = 0; k < NG; ++k) acc[k] = centre;
+          for (int k = 0; k < n; ++k) acc[k] = centre;
         }
         if (!BF16 && g0 > 0) forget_terms(av);
-        tile_mma<BF16, NG, HD, !kCentred, !MOMENTS>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+        tile_mma<BF16, n, HD, !centred, !MOMENTS>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
         if (MOMENTS) {
 #pragma unroll
-          for (int k = 0; k < NG; ++k) col_moments(acc[k], g0 + k);
+          for (int k = 0; k < n; ++k) col_moments(acc[k], g0 + k);
         }
 #pragma unroll
-        for (int k = 0; k < NG; ++k) col_stats(acc[k], g0 + k);
+        for (int k = 0; k < n; ++k) col_stats(acc[k], g0 + k);
       }
     }
     if constexpr (KEYS != KEYS_NONE)
       add_keys<HD, KEYS == KEYS_COS>(av, ident, inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
-    if constexpr (kCentred) {
+    if constexpr (centred) {
       const int c = lane & 31, t = t0 + acc_row(c >> 1, hf);
       // the variance's share of every lane, and the mean (the same in all of them) from the first one
       const float k_var = 0.5f * a.inv_sqrt_d * a.inv_sqrt_d / (float)a.d.N, k_mean = c == 0 ? -a.inv_sqrt_d / k_var : 0.f;
@@ -490,9 +492,9 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   };
   auto block = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0) __attribute__((always_inline)) {
     if (t0 + 32 > T)
-      block_of(av, t0, std::true_type{});
+      block_of(av, t0, std::true_type{}, std::true_type{});
     else
-      block_of(av, t0, std::false_type{});
+      block_of(av, t0, std::false_type{}, std::true_type{});
   };
   // this wave's blocks: every WAVES-th block of 32 tokens up to the end of the chunk (or of the cache)
 #pragma unroll 1
@@ -503,7 +505,26 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     if (t0 + 2 * STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + 2 * STEP, T, lane, av0, blk, c0);
     block(av1, t0 + STEP);
   }
-  if (kCentred) __syncthreads();
+  if constexpr (kCentred) {
+    // A key with an infinite entry has no finite centre, and its logits, minus infinity where the queries of that channel have
+    // one sign, are lost: this wave's blocks again, with the sums relative to the first query.
+    float t = 0.f;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) t = __builtin_fmaf(z[nb], 0.f, t);
+    if (__builtin_expect(__any(t != 0.f), 0)) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        m[nb] = kNegInit;
+        z[nb] = 0.f;
+      }
+#pragma unroll 1
+      for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += STEP) {
+        load_a<BF16, HD>(a, l, b, h, t0, T, lane, av0, blk, c0);
+        block_of(av0, t0, std::true_type{}, std::false_type{});
+      }
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const float m2 = __shfl_xor(m[nb], 32), z2 = __shfl_xor(z[nb], 32);

@@ -136,3 +136,40 @@ def test_fp32_keys_at_the_ends_of_the_range(oracle, heads, T, D, G, W):
         assert np.isfinite(want).all() and (want[[7, 40, T - 1]] == 0).all()
         plain = np.setdiff1d(np.arange(T), [7, T - 1] if G * W % 32 else [])
         assert_close_rel(u[h, plain], want[plain], what=f"u unit {h}")
+
+
+@pytest.mark.parametrize("scorer", [B.SCORER_EXPECTED, B.SCORER_EXPECTED_VNORM])
+@pytest.mark.parametrize("D,G,W", [(128, 1, 1), (128, 1, 8), (128, 2, 20), (128, 4, 32), (128, 7, 32), (64, 1, 3), (64, 2, 16),
+                                   (64, 7, 16), (64, 7, 32), (64, 8, 32)])
+def test_infinite_keys_next_to_the_expected_score(oracle, D, G, W, scorer):
+    """A key with an infinite entry against queries of one sign has logits of minus infinity: no share in the usage, and the
+    keys next to it keep theirs, whatever becomes of its own moment score (no number).  The largest finite number, whose
+    logits are partly minus infinity, likewise.  In a full block, in two blocks of one wave, and in the ragged last one.
+    (Padded query columns multiply the infinity by zero: where there are any, the key's own usage may be no number.)"""
+    T = 1201
+    w = inputs.CONFIGS[1].scaled(L=1, B=2, H=1, D=D, G=G, W=W, T=T, T_min=T, budget=50, S=4, n_spans=2, span_len=(8, 40))
+    host = inputs.dense_cache(w, n_threads=8)
+    q, k = inputs.as_f32(host["Q"]).copy(), inputs.as_f32(host["K"]).copy()
+    q[..., 5] = -np.abs(q[..., 5]) - np.float32(0.01)       # all negative in this channel
+    gone = [7, 140, 290, T - 1]
+    k[0, 0, :, gone, 5] = np.inf
+    k[..., 300, 5] = np.float32(3.3e38)
+    host["Q"], host["K"] = inputs._store(q, "bf16"), inputs._store(k, "bf16")
+    job = Job(w, host, scorer=scorer)
+    job.step()
+    inter = job.intermediates()
+    u, g, m_used = to_host(inter.u), to_host(inter.g), to_host(inter.m_used)
+    for i in range(2):                                      # the second sequence has ordinary keys (and one of 3.3e38)
+        Q, K = host["Q"][0, i].reshape(-1, D), host["K"][0, i, 0]
+        want, _ = oracle.score(Q, K, G, W)
+        assert np.isfinite(want).all() and want[300] == 0 and (i or (want[gone] == 0).all())
+        plain = np.setdiff1d(np.arange(T), gone + [300])
+        assert_close_rel(u[i, plain], want[plain], what=f"u unit {i}")
+        assert (G * W % 32 > 0 and i == 0) or not u[i, gone + [300]][want[gone + [300]] == 0].any()
+        np.testing.assert_allclose(m_used[i, plain], oracle.ema(oracle.mass(want, w.eps), np.zeros(T, np.float32), w.lam, w.beta)[0][plain],
+                                   rtol=1e-5)
+        if scorer == B.SCORER_EXPECTED:
+            assert np.isfinite(g[i, plain]).all() and (i or np.isnan(g[i, gone]).all())
+            with np.errstate(all="ignore"):
+                _, want_g = oracle.score(Q, K[plain], G, W, scorer=B.SCORER_EXPECTED)
+                assert_close_terms(g[i, plain], want_g, score_term_magnitudes(scorer, Q, K[plain]), what=f"g unit {i}")
