@@ -264,6 +264,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   // the centred sweep needs the room: its exchange takes the place of the query window, which is used up by then
   float2(*xch)[NB * 32] = kCentred ? (float2(*)[NB * 32])qlds : xch_own;
   __shared__ __align__(16) char mean_sm[kCentred ? 3 * HD * 2 : 16];  // minus the mean query in three bf16 terms
+  [[maybe_unused]] __shared__ int mean_cut;                           // they do not add up to it
   int unit, chunk;
   sweep_tile(a, TAIL, false, unit, chunk);
   int l, b, h;
@@ -328,6 +329,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
       }
       const float x[2] = {(float)(-t.x / (double)a.d.N), (float)(-t.y / (double)a.d.N)};
       uint32_t term[3] = {0, 0, 0};
+      bool cut = false;
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         float r = x[e];
@@ -337,7 +339,10 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
           term[j] |= e ? h : h >> 16;
           r -= __uint_as_float(h);
         }
+        cut |= r != 0.f;
       }
+      const int any_cut = __any(cut);
+      if (threadIdx.x == 0) mean_cut = any_cut;
 #pragma unroll
       for (int j = 0; j < 3; ++j) *(uint32_t*)(mean_sm + j * HD * 2 + pair * 4) = term[j];
     }
@@ -507,11 +512,12 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   }
   if constexpr (kCentred) {
     // A key with an infinite entry has no finite centre, and its logits, minus infinity where the queries of that channel have
-    // one sign, are lost: this wave's blocks again, with the sums relative to the first query.
+    // one sign, are lost; and below 2^-109 the smallest numbers that bf16 has cut the terms of the mean query short (queries of
+    // 2^-118: 4e-5 of the score's terms).  Then this wave's blocks again, with the sums relative to the first query.
     float t = 0.f;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) t = __builtin_fmaf(z[nb], 0.f, t);
-    if (__builtin_expect(__any(t != 0.f), 0)) {
+    if (__builtin_expect(__any(t != 0.f) || mean_cut, 0)) {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         m[nb] = kNegInit;

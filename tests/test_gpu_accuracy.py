@@ -173,3 +173,26 @@ def test_infinite_keys_next_to_the_expected_score(oracle, D, G, W, scorer):
             with np.errstate(all="ignore"):
                 _, want_g = oracle.score(Q, K[plain], G, W, scorer=B.SCORER_EXPECTED)
                 assert_close_terms(g[i, plain], want_g, score_term_magnitudes(scorer, Q, K[plain]), what=f"g unit {i}")
+
+
+@pytest.mark.parametrize("scorer", [B.SCORER_MEAN_WINDOW, B.SCORER_EXPECTED])
+@pytest.mark.parametrize("dtype", ["bf16"])
+@pytest.mark.parametrize("e", [-118, -110, -60, 60, 110, 118])
+@pytest.mark.parametrize("heads,T", [(2, 700), (130, 300)])     # the sweeps, the one-launch scorer
+def test_scale_of_the_keys_moved_into_the_queries(oracle, heads, T, e, dtype, scorer):
+    """Keys times a power of two and queries divided by it: the same logits, the same results."""
+    D, G, W = 128, 2, 20
+    w = inputs.CONFIGS[0].scaled(L=1, H=heads, D=D, G=G, W=W, T=T, dtype=dtype, budget=50, S=4, n_spans=2, span_len=(8, 40))
+    host = inputs.dense_cache(w, n_threads=8)
+    plain = {n: inputs.as_f32(host[n]).copy() for n in ("Q", "K")}
+    host["K"] = inputs._store((plain["K"] * np.float32(2.0 ** e)).astype(np.float32), dtype)
+    host["Q"] = inputs._store((plain["Q"] * np.float32(2.0 ** -e)).astype(np.float32), dtype)
+    job = Job(w, host, scorer=scorer)
+    job.step()
+    u, g = to_host(job.intermediates().u), to_host(job.intermediates().g)
+    for h in range(0, heads, 43):
+        Q, K = plain["Q"][0, 0, h * G:(h + 1) * G].reshape(-1, D), plain["K"][0, 0, h]
+        want, want_g = oracle.score(inputs._store(Q, dtype), inputs._store(K, dtype), G, W, scorer=B.SCORER_EXPECTED)
+        assert_close_rel(u[h, :T], want, what=f"u unit {h}")
+        if scorer == B.SCORER_EXPECTED:
+            assert_close_terms(g[h, :T], want_g, score_term_magnitudes(scorer, Q, K), what=f"g unit {h}")
