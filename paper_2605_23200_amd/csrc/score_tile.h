@@ -88,9 +88,9 @@ __device__ __forceinline__ void split2(float a, float b, uint32_t& hi, uint32_t&
     if (infinite_or_nan(hi)) hi = (hi & 0xFFFFu) | (__float_as_uint(b) & 0xFFFF0000u);
   }
   float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xFFFF0000u);
-  if (SAFE) {
-    if (infinite_or_nan(hi << 16)) ra = 0.f;
-    if (infinite_or_nan(hi)) rb = 0.f;
+  if (SAFE) {  // (not for a NaN, whose first term may have come out as an infinity: its rest is a NaN)
+    if (fabsf(a) == INFINITY) ra = 0.f;
+    if (fabsf(b) == INFINITY) rb = 0.f;
   }
   mid = round2_bf16(ra, rb);
   lo = round2_bf16(ra - __uint_as_float(mid << 16), rb - __uint_as_float(mid & 0xFFFF0000u));

@@ -196,3 +196,19 @@ def test_scale_of_the_keys_moved_into_the_queries(oracle, heads, T, e, dtype, sc
         assert_close_rel(u[h, :T], want, what=f"u unit {h}")
         if scorer == B.SCORER_EXPECTED:
             assert_close_terms(g[h, :T], want_g, score_term_magnitudes(scorer, Q, K), what=f"g unit {h}")
+
+
+@pytest.mark.parametrize("bits", [0x7F800001, 0x7F80FFFF, 0x7FC00000, 0x7FFFFFFF])
+@pytest.mark.parametrize("heads,T", [(2, 700), (130, 300)])     # the sweeps, the one-launch scorer
+@pytest.mark.parametrize("D,G,W", [(128, 1, 8), (128, 7, 16), (64, 4, 32)])
+def test_fp32_key_that_is_no_number(heads, T, D, G, W, bits):
+    """Whatever its bits, a key entry that is no number leaves no number in its unit's usage (and is not taken for an
+    infinity, whose key would drop out against queries of one sign); the other units keep theirs."""
+    w = inputs.CONFIGS[0].scaled(L=1, H=heads, D=D, G=G, W=W, T=T, budget=50, S=4, n_spans=2, span_len=(8, 40))
+    host = inputs.dense_cache(w, n_threads=8)
+    host["Q"][..., 5] = -np.abs(host["Q"][..., 5]) - np.float32(1e-3)
+    host["K"].view(np.uint32)[0, 0, 0, 100, 5] = bits
+    job = Job(w, host)
+    job.step()
+    u = to_host(job.intermediates().u)[:, :T]
+    assert np.isnan(u[0]).all() and np.isfinite(u[1:]).all()
