@@ -284,7 +284,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     blk = blk_sm;
   }
   if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
-  load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
+  const float q_top = load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
   __shared__ uint4 ident[KEYS ? 2 : 1][64];
   __shared__ __align__(16) double inv_len[KEYS == KEYS_COS ? 4 : 1][32];
   double ksum[KEYS ? HD / 32 : 1];
@@ -299,7 +299,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
 #pragma unroll
     for (int cb = 0; cb < HD / 32; ++cb) ksum[cb] = 0.0;
   }
-  __syncthreads();
+  const int key_exp = settle_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds, q_top);
   float m[NB], z[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
@@ -462,7 +462,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
           for (int k = 0; k < n; ++k) acc[k] = centre;
         }
         if (!BF16 && g0 > 0) forget_terms(av);
-        tile_mma<BF16, n, HD, !centred, !MOMENTS>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+        tile_mma<BF16, n, HD, !centred, !MOMENTS>(av, qlds + qoff + g0 * 32 * QS, lane, acc, key_exp);
         if (MOMENTS) {
 #pragma unroll
           for (int k = 0; k < n; ++k) col_moments(acc[k], g0 + k);
@@ -736,7 +736,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
     blk = blk_sm;
   }
   if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
-  load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
+  const float q_top = load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
   // KEYS: the mean key (or the sum of the unit vectors) as three bf16 terms that add up to its fp32 value, and a row of
   // zeros, behind the query window
   char* krow = qlds + NB * 32 * QS;
@@ -773,7 +773,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
       if (lane == 0) k2_sm[wave] = k2;
     }
   }
-  __syncthreads();
+  const int key_exp = settle_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds, q_top);
   const double kbar2 = KEYS != KEYS_MEAN                            ? 0.0
                        : isinf(k2_sm[0]) || isinf(k2_sm[1]) ? INFINITY
                                                             : k2_sm[0] + k2_sm[1];  // squared length of the mean key
@@ -853,7 +853,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
 #pragma unroll
       for (int g0 = 0; g0 < NB; g0 += NG) {
         floatx16 acc[NG];
-        tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+        tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc, key_exp);
 #pragma unroll
         for (int k = 0; k < NG; ++k) col_usage(acc[k], g0 + k);
       }

@@ -104,13 +104,15 @@ __device__ __forceinline__ void forget_terms(const uint4 (&av)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(v[i].x), "+v"(v[i].y), "+v"(v[i].z), "+v"(v[i].w));
 }
 
-// 16 bytes (column col) of a query row -> its place in LDS.
+// 16 bytes (column col) of a query row -> its place in LDS; fp32: times 2^-exp, and the largest magnitude -> top.
 template <bool BF16, int HD>
-__device__ __forceinline__ void store_q(char* row, int col, const uint4& v) {
+__device__ __forceinline__ void store_q(char* row, int col, const uint4& v, float& top, int exp = 0) {
   if constexpr (BF16) {
     *(uint4*)(row + col * 16) = v;
   } else {
-    const float4 x = __builtin_bit_cast(float4, v);
+    float4 x = __builtin_bit_cast(float4, v);
+    top = fmaxf(fmaxf(top, fmaxf(fabsf(x.x), fabsf(x.y))), fmaxf(fabsf(x.z), fabsf(x.w)));
+    if (exp != 0) x = make_float4(ldexpf(x.x, -exp), ldexpf(x.y, -exp), ldexpf(x.z, -exp), ldexpf(x.w, -exp));
     uint2 t[3];
     split2<true>(x.x, x.y, t[0].x, t[1].x, t[2].x);
     split2<true>(x.z, x.w, t[0].y, t[1].y, t[2].y);
@@ -119,16 +121,53 @@ __device__ __forceinline__ void store_q(char* row, int col, const uint4& v) {
   }
 }
 
-// Query window of the unit -> LDS, rows padded against bank conflicts, rows >= N zero.
+// Query window of the unit -> LDS, rows padded against bank conflicts, rows >= N zero.  Returns the largest magnitude that the
+// thread has seen (fp32).
 template <bool BF16, int NB, int HD = 128, int THREADS = kThreads>
-__device__ __forceinline__ void load_q(const ScoreArgs& a, int l, int b, int h, char* qlds) {
+__device__ __forceinline__ float load_q(const ScoreArgs& a, int l, int b, int h, char* qlds, int exp = 0) {
   constexpr int RB = Tr<BF16, HD>::kRowBytes, QS = Tr<BF16, HD>::kQStride, CPR = RB / 16;
   const char* src = a.q + ((((int64_t)l * a.d.B + b) * a.d.H + h) * a.d.G) * (int64_t)a.d.W * RB;
+  float top = 0.f;
   for (int ch = threadIdx.x; ch < NB * 32 * CPR; ch += THREADS) {
     const int n = ch / CPR, col = ch % CPR;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (n < a.d.N) v = *(const uint4*)(src + (int64_t)n * RB + col * 16);
-    store_q<BF16, HD>(qlds + n * QS, col, v);
+    store_q<BF16, HD>(qlds + n * QS, col, v, top, exp);
+  }
+  return top;
+}
+
+// Barrier after load_q.  fp32: bf16 terms are cut short below 2^-109 (the last one ends at 2^-133), which shows where the
+// other factor is about as large: keys of 2^-118 against queries of 2^118 had logits off by 1e-5.  A window whose largest
+// entry lies outside 2^-100 .. 2^100 is loaded again, scaled to about one, and the power of two taken from it, which is
+// returned (0 otherwise), goes to the keys (tile_mma).
+template <bool BF16, int NB, int HD = 128, int THREADS = kThreads>
+__device__ __forceinline__ int settle_q(const ScoreArgs& a, int l, int b, int h, char* qlds, float top) {
+  if constexpr (BF16) {
+    __syncthreads();
+    return 0;
+  } else {
+    constexpr int WAVES = THREADS / 64;
+    __shared__ int seen[WAVES];
+    __shared__ float tops[WAVES];
+    const int mine = (__any(top >= 0x1p-100f) ? 1 : 0) | (__any(top >= 0x1p100f) ? 2 : 0);
+    if ((threadIdx.x & 63) == 0) seen[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) all |= seen[w];
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(all) == 1, 1)) return 0;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
+    tops[threadIdx.x >> 6] = top;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) top = fmaxf(top, tops[w]);
+    if (!(top > 0.f) || top == INFINITY) return 0;
+    const int exp = __builtin_amdgcn_readfirstlane(max(-126, min(126, __builtin_amdgcn_frexp_expf(top) - 1)));
+    load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds, exp);
+    __syncthreads();
+    return exp;
   }
 }
 
@@ -174,9 +213,10 @@ __device__ __forceinline__ void stage_blocks(const ScoreArgs& a, int b, int c0, 
 // 4096 positions), 2.4e-7 with the fp32 instruction.  us per step, with it and with this: 408 and 290 (20 units of 30000, 128
 // queries), 419 and 239 (130 of 3000), 238 and 194 (20 of 30000, 64 queries), 175 and 165 (8 queries: memory bound), 240 and
 // 170 (176 ragged units of up to 2772, 64 queries).
-// SAFE: keys that are infinite or no number (K1 holds them, and the products with Q2 and Q3, which may be zero, leave them out).
+// SAFE: keys that are infinite or no number (K1 holds them, and the products with Q2 and Q3, which may be zero, leave them out),
+// and keys that take a power of two from the queries (settle_q).
 template <int NB, int HD, bool SAFE, bool AHEAD>
-__device__ __forceinline__ void tile_split(const uint4 (&av)[Tr<false, HD>::kAVecs], const char* qb, floatx16 (&acc)[NB]) {
+__device__ __forceinline__ void tile_split(const uint4 (&av)[Tr<false, HD>::kAVecs], const char* qb, floatx16 (&acc)[NB], int key_exp = 0) {
   constexpr int QS = Tr<false, HD>::kQStride, QT = Tr<false, HD>::kQTerm;
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
@@ -186,7 +226,11 @@ __device__ __forceinline__ void tile_split(const uint4 (&av)[Tr<false, HD>::kAVe
     uint32_t h[4], m[4], l[4], f[4];  // K1, K2, K3, and K1 without what is infinite or no number
   };
   auto split = [&](int ks) __attribute__((always_inline)) {
-    const float4 x0 = __builtin_bit_cast(float4, av[2 * ks]), x1 = __builtin_bit_cast(float4, av[2 * ks + 1]);
+    float4 x0 = __builtin_bit_cast(float4, av[2 * ks]), x1 = __builtin_bit_cast(float4, av[2 * ks + 1]);
+    if (SAFE) {
+      x0 = make_float4(ldexpf(x0.x, key_exp), ldexpf(x0.y, key_exp), ldexpf(x0.z, key_exp), ldexpf(x0.w, key_exp));
+      x1 = make_float4(ldexpf(x1.x, key_exp), ldexpf(x1.y, key_exp), ldexpf(x1.z, key_exp), ldexpf(x1.w, key_exp));
+    }
     Terms t;
     split2<SAFE>(x0.x, x0.y, t.h[0], t.m[0], t.l[0]);
     split2<SAFE>(x0.z, x0.w, t.h[1], t.m[1], t.l[1]);
@@ -238,7 +282,7 @@ __device__ __forceinline__ void tile_split(const uint4 (&av)[Tr<false, HD>::kAVe
 // (CLEAR = false: acc starts from what it holds; AHEAD: registers to spare, see tile_split)
 template <bool BF16, int NB, int HD = 128, bool CLEAR = true, bool AHEAD = true>
 __device__ __forceinline__ void tile_mma(const uint4 (&av)[Tr<BF16, HD>::kAVecs], const char* qlds,
-                                         int lane, floatx16 (&acc)[NB]) {
+                                         int lane, floatx16 (&acc)[NB], int key_exp = 0) {
   constexpr int QS = Tr<BF16, HD>::kQStride;
   [[maybe_unused]] constexpr int NV = Tr<BF16, HD>::kAVecs;
   const char* qb = qlds + (lane & 31) * QS + (lane >> 5) * (Tr<BF16, HD>::kQTerm / 2);
@@ -261,11 +305,11 @@ __device__ __forceinline__ void tile_mma(const uint4 (&av)[Tr<BF16, HD>::kAVecs]
     float t = 0.f;  // a key that is infinite or no number shows in every column
 #pragma unroll
     for (int i = 0; i < 16; ++i) t = __builtin_fmaf(acc[0][i], 0.f, t);
-    if (__builtin_expect(__any(t != 0.f), 0)) {
+    if (__builtin_expect(__any(t != 0.f) || key_exp != 0, 0)) {
       forget_terms(av);
       int off = 0;
       asm volatile("" : "+s"(off));
-      tile_split<NB, HD, true, false>(av, qb + off, acc);
+      tile_split<NB, HD, true, false>(av, qb + off, acc, key_exp);
     }
   }
 }

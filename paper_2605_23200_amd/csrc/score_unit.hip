@@ -18,7 +18,6 @@ constexpr int kUnitThreads = 512, kUnitWaves = kUnitThreads / 64;
 template <bool BF16, int NB, int MODE, int HD>
 __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a) {
   constexpr int NG = (BF16 && NB % 2 == 0 && NB >= 4) ? NB / 2 : NB, QS = Tr<BF16, HD>::kQStride, NQ = NB * 32;
-  constexpr int RB = Tr<BF16, HD>::kRowBytes, CPR = RB / 16;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch[kUnitWaves][NQ];
   __shared__ float4 fin_s[NQ];
@@ -35,15 +34,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
   constexpr int kStep = kUnitWaves * 32;  // tokens between two blocks of one wave
   if (wave * 32 < T) load_a<BF16, HD>(a, l, b, h, wave * 32, T, lane, av0);
-  {  // the query window -> LDS, rows padded against bank conflicts, rows >= N zero
-    const char* src = a.q + ((((int64_t)l * a.d.B + b) * a.d.H + h) * a.d.G) * (int64_t)a.d.W * RB;
-    for (int ch = threadIdx.x; ch < NQ * CPR; ch += kUnitThreads) {
-      const int n = ch / CPR, col = ch % CPR;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (n < a.d.N) v = *(const uint4*)(src + (int64_t)n * RB + col * 16);
-      store_q<BF16, HD>(qlds + n * QS, col, v);
-    }
-  }
+  const float q_top = load_q<BF16, NB, HD, kUnitThreads>(a, l, b, h, qlds);
   // the old credit of the unit (for the EMA normaliser): at most 8 positions per thread, in flight during the walks
   float cr[kScoreChunk / kUnitThreads];
 #pragma unroll
@@ -51,7 +42,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
     const int t = k * kUnitThreads + (int)threadIdx.x;
     cr[k] = (a.vc_part && a.credit && t < T) ? a.credit[(int64_t)unit * a.d.t_stride + t] : 0.f;
   }
-  __syncthreads();
+  const int key_exp = settle_q<BF16, NB, HD, kUnitThreads>(a, l, b, h, qlds, q_top);
   const float c2 = a.c2;
 
   // ---- first walk: per query (max, sum exp2) of the scaled logits over this wave's blocks ----
@@ -68,7 +59,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
 #pragma unroll
     for (int g0 = 0; g0 < NB; g0 += NG) {
       floatx16 acc[NG];
-      tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+      tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc, key_exp);
 #pragma unroll
       for (int k = 0; k < NG; ++k) {
         const int nb = g0 + k;
@@ -137,7 +128,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
 #pragma unroll
     for (int g0 = 0; g0 < NB; g0 += NG) {
       floatx16 acc[NG];
-      tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc);
+      tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc, key_exp);
 #pragma unroll
       for (int k = 0; k < NG; ++k) {
         const int nb = g0 + k;

@@ -176,7 +176,7 @@ def test_infinite_keys_next_to_the_expected_score(oracle, D, G, W, scorer):
 
 
 @pytest.mark.parametrize("scorer", [B.SCORER_MEAN_WINDOW, B.SCORER_EXPECTED])
-@pytest.mark.parametrize("dtype", ["bf16"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("e", [-118, -110, -60, 60, 110, 118])
 @pytest.mark.parametrize("heads,T", [(2, 700), (130, 300)])     # the sweeps, the one-launch scorer
 def test_scale_of_the_keys_moved_into_the_queries(oracle, heads, T, e, dtype, scorer):
