@@ -40,10 +40,9 @@ static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool 
   // wave: 8 fp32 units of 4096 positions 86.7 us per step with 1024 keys (32 workgroups), 69.2 with 512, 59.9
   // with 256, 55.0 with 128; 4 bf16 units of 10126 positions 70.5 / 63.5 / 60.2 / 60.2.  From one workgroup per
   // CU on shorter chunks lose again (8 units of 32768 positions: 96.5 with 1024, 98.0 with 512, 109 with 256)
-  // (the value-weighted score, and the key-based ones of fp32 and causal caches, merge the chunks in one thread or per
-  // workgroup, so that more of them cost more there; with this rule and all else one unit of 32768 positions takes 107 us
-  // per step with the value-weighted score where it took 129 with chunks of 1024, and 123 where it took 168 with the fp32 key
-  // diversity; 1 to 8 units of 8192 to 131072 positions take 0.44 to 0.88 of what they took)
+  // (the key-based scores of fp32 and causal caches add the chunks up per workgroup, so that more of them cost more there; with
+  // this rule and all else one unit of 32768 positions takes 123 us per step with the fp32 key diversity where it took 168 with
+  // chunks of 1024; 1 to 8 units of 8192 to 131072 positions take 0.44 to 0.88 of what they took)
   while (chunk > kMinScoreChunk && units * (size_t)div_up(t_max, chunk) < 256) chunk /= 2;
   // Units of one length whose keys fit one round of workgroups: chunks that give every compute unit the same number of
   // workgroups, two of them (three where a tile takes few registers, one where there is not enough work), if they come out
@@ -74,6 +73,7 @@ WsLayout ws_layout(const ams_params* p) {
   const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY || p->kv_dtype == AMS_F32 ? kKeysChunk : kScoreChunk;
   const bool small_tiles = p->kv_dtype == AMS_BF16 && (p->group * p->window <= 64 || p->head_dim == 64);
   w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles);
+  w.stream_chunk = pick_score_chunk(units, p->t_max, false, most, false, false);
   w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false);
   w.n_chunks = div_up(p->t_max, w.score_chunk);
   w.n_chunks_paged = div_up(p->t_max, w.score_chunk_paged);

@@ -74,6 +74,7 @@ struct WsLayout {
   int n_chunks, n_pad;
   int score_chunk;  // tokens per workgroup of the scoring kernels for these parameters, dense cache
   int score_chunk_paged, n_chunks_paged;  // the same for a paged cache
+  int stream_chunk;  // tokens per workgroup of a kernel that streams a dense cache beside them
   int n_words;     // 32-position words of the kept-set bitmap per unit
 };
 WsLayout ws_layout(const ams_params* p);

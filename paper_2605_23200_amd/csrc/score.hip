@@ -184,33 +184,40 @@ __global__ __launch_bounds__(kThreads) void esoftmax_part_kernel(ScoreArgs a, do
   softmax_part(a.g + (int64_t)unit * a.d.t_stride + c0, min(a.chunk, T - c0), part + (int64_t)unit * a.n_chunks + chunk);
 }
 
+// Chunk statistics (maximum, sum of exp) of a unit's scores merged: every wave for itself, strided over the lanes, then a fixed
+// tree.  (One thread in turn took 15 us for 73 chunks.)
+__device__ __forceinline__ void merge_chunks(const ScoreArgs& a, const double2* part, int unit, int T, double& M, double& Z) {
+  const int nch = (T + a.chunk - 1) / a.chunk, lane = threadIdx.x & 63;
+  const double2* p = part + (int64_t)unit * a.n_chunks;
+  M = -INFINITY;
+  Z = 0.0;
+  for (int c = lane; c < nch; c += 64) M = fmax(M, p[c].x);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) M = fmax(M, __shfl_xor(M, o));
+  for (int c = lane; c < nch; c += 64) Z += p[c].y * exp(p[c].x - M);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) Z += __shfl_xor(Z, o);
+}
+
+// span: positions per workgroup, which need not be the sweeps' chunk.  Bound: the V stream.  A workgroup keeps one row per lane
+// in flight, so it takes many of them: with the long chunks of a sweep that fills one round of workgroups 144 units of 16589
+// positions took 185 us (3328 per workgroup) where spans of 1024 take 152.  Shorter chunks of such a sweep fit here as well.
 template <bool BF16, int HD>
-__global__ __launch_bounds__(kThreads) void vweight_kernel(ScoreArgs a, KvDev v, const double2* part, float eps_f) {
+__global__ __launch_bounds__(kThreads) void vweight_kernel(ScoreArgs a, KvDev v, const double2* part, int span, float eps_f) {
   constexpr int CPR = Tr<BF16, HD>::kRowBytes / 16, EPC = BF16 ? 8 : 4, RPI = kThreads / CPR;
-  __shared__ double2 stat;
   __shared__ float norm2[kScoreChunk];  // per token: v . v
-  const int unit = blockIdx.y, chunk = blockIdx.x;
+  const int unit = blockIdx.y;
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const int c0 = chunk * a.chunk;
+  const int c0 = blockIdx.x * span;
   if (c0 >= T) return;
-  if (threadIdx.x == 0) {  // chunk statistics merged in index order
-    const int nch = (T + a.chunk - 1) / a.chunk;
-    double M = -INFINITY;
-    for (int c = 0; c < nch; ++c) M = fmax(M, part[(int64_t)unit * a.n_chunks + c].x);
-    double Z = 0.0;
-    for (int c = 0; c < nch; ++c) {
-      const double2 s = part[(int64_t)unit * a.n_chunks + c];
-      Z += s.y * exp(s.x - M);
-    }
-    stat = make_double2(M, Z);
-  }
-  __syncthreads();
-  const double M = stat.x, inv_z = 1.0 / stat.y, eps = (double)eps_f;
+  double M, Z;
+  merge_chunks(a, part, unit, T, M, Z);
+  const double inv_z = 1.0 / Z, eps = (double)eps_f;
   const int col = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
   float* g_row = a.g + (int64_t)unit * a.d.t_stride;
-  for (int tb = c0; tb < min(T, c0 + a.chunk); tb += RPI) {
+  for (int tb = c0; tb < min(T, c0 + span); tb += RPI) {
     const int t = tb + r0;
     float n2 = 0.f;  // 128 squares summed in fp32, the rest in double
     if (t < T) {
@@ -228,14 +235,15 @@ __global__ __launch_bounds__(kThreads) void vweight_kernel(ScoreArgs a, KvDev v,
   }
   __syncthreads();
   // one token per thread for the exponential, so that every lane works
-  for (int t = c0 + threadIdx.x; t < min(T, c0 + a.chunk); t += kThreads)
+  for (int t = c0 + threadIdx.x; t < min(T, c0 + span); t += kThreads)
     g_row[t] = (float)((exp((double)g_row[t] - M) * inv_z + eps) * sqrt((double)norm2[t - c0]));
 }
 
 template <bool BF16, int HD>
 hipError_t launch_vweight(const ScoreArgs& a, const KvDev& v, char* ws, const WsLayout& wl, float eps, hipStream_t s) {
-  hipLaunchKernelGGL((vweight_kernel<BF16, HD>), dim3(a.n_chunks, a.d.units), dim3(kThreads), 0, s, a, v,
-                     (const double2*)(ws + wl.kbar), eps);
+  const int span = min(a.chunk, a.k.layout == AMS_LAYOUT_DENSE ? wl.stream_chunk : wl.score_chunk_paged);
+  hipLaunchKernelGGL((vweight_kernel<BF16, HD>), dim3(div_up(a.d.t_max, span), a.d.units), dim3(kThreads), 0, s, a, v,
+                     (const double2*)(ws + wl.kbar), span, eps);
   return hipGetLastError();
 }
 
@@ -257,7 +265,7 @@ constexpr int kMixRun = 4 * kThreads;  // positions per workgroup of the kernel 
 __global__ __launch_bounds__(kThreads) void redundancy_combine_kernel(ScoreArgs a, const double2* part, float mix_lambda,
                                                                        int pool_r) {
   __shared__ __align__(16) float tile[kMixRun + 2 * 31 + 4];
-  const int unit = blockIdx.y, lane = threadIdx.x & 63;
+  const int unit = blockIdx.y;
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
@@ -273,16 +281,8 @@ __global__ __launch_bounds__(kThreads) void redundancy_combine_kernel(ScoreArgs 
   float r[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) r[i] = c0 + e + i < T ? g_row[c0 + e + i] : 0.f;
-  // chunk statistics of the similarities: every wave for itself, strided over the lanes, then a fixed tree
-  const int nch = (T + a.chunk - 1) / a.chunk;
-  const double2* p = part + (int64_t)unit * a.n_chunks;
-  double M = -INFINITY, Z = 0.0;
-  for (int c = lane; c < nch; c += 64) M = fmax(M, p[c].x);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) M = fmax(M, __shfl_xor(M, o));
-  for (int c = lane; c < nch; c += 64) Z += p[c].y * exp(p[c].x - M);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) Z += __shfl_xor(Z, o);
+  double M, Z;
+  merge_chunks(a, part, unit, T, M, Z);
   const double inv_z = 1.0 / Z, lam = (double)mix_lambda, inv_full = 1.0 / (double)(2 * pool_r + 1);
   __syncthreads();
   // the mean of u over the positions t - r .. t + r that exist, stored as fp32: one walk for four positions

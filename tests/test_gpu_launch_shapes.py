@@ -305,7 +305,8 @@ def test_selection_gathers_its_rows(oracle, T, S, budget, gathers, dtype, D, pag
 
 
 @pytest.mark.parametrize("scorer,causal", [(B.SCORER_MEAN_WINDOW, False), (B.SCORER_LAST_QUERY, True), (B.SCORER_KEYDIFF, False),
-                                           (B.SCORER_REDUNDANCY, False), (B.SCORER_EXPECTED_VNORM, True)])
+                                           (B.SCORER_REDUNDANCY, False), (B.SCORER_EXPECTED_VNORM, True),
+                                           (B.SCORER_EXPECTED_VNORM, False)])
 @pytest.mark.parametrize("units,T,dtype,G,W,D", [(5, 30000, "bf16", 7, 32, 128),    # one workgroup per CU, chunks of 640
                                                  (64, 6000, "bf16", 4, 32, 128),    # two, 768
                                                  (64, 7001, "bf16", 2, 8, 128),     # three, 640
