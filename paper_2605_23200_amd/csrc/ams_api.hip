@@ -26,7 +26,7 @@ static int padded_queries(int n, bool bf16) {
 
 // Tokens per workgroup of the scoring sweeps: as many as possible (the query window is loaded once per
 // workgroup), but few enough that the launch has a couple of thousand workgroups to fill 256 CUs.  even: all sequences have
-// t_max positions as far as the host can tell; small_tiles: the sweeps' tiles leave room for four workgroups on a CU.
+// t_max positions as far as the host can tell; small_tiles: the sweeps' tiles leave room for three workgroups on a CU.
 static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool even, bool small_tiles) {
   // measured on 256 units: 4096 tokens at 32k positions (1.060 ms per step against 1.077 with 2048 and
   // 1.13 with 1024), 1024 at 2176 positions (0.208 against 0.229 with 2048); 512 and 256 lose to the
@@ -64,6 +64,16 @@ static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool 
   return chunk;
 }
 
+// Queries per KV head up to which the tiles of both sweeps leave registers and LDS for three workgroups on a CU (bf16).  The
+// moment sums and the unit vectors of the first sweep take some of them.  us per step with chunks for three workgroups where
+// two fit, and for those two: 106 and 95 (16 units of 32835, 64 queries, expected attention), 158 and 145 (49 of 16637, 64
+// queries, mean cosines), 133 and 116 (28 of 24635, 256 queries, 64 channels).
+static int most_queries_of_small_tiles(const ams_params* p) {
+  const bool moments = p->scorer == AMS_SCORER_EXPECTED || p->scorer == AMS_SCORER_EXPECTED_VNORM;
+  if (p->head_dim == 64) return moments ? 64 : 128;
+  return moments || p->scorer == AMS_SCORER_REDUNDANCY ? 32 : 64;
+}
+
 WsLayout ws_layout(const ams_params* p) {
   WsLayout w;
   const size_t units = (size_t)p->n_layers * p->batch * p->n_kv_heads;
@@ -71,7 +81,7 @@ WsLayout ws_layout(const ams_params* p) {
   // workgroups on a CU
   // (fp32: the three terms of the query window take the room)
   const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY || p->kv_dtype == AMS_F32 ? kKeysChunk : kScoreChunk;
-  const bool small_tiles = p->kv_dtype == AMS_BF16 && (p->group * p->window <= 64 || p->head_dim == 64);
+  const bool small_tiles = p->kv_dtype == AMS_BF16 && p->group * p->window <= most_queries_of_small_tiles(p);
   w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles);
   w.stream_chunk = pick_score_chunk(units, p->t_max, false, most, false, false);
   w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false);
