@@ -26,8 +26,9 @@ static int padded_queries(int n, bool bf16) {
 
 // Tokens per workgroup of the scoring sweeps: as many as possible (the query window is loaded once per
 // workgroup), but few enough that the launch has a couple of thousand workgroups to fill 256 CUs.  even: all sequences have
-// t_max positions as far as the host can tell; small_tiles: the sweeps' tiles leave room for three workgroups on a CU.
-static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool even, bool small_tiles) {
+// t_max positions as far as the host can tell; small_tiles: the sweeps' tiles leave room for three workgroups on a CU;
+// large_tiles: more than 128 queries.
+static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool even, bool small_tiles, bool large_tiles) {
   // measured on 256 units: 4096 tokens at 32k positions (1.060 ms per step against 1.077 with 2048 and
   // 1.13 with 1024), 1024 at 2176 positions (0.208 against 0.229 with 2048); 512 and 256 lose to the
   // per-workgroup load of the query window
@@ -50,15 +51,17 @@ static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool 
   // them and with this rule, bf16, 128 channels: 182 and 172 (64 units of 16384, 128 queries), 269 and 263 (90 of 20000), 61.0
   // and 57.1 (8 of 20000), 181 and 141 (20 of 30000, 224 queries); 111 and 99 (57 of 20000, 64 channels); 215 and 180 (20 of
   // 30000, fp32).  One workgroup per CU where two would do, or three large tiles, lose: 84 and 92 (40 of 11000), 316 and 333
-  // (128 of 16384).  Ragged sequences keep the power of two: their workgroups end at different times whatever the cut (209
-  // against 229 for 2 sequences of 11003 and 20011 positions in chunks of 2304).
+  // (128 of 16384); one per CU with chunks of 1024 loses as well (49 units of 5014 with the key diversity: 77.3 and 79.1, 4 of
+  // 61268, 64 channels: 73.6 and 76.6), but not with more than 128 queries (5 of 47809: 102 and 97).  Ragged sequences keep
+  // the power of two: their workgroups end at different times whatever the cut (209 against 229 for 2 sequences of 11003 and
+  // 20011 positions in chunks of 2304).
   if (!paged && even) {
     const bool few = chunk < 1024;
     for (int per_cu = few ? 1 : small_tiles ? 3 : 2; per_cu >= (few ? 1 : 2); --per_cu) {
       const size_t n = (size_t)per_cu * 256 / units;
       if (n == 0) break;
       const int c = div_up(div_up(t_max, (int64_t)n), kMinScoreChunk) * kMinScoreChunk;
-      if (c <= most && (few || c > 512) && (double)units * t_max >= 0.85 * 256.0 * per_cu * c) return c;
+      if (c <= (few && !large_tiles ? 896 : most) && (few || c > 512) && (double)units * t_max >= 0.85 * 256.0 * per_cu * c) return c;
     }
   }
   return chunk;
@@ -82,9 +85,9 @@ WsLayout ws_layout(const ams_params* p) {
   // (fp32: the three terms of the query window take the room)
   const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY || p->kv_dtype == AMS_F32 ? kKeysChunk : kScoreChunk;
   const bool small_tiles = p->kv_dtype == AMS_BF16 && p->group * p->window <= most_queries_of_small_tiles(p);
-  w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles);
-  w.stream_chunk = pick_score_chunk(units, p->t_max, false, most, false, false);
-  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false);
+  w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles, p->group * p->window > 128);
+  w.stream_chunk = pick_score_chunk(units, p->t_max, false, most, false, false, false);
+  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false, false);
   w.n_chunks = div_up(p->t_max, w.score_chunk);
   w.n_chunks_paged = div_up(p->t_max, w.score_chunk_paged);
   const size_t nc_cap = (size_t)max(w.n_chunks, w.n_chunks_paged);  // the parameters do not say which layout comes
