@@ -83,8 +83,9 @@ typedef enum {
   AMS_SCORE_PATH_ONE_LAUNCH = 3  /* short caches (t_max <= 4096): one workgroup walks a unit's keys
                                     twice in one launch; at most 128 queries per KV head, no causal
                                     window, no moment-based scorer; AMS_ERR_UNSUPPORTED otherwise.
-                                    AUTO takes it when it applies, there are >= 128 units (> 176
-                                    beyond 2816 positions), not for key-based scores of bf16 caches */
+                                    AUTO takes it when it applies and there are >= 128 units, not
+                                    for key-based scores of bf16 caches, and beyond 2816 positions
+                                    not for up to 160 units that the sweeps finish in one round     */
 } ams_score_path;
 
 typedef enum {

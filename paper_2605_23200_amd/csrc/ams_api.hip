@@ -27,8 +27,10 @@ static int padded_queries(int n, bool bf16) {
 // Tokens per workgroup of the scoring sweeps: as many as possible (the query window is loaded once per
 // workgroup), but few enough that the launch has a couple of thousand workgroups to fill 256 CUs.  even: all sequences have
 // t_max positions as far as the host can tell; small_tiles: the sweeps' tiles leave room for three workgroups on a CU;
-// large_tiles: more than 128 queries.
-static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool even, bool small_tiles, bool large_tiles) {
+// large_tiles: more than 128 queries; *one_round: the chunks are those that fill one round of workgroups.
+static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool even, bool small_tiles, bool large_tiles,
+                            bool* one_round) {
+  *one_round = false;
   // measured on 256 units: 4096 tokens at 32k positions (1.060 ms per step against 1.077 with 2048 and
   // 1.13 with 1024), 1024 at 2176 positions (0.208 against 0.229 with 2048); 512 and 256 lose to the
   // per-workgroup load of the query window
@@ -61,7 +63,10 @@ static int pick_score_chunk(size_t units, int t_max, bool paged, int most, bool 
       const size_t n = (size_t)per_cu * 256 / units;
       if (n == 0) break;
       const int c = div_up(div_up(t_max, (int64_t)n), kMinScoreChunk) * kMinScoreChunk;
-      if (c <= (few && !large_tiles ? 896 : most) && (few || c > 512) && (double)units * t_max >= 0.85 * 256.0 * per_cu * c) return c;
+      if (c <= (few && !large_tiles ? 896 : most) && (few || c > 512) && (double)units * t_max >= 0.85 * 256.0 * per_cu * c) {
+        *one_round = true;
+        return c;
+      }
     }
   }
   return chunk;
@@ -85,9 +90,11 @@ WsLayout ws_layout(const ams_params* p) {
   // (fp32: the three terms of the query window take the room)
   const int most = p->scorer == AMS_SCORER_KEYDIFF || p->scorer == AMS_SCORER_REDUNDANCY || p->kv_dtype == AMS_F32 ? kKeysChunk : kScoreChunk;
   const bool small_tiles = p->kv_dtype == AMS_BF16 && p->group * p->window <= most_queries_of_small_tiles(p);
-  w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles, p->group * p->window > 128);
-  w.stream_chunk = pick_score_chunk(units, p->t_max, false, most, false, false, false);
-  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false, false);
+  w.score_chunk = pick_score_chunk(units, p->t_max, false, most, p->batch == 1, small_tiles, p->group * p->window > 128,
+                                   &w.one_round);
+  bool never;
+  w.stream_chunk = pick_score_chunk(units, p->t_max, false, most, false, false, false, &never);
+  w.score_chunk_paged = pick_score_chunk(units, p->t_max, true, most, false, false, false, &never);
   w.n_chunks = div_up(p->t_max, w.score_chunk);
   w.n_chunks_paged = div_up(p->t_max, w.score_chunk_paged);
   const size_t nc_cap = (size_t)max(w.n_chunks, w.n_chunks_paged);  // the parameters do not say which layout comes

@@ -73,6 +73,7 @@ struct WsLayout {
   size_t part_stats, fin_stats, u, g, m_used, bounds, seg_mass, quota, kbar, park, vc_part, sub, flags, csum, total;
   int n_chunks, n_pad;
   int score_chunk;  // tokens per workgroup of the scoring kernels for these parameters, dense cache
+  bool one_round;   // with that many tokens the sweeps over a dense cache fill one round of workgroups
   int score_chunk_paged, n_chunks_paged;  // the same for a paged cache
   int stream_chunk;  // tokens per workgroup of a kernel that streams a dense cache beside them
   int n_words;     // 32-position words of the kept-set bitmap per unit

@@ -400,10 +400,12 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   if (!oneread) {
     // Short caches with enough units to fill the chip: one workgroup per unit, one launch.  Not for the key-based scores, which
     // would have to stream K twice more (us per event with and without: 103 and 89 for 142 units of 1836 positions with the key
-    // diversity, 164 and 114 for 128 of 4096, 358 and 249 for 300 of 3500 with the mean cosines), and not for longer ones of
-    // these caches whose single round leaves three CUs in ten idle (90 and 79 for 128 of 3000, 113 and 98 for 128 of 4096,
-    // 122 and 118 for 160 of 4096; but 127 and 131 for 180 of 4096, 156 and 169 for 256, 52 and 53 for 128 of 2600, D = 64).
-    const bool thin = d.t_max > 2816 && d.units <= 176;
+    // diversity, 164 and 114 for 128 of 4096, 358 and 249 for 300 of 3500 with the mean cosines).  And not for longer ones of
+    // these caches where its single round leaves three CUs in eight or more idle and the sweeps run in one round too, two
+    // workgroups to a CU or what fills it: there they take 0.75 to 1.0 of its time (seven lengths from 2817 to 4096 x 128 to 160
+    // units x eight shapes of 8 to 128 queries, 64 and 128 channels, bf16 and fp32).  A second, nearly empty round costs them
+    // more than they gain: up to 1.28 of its time (144 units of 3073, 152 of 3584, 176 of 2900).
+    const bool thin = d.t_max > 2816 && d.units <= 160 && ((int64_t)d.units * a.n_chunks <= 512 || (!paged && wl.one_round));
     const bool want_unit = p->score_path == AMS_SCORE_PATH_ONE_LAUNCH ||
                            (p->score_path == AMS_SCORE_PATH_AUTO && d.units >= kUnitScorerMinUnits && !keys_ride && !thin);
     if (want_unit) {

@@ -398,12 +398,17 @@ def test_gap_of_a_must_keep_set_is_filled(oracle, T, n_sink, n_last):
             np.testing.assert_array_equal(to_host(idx)[i, :n], want, err_msg=f"row {i} budget {budget}")
 
 
-@pytest.mark.parametrize("scorer,units,T,one_launch", [(B.SCORER_MEAN_WINDOW, 128, 2816, True), (B.SCORER_MEAN_WINDOW, 128, 2817, False),
-                                                       (B.SCORER_LAST_QUERY, 178, 4096, True), (B.SCORER_LAST_QUERY, 176, 3500, False),
-                                                       (B.SCORER_KEYDIFF, 128, 900, False), (B.SCORER_REDUNDANCY, 130, 300, False)])
-def test_short_caches_choose_their_scorer(oracle, scorer, units, T, one_launch):
-    """Where the one-launch scorer ends: a round with three CUs in ten idle beyond 2816 positions, scores that need the keys."""
-    w = inputs.CONFIGS[1].scaled(L=units // 2, H=2, G=2, W=4, D=64, T=T, T_min=T, budget=60, S=4, n_spans=2, span_len=(8, 90))
+@pytest.mark.parametrize("scorer,units,T,G,one_launch", [
+    (B.SCORER_MEAN_WINDOW, 128, 2816, 2, True), (B.SCORER_MEAN_WINDOW, 128, 2817, 2, False), (B.SCORER_LAST_QUERY, 178, 4096, 2, True),
+    (B.SCORER_LAST_QUERY, 160, 3500, 2, False), (B.SCORER_LAST_QUERY, 162, 3500, 2, True),
+    (B.SCORER_MEAN_WINDOW, 136, 3073, 32, False),      # 680 workgroups, three to a CU
+    (B.SCORER_MEAN_WINDOW, 136, 3328, 32, True),       # 544 workgroups: a second round
+    (B.SCORER_MEAN_WINDOW, 160, 3072, 32, False), (B.SCORER_MEAN_WINDOW, 160, 3073, 32, True),     # 480 and 640
+    (B.SCORER_KEYDIFF, 128, 900, 2, False), (B.SCORER_REDUNDANCY, 130, 300, 2, False)])
+def test_short_caches_choose_their_scorer(oracle, scorer, units, T, G, one_launch):
+    """Where the one-launch scorer ends: beyond 2816 positions, with up to 160 units, where the sweeps run in one round; scores
+    that need the keys."""
+    w = inputs.CONFIGS[1].scaled(L=units // 2, H=2, G=G, W=4, D=64, T=T, T_min=T, budget=60, S=4, n_spans=2, span_len=(8, 90))
     host = inputs.dense_cache(w, n_threads=8)
     job = Job(w, host, scorer=scorer)
     assert ("score_unit" in _labels(job)) == one_launch
