@@ -78,6 +78,8 @@ __device__ __forceinline__ void softmax_part(const float* e, int n, double2* out
 
 // What a sweep does with the keys besides the products with the queries.
 enum { KEYS_NONE = 0, KEYS_MEAN = 1, KEYS_COS = 2 };
+// Moment sums of the first sweep: none, of the logits relative to the first query's, of the centred logits.
+enum { MOMENTS_NONE = 0, MOMENTS_FIRST = 1, MOMENTS_CENTRED = 2 };
 
 // Squared lengths of a block's keys: K . K^T on the matrix cores, of which the diagonal is wanted.  Token r sits in lane
 // r of the half wave (r >> 2) & 1, in register 4 * (r >> 3) + (r & 3).
@@ -247,17 +249,20 @@ __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool r
 // that add up to its fp32 value, the same in all columns of a tile; the products with the queries then start from minus
 // that tile, so that the accumulators are s - mean and the variance is one multiply-add per logit (24 more matrix
 // instructions per block of 32 keys, one vector instruction per logit for the variance and one for s itself instead of four,
-// one reduction over the lanes instead of three).  256 units of 32768 positions, 128 queries: 1195 -> 1157 us per step, 454 ->
-// 428 with 64 channels and 16384 positions.  With seven or eight column blocks of 128 channels it spills (1835 -> 1933, 659 ->
-// 958): there, in the causal tail and for fp32 caches, where the extra products are not hidden, and for a wave whose
-// statistics come out as no numbers, the sums are those of (s - r) and (s - r)^2 with r the token's logit against the unit's
-// first query (a reference close to the mean keeps the subtraction of the squares harmless).
-template <bool BF16, int NB, bool TAIL, bool MOMENTS, int HD, int KEYS = KEYS_NONE>
+// one reduction over the lanes instead of three).  It gains with 64 channels (1 to 14 %; 454 -> 428 us per step for 256 units of
+// 16384 positions) and with three or four column blocks of 128 in launches of 512 workgroups and more (1134 -> 1109 us for 256
+// units of 32768, 335 -> 317 for 512 of 4096; 439 -> 450 for 304 of 9000, the worst of nine).  Its own start, two barriers,
+// costs 1 us in smaller ones; with one or two column blocks of 128 channels the products are not hidden (319 -> 327 for 144
+// units of 16589, 64 queries), and with seven or eight it spills (1835 -> 1933, 659 -> 958).  There, in the causal tail and for
+// fp32 caches, and for a wave whose statistics come out as no numbers, the sums are those of (s - r) and (s - r)^2 with r the
+// token's logit against the unit's first query (a reference close to the mean keeps the subtraction of the squares harmless).
+template <bool BF16, int NB, bool TAIL, int MOMENTS, int HD, int KEYS = KEYS_NONE>
 __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
   constexpr bool kSpare = KEYS == KEYS_COS && HD == 128 && NB >= 7;  // see KEYS above
   constexpr int THREADS = kSweepThreads<BF16, NB, HD>, WAVES = THREADS / 64, STEP = THREADS / 2;  // STEP: tokens between two blocks of a wave
-  constexpr bool kCentred = MOMENTS && BF16 && !TAIL && (NB <= 4 || HD == 64);  // see MOMENTS above
+  constexpr bool kCentred = MOMENTS == MOMENTS_CENTRED;
+  static_assert(!kCentred || (BF16 && !TAIL), "the causal tail and fp32 caches take the sums relative to the first query");
   constexpr int NG = BF16 || MOMENTS ? kGroup<NB> : NB, QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch_own[kCentred ? 1 : WAVES][NB * 32];
@@ -935,15 +940,21 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
 
 template <bool BF16, int NB, bool TAIL, int HD>
 hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hipStream_t s) {
-  hipError_t e;
-  if (moments) {
-    if ((e = ensure_lds<score_stats_kernel<BF16, NB, TAIL, true, HD>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, true, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
+  auto launch = [&](auto moments_c) {
+    constexpr int M = decltype(moments_c)::value;
+    const hipError_t e = ensure_lds<score_stats_kernel<BF16, NB, TAIL, M, HD>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, M, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
+    return hipGetLastError();
+  };
+  if (!moments) return launch(std::integral_constant<int, MOMENTS_NONE>{});
+  if constexpr (BF16 && !TAIL && HD == 64) {
+    return launch(std::integral_constant<int, MOMENTS_CENTRED>{});
   } else {
-    if ((e = ensure_lds<score_stats_kernel<BF16, NB, TAIL, false, HD>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, false, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
+    if constexpr (BF16 && !TAIL && NB == 4)
+      if ((int64_t)grid.x * grid.y >= 512) return launch(std::integral_constant<int, MOMENTS_CENTRED>{});
+    return launch(std::integral_constant<int, MOMENTS_FIRST>{});
   }
-  return hipGetLastError();
 }
 
 template <bool BF16, int NB, bool TAIL, int HD>
@@ -973,10 +984,10 @@ hipError_t run_key_sweeps(const ScoreArgs& a, hipStream_t s) {
   const int lds = NB * 32 * Tr<true, HD>::kQStride, lds_k = lds + 4 * Tr<true, HD>::kQStride;
   const dim3 grid(a.n_chunks, a.d.units), blk(kThreads);
   hipError_t e;
-  if ((e = ensure_lds<score_stats_kernel<true, NB, false, false, HD, KEYS>>(lds)) != hipSuccess) return e;
+  if ((e = ensure_lds<score_stats_kernel<true, NB, false, MOMENTS_NONE, HD, KEYS>>(lds)) != hipSuccess) return e;
   if ((e = ensure_lds<usage>(lds_k)) != hipSuccess) return e;
   prof_mark("score_stats", s);
-  hipLaunchKernelGGL((score_stats_kernel<true, NB, false, false, HD, KEYS>), grid, blk, lds, s, a);
+  hipLaunchKernelGGL((score_stats_kernel<true, NB, false, MOMENTS_NONE, HD, KEYS>), grid, blk, lds, s, a);
   if (!FOLD) {
     prof_mark("score_reduce", s);
     hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);

@@ -139,15 +139,15 @@ def test_fp32_keys_at_the_ends_of_the_range(oracle, heads, T, D, G, W):
 
 
 @pytest.mark.parametrize("scorer", [B.SCORER_EXPECTED, B.SCORER_EXPECTED_VNORM])
-@pytest.mark.parametrize("D,G,W", [(128, 1, 1), (128, 1, 8), (128, 2, 20), (128, 4, 32), (128, 7, 32), (64, 1, 3), (64, 2, 16),
-                                   (64, 7, 16), (64, 7, 32), (64, 8, 32)])
-def test_infinite_keys_next_to_the_expected_score(oracle, D, G, W, scorer):
+@pytest.mark.parametrize("D,G,W,L", [(128, 1, 8, 1), (128, 4, 32, 1), (128, 4, 32, 130), (128, 3, 25, 130), (128, 7, 32, 1),
+                                     (64, 1, 1, 1), (64, 1, 3, 1), (64, 2, 16, 1), (64, 7, 16, 1), (64, 7, 32, 1), (64, 8, 32, 1)])
+def test_infinite_keys_next_to_the_expected_score(oracle, D, G, W, L, scorer):
     """A key with an infinite entry against queries of one sign has logits of minus infinity: no share in the usage, and the
     keys next to it keep theirs, whatever becomes of its own moment score (no number).  The largest finite number, whose
     logits are partly minus infinity, likewise.  In a full block, in two blocks of one wave, and in the ragged last one.
     (Padded query columns multiply the infinity by zero: where there are any, the key's own usage may be no number.)"""
-    T = 1201
-    w = inputs.CONFIGS[1].scaled(L=1, B=2, H=1, D=D, G=G, W=W, T=T, T_min=T, budget=50, S=4, n_spans=2, span_len=(8, 40))
+    T = 1201                                                # (128 channels: the centred form from 512 workgroups on)
+    w = inputs.CONFIGS[1].scaled(L=L, B=2, H=1, D=D, G=G, W=W, T=T, T_min=T, budget=50, S=4, n_spans=2, span_len=(8, 40))
     host = inputs.dense_cache(w, n_threads=8)
     q, k = inputs.as_f32(host["Q"]).copy(), inputs.as_f32(host["K"]).copy()
     q[..., 5] = -np.abs(q[..., 5]) - np.float32(0.01)       # all negative in this channel
@@ -178,10 +178,10 @@ def test_infinite_keys_next_to_the_expected_score(oracle, D, G, W, scorer):
 @pytest.mark.parametrize("scorer", [B.SCORER_MEAN_WINDOW, B.SCORER_EXPECTED])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("e", [-118, -110, -60, 60, 110, 118])
-@pytest.mark.parametrize("heads,T", [(2, 700), (130, 300)])     # the sweeps, the one-launch scorer
-def test_scale_of_the_keys_moved_into_the_queries(oracle, heads, T, e, dtype, scorer):
+@pytest.mark.parametrize("heads,T,D", [(2, 700, 128), (2, 700, 64), (130, 300, 128)])     # the sweeps, the one-launch scorer
+def test_scale_of_the_keys_moved_into_the_queries(oracle, heads, T, D, e, dtype, scorer):
     """Keys times a power of two and queries divided by it: the same logits, the same results."""
-    D, G, W = 128, 2, 20
+    G, W = 2, 20
     w = inputs.CONFIGS[0].scaled(L=1, H=heads, D=D, G=G, W=W, T=T, dtype=dtype, budget=50, S=4, n_spans=2, span_len=(8, 40))
     host = inputs.dense_cache(w, n_threads=8)
     plain = {n: inputs.as_f32(host[n]).copy() for n in ("Q", "K")}

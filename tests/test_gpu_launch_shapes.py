@@ -322,21 +322,24 @@ def test_chunks_that_fill_one_round(oracle, units, T, dtype, G, W, D, scorer, ca
 
 
 @pytest.mark.parametrize("common", [0.0, 30.0])
-@pytest.mark.parametrize("D,G,W", [(128, 1, 1), (128, 1, 8), (128, 2, 16), (128, 3, 11), (128, 8, 8), (128, 5, 13), (128, 7, 16),
-                                   (128, 4, 32), (64, 1, 3), (64, 4, 32), (64, 3, 43), (64, 7, 32), (64, 9, 25), (64, 8, 32)])
-def test_centred_moments_at_every_number_of_columns(oracle, D, G, W, common):
+@pytest.mark.parametrize("D,G,W,L", [(128, 1, 1, 1), (128, 1, 8, 1), (128, 2, 16, 1), (128, 3, 11, 1), (128, 8, 8, 1), (128, 5, 13, 1),
+                                     (128, 7, 16, 1), (128, 4, 32, 1), (128, 5, 13, 128), (128, 7, 16, 128), (128, 4, 32, 128),
+                                     (128, 4, 32, 127), (64, 1, 3, 1), (64, 4, 32, 1), (64, 3, 43, 1), (64, 7, 32, 1), (64, 9, 25, 1),
+                                     (64, 8, 32, 1)])
+def test_centred_moments_at_every_number_of_columns(oracle, D, G, W, L, common):
     """Padded columns of every tile shape take no part in the variance; queries with a common part far above their
-    differences (the variance must not be a difference of two large numbers)."""
-    w = inputs.CONFIGS[1].scaled(L=1, B=2, H=2, D=D, G=G, W=W, T=700, T_min=700, budget=64, S=4, n_spans=2, span_len=(8, 60))
+    differences (the variance must not be a difference of two large numbers).  With 128 channels and 65 to 128 queries the
+    centred form starts at 512 workgroups (128 layers here)."""
+    w = inputs.CONFIGS[1].scaled(L=L, B=2, H=2, D=D, G=G, W=W, T=700, T_min=700, budget=64, S=4, n_spans=2, span_len=(8, 60))
     host = inputs.dense_cache(w, n_threads=4)
     host["seq_lens"][:] = [700, 681]
     rng = np.random.default_rng(D + G * W)
-    q = inputs.as_f32(host["Q"]) + common * rng.standard_normal((1, 2, 2, 1, 1, D)).repeat(G, 3).reshape(1, 2, 2 * G, 1, D)
+    q = inputs.as_f32(host["Q"]) + common * rng.standard_normal((L, 2, 2, 1, 1, D)).repeat(G, 3).reshape(L, 2, 2 * G, 1, D)
     k = inputs.as_f32(host["K"]) * (0.05 if common else 1.0)      # logits stay in the supported range
     host["Q"], host["K"] = inputs._store(q.astype(np.float32), "bf16"), inputs._store(k.astype(np.float32), "bf16")
     job = Job(w, host, scorer=B.SCORER_EXPECTED)
     job.step()
-    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), list(range(w.units)), scorer=B.SCORER_EXPECTED)
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, 1, 2, w.units - 1], scorer=B.SCORER_EXPECTED)
 
 
 @pytest.mark.parametrize("causal", [False, True])
