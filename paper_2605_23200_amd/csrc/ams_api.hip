@@ -410,7 +410,7 @@ int ams_compress_step(const ams_params* p, const ams_kv_view* src, const int32_t
   float* seg_mass = (float*)(w + wl.seg_mass);
   int32_t* quota = (int32_t*)(w + wl.quota);
   hipError_t e;
-  VcInfo vc{false, 0, 0};
+  VcInfo vc{false, 0, 0, false};
   const KvDev vdev = make_kv(p, src, src->v);
   if ((e = launch_score(p, d, make_kv(p, src, src->k), &vdev, seq_lens, q, u, g, credit, &vc, w, wl, s)) != hipSuccess)
     return status_of(e);

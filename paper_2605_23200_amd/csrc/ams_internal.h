@@ -59,6 +59,12 @@ constexpr int kScoreChunk = AMS_SCORE_CHUNK;  // most tokens per workgroup of th
 constexpr int kKeysChunk = kScoreChunk < 2048 ? kScoreChunk : 2048;  // most, for the key-based scorers
 constexpr int kMinScoreChunk = 128;           // fewest: one 32-key block per wave
 
+// Tokens per chunk where n chunks share a cache of T positions.
+__device__ __forceinline__ int even_chunk(int T, int n) {
+  const int piece = n * kMinScoreChunk;
+  return max(1, (T + piece - 1) / piece) * kMinScoreChunk;
+}
+
 // Segments the thresholds k*delta (every k >= 1 with k*delta < 1) cut the unit interval into.
 inline int initial_segments(float delta) {
   int k = 1;
@@ -85,6 +91,7 @@ struct VcInfo {
   bool have;
   int stride;  // entries per unit row of ws + wl.vc_part
   int tokens;  // positions covered by one entry
+  bool even;   // ... of a cache of t_max positions; of a shorter one even_chunk(length, stride)
 };
 
 // Optional per-kernel timing: when collection is on, every launcher calls prof_mark(label, stream)

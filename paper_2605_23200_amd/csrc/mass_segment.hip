@@ -85,6 +85,7 @@ struct MsArgs {
   int pool_r;        // radius of the average pooling of u before Eq. (1) (0 = off)
   double2* vc_part;  // [units][vc_stride] (sum of max(u,0)+eps, sum of old credit) per vc_tokens positions
   int vc_stride, vc_tokens;
+  bool vc_even;      // see VcInfo
   double* sub;       // [units][n_sub] sum of m_used per kSub positions; stage call: pairs (sum, largest prefix inside)
   int n_sub;
   int32_t* bounds;   // [units][S+1]
@@ -203,7 +204,8 @@ struct MassOf {
   bool ema;
   __device__ __forceinline__ MassOf(const MsArgs& a, int unit, int T, float lambda, float beta, float eps_f)
       : lam((double)lambda), bet((double)beta), eps((double)eps_f), ema(lambda != 0.f) {
-    const int nvc = (T + a.vc_tokens - 1) / a.vc_tokens;
+    const int tokens = a.vc_even && T != a.d.t_max ? even_chunk(T, a.vc_stride) : a.vc_tokens;
+    const int nvc = (T + tokens - 1) / tokens;
     const double2* vc = a.vc_part + (int64_t)unit * a.vc_stride;
     double Z = 0.0, c_old = 0.0;
     for (int i = threadIdx.x & 63; i < nvc; i += 64) {
@@ -694,6 +696,7 @@ MsArgs make_args(const ams_params* p, const Dims& d, const int32_t* seq_lens, ch
   a.l_max = p->l_max;
   a.pool_r = p->pool_kernel > 1 ? p->pool_kernel / 2 : 0;
   a.vc_part = (double2*)(ws + wl.vc_part);
+  a.vc_even = false;
   a.vc_stride = a.vc_tokens = 0;  // set by the launchers once it is known who leaves the sums
   a.sub = (double*)(ws + wl.sub);
   a.n_sub = div_up(p->t_max, kSub);
@@ -806,6 +809,7 @@ hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* s
   if (vc.have && a.pool_r == 0) {  // left by the scorer (sums of the unsmoothed usage)
     a.vc_stride = vc.stride;
     a.vc_tokens = vc.tokens;
+    a.vc_even = vc.even;
   } else {
     usage = own_sums(a, p, u, credit, m_used, s);
   }

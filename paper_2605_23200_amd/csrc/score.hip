@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kThreads) void keysum_kernel(ScoreArgs a, double* k
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const int c0 = chunk * a.chunk;
+  const int len = chunk_len(a, T), c0 = chunk * len;
   if (c0 >= T) return;
   const int col = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
   double s[EPC];
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kThreads) void keysum_kernel(ScoreArgs a, double* k
   for (int e = 0; e < EPC; ++e) s[e] = 0.0;
   // four rows per lane in flight (a row past the end re-reads the last one and is not added)
   constexpr int kRows = 4;
-  const int t_end = min(T, c0 + a.chunk);
+  const int t_end = min(T, c0 + len);
   for (int tb = c0 + r0; tb < t_end; tb += kRows * RPI) {
     uint4 v[kRows];
 #pragma unroll
@@ -107,9 +107,9 @@ __global__ __launch_bounds__(kThreads) void keydiff_kernel(ScoreArgs a, const do
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const int c0 = chunk * a.chunk;
+  const int len = chunk_len(a, T), c0 = chunk * len;
   if (c0 >= T) return;
-  const int nch = (T + a.chunk - 1) / a.chunk;
+  const int nch = (T + len - 1) / len;
   if ((int)threadIdx.x < a.d.D) {
     double t = 0.0;
     for (int c = 0; c < nch; ++c) t += ksum[((int64_t)unit * a.n_chunks + c) * a.d.D + threadIdx.x];
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void keydiff_kernel(ScoreArgs a, const do
   for (int e = 0; e < EPC; ++e) kb[e] = (float)kbar[col * EPC + e];
   // four rows per lane in flight: the loads are unconditional (a row past the end re-reads the last one)
   constexpr int kRows = 4;
-  const int t_end = min(T, c0 + a.chunk);
+  const int t_end = min(T, c0 + len);
   for (int tb = c0; tb < t_end; tb += kRows * RPI) {
     uint4 v[kRows];
 #pragma unroll
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kThreads) void keydiff_kernel(ScoreArgs a, const do
   }
   __syncthreads();
   // one token per thread for the ratio, so that every lane works
-  for (int t = c0 + threadIdx.x; t < min(T, c0 + a.chunk); t += kThreads) {
+  for (int t = c0 + threadIdx.x; t < min(T, c0 + len); t += kThreads) {
     const float2 r = row_sums[t - c0];
     if (MEAN_COS) {
       g_row[t] = (r.y > 0.f && T > 1) ? (float)(((double)r.x / sqrt((double)r.y) - 1.0) / (double)(T - 1)) : 0.f;
@@ -179,15 +179,15 @@ __global__ __launch_bounds__(kThreads) void esoftmax_part_kernel(ScoreArgs a, do
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const int c0 = chunk * a.chunk;
+  const int len = chunk_len(a, T), c0 = chunk * len;
   if (c0 >= T) return;
-  softmax_part(a.g + (int64_t)unit * a.d.t_stride + c0, min(a.chunk, T - c0), part + (int64_t)unit * a.n_chunks + chunk);
+  softmax_part(a.g + (int64_t)unit * a.d.t_stride + c0, min(len, T - c0), part + (int64_t)unit * a.n_chunks + chunk);
 }
 
 // Chunk statistics (maximum, sum of exp) of a unit's scores merged: every wave for itself, strided over the lanes, then a fixed
 // tree.  (One thread in turn took 15 us for 73 chunks.)
 __device__ __forceinline__ void merge_chunks(const ScoreArgs& a, const double2* part, int unit, int T, double& M, double& Z) {
-  const int nch = (T + a.chunk - 1) / a.chunk, lane = threadIdx.x & 63;
+  const int len = chunk_len(a, T), nch = (T + len - 1) / len, lane = threadIdx.x & 63;
   const double2* p = part + (int64_t)unit * a.n_chunks;
   M = -INFINITY;
   Z = 0.0;
@@ -361,6 +361,11 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   const bool paged = k.layout != AMS_LAYOUT_DENSE;
   a.n_chunks = paged ? wl.n_chunks_paged : wl.n_chunks;
   a.chunk = paged ? wl.score_chunk_paged : wl.score_chunk;
+  // Chunks that fill one round of workgroups were cut from t_max, which may be a capacity: a shorter cache is shared by as many
+  // workgroups.  us per step with chunks of a power of two, with the chunks as cut for t_max and with shares: 109, 158 and 90
+  // (90 units of 5000 positions, t_max 20000), 102, 111 and 88 (32 of 13600 of 27209), 99, 109 and 87 (20 of 15000 of 30000, 224
+  // queries); 48 pairs of shape and length take 0.46 to 1.0 of the power of two, 0.51 to 1.45 without the shares.
+  a.even = !paged && wl.one_round;
   a.n_pad = wl.n_pad;
   // Batches whose sequences may differ in length: the workgroups count the chunks that exist (sweep_tile), where the launch has
   // more of them than run at once.  Below that the count's 0.5 us per workgroup is all it does (93.5 and 95.2 us per step for
@@ -439,6 +444,7 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     vc->have = true;
     vc->stride = vc_stride;
     vc->tokens = vc_tokens;
+    vc->even = a.even && vc_stride == a.n_chunks && vc_tokens == a.chunk;
   }
   if (vnorm) {
     if (!a.soft) {

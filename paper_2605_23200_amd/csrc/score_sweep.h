@@ -276,9 +276,10 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   unit_coords(a.d, unit, l, b, h);
   const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all);
   const int T = TAIL ? T_all : t_end;
-  const int c0 = TAIL ? t_end : chunk * a.chunk;
+  const int len = chunk_len(a, T_all);
+  const int c0 = TAIL ? t_end : chunk * len;
   if (c0 >= T) return;
-  const int t_lim = TAIL ? T : min(T, c0 + a.chunk);  // the tail (at most W + 31 keys) may be longer than a chunk
+  const int t_lim = TAIL ? T : min(T, c0 + len);  // the tail (at most W + 31 keys) may be longer than a chunk
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5;
   const int t_vis0 = T_all - a.d.W;  // newest key visible to the oldest query of the window
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
@@ -569,7 +570,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) Z += xch[w][n].y * __builtin_amdgcn_exp2f(xch[w][n].x - M);
     // the tail's entry follows those of the chunks
-    const int slot = TAIL ? (t_end + a.chunk - 1) / a.chunk : chunk;
+    const int slot = TAIL ? (t_end + len - 1) / len : chunk;
     a.part[((int64_t)unit * (a.n_chunks + 1) + slot) * a.n_pad + n] = make_float2(M, Z);
   }
 }
@@ -596,7 +597,7 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const int nch = (causal_t_end(a, T) + a.chunk - 1) / a.chunk + (a.causal ? 1 : 0);
+  const int len = chunk_len(a, T), nch = (causal_t_end(a, T) + len - 1) / len + (a.causal ? 1 : 0);
   const int parts = kReduceThreads / a.n_pad;
   const int n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
   if (part < parts) {
@@ -672,7 +673,7 @@ __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0,
 #pragma unroll 4
     for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) cs += (double)c_row[t];
   }
-  const int nch = (T + a.chunk - 1) / a.chunk;
+  const int len = chunk_len(a, T), nch = (T + len - 1) / len;
   const int parts = THREADS / a.n_pad, n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
   if (part < parts) {
     const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
@@ -728,9 +729,10 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
   unit_coords(a.d, unit, l, b, h);
   const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all);
   const int T = TAIL ? T_all : t_end;
-  const int c0 = TAIL ? t_end : chunk * a.chunk;
+  const int len = chunk_len(a, T_all);
+  const int c0 = TAIL ? t_end : chunk * len;
   if (c0 >= T) return;
-  const int t_lim = TAIL ? T : min(T, c0 + a.chunk);  // the tail (at most W + 31 keys) may be longer than a chunk
+  const int t_lim = TAIL ? T : min(T, c0 + len);  // the tail (at most W + 31 keys) may be longer than a chunk
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5, c = lane & 31;
   const int t_vis0 = T_all - a.d.W;  // newest key visible to the oldest query of the window
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
@@ -752,7 +754,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
       if (threadIdx.x < HD) {
         const double* ks = a.ksum + (int64_t)unit * a.n_chunks * HD + threadIdx.x;
         if (FOLD) {
-          const int nch = (T + a.chunk - 1) / a.chunk;
+          const int nch = (T + len - 1) / len;
 #pragma unroll 8
           for (int i = 0; i < nch; ++i) k += ks[(int64_t)i * HD];
         } else {

@@ -41,6 +41,7 @@ struct ScoreArgs {
   double* ksum;         // [units][n_chunks][D]: sums of the keys (or of the unit vectors); NULL: nobody wants them here
   double2* soft;        // [units][n_chunks]: (max, sum of exp) of the scores in g, left by the sweep that forms them; may be NULL
   float eps;
+  bool even;    // the n_chunks chunks of a unit share the cache evenly, whatever its length up to t_max
   bool compact; // ragged batch: the workgroups of the sweeps count only the chunks that exist
   bool fold;    // the second sweep merges the first one's statistics itself (no reduction kernel between them)
   bool causal;  // causal window (App. A): query w of the window sees keys 0 .. T-W+w
@@ -60,6 +61,11 @@ inline hipError_t ensure_lds(int bytes) {
   e = hipFuncSetAttribute((const void*)Kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e == hipSuccess) granted[dev] = bytes;
   return e;
+}
+
+// Tokens per chunk of a cache of T positions (at t_max a.chunk either way, without the division's 0.2 us in front of the keys).
+__device__ __forceinline__ int chunk_len(const ScoreArgs& a, int T) {
+  return a.even && T != a.d.t_max ? even_chunk(T, a.n_chunks) : a.chunk;
 }
 
 // Row geometry of a cache of HD channels: bytes per row, stride of a query row in LDS (bf16, or the three bf16 terms of an

@@ -417,3 +417,39 @@ def test_short_caches_choose_their_scorer(oracle, scorer, units, T, G, one_launc
     assert ("score_unit" in _labels(job)) == one_launch
     check_properties_all_units(job)
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, units // 2, units - 1], scorer=scorer)
+
+
+def _chunks_of_first_unit(job):
+    """Runs a step over a workspace of ones and counts the chunks of which the first sweep has left statistics: the rows at the
+    head of the workspace, up to the first that nothing has written."""
+    job.ws.fill_(255)
+    job.step()
+    n_pad = next(32 * n for n in (1, 2, 4, 7, 8) if 32 * n >= job.w.G * job.w.W)
+    rows = job.ws[:min(job.ws.numel(), 600 * n_pad * 8) // (n_pad * 8) * n_pad * 8].view(torch.int32).reshape(-1, n_pad * 2)
+    blank = to_host((rows == -1).all(1))
+    return int(np.argmax(blank))
+
+
+@pytest.mark.parametrize("scorer,causal", [(B.SCORER_MEAN_WINDOW, False), (B.SCORER_KEYDIFF, False), (B.SCORER_REDUNDANCY, False),
+                                           (B.SCORER_EXPECTED_VNORM, False), (B.SCORER_LAST_QUERY, True), (B.SCORER_KEYDIFF, True)])
+@pytest.mark.parametrize("units,t_max,dtype,G,W,D", [(5, 30000, "bf16", 7, 32, 128), (64, 7001, "bf16", 2, 8, 128),
+                                                     (20, 15999, "f32", 1, 8, 128)])
+@pytest.mark.parametrize("T", [6000, 3201, 129, 1, 0])
+def test_a_short_cache_is_shared_by_all_workgroups(oracle, units, t_max, dtype, G, W, D, scorer, causal, T):
+    """t_max is a capacity: chunks that would fill one round of workgroups at t_max get shorter with the cache, in steps of 128
+    positions, so that as many workgroups share it."""
+    w = inputs.CONFIGS[1].scaled(L=units // 4 if units % 4 == 0 else 1, H=4 if units % 4 == 0 else units, D=D, G=G, W=W, T=t_max,
+                                 T_min=t_max, dtype=dtype, budget=200, S=8, n_spans=9, span_len=(8, 200), causal=causal)
+    host = inputs.dense_cache(w, n_threads=4)
+    job = Job(w, host, scorer=scorer)
+    at_t_max = _chunks_of_first_unit(job) if not causal else 0
+    host["seq_lens"][:] = T
+    job.lens.fill_(T)
+    if not causal and T > 0:
+        assert _chunks_of_first_unit(job) == -(-T // (-(-T // (at_t_max * 128)) * 128))      # multiples of 128
+    job.ws.fill_(255)
+    job.credit.zero_()
+    job.step()
+    assert to_host(job.n_kept).tolist() == [min(w.budget, T)] * units
+    if T > 0:
+        check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [units // 2] if T > 2000 else [0, units - 1], scorer=scorer)
