@@ -57,7 +57,7 @@ __device__ __forceinline__ int seq_len(const Dims& d, const int32_t* seq_lens, i
 #endif
 constexpr int kScoreChunk = AMS_SCORE_CHUNK;  // most tokens per workgroup of the scoring kernels
 constexpr int kKeysChunk = kScoreChunk < 2048 ? kScoreChunk : 2048;  // most, for the key-based scorers
-constexpr int kMinScoreChunk = 128;           // fewest: one 32-key block per wave
+constexpr int kMinScoreChunk = 128;           // fewest: one 32-key block per wave of a workgroup of four
 
 // Tokens per chunk where n chunks share a cache of T positions.
 __device__ __forceinline__ int even_chunk(int T, int n) {

@@ -289,7 +289,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     stage_blocks<THREADS>(a, b, c0, t_lim, blk_sm);
     blk = blk_sm;
   }
-  if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
+  if (c0 + wave * 32 < t_lim) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
   const float q_top = load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
   __shared__ uint4 ident[KEYS ? 2 : 1][64];
   __shared__ __align__(16) double inv_len[KEYS == KEYS_COS ? 4 : 1][32];
@@ -742,7 +742,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
     stage_blocks<THREADS>(a, b, c0, t_lim, blk_sm);
     blk = blk_sm;
   }
-  if (c0 + wave * 32 < T) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
+  if (c0 + wave * 32 < t_lim) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
   const float q_top = load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
   // KEYS: the mean key (or the sum of the unit vectors) as three bf16 terms that add up to its fp32 value, and a row of
   // zeros, behind the query window

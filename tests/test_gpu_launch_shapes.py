@@ -29,7 +29,8 @@ def _run(oracle, w, lens=None, scorer=B.SCORER_MEAN_WINDOW, units=None, **kw):
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype,G,W,T,paged", [("bf16", 4, 32, 127, False), ("bf16", 4, 32, 129, False),
                                                 ("f32", 1, 8, 257, False), ("f32", 2, 20, 4097, False),
-                                                ("bf16", 7, 32, 385, True), ("bf16", 2, 16, 8193, False)])
+                                                ("bf16", 7, 32, 385, True), ("bf16", 2, 16, 8193, False),
+                                                ("f32", 4, 32, 1000, True), ("f32", 3, 32, 385, False)])   # eight waves, 128 keys
 def test_few_units_are_cut_into_short_chunks(oracle, dtype, G, W, T, paged, causal):
     """Few units: chunks of 128 keys (one block per wave), up to one workgroup per CU; a ragged second sequence ends
     inside, on and before a chunk's edge."""
