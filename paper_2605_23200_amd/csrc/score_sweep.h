@@ -793,7 +793,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
   // (last query with 8 column blocks: LDS is needed for the query window)
   constexpr bool kBufG = KEYS != KEYS_NONE || (MODE == MODE_LAST && NB <= 7);
   constexpr int kBuf = KEYS != KEYS_NONE || !BF16 ? kKeysChunk : kScoreChunk;
-  __shared__ float u_sm[kBuf];
+  __shared__ __align__(16) float u_sm[kBuf];  // (fold_stats uses its head as doubles and float4)
   __shared__ float g_sm[kBufG ? kBuf : 1];
   __shared__ double c_sm[FOLD ? WAVES : 1];
   float4 f[NB];
