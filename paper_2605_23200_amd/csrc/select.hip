@@ -89,6 +89,7 @@ struct Emit {
 
 // What a selection workgroup does with its picks: index list, bits of the unit's map, or index list and gather.
 enum { SELECT_LIST = 0, SELECT_FLAGS = 1, SELECT_GATHER = 2 };
+constexpr int kGatherLongest = 2560;  // expected length of a segment up to which its workgroup gathers as well
 constexpr int kGatherList = 512;  // picks kept in LDS for the gather; later ones are read back from the index list
 
 struct GatherArgs {
@@ -799,7 +800,7 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
 // the kept set is only known after finalize_kernel.
 bool select_gathers(const ams_params* p) {
   const int S = p->n_segments, keep = p->budget < p->t_max ? p->budget : p->t_max;
-  return p->n_sink == 0 && p->n_last == 0 && p->seg_delta == 0.f && (int64_t)p->t_max <= (int64_t)2560 * S &&
+  return p->n_sink == 0 && p->n_last == 0 && p->seg_delta == 0.f && (int64_t)p->t_max <= (int64_t)kGatherLongest * S &&
          (int64_t)keep * 2 < p->t_max && keep >= 8 * S;
 }
 
@@ -853,8 +854,13 @@ hipError_t launch_select(const ams_params* p, const Dims& d, const int32_t* seq_
     prof_mark("finalize", s);
     hipLaunchKernelGGL(finalize_kernel, dim3(d.units), dim3(kFinBlock), 0, s, d, seq_lens, p->budget, p->n_sink,
                        p->n_last, g, flags, n_words, idx);
-  } else if (gather) {
-    AMS_SELECT_SHAPE(SELECT_GATHER);
+  } else if (gather) {  // (select_gathers: no longer segments)
+    if (expect <= 256.0)
+      AMS_SELECT(SELECT_GATHER, 64, 16);
+    else if (expect <= (double)kGatherLongest)
+      AMS_SELECT(SELECT_GATHER, 256, 16);
+    else
+      return hipErrorInvalidValue;
   } else {
     AMS_SELECT_SHAPE(SELECT_LIST);
   }
