@@ -8,7 +8,7 @@ import torch
 from paper_2605_23200_amd import binding as B
 from paper_2605_23200_amd import inputs
 from paper_2605_23200_amd.harness import Job
-from gpu_util import DEV, to_dev, to_host, workspace
+from gpu_util import DEV, assert_close_terms, to_dev, to_host, workspace
 from test_gpu_step import check_properties_all_units, check_units
 
 pytestmark = pytest.mark.gpu
@@ -305,21 +305,50 @@ def test_selection_gathers_its_rows(oracle, T, S, budget, gathers, dtype, D, pag
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), list(range(w.units)))
 
 
+def _chunks_of_first_unit(job):
+    """Runs a step over a workspace of ones and counts the chunks of which the first sweep has left statistics: the rows at the
+    head of the workspace, up to the first that nothing has written."""
+    job.ws.fill_(255)
+    job.step()
+    n_pad = next(32 * n for n in (1, 2, 4, 7, 8) if 32 * n >= job.w.G * job.w.W)
+    rows = job.ws[:min(job.ws.numel(), 600 * n_pad * 8) // (n_pad * 8) * n_pad * 8].view(torch.int32).reshape(-1, n_pad * 2)
+    blank = to_host((rows == -1).all(1))
+    return int(np.argmax(blank))
+
+
 @pytest.mark.parametrize("scorer,causal", [(B.SCORER_MEAN_WINDOW, False), (B.SCORER_LAST_QUERY, True), (B.SCORER_KEYDIFF, False),
                                            (B.SCORER_REDUNDANCY, False), (B.SCORER_EXPECTED_VNORM, True),
                                            (B.SCORER_EXPECTED_VNORM, False)])
-@pytest.mark.parametrize("units,T,dtype,G,W,D", [(5, 30000, "bf16", 7, 32, 128),    # one workgroup per CU, chunks of 640
-                                                 (64, 6000, "bf16", 4, 32, 128),    # two, 768
-                                                 (64, 7001, "bf16", 2, 8, 128),     # three, 640
-                                                 (20, 16001, "f32", 1, 8, 128),     # two, 640
-                                                 (12, 22001, "bf16", 4, 32, 64)])   # three, 384 is too short: two, 640
-def test_chunks_that_fill_one_round(oracle, units, T, dtype, G, W, D, scorer, causal):
+@pytest.mark.parametrize("units,T,dtype,G,W,D,chunk", [(5, 30000, "bf16", 7, 32, 128, 640),    # one workgroup per CU
+                                                       (64, 6000, "bf16", 4, 32, 128, 768),    # two
+                                                       (64, 7001, "bf16", 2, 8, 128, 640),     # three
+                                                       (20, 15999, "f32", 1, 8, 128, 640),     # two
+                                                       (12, 26001, "bf16", 4, 32, 64, 640)])   # three: 512 is too short; two
+def test_chunks_that_fill_one_round(oracle, units, T, dtype, G, W, D, chunk, scorer, causal):
     """Chunks that are no power of two: every part of a step that counts in chunks, ragged last chunks."""
     w = inputs.CONFIGS[1].scaled(L=units // 4 if units % 4 == 0 else 1, H=4 if units % 4 == 0 else units, D=D, G=G, W=W, T=T,
                                  T_min=T, dtype=dtype, budget=200, S=8, n_spans=4, span_len=(8, 200), causal=causal)
-    if scorer == B.SCORER_REDUNDANCY and T > 7000:
-        pytest.skip("the oracle evaluates the T^2 definition: minutes at this length")
-    _run(oracle, w, scorer=scorer, units=[0, units // 2, units - 1] if scorer != B.SCORER_REDUNDANCY else [units - 1])
+    host = inputs.dense_cache(w, n_threads=4)
+    job = Job(w, host, scorer=scorer)
+    if not causal:
+        assert _chunks_of_first_unit(job) == -(-T // chunk)
+        job.credit.zero_()
+        job.ws.zero_()
+    job.step()
+    check_properties_all_units(job)
+    i = units - 1
+    if scorer != B.SCORER_REDUNDANCY or T <= 7000:
+        units = [i] if scorer == B.SCORER_REDUNDANCY else [0, units // 2, i]
+        check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), units, scorer=scorer)
+    else:           # the oracle evaluates the T^2 definition, minutes at these lengths: the sum of the unit vectors in double
+        u, g = to_host(job.intermediates().u)[i, :T], to_host(job.intermediates().g)[i, :T]
+        k = inputs.as_f32(host["K"]).reshape(-1, T, D)[i].astype(np.float64)
+        k /= np.linalg.norm(k, axis=1, keepdims=True)
+        p = np.exp((k @ k.sum(0) - 1) / (T - 1))
+        p /= p.sum()
+        imp = job.p.mix_lambda * oracle.pool(u, job.p.score_kernel).astype(np.float64)
+        p *= 1 - job.p.mix_lambda
+        assert_close_terms(g, imp - p, imp + p, what="g")
 
 
 @pytest.mark.parametrize("common", [0.0, 30.0])
@@ -418,17 +447,6 @@ def test_short_caches_choose_their_scorer(oracle, scorer, units, T, G, one_launc
     assert ("score_unit" in _labels(job)) == one_launch
     check_properties_all_units(job)
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, units // 2, units - 1], scorer=scorer)
-
-
-def _chunks_of_first_unit(job):
-    """Runs a step over a workspace of ones and counts the chunks of which the first sweep has left statistics: the rows at the
-    head of the workspace, up to the first that nothing has written."""
-    job.ws.fill_(255)
-    job.step()
-    n_pad = next(32 * n for n in (1, 2, 4, 7, 8) if 32 * n >= job.w.G * job.w.W)
-    rows = job.ws[:min(job.ws.numel(), 600 * n_pad * 8) // (n_pad * 8) * n_pad * 8].view(torch.int32).reshape(-1, n_pad * 2)
-    blank = to_host((rows == -1).all(1))
-    return int(np.argmax(blank))
 
 
 @pytest.mark.parametrize("scorer,causal", [(B.SCORER_MEAN_WINDOW, False), (B.SCORER_KEYDIFF, False), (B.SCORER_REDUNDANCY, False),
