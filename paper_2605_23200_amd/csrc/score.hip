@@ -368,9 +368,11 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   a.even = !paged && wl.one_round;
   a.n_pad = wl.n_pad;
   // Batches whose sequences may differ in length: the workgroups count the chunks that exist (sweep_tile), where the launch has
-  // more of them than run at once.  Below that the count's 0.5 us per workgroup is all it does (93.5 and 95.2 us per step for
-  // 48 x 3 units of up to 1376, 52.3 and 53.3 for 2 x 3 of up to 20068,
-  // 207.2 and 208.3 for the stage calls of 64 units of up to 20011, 1280 workgroups; but 162 and 143 for 192 of up to 9001).
+  // more of them than run at once (162 and 143 us per step for 192 units of up to 9001; 12 shapes of 1536 to 2400 workgroups
+  // take 0.84 to 1.0 of the time without).  The count costs 0.5 us per workgroup (93.5 and 95.2 for 48 x 3 units of up to 1376,
+  // 52.3 and 53.3 for 2 x 3 of up to 20068).  From 1024 to 1536 workgroups it depends on how the lengths fall: 23 shapes take
+  // 0.87 to 1.01, 0.99 on average, the stage calls of 64 units of up to 20011 (1280 workgroups) 208.3 us with it and 207.2
+  // without, which is within the spread of their runs.  The line lies where none of the measured shapes loses.
   a.compact = d.B > 1 && d.B <= 64 && (int64_t)d.units * a.n_chunks >= 1536;
   // The second sweep merges the statistics itself where that is cheaper than a launch between the sweeps (1.2 us of gap and
   // 5 of its own): every workgroup reads its unit's partial statistics once more.  us per step, with the kernel and without:
@@ -378,6 +380,8 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   // workgroups), 147.8 and 143.6 (32 units of 27209, 864 workgroups), 99.8 and 97.3 (48 units of 1376, 224 queries).  With up
   // to 2048 workgroups or 128 chunks there is no gain any more (828 units of 12608: 822 and 827), and with more than 32 KB of
   // partial statistics per unit every workgroup takes as long as the kernel (4 fp32 units of 7328, 112 queries: 61.6 and 63.9).
+  // With the keys riding along every workgroup also adds up the chunks' key sums, 128 KB at 128 chunks of 128 channels; the same
+  // line holds: 138 shapes (1 to 64 units of 4096 to 131072, 8 to 128 queries) take 0.92 to 1.01 of the time with the kernel.
   a.fold = !causal && (int64_t)d.units * a.n_chunks <= 1024 && a.n_chunks * a.n_pad <= 4096;
   a.inv_sqrt_d = (float)(1.0 / sqrt((double)d.D));
   a.c2 = (float)(1.4426950408889634 / sqrt((double)d.D));
