@@ -146,7 +146,8 @@ __device__ __forceinline__ float load_q(const ScoreArgs& a, int l, int b, int h,
 // Barrier after load_q.  fp32: bf16 terms are cut short below 2^-109 (the last one ends at 2^-133), which shows where the
 // other factor is about as large: keys of 2^-118 against queries of 2^118 had logits off by 1e-5.  A window whose largest
 // entry lies outside 2^-100 .. 2^100 is loaded again, scaled to about one, and the power of two taken from it, which is
-// returned (0 otherwise), goes to the keys (tile_mma).
+// returned (0 otherwise), goes to the keys (tile_mma).  An ordinary window waits for one more read of LDS: 37.9 -> 38.2 to 38.8
+// us per step for 8 units of 4096 positions, no difference in launches of 100 us and more.
 template <bool BF16, int NB, int HD = 128, int THREADS = kThreads>
 __device__ __forceinline__ int settle_q(const ScoreArgs& a, int l, int b, int h, char* qlds, float top) {
   if constexpr (BF16) {
