@@ -397,6 +397,7 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   const int nb = wl.n_pad / 32;
   bool oneread = false;
   int vc_stride = 0, vc_tokens = 0;
+  bool vc_even = false;
   hipError_t e = hipSuccess;
   // AMS_SCORE_PATH_AUTO: the two sweeps, which are the faster of the two on every workload measured so far
   if (p->score_path == AMS_SCORE_PATH_ONE_READ)
@@ -434,6 +435,7 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     a.ksum = nullptr;
     vc_stride = a.n_chunks;
     vc_tokens = a.chunk;
+    vc_even = a.even;
     keys_done = true;
   } else if (!oneread) {
     if (d.D == 64)
@@ -442,13 +444,14 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
       e = bf16 ? run_by_nb<true, 128>(a, nb, mode, s) : run_by_nb<false, 128>(a, nb, mode, s);
     vc_stride = a.n_chunks;
     vc_tokens = a.chunk;
+    vc_even = a.even;
   }
   if (e != hipSuccess) return e;
   if (vc) {
     vc->have = true;
     vc->stride = vc_stride;
     vc->tokens = vc_tokens;
-    vc->even = a.even && vc_stride == a.n_chunks && vc_tokens == a.chunk;
+    vc->even = vc_even;
   }
   if (vnorm) {
     if (!a.soft) {

@@ -472,3 +472,19 @@ def test_a_short_cache_is_shared_by_all_workgroups(oracle, units, t_max, dtype, 
     assert to_host(job.n_kept).tolist() == [min(w.budget, T)] * units
     if T > 0:
         check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [units // 2] if T > 2000 else [0, units - 1], scorer=scorer)
+
+
+@pytest.mark.parametrize("path", [B.SCORE_PATH_ONE_READ, B.SCORE_PATH_TWO_SWEEPS])
+@pytest.mark.parametrize("T", [16384, 10001, 700])
+def test_sums_of_a_short_cache_by_either_scorer(oracle, path, T):
+    """8 units with t_max 16384: the one-read scorer leaves a sum per 512 positions, and the sweeps' chunks have 512 at t_max but
+    less in a shorter cache."""
+    w = inputs.CONFIGS[1].scaled(L=2, H=4, G=2, W=8, T=16384, T_min=16384, budget=300, S=8, n_spans=4, span_len=(8, 200))
+    host = inputs.dense_cache(w, n_threads=4)
+    job = Job(w, host, score_path=path)
+    host["seq_lens"][:] = T
+    job.lens.fill_(T)
+    job.ws.fill_(255)                                       # entries that nobody writes are no numbers
+    job.step()
+    assert to_host(job.n_kept).tolist() == [300] * 8
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, 7])
