@@ -146,7 +146,7 @@ __device__ __forceinline__ float load_q(const ScoreArgs& a, int l, int b, int h,
 // Barrier after load_q.  fp32: bf16 terms are cut short below 2^-109 (the last one ends at 2^-133), which shows where the
 // other factor is about as large: keys of 2^-118 against queries of 2^118 had logits off by 1e-5.  A window whose largest
 // entry lies outside 2^-100 .. 2^100 is loaded again, scaled to about one, and the power of two taken from it, which is
-// returned (0 otherwise), goes to the keys (tile_mma).  An ordinary window waits for one more read of LDS: 37.9 -> 38.2 to 38.8
+// returned (0 otherwise), goes to the keys (tile_mma).  An ordinary window waits for one more read of LDS: 37.2 -> 37.6 to 37.9
 // us per step for 8 units of 4096 positions, no difference in launches of 100 us and more.
 template <bool BF16, int NB, int HD = 128, int THREADS = kThreads>
 __device__ __forceinline__ int settle_q(const ScoreArgs& a, int l, int b, int h, char* qlds, float top) {
@@ -155,14 +155,16 @@ __device__ __forceinline__ int settle_q(const ScoreArgs& a, int l, int b, int h,
     return 0;
   } else {
     constexpr int WAVES = THREADS / 64;
-    __shared__ int seen[WAVES];
+    __shared__ __align__(16) int seen[WAVES];
     __shared__ float tops[WAVES];
-    const int mine = (__any(top >= 0x1p-100f) ? 1 : 0) | (__any(top >= 0x1p100f) ? 2 : 0);
-    if ((threadIdx.x & 63) == 0) seen[threadIdx.x >> 6] = mine;
+    seen[threadIdx.x >> 6] = (__any(top >= 0x1p-100f) ? 1 : 0) | (__any(top >= 0x1p100f) ? 2 : 0);
     __syncthreads();
     int all = 0;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) all |= seen[w];
+    for (int w = 0; w < WAVES; w += 4) {
+      const int4 s4 = *(const int4*)&seen[w];
+      all |= (s4.x | s4.y) | (s4.z | s4.w);
+    }
     if (__builtin_expect(__builtin_amdgcn_readfirstlane(all) == 1, 1)) return 0;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
