@@ -12,7 +12,7 @@
 // finalize_kernel  (only with a must-keep set) one workgroup per unit.  The segment picks arrive as
 //                bits of a per-unit bitmap, so the union with the must-keep positions and the removal
 //                of duplicates are one OR; what the duplicates leave open is filled with the best
-//                scores outside the set (the same selection over the unset positions; radix passes where the
+//                scores outside the set (the same selection over the unset positions, from memory where the
 //                sequence is too long for registers), and the ascending index list is read off the bitmap.
 #include "ams_internal.h"
 #include "quota.h"
@@ -137,81 +137,6 @@ __device__ __forceinline__ void gather_rows(const Dims& d, const GatherArgs& ga,
 // many short segments (no barriers between waves), 256, 512 and 1024 threads the longer ones; a segment that is longer
 // than its shape's BLOCK * PER is selected from memory.
 
-// Segment longer than the registers hold: the scores are re-read from memory for every pass.
-template <bool FLAGS, int BLOCK>
-__device__ void select_from_memory(const float* g, int a, int b, int q, const Emit<FLAGS>& emit, int* hist,
-                                   uint32_t* sel_prefix, int* sel_rem, int2* wave_cnt) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // radix select of the q-th largest key, 8 bits at a time from the top
-  uint32_t prefix = 0, mask = 0;
-  int rem = q;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    for (int i = threadIdx.x; i < 256; i += BLOCK) hist[i] = 0;
-    __syncthreads();
-    for (int t = a + threadIdx.x; t < b; t += BLOCK) {
-      const uint32_t k = score_key(g[t]);
-      if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255], 1);
-    }
-    __syncthreads();
-    if (wave == 0) {
-      int hb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) hb[i] = hist[lane * 4 + i];
-      const int s = hb[0] + hb[1] + hb[2] + hb[3];
-      int incl = s;  // sum over lanes >= this one
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_down(incl, o);
-        if (lane + o < 64) incl += v;
-      }
-      int cum = incl - s;  // keys in bins above this lane's
-#pragma unroll
-      for (int i = 3; i >= 0; --i) {
-        if (cum < rem && rem <= cum + hb[i]) {
-          *sel_prefix = prefix | ((uint32_t)(lane * 4 + i) << shift);
-          *sel_rem = rem - cum;
-        }
-        cum += hb[i];
-      }
-    }
-    __syncthreads();
-    prefix = *sel_prefix;
-    rem = *sel_rem;
-    mask |= 0xFFu << shift;
-    __syncthreads();
-  }
-  // prefix = key of the q-th largest score; rem = how many of the keys equal to it are kept
-  const uint32_t thr = prefix;
-  int base_gt = 0, base_eq = 0;  // counts over the positions before the current tile
-  for (int t0 = a; t0 < b; t0 += BLOCK) {
-    const int t = t0 + threadIdx.x;
-    uint32_t k = 0;
-    const bool in = t < b;
-    if (in) k = score_key(g[t]);
-    const bool gt = in && k > thr, eq = in && k == thr;
-    const uint64_t bgt = __ballot(gt), beq = __ballot(eq);
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (lane == 0) wave_cnt[wave] = make_int2(__popcll(bgt), __popcll(beq));
-    __syncthreads();
-    int n_gt = base_gt + __popcll(bgt & below), n_eq = base_eq + __popcll(beq & below);
-    int tot_gt = 0, tot_eq = 0;
-#pragma unroll
-    for (int w = 0; w < (BLOCK / 64); ++w) {
-      const int2 c = wave_cnt[w];
-      if (w < wave) {
-        n_gt += c.x;
-        n_eq += c.y;
-      }
-      tot_gt += c.x;
-      tot_eq += c.y;
-    }
-    if (gt || (eq && n_eq < rem)) emit(n_gt + min(n_eq, rem), t);
-    base_gt += tot_gt;
-    base_eq += tot_eq;
-    __syncthreads();
-  }
-}
-
 // Inclusive sum over the lanes of a wave (DPP: inside the rows of 16, then the rows' ends into the rows after them).
 __device__ __forceinline__ int wave_scan(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
@@ -264,6 +189,235 @@ __device__ __forceinline__ void top_bin(const int* h, int lane, int& rem, uint32
   lo += (uint32_t)bin << sh;
 }
 
+// ---- Segments longer than the registers hold: the scores are read from memory in every pass ----
+// Bound: one CU reads the scores four to six times and adds every key to its bin in LDS once or twice.  The range of the keys;
+// bins over it (2048 with 1024 threads) until the bin with the last pick holds few keys; those keys into LDS, where the bins are
+// refined down to one key; the picks in ascending order.  Every wave reads a stretch of its own with 16-byte loads, so that its
+// counts place its picks and no pass has a barrier inside.  A unit in one segment: 72 us for 32 units of 74913 scores (181 with
+// four radix passes of 4-byte loads and two barriers per 1024 positions of the last one), 42 for 16 of 40000 (98).
+template <int BLOCK>
+struct FarLds {
+  static constexpr int kW = BLOCK / 64, kLogBins = BLOCK == 1024 ? 11 : 8, kBins = 1 << kLogBins;
+  static constexpr int kKeys = BLOCK == 1024 ? 1024 : 64;  // at most one per thread
+  int bins[kBins + kBins / 32];  // a word of padding per 32: a lane sums up neighbouring bins
+  uint2 key[kKeys];              // (key, wave that reads its position)
+  uint2 red[kW];
+  int above[kW], equal[kW];      // picks of a wave's stretch above the threshold, keys equal to it
+  int n_keys;
+};
+
+template <int BLOCK>
+union BinsOrFar {
+  int hist[2][256];  // keys in registers: the bins of two passes
+  FarLds<BLOCK> far;
+};
+
+// Calls f(t, k, kept) for this wave's stretch of [a, b), four positions t .. t + 3 per lane; load(t, k) gives their keys (0: not
+// to be considered) and returns the mask of positions that are kept whatever their key.
+template <int BLOCK, typename Load, typename F>
+__device__ __forceinline__ void far_walk(int a, int b, Load load, F f) {
+  constexpr int kW = BLOCK / 64, kAhead = BLOCK == 1024 ? 6 : 2;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int first = a & ~255, groups = (b - first + 255) >> 8;
+  const int g0 = groups * wave / kW, g1 = groups * (wave + 1) / kW;
+  for (int g = g0; g < g1; g += kAhead) {
+    uint32_t k[kAhead][4], kept[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      kept[i] = k[i][0] = k[i][1] = k[i][2] = k[i][3] = 0;
+      if (g + i < g1) kept[i] = load(first + (g + i) * 256 + lane * 4, k[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if (g + i < g1) f(first + (g + i) * 256 + lane * 4, k[i], kept[i]);
+  }
+}
+
+// The scores at t .. t + 3 that lie in [a, b), t a multiple of 4; vec: 16-byte reads are aligned and stay in the row.
+__device__ __forceinline__ void far_scores(const float* g, int a, int b, int t, bool vec, uint32_t (&k)[4]) {
+  float x[4] = {0.f, 0.f, 0.f, 0.f};
+  if (t + 3 >= a && t < b) {
+    if (vec) {
+      const float4 v = *reinterpret_cast<const float4*>(g + t);
+      x[0] = v.x, x[1] = v.y, x[2] = v.z, x[3] = v.w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (t + i >= a && t + i < b) x[i] = g[t + i];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) k[i] = t + i >= a && t + i < b ? score_key(x[i]) : 0u;  // no score has the key 0
+}
+
+// See top_bin; the bins of a FarLds.
+template <int BLOCK>
+__device__ __forceinline__ void far_top_bin(const FarLds<BLOCK>& s, int& rem, uint32_t& lo, int sh, int& n_bin) {
+  constexpr int kPer = FarLds<BLOCK>::kBins / 64;
+  const int lane = threadIdx.x & 63, b0 = kPer * (63 - lane);  // lane 0 the highest bins
+  int c[kPer], t = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    c[i] = s.bins[b0 + i + (b0 + i) / 32];
+    t += c[i];
+  }
+  const int front = wave_scan(t) - t;
+  int bin = b0, cum = front, in = 0, run = front;
+  bool open = true;
+#pragma unroll
+  for (int i = kPer - 1; i >= 0; --i) {
+    if (open && rem <= run + c[i]) {
+      open = false;
+      bin = b0 + i, cum = run, in = c[i];
+    }
+    run += c[i];
+  }
+  const int src = __ffsll((long long)__ballot(front < rem && rem <= front + t)) - 1;
+  bin = __builtin_amdgcn_readlane(bin, src);
+  rem -= __builtin_amdgcn_readlane(cum, src);
+  n_bin = __builtin_amdgcn_readlane(in, src);
+  lo += (uint32_t)bin << sh;
+}
+
+// The q best keys of [a, b) (load: see far_walk; 1 <= q, fewer than there are keys to consider) and the positions kept whatever
+// their key, in ascending order: emit(slot, t).  any = false: those positions alone.
+template <int BLOCK, typename Load, typename Emit>
+__device__ __forceinline__ void far_select(FarLds<BLOCK>& s, int a, int b, int q, bool any, Load load, Emit emit) {
+  using F = FarLds<BLOCK>;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto clear = [&]() __attribute__((always_inline)) {
+    for (int i = threadIdx.x; i < F::kBins + F::kBins / 32; i += BLOCK) s.bins[i] = 0;
+  };
+  clear();
+  if (threadIdx.x == 0) s.n_keys = 0;
+  uint32_t thr = 0xFFFFFFFFu;  // keys above it are picked, and the first rem equal to it
+  int rem = 0;
+  bool counted = false;
+  if (any) {
+    uint32_t lo = 0xFFFFFFFFu, hi = 0;
+    far_walk<BLOCK>(a, b, load, [&](int, const uint32_t (&k)[4], uint32_t) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (k[i]) lo = min(lo, k[i]);
+        hi = max(hi, k[i]);
+      }
+    });
+    wave_min_max(lo, hi);
+    if (lane == 0) s.red[wave] = make_uint2(lo, hi);
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < F::kW; ++w) {
+      lo = min(lo, s.red[w].x);
+      hi = max(hi, s.red[w].y);
+    }
+    int sh = max(0, 32 - F::kLogBins - (int)__clz((int)((hi - lo) | 1u))), n_bin = 0;
+    uint32_t span = hi - lo;  // see select_kernel
+    auto add = [&](uint32_t k) __attribute__((always_inline)) {
+      const uint32_t off = k - lo;
+      if (k >= lo && off <= span) atomicAdd(&s.bins[(off >> sh) + (off >> sh) / 32], 1);
+    };
+    auto narrow = [&]() __attribute__((always_inline)) {
+      __syncthreads();
+      far_top_bin<BLOCK>(s, rem, lo, sh, n_bin);
+      span = (1u << sh) - 1u;
+    };
+    auto finer = [&]() __attribute__((always_inline)) {
+      sh = max(0, sh - F::kLogBins);
+      __syncthreads();
+      clear();
+      __syncthreads();
+    };
+    rem = q;
+    for (;;) {
+      far_walk<BLOCK>(a, b, load, [&](int, const uint32_t (&k)[4], uint32_t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) add(k[i]);  // (lo is above 0)
+      });
+      narrow();
+      if (n_bin <= F::kKeys || n_bin == rem || sh == 0) break;
+      finer();
+    }
+    if (n_bin != rem && n_bin <= F::kKeys) {  // the rest among the bin's keys, in LDS
+      int above = 0;
+      far_walk<BLOCK>(a, b, load, [&](int, const uint32_t (&k)[4], uint32_t kept) __attribute__((always_inline)) {
+        above += __popc(kept);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (k[i] < lo) continue;
+          if (k[i] - lo > span)
+            ++above;
+          else
+            s.key[atomicAdd(&s.n_keys, 1)] = make_uint2(k[i], (uint32_t)wave);
+        }
+      });
+      above = wave_sum(above);
+      if (lane == 0) {
+        s.above[wave] = above;
+        s.equal[wave] = 0;
+      }
+      __syncthreads();
+      const int n = s.n_keys;
+      const uint2 mine = (int)threadIdx.x < n ? s.key[threadIdx.x] : make_uint2(0u, 0u);
+      while (n_bin != rem && sh > 0) {
+        finer();
+        add(mine.x);
+        narrow();
+      }
+      thr = lo;
+      if (n_bin == rem) thr = lo - 1, rem = 0;
+      if (mine.x > thr) atomicAdd(&s.above[mine.y], 1);
+      if (mine.x == thr) atomicAdd(&s.equal[mine.y], 1);
+      counted = true;
+    } else {  // the bin as a whole, or its keys are equal
+      thr = lo;
+      if (n_bin == rem) thr = lo - 1, rem = 0;
+    }
+  }
+  if (!counted) {
+    int above = 0, equal = 0;
+    far_walk<BLOCK>(a, b, load, [&](int, const uint32_t (&k)[4], uint32_t kept) __attribute__((always_inline)) {
+      above += __popc(kept);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        above += k[i] > thr;
+        equal += k[i] == thr;
+      }
+    });
+    above = wave_sum(above);
+    equal = wave_sum(equal);
+    if (lane == 0) {
+      s.above[wave] = above;
+      s.equal[wave] = equal;
+    }
+  }
+  __syncthreads();
+  int n_gt = 0, n_eq = 0;  // in front of this wave's stretch
+  for (int w = 0; w < wave; ++w) {
+    n_gt += s.above[w];
+    n_eq += s.equal[w];
+  }
+  far_walk<BLOCK>(a, b, load, [&](int t, const uint32_t (&k)[4], uint32_t kept) __attribute__((always_inline)) {
+    uint32_t gt = kept, eq = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      gt |= (k[i] > thr ? 1u : 0u) << i;
+      eq |= (k[i] == thr ? 1u : 0u) << i;
+    }
+    const int c = __popc(gt) | __popc(eq) << 16;
+    const int incl = wave_scan(c), before = incl - c, all = __builtin_amdgcn_readlane(incl, 63);
+    int gt_in_front = n_gt + (before & 0xFFFF), eq_in_front = n_eq + (before >> 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool is_gt = (gt >> i) & 1u, is_eq = (eq >> i) & 1u;
+      if (is_gt || (is_eq && eq_in_front < rem)) emit(gt_in_front + min(eq_in_front, rem), t + i);
+      gt_in_front += is_gt;
+      eq_in_front += is_eq;
+    }
+    n_gt += all & 0xFFFF;
+    n_eq += all >> 16;
+  });
+}
+
 // The q largest keys of a segment.  Latency and LDS atomics bound this kernel (a few thousand keys per workgroup), so the
 // steps that need all threads are few: the keys stay in registers, 256 bins cut the range between the lowest and the
 // highest key, and once the bin with the q-th largest holds no more than 64 keys, those are listed and one wave counts for
@@ -279,15 +433,13 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget
   constexpr bool FLAGS = MODE == SELECT_FLAGS, GATHER = MODE == SELECT_GATHER;
   constexpr int kW = BLOCK / 64, kCap = BLOCK * PER, kWords = kCap / 64, kPerLane = (kWords + 63) / 64;
   constexpr int kList = 64;  // keys that one wave ranks
-  __shared__ __align__(16) int hist[2][256];
+  __shared__ __align__(16) BinsOrFar<BLOCK> bins;
+  auto& hist = bins.hist;
   __shared__ uint2 list[kList];          // (key, position in the segment) of the keys in the bin
   __shared__ __align__(8) uint64_t picked[kWords], equal[kWords];
   __shared__ int before[kWords];         // picks in front of each word
   __shared__ int n_list;
   __shared__ uint2 red[kW];
-  __shared__ int2 wave_cnt[kW];
-  __shared__ uint32_t mem_prefix;
-  __shared__ int mem_rem;
   __shared__ int32_t rows[GATHER ? kGatherList : 1];
   const int unit = blockIdx.y, seg = GATHER ? (int)blockIdx.x / ga.parts : (int)blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -326,12 +478,29 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget
     if (GATHER) gather_rows<BLOCK>(d, ga, unit, out0, r0, r1, [&](int j) { return a + j; });
     return;
   }
+  // a pick, the j-th of the segment
+  auto take = [&](int j, int t) __attribute__((always_inline)) {
+    emit(j, t);
+    if (GATHER && j >= r0 && j < r1 && j - r0 < kGatherList) rows[j - r0] = t;
+  };
+  auto gather = [&]() __attribute__((always_inline)) {
+    __syncthreads();
+    gather_rows<BLOCK>(d, ga, unit, out0, r0, r1, [&](int j) __attribute__((always_inline)) {
+      int t = rows[min(j - r0, kGatherList - 1)];
+      asm volatile("" : "+v"(t));  // two loads, not one through a pointer to either memory
+      if (j - r0 >= kGatherList) t = emit.out[j];
+      return t;
+    });
+  };
   if (from_memory) {
-    select_from_memory<FLAGS, BLOCK>(g, a, b, q, emit, &hist[0][0], &mem_prefix, &mem_rem, wave_cnt);
-    if (GATHER) {
-      __syncthreads();
-      gather_rows<BLOCK>(d, ga, unit, out0, r0, r1, [&](int j) { return emit.out[j]; });
-    }
+    const bool vec = (d.t_stride & 3) == 0 && ((uintptr_t)g_all & 15) == 0;
+    far_select<BLOCK>(bins.far, a, b, q, true,
+                      [&](int t, uint32_t (&k)[4]) __attribute__((always_inline)) {
+                        far_scores(g, a, b, t, vec, k);
+                        return 0u;
+                      },
+                      take);
+    if (GATHER) gather();
     return;
   }
 
@@ -466,16 +635,11 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(Dims d, int S, int budget
       const uint64_t m = picked[w];
       if ((m >> lane) & 1ull) {
         const int j = before[w] + __popcll(m & ((1ull << lane) - 1ull)), t = a + i * BLOCK + (int)threadIdx.x;
-        emit(j, t);
-        if (GATHER && j >= r0 && j - r0 < kGatherList) rows[j - r0] = t;
+        take(j, t);
       }
     }
   }
-  if (GATHER) {
-    __syncthreads();
-    gather_rows<BLOCK>(d, ga, unit, out0, r0, r1,
-                       [&](int j) { return j - r0 < kGatherList ? rows[j - r0] : emit.out[j]; });
-  }
+  if (GATHER) gather();
 }
 
 // Bits of word w (positions 32w .. 32w+31) that lie in [lo, hi).
@@ -494,12 +658,11 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
                                                              int n_sink, int n_last, const float* g_all,
                                                              uint32_t* flags_all, int n_words,
                                                              int32_t* idx_all) {
-  __shared__ __align__(16) int hist[kFinWaves][256];
-  __shared__ uint32_t sel_digit;
-  __shared__ int sel_rem;
+  __shared__ __align__(16) BinsOrFar<kFinBlock> bins;
+  auto& hist = bins.hist;
   __shared__ int red[kFinWaves];
-  __shared__ uint32_t red_and[kFinWaves], red_or[kFinWaves];
-  __shared__ int2 wave_cnt[kFinWaves];
+  __shared__ uint32_t red_lo[kFinWaves], red_hi[kFinWaves];
+  __shared__ int wave_cnt[kFinWaves];
   __shared__ uint32_t bm[kFinBlock];  // the bitmap of a sequence of up to 32768 positions
   __shared__ uint2 list[64];          // (key, position) of the keys of the last bin
   __shared__ int n_list;
@@ -516,7 +679,7 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
   const int nw = (T + 31) >> 5;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // Up to 32768 positions the bitmap is worked on in LDS and the keys are read once into registers;
-  // longer sequences keep the bitmap in memory and re-read the scores in every pass.
+  // longer sequences keep the bitmap in memory and re-read the scores in every pass (far_select).
   const bool inreg = T <= kFinBlock * kFinPer;
 
   // union with the must-keep positions; size of the union
@@ -543,98 +706,14 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
   uint32_t kreg[kFinPer];
   auto key_at = [&](int t) __attribute__((always_inline)) -> uint32_t {
     if (t >= T) return 0u;
-    const uint32_t word = inreg ? bm[t >> 5] : flags[t >> 5];
-    return ((word >> (t & 31)) & 1u) ? 0u : score_key(g[t]);
+    return ((bm[t >> 5] >> (t & 31)) & 1u) ? 0u : score_key(g[t]);
   };
   if (fill && inreg) {
 #pragma unroll
     for (int j = 0; j < kFinPer; ++j) kreg[j] = key_at(threadIdx.x + j * kFinBlock);
   }
 
-  // key of the deficit-th largest score among the positions outside the set
-  uint32_t thr = 0xFFFFFFFFu;
   int rem = 0;
-  if (fill && !inreg) {
-    // bits that are the same in every key need no radix pass
-    uint32_t k_and = 0xFFFFFFFFu, k_or = 0u;
-    for (int t = threadIdx.x; t < T; t += kFinBlock) {
-      const uint32_t k = key_at(t);
-      if (k) {
-        k_and &= k;
-        k_or |= k;
-      }
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      k_and &= __shfl_xor(k_and, o);
-      k_or |= __shfl_xor(k_or, o);
-    }
-    if (lane == 0) {
-      red_and[wave] = k_and;
-      red_or[wave] = k_or;
-    }
-    __syncthreads();
-    k_and = 0xFFFFFFFFu;
-    k_or = 0u;
-#pragma unroll
-    for (int w = 0; w < kFinWaves; ++w) {
-      k_and &= red_and[w];
-      k_or |= red_or[w];
-    }
-    const uint32_t diff = k_and ^ k_or;
-    thr = k_and;  // all keys equal: the threshold is that key
-    rem = deficit;
-    if (diff != 0) {
-      const int hb = 31 - __clz(diff);  // highest bit in which two keys differ
-      uint32_t mask = hb == 31 ? 0u : ~((2u << hb) - 1u);  // bits known so far
-      uint32_t prefix = k_and & mask;
-      int shift = max(hb - 7, 0);
-      for (;;) {
-        for (int i = threadIdx.x; i < kFinWaves * 256; i += kFinBlock) (&hist[0][0])[i] = 0;
-        __syncthreads();
-        for (int t = threadIdx.x; t < T; t += kFinBlock) {
-          const uint32_t k = key_at(t);
-          if (k && (k & mask) == prefix) atomicAdd(&hist[wave][(k >> shift) & 255], 1);
-        }
-        __syncthreads();
-        if (wave == 0) {
-          int hbin[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            hbin[i] = 0;
-#pragma unroll
-            for (int w = 0; w < kFinWaves; ++w) hbin[i] += hist[w][lane * 4 + i];
-          }
-          const int s = hbin[0] + hbin[1] + hbin[2] + hbin[3];
-          int incl = s;  // sum over lanes >= this one
-#pragma unroll
-          for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_down(incl, o);
-            if (lane + o < 64) incl += v;
-          }
-          int cum = incl - s;  // keys in bins above this lane's
-#pragma unroll
-          for (int i = 3; i >= 0; --i) {
-            if (cum < rem && rem <= cum + hbin[i]) {
-              sel_digit = (uint32_t)(lane * 4 + i);
-              sel_rem = rem - cum;
-            }
-            cum += hbin[i];
-          }
-        }
-        __syncthreads();
-        // the digit may overlap bits that are already known; OR-ing it in is then a no-op for those bits
-        prefix |= sel_digit << shift;
-        rem = sel_rem;
-        mask = shift == 0 ? 0xFFFFFFFFu : ~((1u << shift) - 1u);
-        __syncthreads();
-        if (shift == 0) break;
-        shift = max(shift - 8, 0);
-      }
-      thr = prefix;
-    }
-  }
-
   const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   if (inreg) {
     // The positions that fill the gap get their bits.  As in select_kernel: 256 bins over the range of the keys, the bin that
@@ -654,14 +733,14 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
       if (threadIdx.x == 0) n_list = 0;
       wave_min_max(lo, hi);
       if (lane == 0) {
-        red_and[wave] = lo;
-        red_or[wave] = hi;
+        red_lo[wave] = lo;
+        red_hi[wave] = hi;
       }
       __syncthreads();
 #pragma unroll
       for (int w = 0; w < kFinWaves; ++w) {
-        lo = min(lo, red_and[w]);
-        hi = max(hi, red_or[w]);
+        lo = min(lo, red_lo[w]);
+        hi = max(hi, red_hi[w]);
       }
       int sh = max(0, 24 - (int)__clz((int)((hi - lo) | 1u)));
       uint32_t span = hi - lo;
@@ -742,51 +821,27 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(Dims d, const int32
       const int v = __shfl_up(incl, o);
       if (lane >= o) incl += v;
     }
-    if (lane == 63) wave_cnt[wave].x = incl;
+    if (lane == 63) wave_cnt[wave] = incl;
     __syncthreads();
     int slot = incl - c;
-    for (int v = 0; v < wave; ++v) slot += wave_cnt[v].x;
+    for (int v = 0; v < wave; ++v) slot += wave_cnt[v];
     for (uint32_t m = f; m; m &= m - 1) idx[slot++] = threadIdx.x * 32 + __ffs((int)m) - 1;
     return;
   }
 
-  // long sequences: one position per thread and round; a position is kept when its bit is set or its
-  // score is above the threshold, and the first rem positions equal to the threshold join
-  int base_keep = 0, base_eq = 0;
-  for (int t0 = 0; t0 < T; t0 += kFinBlock) {
-    const int t = t0 + threadIdx.x;
-    bool keep = false, eq = false;
-    if (t < T) {
-      keep = (flags[t >> 5] >> (t & 31)) & 1u;
-      if (fill && !keep) {
-        const uint32_t k = score_key(g[t]);
-        keep = k > thr;
-        eq = k == thr;
-      }
-    }
-    const uint64_t bk = __ballot(keep), be = __ballot(eq);
-    if (lane == 0) wave_cnt[wave] = make_int2(__popcll(bk), __popcll(be));
-    __syncthreads();
-    int n_keep = base_keep + __popcll(bk & below), n_eq = base_eq + __popcll(be & below);
-    int tot_keep = 0, tot_eq = 0;
+  // long sequences: the gap is filled and the list written in passes over the scores (26 units of 88025 positions: 85 us, 264
+  // with radix passes and two barriers per 1024 positions; 10 of 131072: 116 and 388)
+  const bool vec = (d.t_stride & 3) == 0 && ((uintptr_t)g_all & 15) == 0;
+  far_select<kFinBlock>(bins.far, 0, T, deficit, fill,
+                        [&](int t, uint32_t (&k)[4]) __attribute__((always_inline)) {
+                          const uint32_t set = t < T ? flags[t >> 5] >> (t & 31) & 15u : 0u;
+                          far_scores(g, 0, T, t, vec, k);
 #pragma unroll
-    for (int v = 0; v < kFinWaves; ++v) {
-      const int2 c = wave_cnt[v];
-      if (v < wave) {
-        n_keep += c.x;
-        n_eq += c.y;
-      }
-      tot_keep += c.x;
-      tot_eq += c.y;
-    }
-    if (keep)
-      idx[n_keep + min(n_eq, rem)] = t;
-    else if (eq && n_eq < rem)
-      idx[n_keep + n_eq] = t;
-    base_keep += tot_keep;
-    base_eq += tot_eq;
-    __syncthreads();
-  }
+                          for (int i = 0; i < 4; ++i)
+                            if ((set >> i) & 1u) k[i] = 0u;
+                          return set;
+                        },
+                        [&](int slot, int t) __attribute__((always_inline)) { idx[slot] = t; });
 }
 
 }  // namespace

@@ -180,6 +180,47 @@ def test_select_at_the_edges_of_its_shapes(oracle, threads, lens, must):
             np.testing.assert_array_equal(to_host(idx)[i], want, err_msg=f"row {i} budget {budget}")
 
 
+@pytest.mark.parametrize("must", [False, True])
+@pytest.mark.parametrize("pad", [0, 4])
+@pytest.mark.parametrize("lens", [[70001], [131072], [33001, 2, 90001], [32769, 40000],           # 1024 threads
+                                  [9, 12001, 8193, 1], [4100, 4097, 3, 300],                       # 512, 256
+                                  [5003, 17, 1030, 40] + [9] * 60])                                # one wave
+def test_segments_longer_than_the_registers(oracle, lens, pad, must):
+    """Selected from memory, by stretches of 256 positions per wave: segments that start and end anywhere, rows whose 16-byte reads
+    are aligned (pad) and not; thousands of keys in one bin, bins that hold what is wanted, equal keys in order."""
+    S, T = len(lens), sum(lens)
+    bounds = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    stride = -(-T // 4) * 4 + pad if pad else T + 1 - T % 2   # odd: no row but the first is aligned
+    rng = np.random.default_rng(T + S + pad)
+    g = rng.standard_normal((7, T)).astype(np.float32)
+    g[1] = (1 + rng.integers(0, 70, T) * 2.0 ** -23).astype(np.float32)
+    g[1, ::501] = 3e38
+    g[2] = np.round(g[2] * 4)
+    g[3] = -1.5
+    g[4] = np.exp(6 * g[4])
+    g[4, T // 3:2 * T // 3] = 1 + rng.random(2 * T // 3 - T // 3).astype(np.float32) * 1e-4
+    g[5, ::3], g[5, 1::5], g[5, 2::7], g[5, 4::11] = np.nan, -np.inf, np.inf, -0.0
+    g[6] = np.where(rng.random(T) < 0.01, 1.0, 0.5)
+    rows = np.full((7, stride), 9e9, np.float32)                       # past the end: would win
+    rows[:, :T] = g
+    for budget in (max(1, T // 16), T // 2, T - 1):
+        p = _stage_params(7, T, S)
+        p.t_stride, p.budget = stride, budget
+        if must:
+            p.n_sink, p.n_last = 3, 33
+        mass = np.tile(np.array(lens, np.float32) / T, (7, 1))
+        quota = torch.zeros((7, S), dtype=torch.int32, device=DEV)
+        idx, n_kept = torch.zeros((7, budget), dtype=torch.int32, device=DEV), torch.zeros(7, dtype=torch.int32, device=DEV)
+        B.ams_select(p, to_dev(np.array([T], np.int32)), to_dev(rows), to_dev(np.tile(bounds, (7, 1))), to_dev(mass), quota,
+                     idx, n_kept, workspace(p))
+        sinks, last, seg_budget = oracle.must_keep(T, budget, p.n_sink, p.n_last)
+        for i in range(7):
+            q = oracle.quota(bounds, mass[i], seg_budget, 1)
+            np.testing.assert_array_equal(to_host(quota)[i], q)
+            want = oracle.finalize(g[i], oracle.select(g[i], bounds, q), sinks, last, budget)
+            np.testing.assert_array_equal(to_host(idx)[i], want, err_msg=f"row {i} budget {budget}")
+
+
 @pytest.mark.parametrize("H", [1, 2, 3, 8])
 def test_paged_heads_move_over_the_workgroups(oracle, H):
     """Paged sweeps give the heads of a chunk to workgroups in an order that moves on: every (unit, chunk) once, for head
