@@ -382,7 +382,8 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   // partial statistics per unit every workgroup takes as long as the kernel (4 fp32 units of 7328, 112 queries: 61.6 and 63.9).
   // With the keys riding along every workgroup also adds up the chunks' key sums, 128 KB at 128 chunks of 128 channels; the same
   // line holds: 138 shapes (1 to 64 units of 4096 to 131072, 8 to 128 queries) take 0.92 to 1.01 of the time with the kernel.
-  a.fold = !causal && (int64_t)d.units * a.n_chunks <= 1024 && a.n_chunks * a.n_pad <= 4096;
+  // Causal launches likewise, whose statistics have the tails' entry more (16 units of up to 2649: 88 and 82).
+  a.fold = (int64_t)d.units * a.n_chunks <= 1024 && a.n_chunks * a.n_pad <= 4096;
   a.inv_sqrt_d = (float)(1.0 / sqrt((double)d.D));
   a.c2 = (float)(1.4426950408889634 / sqrt((double)d.D));
   const bool bf16 = p->kv_dtype == AMS_BF16;
@@ -438,10 +439,7 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     vc_even = a.even;
     keys_done = true;
   } else if (!oneread) {
-    if (d.D == 64)
-      e = bf16 ? run_by_nb<true, 64>(a, nb, mode, s) : run_by_nb<false, 64>(a, nb, mode, s);
-    else
-      e = bf16 ? run_by_nb<true, 128>(a, nb, mode, s) : run_by_nb<false, 128>(a, nb, mode, s);
+    e = causal ? launch_causal_sweeps(a, nb, d.D, mode, bf16, s) : launch_sweeps<false>(a, nb, d.D, mode, bf16, s);
     vc_stride = a.n_chunks;
     vc_tokens = a.chunk;
     vc_even = a.even;

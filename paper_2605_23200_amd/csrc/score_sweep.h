@@ -152,9 +152,13 @@ constexpr int kSweepThreads = !BF16 && NB == 4 && HD == 128 ? 2 * kThreads : kTh
 //
 // Causal window (App. A "Mass construction"): query w of the window sits at position T-W+w and sees
 // the keys up to its own position.  The 32-token blocks that lie entirely before the newest W-1 keys
-// are seen by every query and run through the plain kernels, which then stop at t_end; the few
-// blocks from t_end on go through the TAIL instantiation of the same kernels (one workgroup per
-// unit), where a (query, key) pair the mask hides is left out.
+// are seen by every query and run like those of the plain sweeps, which then stop at t_end; the few
+// blocks from t_end on go to one workgroup more per unit, the last ones of the launch, where a (query, key) pair
+// the mask hides is left out.  As launches of their own they took 7 to 16 us each; beside the others they cost nothing in
+// large launches and 1 to 4 us in small ones: us per step 1055 and 1044 (256 units of 32768), 106 and 91 (64 of 4000), 252 and
+// 229 (40 of 30000, 224 queries), 65 and 52 (6 of 1090 with the paper's options, without the reduction's launch as well).  Mixed
+// in with the units' chunks (one of them first in every unit) they break the order of the key stream: 1092, 99, 241; 100 units
+// of 20000 take 320 in two launches, 362 mixed and 298 at the end.
 // Which (unit, chunk) a workgroup of the sweeps takes.  Dense caches: grid x = chunk, grid y = unit.
 // Paged caches keep the rows of a position's KV heads next to each other in a slot, so there the
 // heads of one (layer, sequence, chunk) are given to consecutive workgroups: they run at the same
@@ -172,8 +176,17 @@ constexpr int kSweepThreads = !BF16 && NB == 4 && HD == 128 ? 2 * kThreads : kTh
 __device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
   return a.causal ? max(0, (T - a.d.W + 1) / 32 * 32) : T;
 }
-__device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool reversed, int& unit, int& chunk) {
-  if (a.compact && !tail) {
+// Returns whether it is the unit's tail of a causal window.
+template <bool CAUSAL>
+__device__ __forceinline__ bool sweep_tile(const ScoreArgs& a, bool reversed, int& unit, int& chunk) {
+  int bx = blockIdx.x, by = blockIdx.y;
+  const int chunks = gridDim.x;
+  if (CAUSAL && by >= a.d.units) {
+    unit = (by - a.d.units) * chunks + bx;
+    chunk = unit < a.d.units ? 0 : -1;
+    return true;
+  }
+  if (a.compact) {
     const int lane = threadIdx.x & 63, B = a.d.B, H = a.d.H;
     const int len = lane < B ? max(0, min(a.seq_lens[lane], a.d.t_max)) : 0;
     const int n = (causal_t_end(a, len) + a.chunk - 1) / a.chunk;  // chunks of this lane's sequence
@@ -185,10 +198,10 @@ __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool r
     incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast: 15, 31
     incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);
     const int per_layer = __builtin_amdgcn_readlane(incl, 63), total = per_layer * H * a.d.L;
-    int lin = blockIdx.y * gridDim.x + blockIdx.x;
+    int lin = by * chunks + bx;
     unit = 0;
     chunk = a.n_chunks;  // past every sequence: nothing to do
-    if (lin >= total) return;
+    if (lin >= total) return false;
     if (reversed) lin = total - 1 - lin;
     int rest, h = 0;  // (sequence, chunk) of the layer, counted over what there is
     int l;
@@ -211,22 +224,22 @@ __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool r
     }
     chunk = rest;
     unit = (l * B + b) * H + h;
-    return;
+    return false;
   }
-  int bx = blockIdx.x, by = blockIdx.y;
   if (reversed) {
-    bx = gridDim.x - 1 - bx;
-    by = gridDim.y - 1 - by;
+    bx = chunks - 1 - bx;
+    by = a.d.units - 1 - by;
   }
-  if (a.k.layout != AMS_LAYOUT_PAGED || tail) {
+  if (a.k.layout != AMS_LAYOUT_PAGED) {
     unit = by;
-    chunk = tail ? 0 : bx;
-    return;
+    chunk = bx;
+    return false;
   }
-  const int lin = by * gridDim.x + bx;  // gridDim.x = chunks per unit, gridDim.y = units
+  const int lin = by * chunks + bx;  // gridDim.x = chunks per unit
   const int rest = lin / a.d.H, h = (lin + rest / 8) % a.d.H;
-  chunk = rest % (int)gridDim.x;
-  unit = (rest / (int)gridDim.x) * a.d.H + h;
+  chunk = rest % chunks;
+  unit = (rest / chunks) * a.d.H + h;
+  return false;
 }
 
 // The reference of the exponentials follows the running maximum, so that the largest logit of a wave has the exponent 0.  A
@@ -256,8 +269,23 @@ __device__ __forceinline__ void sweep_tile(const ScoreArgs& a, bool tail, bool r
 // units of 16589, 64 queries), and with seven or eight it spills (1835 -> 1933, 659 -> 958).  There, in the causal tail and for
 // fp32 caches, and for a wave whose statistics come out as no numbers, the sums are those of (s - r) and (s - r)^2 with r the
 // token's logit against the unit's first query (a reference close to the mean keeps the subtraction of the squares harmless).
-template <bool BF16, int NB, bool TAIL, int MOMENTS, int HD, int KEYS = KEYS_NONE>
-__global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
+template <bool BF16, int NB, int MOMENTS, int HD, int KEYS>
+struct StatsLds {
+  static constexpr int kWaves = kSweepThreads<BF16, NB, HD> / 64;
+  static constexpr bool kCentred = MOMENTS == MOMENTS_CENTRED;
+  __align__(16) char mean[kCentred ? 3 * HD * 2 : 16];  // minus the mean query in three bf16 terms
+  __align__(16) float g[MOMENTS ? kScoreChunk : 4];     // the chunk's moment scores, written once at the end
+  __align__(16) uint4 ident[KEYS ? 2 : 1][KEYS ? 64 : 1];
+  __align__(16) double inv_len[KEYS == KEYS_COS ? 4 : 1][KEYS ? 32 : 1];
+  double ksum[KEYS ? 8 : 1][KEYS ? HD : 1];
+  float2 xch[kCentred ? 1 : kWaves][NB * 32];
+  int32_t blk[kScoreChunk / 16];  // paged caches: this chunk's block numbers
+  int mean_cut;                   // the terms do not add up to the mean query
+};
+
+// XCH_IN_Q: the exchange takes the place of the query window (the centred sweep needs the room).
+template <bool BF16, int NB, bool TAIL, int MOMENTS, int HD, int KEYS, bool XCH_IN_Q, typename Lds>
+__device__ __forceinline__ void stats_body(const ScoreArgs& a, Lds& sm, int unit, int chunk) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
   constexpr bool kSpare = KEYS == KEYS_COS && HD == 128 && NB >= 7;  // see KEYS above
   constexpr int THREADS = kSweepThreads<BF16, NB, HD>, WAVES = THREADS / 64, STEP = THREADS / 2;  // STEP: tokens between two blocks of a wave
@@ -265,13 +293,12 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   static_assert(!kCentred || (BF16 && !TAIL), "the causal tail and fp32 caches take the sums relative to the first query");
   constexpr int NG = BF16 || MOMENTS ? kGroup<NB> : NB, QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
-  __shared__ float2 xch_own[kCentred ? 1 : WAVES][NB * 32];
-  // the centred sweep needs the room: its exchange takes the place of the query window, which is used up by then
-  float2(*xch)[NB * 32] = kCentred ? (float2(*)[NB * 32])qlds : xch_own;
-  __shared__ __align__(16) char mean_sm[kCentred ? 3 * HD * 2 : 16];  // minus the mean query in three bf16 terms
-  [[maybe_unused]] __shared__ int mean_cut;                           // they do not add up to it
-  int unit, chunk;
-  sweep_tile(a, TAIL, false, unit, chunk);
+  auto xch_at = [&](int w, int n) __attribute__((always_inline)) -> float2& {
+    if constexpr (XCH_IN_Q)
+      return ((float2*)qlds)[w * NB * 32 + n];
+    else
+      return sm.xch[w][n];
+  };
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all);
@@ -283,16 +310,13 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5;
   const int t_vis0 = T_all - a.d.W;  // newest key visible to the oldest query of the window
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
-  __shared__ int32_t blk_sm[kScoreChunk / 16];
   const int32_t* blk = nullptr;  // paged caches: this chunk's block numbers, staged once
   if (a.k.layout == AMS_LAYOUT_PAGED) {
-    stage_blocks<THREADS>(a, b, c0, t_lim, blk_sm);
-    blk = blk_sm;
+    stage_blocks<THREADS>(a, b, c0, t_lim, sm.blk);
+    blk = sm.blk;
   }
   if (c0 + wave * 32 < t_lim) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
   const float q_top = load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
-  __shared__ uint4 ident[KEYS ? 2 : 1][64];
-  __shared__ __align__(16) double inv_len[KEYS == KEYS_COS ? 4 : 1][32];
   double ksum[KEYS ? HD / 32 : 1];
   if constexpr (KEYS != KEYS_NONE) {
     if (threadIdx.x < 128) {
@@ -300,7 +324,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
       uint32_t v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) v[j] = (one == 2 * j ? 0x3F80u : 0u) | (one == 2 * j + 1 ? 0x3F800000u : 0u);
-      ident[p][lane] = make_uint4(v[0], v[1], v[2], v[3]);
+      sm.ident[p][lane] = make_uint4(v[0], v[1], v[2], v[3]);
     }
 #pragma unroll
     for (int cb = 0; cb < HD / 32; ++cb) ksum[cb] = 0.0;
@@ -314,10 +338,9 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   }
   const float c2 = a.c2;
   float* g_row = MOMENTS ? a.g + (int64_t)unit * a.d.t_stride : nullptr;
-  __shared__ __align__(16) float g_sm[MOMENTS ? kScoreChunk : 4];  // the chunk's moment scores, written once at the end
   if constexpr (kCentred) {
     constexpr int PAIRS = HD / 2, PARTS = kThreads / PAIRS;
-    double2* sums = (double2*)g_sm;
+    double2* sums = (double2*)sm.g;
     const int pair = threadIdx.x % PAIRS;
     double2 t = make_double2(0.0, 0.0);
 #pragma unroll 8
@@ -348,9 +371,9 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
         cut |= r != 0.f;
       }
       const int any_cut = __any(cut);
-      if (threadIdx.x == 0) mean_cut = any_cut;
+      if (threadIdx.x == 0) sm.mean_cut = any_cut;
 #pragma unroll
-      for (int j = 0; j < 3; ++j) *(uint32_t*)(mean_sm + j * HD * 2 + pair * 4) = term[j];
+      for (int j = 0; j < 3; ++j) *(uint32_t*)(sm.mean + j * HD * 2 + pair * 4) = term[j];
     }
     __syncthreads();
   }
@@ -366,7 +389,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     if constexpr (centred) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) centre[i] = s2[i] = 0.f;
-      const char* mb = mean_sm + qoff + hf * HD;
+      const char* mb = sm.mean + qoff + hf * HD;
 #pragma unroll
       for (int j = 2; j >= 0; --j)  // smallest terms first
 #pragma unroll
@@ -478,7 +501,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
       }
     }
     if constexpr (KEYS != KEYS_NONE)
-      add_keys<HD, KEYS == KEYS_COS>(av, ident, inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
+      add_keys<HD, KEYS == KEYS_COS>(av, sm.ident, sm.inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
     if constexpr (centred) {
       const int c = lane & 31, t = t0 + acc_row(c >> 1, hf);
       // the variance's share of every lane, and the mean (the same in all of them) from the first one
@@ -486,7 +509,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
 #pragma unroll
       for (int i = 0; i < 16; ++i) s2[i] = __builtin_fmaf(centre[i], k_mean, s2[i]);
       const float e = reduce16_over32(s2, c) * k_var;
-      if ((c & 1) == 0 && t < T_all) g_sm[t - c0] = e;
+      if ((c & 1) == 0 && t < T_all) sm.g[t - c0] = e;
     } else if (MOMENTS) {
       const int c = lane & 31;
       float rr[16];
@@ -498,7 +521,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
       const float d_sq = reduce16_over32(s2, c) * inv_n;     // mean of (s - r)^2
       const int t = t0 + acc_row(c >> 1, hf);
       if ((c & 1) == 0 && t < T_all)
-        g_sm[t - c0] = (r_tok + d_mean) * a.inv_sqrt_d + 0.5f * (d_sq - d_mean * d_mean) * (a.inv_sqrt_d * a.inv_sqrt_d);
+        sm.g[t - c0] = (r_tok + d_mean) * a.inv_sqrt_d + 0.5f * (d_sq - d_mean * d_mean) * (a.inv_sqrt_d * a.inv_sqrt_d);
     }
   };
   auto block = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0) __attribute__((always_inline)) {
@@ -509,7 +532,12 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   };
   // this wave's blocks: every WAVES-th block of 32 tokens up to the end of the chunk (or of the cache)
 #pragma unroll 1
-  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 2 * STEP) {
+  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += (TAIL ? 1 : 2) * STEP) {
+    if constexpr (TAIL) {  // a wave has one block, seldom more: no second buffer
+      block(av0, t0);
+      if (t0 + STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + STEP, T, lane, av0, blk, c0);
+      continue;
+    }
     if (t0 + STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + STEP, T, lane, av1, blk, c0);
     block(av0, t0);
     if (t0 + STEP >= t_lim) break;
@@ -523,7 +551,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     float t = 0.f;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) t = __builtin_fmaf(z[nb], 0.f, t);
-    if (__builtin_expect(__any(t != 0.f) || mean_cut, 0)) {
+    if (__builtin_expect(__any(t != 0.f) || sm.mean_cut, 0)) {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) {
         m[nb] = kNegInit;
@@ -535,8 +563,8 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
         block_of(av0, t0, std::true_type{}, std::false_type{});
       }
     }
-    __syncthreads();
   }
+  if (XCH_IN_Q) __syncthreads();  // the query window is used up
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const float m2 = __shfl_xor(m[nb], 32), z2 = __shfl_xor(z[nb], 32);
@@ -544,35 +572,52 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
     // lower half first so that both halves compute the same value
     const float zl = hf ? z2 : z[nb], ml = hf ? m2 : m[nb], zh = hf ? z[nb] : z2, mh = hf ? m[nb] : m2;
     const float Z = zl * __builtin_amdgcn_exp2f(ml - M) + zh * __builtin_amdgcn_exp2f(mh - M);
-    if (hf == 0) xch[wave][nb * 32 + (lane & 31)] = make_float2(M, Z);
+    if (hf == 0) xch_at(wave, nb * 32 + (lane & 31)) = make_float2(M, Z);
   }
   if constexpr (KEYS != KEYS_NONE) {
-    __shared__ double ks_sm[8][HD];  // half waves side by side, added up in a fixed order
+    // half waves side by side, added up in a fixed order
 #pragma unroll
-    for (int cb = 0; cb < HD / 32; ++cb) ks_sm[wave * 2 + hf][key_channel<HD>(cb, lane & 31)] = ksum[cb];
+    for (int cb = 0; cb < HD / 32; ++cb) sm.ksum[wave * 2 + hf][key_channel<HD>(cb, lane & 31)] = ksum[cb];
     __syncthreads();
     if (threadIdx.x < HD) {
       double t = 0.0;
 #pragma unroll
-      for (int r = 0; r < 8; ++r) t += ks_sm[r][threadIdx.x];
+      for (int r = 0; r < 8; ++r) t += sm.ksum[r][threadIdx.x];
       a.ksum[((int64_t)unit * a.n_chunks + chunk) * HD + threadIdx.x] = t;
     }
   }
   __syncthreads();
   if (MOMENTS)
-    for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) g_row[t] = g_sm[t - c0];
-  if (MOMENTS && !TAIL && a.soft) softmax_part<THREADS>(g_sm, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
+    for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) g_row[t] = sm.g[t - c0];
+  if (MOMENTS && !TAIL && a.soft) softmax_part<THREADS>(sm.g, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
   for (int n = threadIdx.x; n < NB * 32; n += THREADS) {
     float M = kNegInit;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) M = fmaxf(M, xch[w][n].x);
+    for (int w = 0; w < WAVES; ++w) M = fmaxf(M, xch_at(w, n).x);
     float Z = 0.f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) Z += xch[w][n].y * __builtin_amdgcn_exp2f(xch[w][n].x - M);
+    for (int w = 0; w < WAVES; ++w) Z += xch_at(w, n).y * __builtin_amdgcn_exp2f(xch_at(w, n).x - M);
     // the tail's entry follows those of the chunks
     const int slot = TAIL ? (t_end + len - 1) / len : chunk;
     a.part[((int64_t)unit * (a.n_chunks + 1) + slot) * a.n_pad + n] = make_float2(M, Z);
   }
+}
+
+// CAUSAL: the last rows of the grid take the tails of the units (moment sums relative to the first query).
+template <bool BF16, int NB, bool CAUSAL, int MOMENTS, int HD, int KEYS = KEYS_NONE>
+__global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && !MOMENTS && KEYS != KEYS_COS) ? AMS_SCORE_MIN_WAVES : 2) void score_stats_kernel(ScoreArgs a) {
+  constexpr bool kXchInQ = MOMENTS == MOMENTS_CENTRED;
+  __shared__ StatsLds<BF16, NB, MOMENTS, HD, KEYS> sm;
+  int unit, chunk;
+  const bool tail = sweep_tile<CAUSAL>(a, false, unit, chunk);
+  if constexpr (CAUSAL) {
+    if (tail) {
+      if (chunk < 0) return;
+      stats_body<BF16, NB, true, MOMENTS ? MOMENTS_FIRST : MOMENTS_NONE, HD, KEYS_NONE, kXchInQ>(a, sm, unit, chunk);
+      return;
+    }
+  }
+  stats_body<BF16, NB, false, MOMENTS, HD, KEYS, kXchInQ>(a, sm, unit, chunk);
 }
 
 // What the second sweep needs of query n: reference, weight of its shares in u and in the last-query g, whether it exists.
@@ -673,7 +718,7 @@ __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0,
 #pragma unroll 4
     for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) cs += (double)c_row[t];
   }
-  const int len = chunk_len(a, T), nch = (T + len - 1) / len;
+  const int len = chunk_len(a, T), nch = (causal_t_end(a, T) + len - 1) / len + (a.causal ? 1 : 0);
   const int parts = THREADS / a.n_pad, n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
   if (part < parts) {
     const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
@@ -714,17 +759,26 @@ __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0,
 
 // TAIL (causal window, blocks from t_end on): a (query, key) pair the mask hides adds nothing, and
 // every observation a key is missing counts as the largest share it got.
-template <bool BF16, int NB, int MODE, bool TAIL, int HD, int KEYS = KEYS_NONE, bool FOLD = false>
-__global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES : 2) void score_usage_kernel(ScoreArgs a) {
+template <bool BF16, int NB, int MODE, int HD, int KEYS, bool FOLD>
+struct UsageLds {
+  static constexpr int kWaves = kSweepThreads<BF16, NB, HD> / 64;
+  // u (and the last-query g) of the chunk are collected in LDS and written once at the end: stores
+  // scattered through the sweep cost the key stream 7 % of its rate
+  // (last query with 8 column blocks: LDS is needed for the query window)
+  static constexpr bool kBufG = KEYS != KEYS_NONE || (MODE == MODE_LAST && NB <= 7);
+  static constexpr int kBuf = KEYS != KEYS_NONE || !BF16 ? kKeysChunk : kScoreChunk;
+  __align__(16) float u[kBuf];  // (fold_stats uses its head as doubles and float4)
+  float g[kBufG ? kBuf : 1];
+  double c[FOLD ? kWaves : 1], v[kWaves], k2[2];
+  int32_t blk[kScoreChunk / 16];  // paged caches: this chunk's block numbers
+};
+
+template <bool BF16, int NB, int MODE, bool TAIL, int HD, int KEYS, bool FOLD, typename Lds>
+__device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit, int chunk) {
   constexpr int THREADS = kSweepThreads<BF16, NB, HD>, WAVES = THREADS / 64, STEP = THREADS / 2;  // STEP: tokens between two blocks of a wave
-  constexpr int NG = BF16 ? kGroup<NB> : NB;
+  constexpr int NG = TAIL ? 1 : BF16 ? kGroup<NB> : NB;  // (the mask and the maxima of the tail take registers)
   constexpr int QS = Tr<BF16, HD>::kQStride;
   extern __shared__ __align__(16) char qlds[];
-  if (FOLD && a.status && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *a.status = 0;  // no bounded wait on this path
-  // the second sweep walks the cache backwards: what the first sweep read last is still in the
-  // memory-side cache (about a tenth of the keys at the headline size)
-  int unit, chunk;
-  sweep_tile(a, TAIL, true, unit, chunk);
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all);
@@ -736,18 +790,16 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5, c = lane & 31;
   const int t_vis0 = T_all - a.d.W;  // newest key visible to the oldest query of the window
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
-  __shared__ int32_t blk_sm[kScoreChunk / 16];
   const int32_t* blk = nullptr;  // paged caches: this chunk's block numbers, staged once
   if (a.k.layout == AMS_LAYOUT_PAGED) {
-    stage_blocks<THREADS>(a, b, c0, t_lim, blk_sm);
-    blk = blk_sm;
+    stage_blocks<THREADS>(a, b, c0, t_lim, sm.blk);
+    blk = sm.blk;
   }
   if (c0 + wave * 32 < t_lim) load_a<BF16, HD>(a, l, b, h, c0 + wave * 32, T, lane, av0, blk, c0);
   const float q_top = load_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds);
   // KEYS: the mean key (or the sum of the unit vectors) as three bf16 terms that add up to its fp32 value, and a row of
   // zeros, behind the query window
   char* krow = qlds + NB * 32 * QS;
-  __shared__ double k2_sm[2];
   if constexpr (KEYS != KEYS_NONE) {
     if (threadIdx.x < 128) {
       double k = 0.0;
@@ -777,30 +829,23 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
       for (int o = 32; o >= 1; o >>= 1) k2 += __shfl_xor(k2, o);
       // an infinite key: the identity product spreads NaN to the channels next to it, where the sum is none
       if (__ballot(isinf(k))) k2 = INFINITY;
-      if (lane == 0) k2_sm[wave] = k2;
+      if (lane == 0) sm.k2[wave] = k2;
     }
   }
   const int key_exp = settle_q<BF16, NB, HD, THREADS>(a, l, b, h, qlds, q_top);
   const double kbar2 = KEYS != KEYS_MEAN                            ? 0.0
-                       : isinf(k2_sm[0]) || isinf(k2_sm[1]) ? INFINITY
-                                                            : k2_sm[0] + k2_sm[1];  // squared length of the mean key
+                       : isinf(sm.k2[0]) || isinf(sm.k2[1]) ? INFINITY
+                                                            : sm.k2[0] + sm.k2[1];  // squared length of the mean key
   const double inv_others = KEYS == KEYS_COS && T > 1 ? 1.0 / (double)(T - 1) : 0.0;
   float* u_row = a.u + (int64_t)unit * a.d.t_stride;
   float* g_row = a.g ? a.g + (int64_t)unit * a.d.t_stride : nullptr;
   const float c2 = a.c2;
-  // u (and the last-query g) of the chunk are collected in LDS and written once at the end: stores
-  // scattered through the sweep cost the key stream 7 % of its rate
-  // (last query with 8 column blocks: LDS is needed for the query window)
-  constexpr bool kBufG = KEYS != KEYS_NONE || (MODE == MODE_LAST && NB <= 7);
-  constexpr int kBuf = KEYS != KEYS_NONE || !BF16 ? kKeysChunk : kScoreChunk;
-  __shared__ __align__(16) float u_sm[kBuf];  // (fold_stats uses its head as doubles and float4)
-  __shared__ float g_sm[kBufG ? kBuf : 1];
-  __shared__ double c_sm[FOLD ? WAVES : 1];
+  constexpr bool kBufG = Lds::kBufG;
   float4 f[NB];
   if constexpr (FOLD) {
-    fold_stats<THREADS>(a, unit, c0, t_lim, T_all, (char*)u_sm, c_sm);
+    fold_stats<THREADS>(a, unit, c0, t_lim, T_all, (char*)sm.u, sm.c);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) f[nb] = ((const float4*)u_sm)[nb * 32 + c];
+    for (int nb = 0; nb < NB; ++nb) f[nb] = ((const float4*)sm.u)[nb * 32 + c];
     __syncthreads();
   } else {
 #pragma unroll
@@ -863,6 +908,7 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
         tile_mma<BF16, NG, HD>(av, qlds + qoff + g0 * 32 * QS, lane, acc, key_exp);
 #pragma unroll
         for (int k = 0; k < NG; ++k) col_usage(acc[k], g0 + k);
+        if (TAIL) __builtin_amdgcn_sched_barrier(0);
       }
     }
     const int t = t0 + acc_row(c >> 1, hf);
@@ -896,9 +942,9 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
     }
     if (MODE == MODE_LAST) rg = reduce16_over32(pg, c);
     if ((c & 1) == 0 && t < T) {
-      u_sm[t - c0] = ru;
+      sm.u[t - c0] = ru;
       if (kBufG)
-        g_sm[t - c0] = rg;
+        sm.g[t - c0] = rg;
       else if (g_row)
         g_row[t] = rg;
       v_part += fmaxf(ru, 0.f) + a.eps;
@@ -906,7 +952,12 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
   };
   // this wave's blocks: every WAVES-th block of 32 tokens up to the end of the chunk (or of the cache)
 #pragma unroll 1
-  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += 2 * STEP) {
+  for (int t0 = c0 + wave * 32; t0 < t_lim; t0 += (TAIL ? 1 : 2) * STEP) {
+    if constexpr (TAIL) {  // a wave has one block, seldom more: no second buffer
+      block(av0, t0);
+      if (t0 + STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + STEP, T, lane, av0, blk, c0);
+      continue;
+    }
     if (t0 + STEP < t_lim) load_a<BF16, HD>(a, l, b, h, t0 + STEP, T, lane, av1, blk, c0);
     block(av0, t0);
     if (t0 + STEP >= t_lim) break;
@@ -915,16 +966,15 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
   }
   __syncthreads();
   for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) {
-    u_row[t] = u_sm[t - c0];
-    if (kBufG) g_row[t] = g_sm[t - c0];
+    u_row[t] = sm.u[t - c0];
+    if (kBufG) g_row[t] = sm.g[t - c0];
   }
-  if (KEYS == KEYS_COS) softmax_part(g_sm, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
+  if (KEYS == KEYS_COS) softmax_part(sm.g, t_lim - c0, a.soft + (int64_t)unit * a.n_chunks + chunk);
   if (a.vc_part) {  // chunk sums of max(u,0)+eps in a fixed order: lanes, then waves
-    __shared__ double v_sm[WAVES];
     double v_acc = (double)v_part;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v_acc += __shfl_xor(v_acc, o);
-    if (lane == 0) v_sm[wave] = v_acc;
+    if (lane == 0) sm.v[wave] = v_acc;
     __syncthreads();
     if (threadIdx.x == 0) {
       // the unit's credit sum (formed between the sweeps) rides in the first chunk's entry
@@ -932,48 +982,64 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
       double v = 0.0;
 #pragma unroll
       for (int w = 0; w < WAVES; w += 2) {
-        v += v_sm[w] + v_sm[w + 1];
-        if (FOLD) c += c_sm[w] + c_sm[w + 1];
+        v += sm.v[w] + sm.v[w + 1];
+        if (FOLD) c += sm.c[w] + sm.c[w + 1];
       }
       a.vc_part[(int64_t)unit * a.n_chunks + chunk] = make_double2(v, c);
     }
   }
 }
 
-template <bool BF16, int NB, bool TAIL, int HD>
+template <bool BF16, int NB, int MODE, bool CAUSAL, int HD, int KEYS = KEYS_NONE, bool FOLD = false>
+__global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? AMS_SCORE_MIN_WAVES : 2) void score_usage_kernel(ScoreArgs a) {
+  __shared__ UsageLds<BF16, NB, MODE, HD, KEYS, FOLD> sm;
+  if (FOLD && a.status && (blockIdx.x | blockIdx.y | threadIdx.x) == 0) *a.status = 0;  // no bounded wait on this path
+  // the second sweep walks the cache backwards: what the first sweep read last is still in the
+  // memory-side cache (about a tenth of the keys at the headline size)
+  int unit, chunk;
+  const bool tail = sweep_tile<CAUSAL>(a, true, unit, chunk);
+  if constexpr (CAUSAL) {
+    if (tail) {
+      if (chunk < 0) return;
+      usage_body<BF16, NB, MODE, true, HD, KEYS, FOLD>(a, sm, unit, chunk);
+      return;
+    }
+  }
+  usage_body<BF16, NB, MODE, false, HD, KEYS, FOLD>(a, sm, unit, chunk);
+}
+
+template <bool BF16, int NB, bool CAUSAL, int HD>
 hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hipStream_t s) {
   auto launch = [&](auto moments_c) {
     constexpr int M = decltype(moments_c)::value;
-    const hipError_t e = ensure_lds<score_stats_kernel<BF16, NB, TAIL, M, HD>>(lds);
+    const hipError_t e = ensure_lds<score_stats_kernel<BF16, NB, CAUSAL, M, HD>>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, TAIL, M, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
+    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, CAUSAL, M, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
     return hipGetLastError();
   };
   if (!moments) return launch(std::integral_constant<int, MOMENTS_NONE>{});
-  if constexpr (BF16 && !TAIL && HD == 64) {
+  if constexpr (BF16 && HD == 64) {
     return launch(std::integral_constant<int, MOMENTS_CENTRED>{});
   } else {
-    if constexpr (BF16 && !TAIL && NB == 4)
-      if ((int64_t)grid.x * grid.y >= 512) return launch(std::integral_constant<int, MOMENTS_CENTRED>{});
+    if constexpr (BF16 && NB == 4)
+      if ((int64_t)a.n_chunks * a.d.units >= 512) return launch(std::integral_constant<int, MOMENTS_CENTRED>{});
     return launch(std::integral_constant<int, MOMENTS_FIRST>{});
   }
 }
 
-template <bool BF16, int NB, bool TAIL, int HD>
+template <bool BF16, int NB, bool CAUSAL, int HD>
 hipError_t launch_usage(const ScoreArgs& a, int mode, dim3 grid, int lds, hipStream_t s) {
   const dim3 blk(kSweepThreads<BF16, NB, HD>);
   hipError_t e;
   auto launch = [&](auto mode_c, auto fold_c) {
     constexpr int M = decltype(mode_c)::value;
     constexpr bool F = decltype(fold_c)::value;
-    if ((e = ensure_lds<score_usage_kernel<BF16, NB, M, TAIL, HD, KEYS_NONE, F>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((score_usage_kernel<BF16, NB, M, TAIL, HD, KEYS_NONE, F>), grid, blk, lds, s, a);
+    if ((e = ensure_lds<score_usage_kernel<BF16, NB, M, CAUSAL, HD, KEYS_NONE, F>>(lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL((score_usage_kernel<BF16, NB, M, CAUSAL, HD, KEYS_NONE, F>), grid, blk, lds, s, a);
     return hipGetLastError();
   };
   auto by_fold = [&](auto mode_c) {
-    if constexpr (!TAIL)
-      if (a.fold) return launch(mode_c, std::true_type{});
-    return launch(mode_c, std::false_type{});
+    return a.fold ? launch(mode_c, std::true_type{}) : launch(mode_c, std::false_type{});
   };
   return mode == MODE_LAST ? by_fold(std::integral_constant<int, MODE_LAST>{})
                            : by_fold(std::integral_constant<int, MODE_MEAN>{});
@@ -999,17 +1065,13 @@ hipError_t run_key_sweeps(const ScoreArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool BF16, int NB, int HD>
+template <bool BF16, int NB, bool CAUSAL, int HD>
 hipError_t run_softmax_sweeps(const ScoreArgs& a, int mode, hipStream_t s) {
   const int lds = NB * 32 * Tr<BF16, HD>::kQStride;
-  const dim3 grid(a.n_chunks, a.d.units);
+  const dim3 grid(a.n_chunks, a.d.units + (CAUSAL ? div_up(a.d.units, a.n_chunks) : 0));
   hipError_t e;
   prof_mark("score_stats", s);
-  if ((e = launch_stats<BF16, NB, false, HD>(a, mode == MODE_EXPECTED, grid, lds, s)) != hipSuccess) return e;
-  if (a.causal) {
-    prof_mark("score_stats_tail", s);
-    if ((e = launch_stats<BF16, NB, true, HD>(a, mode == MODE_EXPECTED, dim3(1, a.d.units), lds, s)) != hipSuccess) return e;
-  }
+  if ((e = launch_stats<BF16, NB, CAUSAL, HD>(a, mode == MODE_EXPECTED, grid, lds, s)) != hipSuccess) return e;
   if (!a.fold) {
     prof_mark("score_reduce", s);
     hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
@@ -1018,24 +1080,26 @@ hipError_t run_softmax_sweeps(const ScoreArgs& a, int mode, hipStream_t s) {
   ScoreArgs a2 = a;
   if (mode == MODE_EXPECTED) a2.g = nullptr;
   prof_mark("score_usage", s);
-  if ((e = launch_usage<BF16, NB, false, HD>(a2, mode, grid, lds, s)) != hipSuccess) return e;
-  if (a.causal) {
-    prof_mark("score_usage_tail", s);
-    if ((e = launch_usage<BF16, NB, true, HD>(a2, mode, dim3(1, a.d.units), lds, s)) != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return launch_usage<BF16, NB, CAUSAL, HD>(a2, mode, grid, lds, s);
 }
 
-template <bool BF16, int HD>
+template <bool BF16, bool CAUSAL, int HD>
 hipError_t run_by_nb(const ScoreArgs& a, int nb, int mode, hipStream_t s) {
-  if (nb <= 1) return run_softmax_sweeps<BF16, 1, HD>(a, mode, s);
-  if (nb <= 2) return run_softmax_sweeps<BF16, 2, HD>(a, mode, s);
-  if (nb <= 4) return run_softmax_sweeps<BF16, 4, HD>(a, mode, s);
+  if (nb <= 1) return run_softmax_sweeps<BF16, 1, CAUSAL, HD>(a, mode, s);
+  if (nb <= 2) return run_softmax_sweeps<BF16, 2, CAUSAL, HD>(a, mode, s);
+  if (nb <= 4) return run_softmax_sweeps<BF16, 4, CAUSAL, HD>(a, mode, s);
   if constexpr (BF16) {
-    if (nb <= 7) return run_softmax_sweeps<BF16, 7, HD>(a, mode, s);
-    if (nb <= 8) return run_softmax_sweeps<BF16, 8, HD>(a, mode, s);
+    if (nb <= 7) return run_softmax_sweeps<BF16, 7, CAUSAL, HD>(a, mode, s);
+    if (nb <= 8) return run_softmax_sweeps<BF16, 8, CAUSAL, HD>(a, mode, s);
   }
   return hipErrorInvalidValue;
+}
+
+template <bool CAUSAL>
+hipError_t launch_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s) {
+  if (head_dim == 64)
+    return bf16 ? run_by_nb<true, CAUSAL, 64>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 64>(a, nb, mode, s);
+  return bf16 ? run_by_nb<true, CAUSAL, 128>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 128>(a, nb, mode, s);
 }
 
 }  // namespace

@@ -301,6 +301,28 @@ def test_second_sweep_merges_the_statistics_of_small_launches(oracle, T, dtype, 
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [1] if T > 1 else [0, 1], scorer=scorer)
 
 
+@pytest.mark.parametrize("scorer", [B.SCORER_MEAN_WINDOW, B.SCORER_LAST_QUERY, B.SCORER_REDUNDANCY, B.SCORER_EXPECTED_VNORM])
+@pytest.mark.parametrize("H,T,dtype,G,W,D,folded", [(7, 300, "bf16", 4, 32, 128, True),      # 3 chunks: rows of 3, 3 and 1 tails
+                                                    (300, 130, "bf16", 1, 8, 64, True),      # 1 chunk: a tail in every row
+                                                    (2, 8192, "bf16", 2, 32, 128, True), (1, 8193, "bf16", 2, 32, 64, False),
+                                                    (3, 2304, "bf16", 7, 32, 128, True), (2, 1000, "f32", 3, 32, 128, True),
+                                                    (5, 5, "bf16", 4, 32, 128, True), (2, 160, "bf16", 1, 256, 128, True),
+                                                    (2, 700, "f32", 1, 100, 64, True)])
+def test_tails_of_a_causal_window_run_beside_the_sweeps(oracle, H, T, dtype, G, W, D, folded, scorer):
+    """The tails are the last workgroups of the sweeps' launches, a row of the grid for as many as a unit has chunks; their
+    statistics are one more entry, merged by the second sweep or by the reduction; caches shorter than the window; tails of
+    several blocks per wave."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=1, H=H, G=G, W=W, D=D, T=T, T_min=T, dtype=dtype, budget=max(1, min(96, T // 3)), S=4,
+                                 n_spans=2, span_len=(1, max(1, min(40, T // 2))), causal=True)
+    host = inputs.dense_cache(w, n_threads=4)
+    job = Job(w, host, scorer=scorer)
+    job.ws.fill_(255)
+    labels = _labels(job)
+    assert ("score_reduce" not in labels) == folded and not any("tail" in x for x in labels)
+    assert to_host(job.n_kept).tolist() == [min(w.budget, T)] * H
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), sorted({0, H // 2, H - 1}), scorer=scorer)
+
+
 @pytest.mark.parametrize("vec", [True, False])
 @pytest.mark.parametrize("T,S,fused", [(2048, 64, True), (2049, 5, True), (4096, 64, True), (4097, 7, True), (8192, 64, True),
                                        (8193, 16, False), (3000, 65, False), (63, 3, True)])
