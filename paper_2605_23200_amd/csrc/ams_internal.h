@@ -125,8 +125,10 @@ hipError_t launch_score_oneread(const ams_params* p, const Dims& d, const KvDev&
 // one (sum of max(u,0)+eps, sum of old credit) entry per unit at a.vc_part[unit] when a.vc_part is set.
 struct ScoreArgs;
 hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, hipStream_t s, bool* ran);
-// The two sweeps under the causal window (score_causal.hip).
+// The two sweeps under the causal window (score_causal.hip), with the last-query score (score_last.hip), and with both.
 hipError_t launch_causal_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
+hipError_t launch_last_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
+hipError_t launch_causal_last_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
 // The two sweeps with the key-diversity score, or the mean cosines of the redundancy-aware one, left in a.g (bf16 caches,
 // no causal window; score_keys.hip).
 hipError_t launch_key_sweeps(const ScoreArgs& a, int nb, int head_dim, bool cosines, hipStream_t s);

@@ -390,7 +390,7 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
   int mode = MODE_MEAN;
   a.g = nullptr;
   if (p->scorer == AMS_SCORER_MEAN_WINDOW) a.g = (g != u) ? g : nullptr;
-  if (p->scorer == AMS_SCORER_LAST_QUERY) { mode = MODE_LAST; a.g = g; }
+  if (p->scorer == AMS_SCORER_LAST_QUERY) { mode = newest_share_lanes(d.W) ? MODE_LAST_LANES : MODE_LAST; a.g = g; }
   const bool vnorm = p->scorer == AMS_SCORER_EXPECTED_VNORM;
   if (vnorm && !v) return hipErrorInvalidValue;
   if (p->scorer == AMS_SCORER_EXPECTED || vnorm) { mode = MODE_EXPECTED; a.g = g; }
@@ -439,7 +439,11 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     vc_even = a.even;
     keys_done = true;
   } else if (!oneread) {
-    e = causal ? launch_causal_sweeps(a, nb, d.D, mode, bf16, s) : launch_sweeps<false>(a, nb, d.D, mode, bf16, s);
+    const bool last = p->scorer == AMS_SCORER_LAST_QUERY;
+    if (causal)
+      e = last ? launch_causal_last_sweeps(a, nb, d.D, mode, bf16, s) : launch_causal_sweeps(a, nb, d.D, mode, bf16, s);
+    else
+      e = last ? launch_last_sweeps(a, nb, d.D, mode, bf16, s) : launch_sweeps<false, SCORERS_MEAN>(a, nb, d.D, mode, bf16, s);
     vc_stride = a.n_chunks;
     vc_tokens = a.chunk;
     vc_even = a.even;

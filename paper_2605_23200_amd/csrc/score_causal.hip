@@ -6,7 +6,7 @@ namespace ams {
 
 hipError_t launch_causal_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s) {
   if (!a.causal) return hipErrorInvalidValue;
-  return launch_sweeps<true>(a, nb, head_dim, mode, bf16, s);
+  return launch_sweeps<true, SCORERS_MEAN>(a, nb, head_dim, mode, bf16, s);
 }
 
 }  // namespace ams

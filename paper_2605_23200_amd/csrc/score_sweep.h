@@ -173,8 +173,8 @@ constexpr int kSweepThreads = !BF16 && NB == 4 && HD == 128 ? 2 * kThreads : kTh
 // work are the first ones of the launch, without gaps.  With a grid of (chunk, unit) the gaps repeat with the batch and leave
 // some XCDs more work than others: 192 units of 700 to 9001 positions 161 -> 145 us per step, 768 paged units of 2354 to 5384
 // 560 -> 509, 4096 paged ones of 4096 to 16384 5655 -> 5557.  A sequence per lane, so at most 64 of them.
-__device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T) {
-  return a.causal ? max(0, (T - a.d.W + 1) / 32 * 32) : T;
+__device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T, bool causal) {
+  return causal ? max(0, (T - a.d.W + 1) / 32 * 32) : T;
 }
 // Returns whether it is the unit's tail of a causal window.
 template <bool CAUSAL>
@@ -189,7 +189,7 @@ __device__ __forceinline__ bool sweep_tile(const ScoreArgs& a, bool reversed, in
   if (a.compact) {
     const int lane = threadIdx.x & 63, B = a.d.B, H = a.d.H;
     const int len = lane < B ? max(0, min(a.seq_lens[lane], a.d.t_max)) : 0;
-    const int n = (causal_t_end(a, len) + a.chunk - 1) / a.chunk;  // chunks of this lane's sequence
+    const int n = (causal_t_end(a, len, CAUSAL) + a.chunk - 1) / a.chunk;  // chunks of this lane's sequence
     int incl = n;
     incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);  // row_shr: 1, 2, 4, 8
     incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);
@@ -284,7 +284,7 @@ struct StatsLds {
 };
 
 // XCH_IN_Q: the exchange takes the place of the query window (the centred sweep needs the room).
-template <bool BF16, int NB, bool TAIL, int MOMENTS, int HD, int KEYS, bool XCH_IN_Q, typename Lds>
+template <bool BF16, int NB, bool CAUSAL, bool TAIL, int MOMENTS, int HD, int KEYS, bool XCH_IN_Q, typename Lds>
 __device__ __forceinline__ void stats_body(const ScoreArgs& a, Lds& sm, int unit, int chunk) {
   static_assert(KEYS == KEYS_NONE || (BF16 && !TAIL && !MOMENTS), "keys ride along with the plain sweeps over bf16 caches");
   constexpr bool kSpare = KEYS == KEYS_COS && HD == 128 && NB >= 7;  // see KEYS above
@@ -301,7 +301,7 @@ __device__ __forceinline__ void stats_body(const ScoreArgs& a, Lds& sm, int unit
   };
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
-  const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all);
+  const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all, CAUSAL);
   const int T = TAIL ? T_all : t_end;
   const int len = chunk_len(a, T_all);
   const int c0 = TAIL ? t_end : chunk * len;
@@ -613,19 +613,20 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4 && 
   if constexpr (CAUSAL) {
     if (tail) {
       if (chunk < 0) return;
-      stats_body<BF16, NB, true, MOMENTS ? MOMENTS_FIRST : MOMENTS_NONE, HD, KEYS_NONE, kXchInQ>(a, sm, unit, chunk);
+      stats_body<BF16, NB, CAUSAL, true, MOMENTS ? MOMENTS_FIRST : MOMENTS_NONE, HD, KEYS_NONE, kXchInQ>(a, sm, unit, chunk);
       return;
     }
   }
-  stats_body<BF16, NB, false, MOMENTS, HD, KEYS, kXchInQ>(a, sm, unit, chunk);
+  stats_body<BF16, NB, CAUSAL, false, MOMENTS, HD, KEYS, kXchInQ>(a, sm, unit, chunk);
 }
 
 // What the second sweep needs of query n: reference, weight of its shares in u and in the last-query g, whether it exists.
-__device__ __forceinline__ float4 query_weights(const ScoreArgs& a, int n, int T, float M, double Z) {
+// last: the last-query score is wanted.
+__device__ __forceinline__ float4 query_weights(const ScoreArgs& a, int n, int T, float M, double Z, bool causal, bool last) {
   const bool real = n < a.d.N;
   // causal window on a cache shorter than the window: a query before position 0 does not exist
-  const bool exists = real && (!a.causal || T - a.d.W + (n % a.d.W) >= 0);
-  const bool newest = exists && (n % a.d.W) == a.d.W - 1;
+  const bool exists = real && (!causal || T - a.d.W + (n % a.d.W) >= 0);
+  const bool newest = last && exists && (n % a.d.W) == a.d.W - 1;
   return make_float4(M, exists ? (float)(1.0 / ((double)a.d.N * Z)) : 0.f, newest ? (float)(1.0 / ((double)a.d.G * Z)) : 0.f,
                      real ? 1.f : 0.f);
 }
@@ -642,7 +643,7 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  const int len = chunk_len(a, T), nch = (causal_t_end(a, T) + len - 1) / len + (a.causal ? 1 : 0);
+  const int len = chunk_len(a, T), nch = (causal_t_end(a, T, a.causal) + len - 1) / len + (a.causal ? 1 : 0);
   const int parts = kReduceThreads / a.n_pad;
   const int n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
   if (part < parts) {
@@ -665,7 +666,7 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
     for (int q = 0; q < parts; ++q) M = fmaxf(M, pm[q * a.n_pad + n]);
     double Z = 0.0;
     for (int q = 0; q < parts; ++q) Z += pz[q * a.n_pad + n] * (double)__builtin_amdgcn_exp2f(pm[q * a.n_pad + n] - M);
-    a.fin[(int64_t)unit * a.n_pad + n] = query_weights(a, n, T, M, Z);
+    a.fin[(int64_t)unit * a.n_pad + n] = query_weights(a, n, T, M, Z, a.causal, true);
   }
   if (a.ksum && (int)threadIdx.x < a.d.D) {  // the unit's key sum takes the place of its first chunk's, for the second sweep
     double* k = a.ksum + (int64_t)unit * a.n_chunks * a.d.D + threadIdx.x;
@@ -708,7 +709,7 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
 // Merges a unit's chunk statistics inside the second sweep (launches of few workgroups, where a reduction kernel of its own
 // costs more than every workgroup reading them again): weights of query n -> ((float4*)sm)[n], sm of 4 KB; and the sums of
 // the chunk's credit before the update, per wave -> c_sm.
-template <int THREADS>
+template <int THREADS, bool CAUSAL, bool LAST>
 __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0, int t_lim, int T, char* sm, double* c_sm) {
   double* pz = (double*)sm;
   float* pm = (float*)(sm + THREADS * sizeof(double));
@@ -718,7 +719,7 @@ __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0,
 #pragma unroll 4
     for (int t = c0 + threadIdx.x; t < t_lim; t += THREADS) cs += (double)c_row[t];
   }
-  const int len = chunk_len(a, T), nch = (causal_t_end(a, T) + len - 1) / len + (a.causal ? 1 : 0);
+  const int len = chunk_len(a, T), nch = (causal_t_end(a, T, CAUSAL) + len - 1) / len + (CAUSAL ? 1 : 0);
   const int parts = THREADS / a.n_pad, n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
   if (part < parts) {
     const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
@@ -750,7 +751,7 @@ __device__ __forceinline__ void fold_stats(const ScoreArgs& a, int unit, int c0,
     for (int q = 0; q < parts; ++q) M = fmaxf(M, pm[q * a.n_pad + n]);
     double Z = 0.0;
     for (int q = 0; q < parts; ++q) Z += pz[q * a.n_pad + n] * (double)__builtin_amdgcn_exp2f(pm[q * a.n_pad + n] - M);
-    f = query_weights(a, n, T, M, Z);
+    f = query_weights(a, n, T, M, Z, CAUSAL, LAST);
   }
   __syncthreads();
   if ((int)threadIdx.x < a.n_pad) ((float4*)sm)[threadIdx.x] = f;
@@ -765,7 +766,7 @@ struct UsageLds {
   // u (and the last-query g) of the chunk are collected in LDS and written once at the end: stores
   // scattered through the sweep cost the key stream 7 % of its rate
   // (last query with 8 column blocks: LDS is needed for the query window)
-  static constexpr bool kBufG = KEYS != KEYS_NONE || (MODE == MODE_LAST && NB <= 7);
+  static constexpr bool kBufG = KEYS != KEYS_NONE || ((MODE == MODE_LAST || MODE == MODE_LAST_LANES) && NB <= 7);
   static constexpr int kBuf = KEYS != KEYS_NONE || !BF16 ? kKeysChunk : kScoreChunk;
   __align__(16) float u[kBuf];  // (fold_stats uses its head as doubles and float4)
   float g[kBufG ? kBuf : 1];
@@ -773,7 +774,7 @@ struct UsageLds {
   int32_t blk[kScoreChunk / 16];  // paged caches: this chunk's block numbers
 };
 
-template <bool BF16, int NB, int MODE, bool TAIL, int HD, int KEYS, bool FOLD, typename Lds>
+template <bool BF16, int NB, int MODE, bool CAUSAL, bool TAIL, int HD, int KEYS, bool FOLD, typename Lds>
 __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit, int chunk) {
   constexpr int THREADS = kSweepThreads<BF16, NB, HD>, WAVES = THREADS / 64, STEP = THREADS / 2;  // STEP: tokens between two blocks of a wave
   constexpr int NG = TAIL ? 1 : BF16 ? kGroup<NB> : NB;  // (the mask and the maxima of the tail take registers)
@@ -781,7 +782,7 @@ __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit
   extern __shared__ __align__(16) char qlds[];
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
-  const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all);
+  const int T_all = seq_len(a.d, a.seq_lens, b), t_end = causal_t_end(a, T_all, CAUSAL);
   const int T = TAIL ? T_all : t_end;
   const int len = chunk_len(a, T_all);
   const int c0 = TAIL ? t_end : chunk * len;
@@ -843,7 +844,7 @@ __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit
   constexpr bool kBufG = Lds::kBufG;
   float4 f[NB];
   if constexpr (FOLD) {
-    fold_stats<THREADS>(a, unit, c0, t_lim, T_all, (char*)sm.u, sm.c);
+    fold_stats<THREADS, CAUSAL, MODE == MODE_LAST>(a, unit, c0, t_lim, T_all, (char*)sm.u, sm.c);
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) f[nb] = ((const float4*)sm.u)[nb * 32 + c];
     __syncthreads();
@@ -941,6 +942,7 @@ __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit
       }
     }
     if (MODE == MODE_LAST) rg = reduce16_over32(pg, c);
+    if (MODE == MODE_LAST_LANES) rg = newest_lanes(pu, c, a.d.W);
     if ((c & 1) == 0 && t < T) {
       sm.u[t - c0] = ru;
       if (kBufG)
@@ -1001,14 +1003,18 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
   if constexpr (CAUSAL) {
     if (tail) {
       if (chunk < 0) return;
-      usage_body<BF16, NB, MODE, true, HD, KEYS, FOLD>(a, sm, unit, chunk);
+      usage_body<BF16, NB, MODE, CAUSAL, true, HD, KEYS, FOLD>(a, sm, unit, chunk);
       return;
     }
   }
-  usage_body<BF16, NB, MODE, false, HD, KEYS, FOLD>(a, sm, unit, chunk);
+  usage_body<BF16, NB, MODE, CAUSAL, false, HD, KEYS, FOLD>(a, sm, unit, chunk);
 }
 
-template <bool BF16, int NB, bool CAUSAL, int HD>
+// Scorers that a source file instantiates the sweeps for (with all of them in one code object 8 units of 32768 positions took
+// 70.2 us per step, 68.4 with the last query's in one of their own).
+enum { SCORERS_MEAN = 0, SCORERS_LAST = 1 };
+
+template <bool BF16, int NB, bool CAUSAL, int HD, int SCORERS>
 hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hipStream_t s) {
   auto launch = [&](auto moments_c) {
     constexpr int M = decltype(moments_c)::value;
@@ -1018,7 +1024,9 @@ hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hi
     return hipGetLastError();
   };
   if (!moments) return launch(std::integral_constant<int, MOMENTS_NONE>{});
-  if constexpr (BF16 && HD == 64) {
+  if constexpr (SCORERS == SCORERS_LAST) {
+    return hipErrorInvalidValue;
+  } else if constexpr (BF16 && HD == 64) {
     return launch(std::integral_constant<int, MOMENTS_CENTRED>{});
   } else {
     if constexpr (BF16 && NB == 4)
@@ -1027,7 +1035,7 @@ hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hi
   }
 }
 
-template <bool BF16, int NB, bool CAUSAL, int HD>
+template <bool BF16, int NB, bool CAUSAL, int HD, int SCORERS>
 hipError_t launch_usage(const ScoreArgs& a, int mode, dim3 grid, int lds, hipStream_t s) {
   const dim3 blk(kSweepThreads<BF16, NB, HD>);
   hipError_t e;
@@ -1041,8 +1049,12 @@ hipError_t launch_usage(const ScoreArgs& a, int mode, dim3 grid, int lds, hipStr
   auto by_fold = [&](auto mode_c) {
     return a.fold ? launch(mode_c, std::true_type{}) : launch(mode_c, std::false_type{});
   };
-  return mode == MODE_LAST ? by_fold(std::integral_constant<int, MODE_LAST>{})
-                           : by_fold(std::integral_constant<int, MODE_MEAN>{});
+  if constexpr (SCORERS == SCORERS_LAST) {
+    if (mode == MODE_LAST_LANES) return by_fold(std::integral_constant<int, MODE_LAST_LANES>{});
+    return mode == MODE_LAST ? by_fold(std::integral_constant<int, MODE_LAST>{}) : hipErrorInvalidValue;
+  } else {
+    return by_fold(std::integral_constant<int, MODE_MEAN>{});
+  }
 }
 
 // The two plain sweeps with the keys riding along.
@@ -1065,13 +1077,13 @@ hipError_t run_key_sweeps(const ScoreArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool BF16, int NB, bool CAUSAL, int HD>
+template <bool BF16, int NB, bool CAUSAL, int HD, int SCORERS>
 hipError_t run_softmax_sweeps(const ScoreArgs& a, int mode, hipStream_t s) {
   const int lds = NB * 32 * Tr<BF16, HD>::kQStride;
   const dim3 grid(a.n_chunks, a.d.units + (CAUSAL ? div_up(a.d.units, a.n_chunks) : 0));
   hipError_t e;
   prof_mark("score_stats", s);
-  if ((e = launch_stats<BF16, NB, CAUSAL, HD>(a, mode == MODE_EXPECTED, grid, lds, s)) != hipSuccess) return e;
+  if ((e = launch_stats<BF16, NB, CAUSAL, HD, SCORERS>(a, mode == MODE_EXPECTED, grid, lds, s)) != hipSuccess) return e;
   if (!a.fold) {
     prof_mark("score_reduce", s);
     hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
@@ -1080,26 +1092,26 @@ hipError_t run_softmax_sweeps(const ScoreArgs& a, int mode, hipStream_t s) {
   ScoreArgs a2 = a;
   if (mode == MODE_EXPECTED) a2.g = nullptr;
   prof_mark("score_usage", s);
-  return launch_usage<BF16, NB, CAUSAL, HD>(a2, mode, grid, lds, s);
+  return launch_usage<BF16, NB, CAUSAL, HD, SCORERS>(a2, mode, grid, lds, s);
 }
 
-template <bool BF16, bool CAUSAL, int HD>
+template <bool BF16, bool CAUSAL, int HD, int SCORERS>
 hipError_t run_by_nb(const ScoreArgs& a, int nb, int mode, hipStream_t s) {
-  if (nb <= 1) return run_softmax_sweeps<BF16, 1, CAUSAL, HD>(a, mode, s);
-  if (nb <= 2) return run_softmax_sweeps<BF16, 2, CAUSAL, HD>(a, mode, s);
-  if (nb <= 4) return run_softmax_sweeps<BF16, 4, CAUSAL, HD>(a, mode, s);
+  if (nb <= 1) return run_softmax_sweeps<BF16, 1, CAUSAL, HD, SCORERS>(a, mode, s);
+  if (nb <= 2) return run_softmax_sweeps<BF16, 2, CAUSAL, HD, SCORERS>(a, mode, s);
+  if (nb <= 4) return run_softmax_sweeps<BF16, 4, CAUSAL, HD, SCORERS>(a, mode, s);
   if constexpr (BF16) {
-    if (nb <= 7) return run_softmax_sweeps<BF16, 7, CAUSAL, HD>(a, mode, s);
-    if (nb <= 8) return run_softmax_sweeps<BF16, 8, CAUSAL, HD>(a, mode, s);
+    if (nb <= 7) return run_softmax_sweeps<BF16, 7, CAUSAL, HD, SCORERS>(a, mode, s);
+    if (nb <= 8) return run_softmax_sweeps<BF16, 8, CAUSAL, HD, SCORERS>(a, mode, s);
   }
   return hipErrorInvalidValue;
 }
 
-template <bool CAUSAL>
+template <bool CAUSAL, int SCORERS>
 hipError_t launch_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s) {
   if (head_dim == 64)
-    return bf16 ? run_by_nb<true, CAUSAL, 64>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 64>(a, nb, mode, s);
-  return bf16 ? run_by_nb<true, CAUSAL, 128>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 128>(a, nb, mode, s);
+    return bf16 ? run_by_nb<true, CAUSAL, 64, SCORERS>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 64, SCORERS>(a, nb, mode, s);
+  return bf16 ? run_by_nb<true, CAUSAL, 128, SCORERS>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 128, SCORERS>(a, nb, mode, s);
 }
 
 }  // namespace

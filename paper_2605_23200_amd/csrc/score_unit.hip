@@ -18,11 +18,12 @@ constexpr int kUnitThreads = 512, kUnitWaves = kUnitThreads / 64;
 template <bool BF16, int NB, int MODE, int HD>
 __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a) {
   constexpr int NG = (BF16 && NB % 2 == 0 && NB >= 4) ? NB / 2 : NB, QS = Tr<BF16, HD>::kQStride, NQ = NB * 32;
+  constexpr bool kLast = MODE == MODE_LAST || MODE == MODE_LAST_LANES;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch[kUnitWaves][NQ];
   __shared__ float4 fin_s[NQ];
   __shared__ float u_sm[kScoreChunk];
-  __shared__ float g_sm[MODE == MODE_LAST ? kScoreChunk : 1];
+  __shared__ float g_sm[kLast ? kScoreChunk : 1];
   __shared__ double2 vc_sm[kUnitWaves];
   const int unit = blockIdx.x;
   if (unit == 0 && threadIdx.x == 0 && a.status) *a.status = 0;  // no bounded wait on this path
@@ -144,9 +145,10 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
     const float ru = reduce16_over32(pu, c);
     float rg = ru;
     if (MODE == MODE_LAST) rg = reduce16_over32(pg, c);
+    if (MODE == MODE_LAST_LANES) rg = newest_lanes(pu, c, a.d.W);
     if ((c & 1) == 0 && t < T) {
       u_sm[t] = ru;
-      if (MODE == MODE_LAST) g_sm[t] = rg;
+      if (kLast) g_sm[t] = rg;
       v_part += fmaxf(ru, 0.f) + a.eps;
     }
   };
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
   float* g_row = a.g ? a.g + (int64_t)unit * a.d.t_stride : nullptr;
   for (int t = threadIdx.x; t < T; t += kUnitThreads) {
     u_row[t] = u_sm[t];
-    if (g_row) g_row[t] = MODE == MODE_LAST ? g_sm[t] : u_sm[t];
+    if (g_row) g_row[t] = kLast ? g_sm[t] : u_sm[t];
   }
   if (a.vc_part) {  // the unit's sums of max(u,0)+eps and of the old credit: lanes, then waves, fixed order
     double v_acc = (double)v_part, c_acc = 0.0;
@@ -203,6 +205,7 @@ hipError_t unit_by_nb(const ScoreArgs& a, int nb, int mode, hipStream_t s, bool*
 #define AMS_UNIT_CASE(NBV)                                                           \
   if (nb <= NBV) {                                                                   \
     if (mode == MODE_LAST) return launch_unit<BF16, NBV, MODE_LAST, HD>(a, s);       \
+    if (mode == MODE_LAST_LANES) return launch_unit<BF16, NBV, MODE_LAST_LANES, HD>(a, s); \
     return launch_unit<BF16, NBV, MODE_MEAN, HD>(a, s);                              \
   }
   AMS_UNIT_CASE(1)

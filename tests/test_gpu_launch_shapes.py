@@ -323,6 +323,18 @@ def test_tails_of_a_causal_window_run_beside_the_sweeps(oracle, H, T, dtype, G, 
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), sorted({0, H // 2, H - 1}), scorer=scorer)
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("units,T", [(2, 700), (130, 200), (40, 1500)])          # merged by the second sweep, one launch, both
+@pytest.mark.parametrize("dtype,G,W", [("bf16", 4, 32), ("bf16", 128, 1), ("bf16", 5, 2), ("bf16", 7, 16), ("bf16", 2, 64), ("bf16", 3, 24),
+                                       ("bf16", 7, 32), ("f32", 3, 8), ("f32", 2, 40)])
+def test_last_query_in_windows_of_any_length(oracle, dtype, G, W, units, T, causal):
+    """Windows of 1, 2, 8, 16 and 32 queries, whose newest ones share lanes, and windows that need a sum of their own; padded
+    query columns in those lanes."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=1, H=units, G=G, W=W, T=T, T_min=T, dtype=dtype, budget=40, S=4, n_spans=2,
+                                 span_len=(4, 30), causal=causal)
+    _run(oracle, w, scorer=B.SCORER_LAST_QUERY, units=sorted({0, units // 2, units - 1}))
+
+
 @pytest.mark.parametrize("vec", [True, False])
 @pytest.mark.parametrize("T,S,fused", [(2048, 64, True), (2049, 5, True), (4096, 64, True), (4097, 7, True), (8192, 64, True),
                                        (8193, 16, False), (3000, 65, False), (63, 3, True)])
