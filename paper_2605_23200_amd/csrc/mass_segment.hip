@@ -36,6 +36,7 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kMaxSegments = 1024;
 
 // Sum over the workgroup, same value in every thread, fixed order.
+template <int WAVES = kWaves>
 __device__ __forceinline__ double block_sum(double v, double* sm) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
@@ -44,7 +45,7 @@ __device__ __forceinline__ double block_sum(double v, double* sm) {
   __syncthreads();
   double t = 0.0;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) t += sm[w];
+  for (int w = 0; w < WAVES; ++w) t += sm[w];
   return t;
 }
 
@@ -72,6 +73,28 @@ __device__ __forceinline__ void store_run(float* row, int j0, int T, bool vec, c
 #pragma unroll
     for (int i = 0; i < N; ++i)
       if (j0 + i < T) row[j0 + i] = x[i];
+  }
+}
+
+// Mean of u over the positions t - r .. t + r that exist, for the four positions from t0 on, from one walk over the scores that
+// they see; tile[e] is position t0 - r, positions that do not exist hold zeros.
+__device__ __forceinline__ void pool_run(const float* tile, int e, int t0, int T, int r, float (&pooled)[4]) {
+  const double inv_full = 1.0 / (double)(2 * r + 1);
+  double sum[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int q = 0; q < 2 * r + 4; q += 4) {
+    const float4 x4 = *reinterpret_cast<const float4*>(&tile[e + q]);
+    const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (q + j >= i && q + j <= i + 2 * r) sum[i] += (double)x[j];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int t = t0 + i;
+    const int n = min(T - 1, t + r) - max(0, t - r) + 1;
+    pooled[i] = (float)(n == 2 * r + 1 ? sum[i] * inv_full : sum[i] / (double)n);
   }
 }
 
@@ -130,28 +153,14 @@ __global__ __launch_bounds__(kBlock) void vc_sums_kernel(MsArgs a, const float* 
     }
     __syncthreads();
     float* out = pooled_all + (int64_t)unit * a.d.t_stride;
-    const double inv_full = 1.0 / (double)(2 * r + 1);
 #pragma unroll
-    for (int rd = 0; rd < ROUNDS; ++rd) {  // four positions per thread from one walk over the scores they see
+    for (int rd = 0; rd < ROUNDS; ++rd) {
       const int e = (rd * kBlock + (int)threadIdx.x) * 4;
-      double sum[4] = {0.0, 0.0, 0.0, 0.0};
-      for (int q = 0; q < 2 * r + 4; q += 4) {
-        const float4 x4 = *reinterpret_cast<const float4*>(&tile[e + q]);  // positions that do not exist hold zeros
-        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (q + j >= i && q + j <= i + 2 * r) sum[i] += (double)x[j];
-      }
       float pooled[4];
+      pool_run(tile, e, c0 + e, T, r, pooled);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t = c0 + e + i;
-        const int n = min(T - 1, t + r) - max(0, t - r) + 1;
-        pooled[i] = (float)(n == 2 * r + 1 ? sum[i] * inv_full : sum[i] / (double)n);
-        if (t < T) v += fmax((double)pooled[i], 0.0) + (double)eps_f;
-      }
+      for (int i = 0; i < 4; ++i)
+        if (c0 + e + i < T) v += fmax((double)pooled[i], 0.0) + (double)eps_f;
       store_run(out, c0 + e, T, a.vec, pooled);
     }
   }
@@ -202,6 +211,14 @@ __device__ __forceinline__ void sub_scan(const float (&x)[4], double (&p)[4]) {
 struct MassOf {
   double lam, bet, eps, inv_z, inv_csum;
   bool ema;
+  __device__ __forceinline__ MassOf(float lambda, float beta, float eps_f, double Z, double c_old)
+      : lam((double)lambda), bet((double)beta), eps((double)eps_f), ema(lambda != 0.f) {
+    normalise(Z, c_old);
+  }
+  __device__ __forceinline__ void normalise(double Z, double c_old) {
+    inv_z = 1.0 / Z;
+    inv_csum = 1.0 / (lam * c_old + (1.0 - lam));
+  }
   __device__ __forceinline__ MassOf(const MsArgs& a, int unit, int T, float lambda, float beta, float eps_f)
       : lam((double)lambda), bet((double)beta), eps((double)eps_f), ema(lambda != 0.f) {
     const int tokens = a.vc_even && T != a.d.t_max ? even_chunk(T, a.vc_stride) : a.vc_tokens;
@@ -218,8 +235,7 @@ struct MassOf {
       Z += __shfl_xor(Z, o);
       c_old += __shfl_xor(c_old, o);
     }
-    inv_z = 1.0 / Z;
-    inv_csum = 1.0 / (lam * c_old + (1.0 - lam));
+    normalise(Z, c_old);
   }
   // m_used of a position with usage u; its credit is replaced by the new one
   __device__ __forceinline__ float operator()(float u, float& credit) const {
@@ -366,7 +382,8 @@ __device__ __forceinline__ int split_merge_pass(Cut cut, int K, int T, int l_min
 //   CUTS_STAGE    ams_mass_segment: no quotas, any sign of m_used (the bisection runs over the largest prefix so far)
 //   CUTS_OWN      the same without the sums of 64 in memory: the workgroup forms them from m_used, in the same order
 //   CUTS_MASS     CUTS_STEP for caches of up to 8 * BLOCK positions, which forms the masses itself (mass_kernel's arithmetic)
-enum { CUTS_STEP = 0, CUTS_GENERAL = 1, CUTS_STAGE = 2, CUTS_OWN = 3, CUTS_MASS = 4 };
+//   CUTS_ALL      CUTS_GENERAL for caches of up to 4 * ROUNDS * BLOCK, from the usage alone: pooling, normalisers, masses as well
+enum { CUTS_STEP = 0, CUTS_GENERAL = 1, CUTS_STAGE = 2, CUTS_OWN = 3, CUTS_MASS = 4, CUTS_ALL = 5 };
 constexpr int kStepMaxSeg = 64;
 
 struct CutsOut {
@@ -381,14 +398,14 @@ struct CutsOut {
   float lambda, beta, eps;
 };
 
-template <int BLOCK, int KIND>
+template <int BLOCK, int KIND, int ROUNDS = 2>
 __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel(MsArgs a, const float* m_all, CutsOut o) {
   constexpr int kW = BLOCK / 64, kPerThread = 4, kCapSub = BLOCK * kPerThread, kGroups16 = BLOCK / kSubLanes;
-  constexpr bool kOwn = KIND == CUTS_OWN, kSigned = KIND == CUTS_STAGE || kOwn, kMass = KIND == CUTS_MASS;
-  constexpr bool kStep = KIND == CUTS_STEP || kMass;  // thresholds k/S, few of them
+  constexpr bool kOwn = KIND == CUTS_OWN, kSigned = KIND == CUTS_STAGE || kOwn, kAll = KIND == CUTS_ALL, kMass = KIND == CUTS_MASS || kAll;
+  constexpr bool kStep = KIND == CUTS_STEP || KIND == CUTS_MASS;  // thresholds k/S, few of them
   constexpr int kCap = kStep ? kStepMaxSeg : kMaxSegments;
-  constexpr int ROUNDS = 2;  // CUTS_MASS: runs of four positions per thread
-  __shared__ __align__(16) float m_sm[kMass ? BLOCK * 4 * ROUNDS : 4];
+  __shared__ __align__(16) float m_sm[kMass ? BLOCK * 4 * ROUNDS + (kAll ? 2 * kMaxPoolR + 4 : 0) : 4];
+  __shared__ double piece_sm[kAll ? BLOCK * 4 * ROUNDS / kSub : 1];  // the sums of 64, which the prefixes replace
   __shared__ double ends[kCapSub];                   // prefix at the end of every piece of the group
   __shared__ double peak[kSigned ? kCapSub : 1];     // largest prefix up to the end of the piece
   __shared__ double wave_tot[kW], wave_top[kSigned ? kW : 1];
@@ -426,7 +443,37 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
         load_run(u, j0, T, a.vec, ux[r], 0.f);
         load_run(credit, j0, T, a.vec, cx[r], 0.f);
       }
-      const MassOf mass(a, unit, T, o.lambda, o.beta, o.eps);
+      double Z = 0.0, c_old = 0.0;
+      if constexpr (kAll) {
+        if (a.pool_r > 0) {  // tile[e] = position e - pool_r
+          for (int e = threadIdx.x; e < a.pool_r; e += BLOCK) {
+            m_sm[e] = 0.f;
+            m_sm[BLOCK * 4 * ROUNDS + a.pool_r + e] = 0.f;
+          }
+#pragma unroll
+          for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) m_sm[(r * BLOCK + (int)threadIdx.x) * 4 + i + a.pool_r] = ux[r][i];  // (0 past the end)
+          __syncthreads();
+#pragma unroll
+          for (int r = 0; r < ROUNDS; ++r) {
+            const int j0 = (r * BLOCK + (int)threadIdx.x) * 4;
+            pool_run(m_sm, j0, j0, T, a.pool_r, ux[r]);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if ((r * BLOCK + (int)threadIdx.x) * 4 + i < T) {
+              Z += fmax((double)ux[r][i], 0.0) + (double)o.eps;
+              c_old += (double)cx[r][i];
+            }
+        Z = block_sum<kW>(Z, wave_tot);
+        c_old = block_sum<kW>(c_old, wave_tot);
+        __syncthreads();  // wave_tot and the tile are written again
+      }
+      const MassOf mass = kAll ? MassOf(o.lambda, o.beta, o.eps, Z, c_old) : MassOf(a, unit, T, o.lambda, o.beta, o.eps);
 #pragma unroll
       for (int r = 0; r < ROUNDS; ++r) {
         const int j0 = (r * BLOCK + (int)threadIdx.x) * 4;
@@ -436,7 +483,10 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
         *reinterpret_cast<float4*>(&m_sm[j0]) = make_float4(mu[0], mu[1], mu[2], mu[3]);
         double p[4];
         sub_scan(mu, p);
-        if (l16 == kSubLanes - 1 && j0 - (kSub - 4) < T) ends[j0 / kSub] = p[3];
+        if (l16 == kSubLanes - 1 && j0 - (kSub - 4) < T) {
+          ends[j0 / kSub] = p[3];
+          if (kAll) piece_sm[j0 / kSub] = p[3];
+        }
         store_run(credit, j0, T, a.vec, cx[r]);
         store_run(out, j0, T, a.vec, mu);
       }
@@ -604,8 +654,16 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
       if (hi > lo) {
         const int t0 = q0 * kSub + l16 * 4, t1 = q1 * kSub + l16 * 4;
         float x0[4], x1[4] = {0.f, 0.f, 0.f, 0.f};
-        load_run(m_used, t0, hi, a.vec, x0, 0.f);
-        if (q1 > q0) load_run(m_used, t1, hi, a.vec, x1, 0.f);
+        if constexpr (kMass) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            x0[i] = t0 + i < hi ? m_sm[t0 + i] : 0.f;
+            if (q1 > q0 && t1 + i < hi) x1[i] = m_sm[t1 + i];
+          }
+        } else {
+          load_run(m_used, t0, hi, a.vec, x0, 0.f);
+          if (q1 > q0) load_run(m_used, t1, hi, a.vec, x1, 0.f);
+        }
         if (kOwn && n_sub > kCapSub) {
           for (int q = q0 + 1; q < q1; q += 4) {
             float x[4][4];
@@ -623,7 +681,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 1) void unit_cuts_kernel
 #pragma unroll 4
           for (int q = q0 + 1 + l16; q < q1; q += kSubLanes) {
             const int64_t at = (int64_t)unit * a.n_sub + q;
-            sum += kOwn ? peak[q] : kSigned ? ((const double2*)a.sub)[at].x : a.sub[at];
+            sum += kAll ? piece_sm[q] : kOwn ? peak[q] : kSigned ? ((const double2*)a.sub)[at].x : a.sub[at];
           }
         }
 #pragma unroll
@@ -806,7 +864,14 @@ hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* s
   const bool must = p->n_sink > 0 || p->n_last > 0;
   if (must && !flags) return hipErrorInvalidValue;
   const float* usage = u;
-  if (vc.have && a.pool_r == 0) {  // left by the scorer (sums of the unsmoothed usage)
+  // The scorer has left no sums (pooled usage, causal window): a workgroup per unit pools the usage of a short cache, forms its
+  // normalisers and masses and finds the cuts, one launch where there were three.  us per step: 48.0 -> 42.2 (12 units of 1284,
+  // the paper's options), 56.1 -> 50.7 (3 of 4093), 145 -> 137 (180 of 3731), 377 -> 362 (512 of 2000), 67.5 -> 64.8 (4 of 5105),
+  // 376 -> 362 (256 of 8000), 718 -> 705 (512 of 8192).  From 4097 positions on 512 threads with 16 positions each; 1024 threads
+  // with 8 spill (376 -> 372, 74 -> 77 for 32 units of 4791).  Same limits as CUTS_MASS below.
+  const bool all = !(vc.have && a.pool_r == 0) && d.t_max <= 8192 && d.units <= 512;
+  if (all) {  // (unit_cuts_kernel forms the sums)
+  } else if (vc.have && a.pool_r == 0) {  // left by the scorer (sums of the unsmoothed usage)
     a.vc_stride = vc.stride;
     a.vc_tokens = vc.tokens;
     a.vc_even = vc.even;
@@ -821,6 +886,16 @@ hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* s
   // 172.2 -> 170.8 for 256 of 2176.  Up to 512 units; more of them keep the whole chip busy with the position-wise kernel
   // (1152 ragged units of 2435: 230.7 without and 235.3 with, 768 of 5384: 548 and 573).  At 16384 positions there is no gain
   // any more (24 units of 9804: 91 without and 97 with).
+  if (all) {
+    prof_mark("unit_mass_cuts", s);
+    if (d.t_max <= 2048)
+      hipLaunchKernelGGL((unit_cuts_kernel<256, CUTS_ALL>), dim3(d.units), dim3(256), 0, s, a, m_used, o);
+    else if (d.t_max <= 4096)
+      hipLaunchKernelGGL((unit_cuts_kernel<512, CUTS_ALL>), dim3(d.units), dim3(512), 0, s, a, m_used, o);
+    else
+      hipLaunchKernelGGL((unit_cuts_kernel<512, CUTS_ALL, 4>), dim3(d.units), dim3(512), 0, s, a, m_used, o);
+    return hipGetLastError();
+  }
   if (p->seg_delta == 0.f && p->n_segments <= kStepMaxSeg && d.t_max <= 8192 && d.units <= 512) {
     prof_mark("unit_mass_cuts", s);
     if (d.t_max <= 2048)

@@ -336,6 +336,39 @@ def test_last_query_in_windows_of_any_length(oracle, dtype, G, W, units, T, caus
 
 
 @pytest.mark.parametrize("vec", [True, False])
+@pytest.mark.parametrize("T,S,delta,l_min,l_max,pool,causal,must,one", [
+    (2048, 24, 0.1, 16, 256, 5, True, True, True), (2049, 24, 0.1, 16, 256, 5, True, True, True),
+    (4096, 30, 0.1, 16, 256, 63, False, False, True), (4097, 32, 0.1, 0, 256, 3, True, False, True),
+    (8192, 60, 0.1, 16, 200, 5, True, True, True), (8193, 60, 0.1, 16, 200, 5, True, True, False),
+    (3000, 70, 0.0, 0, 0, 0, True, False, True), (1000, 8, 0.0, 0, 0, 31, False, True, True),
+    (63, 12, 0.1, 4, 0, 63, False, False, True), (1, 12, 0.1, 0, 0, 3, True, False, True), (700, 1000, 0.001, 0, 0, 5, False, False, True)])
+def test_short_caches_form_everything_after_the_scores_in_one_launch(oracle, T, S, delta, l_min, l_max, pool, causal, must, one, vec):
+    """Pooled usage or a causal window: pooling, normalisers, masses, cuts and quotas in one workgroup per unit; its three sizes
+    and their edges, the widest pool, ragged and empty sequences, 1000 segments, rows of odd stride."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=3, H=2, G=1, W=8, T=T, T_min=T, budget=max(1, T // 5), S=S, n_spans=3, span_len=(1, max(1, min(30, T))),
+                                 causal=causal, pool_kernel=pool, seg_delta=delta, l_min=l_min, l_max=l_max,
+                                 n_sink=4 * must, n_last=32 * must)
+    host = inputs.dense_cache(w, n_threads=4)
+    host["seq_lens"][:] = [T, 0, max(1, T // 2 - 1)]
+    credit = np.abs(np.random.default_rng(T + S).standard_normal((6, T))).astype(np.float32)
+    credit /= credit.sum(1, keepdims=True)
+    for i, n in enumerate(n for n in host["seq_lens"] for _ in range(2)):
+        credit[i, n:] = 0
+    job = Job(w, host, credit=credit)
+    if not vec:
+        job.t_stride = job.p.t_stride = T | 1
+        job.credit = torch.zeros((job.units, job.t_stride), device=DEV)
+        job.credit[:, :T] = to_dev(credit)
+        job.ws = torch.zeros(B.ams_workspace_bytes(job.p), dtype=torch.uint8, device=DEV)
+    labels = _labels(job)
+    assert ("unit_mass_cuts" in labels) == one and ("mass_ema" in labels) != one and ("vc_sums" in labels) != one
+    assert to_host(job.n_kept).tolist() == [min(w.budget, int(t)) for t in host["seq_lens"] for _ in range(2)]
+    before = np.zeros((6, job.t_max), np.float32)
+    before[:, :T] = credit
+    check_units(oracle, job, host, before, [0, 1, 4, 5])
+
+
+@pytest.mark.parametrize("vec", [True, False])
 @pytest.mark.parametrize("T,S,fused", [(2048, 64, True), (2049, 5, True), (4096, 64, True), (4097, 7, True), (8192, 64, True),
                                        (8193, 16, False), (3000, 65, False), (63, 3, True)])
 def test_short_caches_form_masses_and_cuts_in_one_launch(oracle, T, S, fused, vec):
