@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include "ams_internal.h"
+#include "mass_cuts.h"
 
 namespace ams {
 
@@ -410,13 +411,15 @@ int ams_compress_step(const ams_params* p, const ams_kv_view* src, const int32_t
   float* seg_mass = (float*)(w + wl.seg_mass);
   int32_t* quota = (int32_t*)(w + wl.quota);
   hipError_t e;
-  VcInfo vc{false, 0, 0, false};
+  UnitCuts cuts;
+  if (unit_cuts_args(p, d, seq_lens, u, credit, m_used, bounds, seg_mass, quota, idx, n_kept, (uint32_t*)(w + wl.flags), wl.n_words,
+                     w, wl, &cuts) != hipSuccess)
+    return AMS_ERR_HIP;
+  VcInfo vc{unit_scorer_cuts(p) ? &cuts : nullptr, false, false, 0, 0, false};
   const KvDev vdev = make_kv(p, src, src->v);
   if ((e = launch_score(p, d, make_kv(p, src, src->k), &vdev, seq_lens, q, u, g, credit, &vc, w, wl, s)) != hipSuccess)
     return status_of(e);
-  if ((e = launch_unit_mass(p, d, seq_lens, u, credit, m_used, bounds, seg_mass, quota, idx, n_kept,
-                            (uint32_t*)(w + wl.flags), wl.n_words, vc, w, wl, s)) != hipSuccess)
-    return AMS_ERR_HIP;
+  if ((e = launch_unit_mass(p, d, seq_lens, cuts, vc, s)) != hipSuccess) return AMS_ERR_HIP;
   const Gather ga{make_kv(p, src, src->k), vdev, make_kv(p, dst, dst->k), make_kv(p, dst, dst->v), credit, credit_dst};
   const bool fused = select_gathers(p);
   if ((e = launch_select(p, d, seq_lens, g, bounds, seg_mass, quota, idx, n_kept, (uint32_t*)(w + wl.flags),

@@ -87,7 +87,10 @@ struct WsLayout {
 WsLayout ws_layout(const ams_params* p);
 
 // Where the scorer left the per-chunk sums that Eq. (1) and the EMA need (have = false: nowhere).
+struct UnitCuts;
 struct VcInfo {
+  const UnitCuts* unit_cuts;  // what the scorer may do beyond the scores; NULL: nothing
+  bool cuts;                  // it has
   bool have;
   int stride;  // entries per unit row of ws + wl.vc_part
   int tokens;  // positions covered by one entry
@@ -122,9 +125,10 @@ hipError_t launch_score_oneread(const ams_params* p, const Dims& d, const KvDev&
                                 int* vc_stride, int* vc_tokens, char* ws, const WsLayout& wl,
                                 hipStream_t s, bool* ran);
 // The one-launch scorer for short caches (score_unit.hip); *ran = false when it does not apply.  It leaves
-// one (sum of max(u,0)+eps, sum of old credit) entry per unit at a.vc_part[unit] when a.vc_part is set.
+// one (sum of max(u,0)+eps, sum of old credit) entry per unit at a.vc_part[unit] when a.vc_part is set, or (cuts given) goes on
+// to the quotas.
 struct ScoreArgs;
-hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, hipStream_t s, bool* ran);
+hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, const UnitCuts* cuts, hipStream_t s, bool* ran);
 // The two sweeps under the causal window (score_causal.hip), with the last-query score (score_last.hip), and with both.
 hipError_t launch_causal_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
 hipError_t launch_last_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
@@ -145,11 +149,13 @@ hipError_t launch_segment_static(const ams_params* p, const Dims& d, const int32
                                  WsLayout wl, hipStream_t s);
 // The fused step's mass / EMA / segmentation / quota stages; it also
 // leaves the -1 tail of idx, the kept counts and the cleared bitmap, so launch_select follows with
-// quota_done = true.  vc: the chunk sums the scorer left, if any.
-hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* u,
-                            float* credit, float* m_used, int32_t* bounds, float* seg_mass, int32_t* quota,
-                            int32_t* idx, int32_t* n_kept, uint32_t* flags, int n_words, const VcInfo& vc,
-                            char* ws, const WsLayout& wl, hipStream_t s);
+// quota_done = true.  vc: the chunk sums the scorer left, if any, or that it has done all of this.
+hipError_t unit_cuts_args(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* u, float* credit, float* m_used,
+                          int32_t* bounds, float* seg_mass, int32_t* quota, int32_t* idx, int32_t* n_kept, uint32_t* flags,
+                          int n_words, char* ws, const WsLayout& wl, UnitCuts* out);
+bool unit_scorer_cuts(const ams_params* p);
+hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* seq_lens, const UnitCuts& uc, const VcInfo& vc,
+                            hipStream_t s);
 // flags (n_words words per unit): bitmap of the kept set, needed when a must-keep set is configured, else
 // may be null.  quota_done: the quotas (and what the quota kernels do besides) are already in place.
 // gather: the compaction that follows, done by the workgroups that select (no must-keep set only).

@@ -8,6 +8,7 @@
 // two-sweep kernels (score.hip): the same tiles, the same running statistics, the normaliser in double; what
 // goes away are two launches and the trip of the statistics through memory, which is most of the scorer's
 // time when an event moves only a couple of megabytes per unit.
+#include "mass_cuts.h"
 #include "score_tile.h"
 
 namespace ams {
@@ -15,14 +16,20 @@ namespace {
 
 constexpr int kUnitThreads = 512, kUnitWaves = kUnitThreads / 64;
 
-template <bool BF16, int NB, int MODE, int HD>
-__global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a) {
+// CUTS: the workgroup goes on to the masses, the cuts and the quotas (mass_cuts.h) on the usage that it holds, 4 to 9 us at its end
+// for one or two launches of 11 to 17.  us per step without and with: 170.5 and 166.1 (256 units of 2176, 128 queries), 86.9 and
+// 82.2 (192 of 4093, 64 channels), 110.3 and 101.8 (832 of 1425, 64 channels), 58.6 and 55.5 (300 of 1024, 8 queries), 407 and 398
+// (1224 of 3000, 32 queries), 119.0 and 117.0 (512 of 1500, 64 queries), 309 and 308 (600 fp32 units of 2000).
+template <bool BF16, int NB, int MODE, int HD, bool CUTS>
+__global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a, MsArgs ms, CutsOut out) {
   constexpr int NG = (BF16 && NB % 2 == 0 && NB >= 4) ? NB / 2 : NB, QS = Tr<BF16, HD>::kQStride, NQ = NB * 32;
   constexpr bool kLast = MODE == MODE_LAST || MODE == MODE_LAST_LANES;
   extern __shared__ __align__(16) char qlds[];
   __shared__ float2 xch[kUnitWaves][NQ];
   __shared__ float4 fin_s[NQ];
-  __shared__ float u_sm[kScoreChunk];
+  __shared__ __align__(16) float u_sm[kScoreChunk];
+  constexpr int kRounds = kScoreChunk / (kUnitThreads * 4);  // runs of four positions per thread
+  [[maybe_unused]] __shared__ CutsLds<kUnitThreads, CUTS ? CUTS_UNIT : CUTS_STEP, CUTS ? kRounds : 1> cuts_sm;
   __shared__ float g_sm[kLast ? kScoreChunk : 1];
   __shared__ double2 vc_sm[kUnitWaves];
   const int unit = blockIdx.x;
@@ -30,19 +37,24 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
   int l, b, h;
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
-  if (T <= 0) return;
+  float cr[kRounds][4];  // the old credit of the unit (for the EMA normaliser)
+  auto go_on = [&](double Z, double c_old) __attribute__((always_inline)) {
+    if constexpr (CUTS) cuts_body<kUnitThreads, CUTS_UNIT, kRounds>(ms, out.m_used, out, unit, cuts_sm, u_sm, cr, Z, c_old);
+  };
+  if (T <= 0) {
+    go_on(0.0, 0.0);
+    return;
+  }
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5, c = lane & 31;
   uint4 av0[Tr<BF16, HD>::kAVecs], av1[Tr<BF16, HD>::kAVecs];
   constexpr int kStep = kUnitWaves * 32;  // tokens between two blocks of one wave
   if (wave * 32 < T) load_a<BF16, HD>(a, l, b, h, wave * 32, T, lane, av0);
   const float q_top = load_q<BF16, NB, HD, kUnitThreads>(a, l, b, h, qlds);
-  // the old credit of the unit (for the EMA normaliser): at most 8 positions per thread, in flight during the walks
-  float cr[kScoreChunk / kUnitThreads];
+  // in flight during the walks
+  const bool credit = a.vc_part && a.credit;
 #pragma unroll
-  for (int k = 0; k < kScoreChunk / kUnitThreads; ++k) {
-    const int t = k * kUnitThreads + (int)threadIdx.x;
-    cr[k] = (a.vc_part && a.credit && t < T) ? a.credit[(int64_t)unit * a.d.t_stride + t] : 0.f;
-  }
+  for (int r = 0; r < kRounds; ++r)
+    load_run(a.credit + (int64_t)unit * a.d.t_stride, (r * kUnitThreads + (int)threadIdx.x) * 4, credit ? T : 0, CUTS && ms.vec, cr[r], 0.f);
   const int key_exp = settle_q<BF16, NB, HD, kUnitThreads>(a, l, b, h, qlds, q_top);
   const float c2 = a.c2;
 
@@ -170,7 +182,9 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
   if (a.vc_part) {  // the unit's sums of max(u,0)+eps and of the old credit: lanes, then waves, fixed order
     double v_acc = (double)v_part, c_acc = 0.0;
 #pragma unroll
-    for (int k = 0; k < kScoreChunk / kUnitThreads; ++k) c_acc += (double)cr[k];
+    for (int r = 0; r < kRounds; ++r)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c_acc += (double)cr[r][i];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
       v_acc += __shfl_xor(v_acc, o);
@@ -178,35 +192,45 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
     }
     if (lane == 0) vc_sm[wave] = make_double2(v_acc, c_acc);
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (CUTS || threadIdx.x == 0) {
       double2 t = vc_sm[0];
       for (int w = 1; w < kUnitWaves; ++w) {
         t.x += vc_sm[w].x;
         t.y += vc_sm[w].y;
       }
-      a.vc_part[unit] = t;
+      if constexpr (CUTS)
+        go_on(t.x, t.y);
+      else
+        a.vc_part[unit] = t;
     }
   }
 }
 
 template <bool BF16, int NB, int MODE, int HD>
-hipError_t launch_unit(const ScoreArgs& a, hipStream_t s) {
+hipError_t launch_unit(const ScoreArgs& a, const UnitCuts* cuts, hipStream_t s) {
   const int lds = NB * 32 * Tr<BF16, HD>::kQStride;
-  const hipError_t e = ensure_lds<score_unit_kernel<BF16, NB, MODE, HD>>(lds);
-  if (e != hipSuccess) return e;
-  prof_mark("score_unit", s);
-  hipLaunchKernelGGL((score_unit_kernel<BF16, NB, MODE, HD>), dim3(a.d.units), dim3(kUnitThreads), lds, s, a);
-  return hipGetLastError();
+  auto launch = [&](auto cuts_c, const UnitCuts& u) {
+    constexpr bool C = decltype(cuts_c)::value;
+    const hipError_t e = ensure_lds<score_unit_kernel<BF16, NB, MODE, HD, C>>(lds);
+    if (e != hipSuccess) return e;
+    prof_mark("score_unit", s);
+    hipLaunchKernelGGL((score_unit_kernel<BF16, NB, MODE, HD, C>), dim3(a.d.units), dim3(kUnitThreads), lds, s, a, u.a, u.o);
+    return hipGetLastError();
+  };
+  if (!cuts) return launch(std::false_type{}, UnitCuts{});
+  UnitCuts u = *cuts;
+  u.o.status = nullptr;  // no bounded wait on this path, and unit 0 clears the word while others would read it
+  return launch(std::true_type{}, u);
 }
 
 template <bool BF16, int HD>
-hipError_t unit_by_nb(const ScoreArgs& a, int nb, int mode, hipStream_t s, bool* ran) {
+hipError_t unit_by_nb(const ScoreArgs& a, int nb, int mode, const UnitCuts* cuts, hipStream_t s, bool* ran) {
   *ran = true;
 #define AMS_UNIT_CASE(NBV)                                                           \
   if (nb <= NBV) {                                                                   \
-    if (mode == MODE_LAST) return launch_unit<BF16, NBV, MODE_LAST, HD>(a, s);       \
-    if (mode == MODE_LAST_LANES) return launch_unit<BF16, NBV, MODE_LAST_LANES, HD>(a, s); \
-    return launch_unit<BF16, NBV, MODE_MEAN, HD>(a, s);                              \
+    if (mode == MODE_LAST) return launch_unit<BF16, NBV, MODE_LAST, HD>(a, cuts, s);       \
+    if (mode == MODE_LAST_LANES) return launch_unit<BF16, NBV, MODE_LAST_LANES, HD>(a, cuts, s); \
+    return launch_unit<BF16, NBV, MODE_MEAN, HD>(a, cuts, s);                              \
   }
   AMS_UNIT_CASE(1)
   AMS_UNIT_CASE(2)
@@ -221,13 +245,13 @@ hipError_t unit_by_nb(const ScoreArgs& a, int nb, int mode, hipStream_t s, bool*
 // Runs the one-launch scorer when it applies: caches of at most kScoreChunk positions, bf16 or fp32, up to
 // 128 queries per KV head, no causal window, mean-window / last-query statistics (the key-diversity scorer
 // takes its usage from here too).  *ran = false: the caller uses the two sweeps.
-hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, hipStream_t s, bool* ran) {
+hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, const UnitCuts* cuts, hipStream_t s, bool* ran) {
   *ran = false;
   if (a.d.t_max > kScoreChunk || a.causal || mode == MODE_EXPECTED || a.n_pad > 128) return hipSuccess;
   const int nb = a.n_pad / 32;
   if (head_dim == 64)
-    return bf16 ? unit_by_nb<true, 64>(a, nb, mode, s, ran) : unit_by_nb<false, 64>(a, nb, mode, s, ran);
-  return bf16 ? unit_by_nb<true, 128>(a, nb, mode, s, ran) : unit_by_nb<false, 128>(a, nb, mode, s, ran);
+    return bf16 ? unit_by_nb<true, 64>(a, nb, mode, cuts, s, ran) : unit_by_nb<false, 64>(a, nb, mode, cuts, s, ran);
+  return bf16 ? unit_by_nb<true, 128>(a, nb, mode, cuts, s, ran) : unit_by_nb<false, 128>(a, nb, mode, cuts, s, ran);
 }
 
 }  // namespace ams

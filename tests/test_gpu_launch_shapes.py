@@ -369,6 +369,39 @@ def test_short_caches_form_everything_after_the_scores_in_one_launch(oracle, T, 
 
 
 @pytest.mark.parametrize("vec", [True, False])
+@pytest.mark.parametrize("T,S,dtype,G,W,D,scorer,must,one", [
+    (4096, 64, "bf16", 4, 32, 128, B.SCORER_MEAN_WINDOW, False, True), (4095, 65, "bf16", 4, 32, 128, B.SCORER_MEAN_WINDOW, False, False),
+    (2049, 7, "bf16", 1, 8, 64, B.SCORER_LAST_QUERY, True, True), (2048, 16, "f32", 2, 20, 128, B.SCORER_MEAN_WINDOW, True, True),
+    (65, 3, "bf16", 2, 32, 128, B.SCORER_LAST_QUERY, False, True), (64, 1, "f32", 1, 8, 64, B.SCORER_MEAN_WINDOW, False, True),
+    (1, 4, "bf16", 1, 8, 128, B.SCORER_MEAN_WINDOW, False, True)])
+def test_one_launch_scorer_goes_on_to_the_quotas(oracle, T, S, dtype, G, W, D, scorer, must, one, vec):
+    """Masses, cuts and quotas in the scorer's workgroups: full and ragged last pieces, an empty sequence, 64 and 65 segments, a
+    must-keep set (whose bitmap they clear), rows of odd stride, scratch that holds garbage."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=3, H=2, G=G, W=W, D=D, T=T, T_min=T, dtype=dtype, budget=max(1, T // 5), S=S, n_spans=3,
+                                 span_len=(1, max(1, min(30, T))), n_sink=3 * must, n_last=20 * must)
+    host = inputs.dense_cache(w, n_threads=4)
+    host["seq_lens"][:] = [T, 0, max(1, T // 2 - 1)]
+    credit = np.abs(np.random.default_rng(T + S).standard_normal((6, T))).astype(np.float32)
+    credit /= credit.sum(1, keepdims=True)
+    for i, n in enumerate(n for n in host["seq_lens"] for _ in range(2)):
+        credit[i, n:] = 0
+    job = Job(w, host, scorer=scorer, credit=credit, score_path=B.SCORE_PATH_ONE_LAUNCH)
+    if not vec:
+        job.t_stride = job.p.t_stride = T | 1
+        job.credit = torch.zeros((job.units, job.t_stride), device=DEV)
+        job.credit[:, :T] = to_dev(credit)
+        job.ws = torch.zeros(B.ams_workspace_bytes(job.p), dtype=torch.uint8, device=DEV)
+    job.ws.fill_(255)
+    labels = _labels(job)
+    assert "score_unit" in labels and any("cuts" in x for x in labels) != one
+    assert to_host(job.n_kept).tolist() == [min(w.budget, int(t)) for t in host["seq_lens"] for _ in range(2)]
+    assert (to_host(job.idx)[2:4] == -1).all() and (to_host(job.intermediates().bounds)[2:4] == 0).all()
+    before = np.zeros((6, job.t_max), np.float32)
+    before[:, :T] = credit
+    check_units(oracle, job, host, before, [0, 1, 4, 5], scorer=scorer)
+
+
+@pytest.mark.parametrize("vec", [True, False])
 @pytest.mark.parametrize("T,S,fused", [(2048, 64, True), (2049, 5, True), (4096, 64, True), (4097, 7, True), (8192, 64, True),
                                        (8193, 16, False), (3000, 65, False), (63, 3, True)])
 def test_short_caches_form_masses_and_cuts_in_one_launch(oracle, T, S, fused, vec):
