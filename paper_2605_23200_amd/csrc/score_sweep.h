@@ -631,6 +631,9 @@ __device__ __forceinline__ float4 query_weights(const ScoreArgs& a, int n, int T
                      real ? 1.f : 0.f);
 }
 
+// Latency bounds this kernel: up to eight chunks of a thread's range travel at once, more of them four at a time, and the credit
+// before them (4 units of 10126 positions, 80 chunks: 12.1 -> 10.3 us, 45.0 -> 42.9 per step; 10 of 87760 22.6 -> 20.0; sixteen at
+// once lose, 46.0; no difference where the credit's bytes bound it, 14.6 and 14.2 for 256 of 32768).
 // Chunk statistics merged per query: the 1024 threads split into (query, contiguous range of
 // chunks) pairs, the ranges are then combined in ascending order (fixed association) -> M_n and
 // the per-query weights of the column sums.
@@ -644,6 +647,22 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
   unit_coords(a.d, unit, l, b, h);
   const int T = seq_len(a.d, a.seq_lens, b);
   const int len = chunk_len(a, T), nch = (causal_t_end(a, T, a.causal) + len - 1) / len + (a.causal ? 1 : 0);
+  double credit = 0.0;  // sum of the credit before the update (for the EMA normaliser), strided partials in a fixed tree
+  if (a.csum) {         // first, so that the statistics travel meanwhile
+    const float* c_row = a.credit + (int64_t)unit * a.d.t_stride;
+    if ((a.d.t_stride & 3) == 0 && ((uintptr_t)a.credit & 15) == 0) {  // 16-byte loads, several in flight
+      const float4* c4 = (const float4*)c_row;
+      const int n4 = T >> 2;
+#pragma unroll 8
+      for (int q = threadIdx.x; q < n4; q += kReduceThreads) {
+        const float4 v = c4[q];
+        credit += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
+      }
+      for (int t = (n4 << 2) + threadIdx.x; t < T; t += kReduceThreads) credit += (double)c_row[t];
+    } else {
+      for (int t = threadIdx.x; t < T; t += kReduceThreads) credit += (double)c_row[t];
+    }
+  }
   const int parts = kReduceThreads / a.n_pad;
   const int n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
   if (part < parts) {
@@ -651,11 +670,23 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
     const int c0 = part * per, c1 = min(nch, c0 + per);
     const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
     float M = kNegInit;
-    for (int c = c0; c < c1; ++c) M = fmaxf(M, p[(int64_t)c * a.n_pad].x);
     double Z = 0.0;
-    for (int c = c0; c < c1; ++c) {
-      const float2 s = p[(int64_t)c * a.n_pad];
-      Z += (double)s.y * (double)__builtin_amdgcn_exp2f(s.x - M);
+    if (per <= 8) {  // all entries in flight
+      float2 s[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s[i] = c0 + i < c1 ? p[(int64_t)(c0 + i) * a.n_pad] : make_float2(kNegInit, 0.f);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) M = fmaxf(M, s[i].x);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) Z += (double)s[i].y * (double)__builtin_amdgcn_exp2f(s[i].x - M);
+    } else {
+#pragma unroll 4
+      for (int c = c0; c < c1; ++c) M = fmaxf(M, p[(int64_t)c * a.n_pad].x);
+#pragma unroll 4
+      for (int c = c0; c < c1; ++c) {
+        const float2 s = p[(int64_t)c * a.n_pad];
+        Z += (double)s.y * (double)__builtin_amdgcn_exp2f(s.x - M);
+      }
     }
     pm[threadIdx.x] = M;
     pz[threadIdx.x] = Z;
@@ -675,25 +706,11 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
     for (int c = 0; c < nch; ++c) t += k[(int64_t)c * a.d.D];
     *k = t;
   }
-  if (a.csum) {  // sum of the credit before the update (for the EMA normaliser), strided partials in a fixed tree
+  if (a.csum) {
     __shared__ double cs[kReduceThreads / 64];
-    const float* c_row = a.credit + (int64_t)unit * a.d.t_stride;
-    double c = 0.0;
-    if ((a.d.t_stride & 3) == 0 && ((uintptr_t)a.credit & 15) == 0) {  // 16-byte loads, several in flight
-      const float4* c4 = (const float4*)c_row;
-      const int n4 = T >> 2;
-#pragma unroll 8
-      for (int q = threadIdx.x; q < n4; q += kReduceThreads) {
-        const float4 v = c4[q];
-        c += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
-      }
-      for (int t = (n4 << 2) + threadIdx.x; t < T; t += kReduceThreads) c += (double)c_row[t];
-    } else {
-      for (int t = threadIdx.x; t < T; t += kReduceThreads) c += (double)c_row[t];
-    }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o);
-    if ((threadIdx.x & 63) == 0) cs[threadIdx.x >> 6] = c;
+    for (int o = 32; o >= 1; o >>= 1) credit += __shfl_xor(credit, o);
+    if ((threadIdx.x & 63) == 0) cs[threadIdx.x >> 6] = credit;
     __syncthreads();
     if (threadIdx.x == 0) {
       double t = 0.0;
