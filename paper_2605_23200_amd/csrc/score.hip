@@ -420,11 +420,14 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     const bool want_unit = p->score_path == AMS_SCORE_PATH_ONE_LAUNCH ||
                            (p->score_path == AMS_SCORE_PATH_AUTO && d.units >= kUnitScorerMinUnits && !keys_ride && !thin);
     if (want_unit) {
-      // The scorer's workgroups go on to the quotas (score_unit_kernel), unless a CU holds one of them at a time and takes many in
-      // turn, so that nothing runs beside the end of each: 512 units of 2048 with 112 queries 167.9 us per step without and 165.7
-      // with, 1392 of 3013 with 128 594 and 601 (64 segments: 667 and 662).
-      const bool one_per_cu = nb >= 4 && d.D == 128, in_turn = one_per_cu && d.units > 1024;
-      const UnitCuts* cuts = vc && !in_turn ? vc->unit_cuts : nullptr;
+      // The scorer's workgroups go on to the quotas (score_unit_kernel) in the few rounds in which the 6 to 8 us at the end of each
+      // cost less than the launches: a CU holds two of them with small bf16 tiles, else one, so that nothing runs beside the end.
+      // Time without over time with, by rounds: fp32 one 1.02 to 1.03, two 0.98 to 0.99 (300 units of 1200, 400 of 1100, 64
+      // channels); large bf16 tiles one 1.03 to 1.07, two 1.01 to 1.02 (512 of 1500 and 2048), four 0.98 (900 of 1100), six to
+      // eight 0.98 to 0.99; small ones one 1.06 to 1.08, two 1.08 (832 of 1425), three 1.02 (1224 of 3000).
+      const bool small = bf16 && nb <= (d.D == 64 ? 2 : 1);
+      const bool few = d.units <= (small ? 3 * 512 : bf16 ? 2 * 256 : 256);
+      const UnitCuts* cuts = vc && few ? vc->unit_cuts : nullptr;
       e = launch_score_unit(a, bf16, d.D, mode, cuts, s, &oneread);
       if (cuts && oneread) vc->cuts = true;
       if (e != hipSuccess) return e;
