@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "score_tile.h"
+#include "sweep_grid.h"
 
 namespace ams {
 namespace {
@@ -180,11 +181,14 @@ __device__ __forceinline__ int causal_t_end(const ScoreArgs& a, int T, bool caus
 template <bool CAUSAL>
 __device__ __forceinline__ bool sweep_tile(const ScoreArgs& a, bool reversed, int& unit, int& chunk) {
   int bx = blockIdx.x, by = blockIdx.y;
-  const int chunks = gridDim.x;
-  if (CAUSAL && by >= a.d.units) {
-    unit = (by - a.d.units) * chunks + bx;
-    chunk = unit < a.d.units ? 0 : -1;
-    return true;
+  const int chunks = CAUSAL ? a.n_chunks : (int)gridDim.x;
+  if constexpr (CAUSAL) {
+    sweep_place(blockIdx.x, blockIdx.y, gridDim.x, chunks, bx, by);
+    if (by >= a.d.units) {
+      unit = sweep_tail(bx, by, chunks, a.d.units);
+      chunk = unit < 0 ? -1 : 0;
+      return true;
+    }
   }
   if (a.compact) {
     const int lane = threadIdx.x & 63, B = a.d.B, H = a.d.H;
@@ -235,7 +239,7 @@ __device__ __forceinline__ bool sweep_tile(const ScoreArgs& a, bool reversed, in
     chunk = bx;
     return false;
   }
-  const int lin = by * chunks + bx;  // gridDim.x = chunks per unit
+  const int lin = by * chunks + bx;
   const int rest = lin / a.d.H, h = (lin + rest / 8) % a.d.H;
   chunk = rest % chunks;
   unit = (rest / chunks) * a.d.H + h;
@@ -1097,7 +1101,8 @@ hipError_t run_key_sweeps(const ScoreArgs& a, hipStream_t s) {
 template <bool BF16, int NB, bool CAUSAL, int HD, int SCORERS>
 hipError_t run_softmax_sweeps(const ScoreArgs& a, int mode, hipStream_t s) {
   const int lds = NB * 32 * Tr<BF16, HD>::kQStride;
-  const dim3 grid(a.n_chunks, a.d.units + (CAUSAL ? div_up(a.d.units, a.n_chunks) : 0));
+  const SweepGrid sg = sweep_grid(a.d.units, a.n_chunks, CAUSAL);
+  const dim3 grid(sg.x, sg.y);
   hipError_t e;
   prof_mark("score_stats", s);
   if ((e = launch_stats<BF16, NB, CAUSAL, HD, SCORERS>(a, mode == MODE_EXPECTED, grid, lds, s)) != hipSuccess) return e;

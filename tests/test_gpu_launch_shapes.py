@@ -629,3 +629,17 @@ def test_sums_of_a_short_cache_by_either_scorer(oracle, path, T):
     job.step()
     assert to_host(job.n_kept).tolist() == [300] * 8
     check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, 7])
+
+
+@pytest.mark.parametrize("units", [32767, 32769])             # 65534 rows of the sweeps; 65538 of them, two to a row of the grid
+def test_causal_window_over_more_units_than_half_the_grids_rows(oracle, units):
+    """One chunk and one tail per unit."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=1, H=units, G=1, W=8, D=64, T=40, T_min=40, budget=12, S=2, causal=True)
+    rng = np.random.default_rng(units)
+    bits = lambda *shape: (rng.standard_normal(shape, np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    host = {"K": bits(1, 1, units, 40, 64), "V": bits(1, 1, units, 40, 64), "Q": bits(1, 1, units, 8, 64),
+            "seq_lens": np.array([40], np.int32)}
+    job = Job(w, host)
+    job.step()
+    check_properties_all_units(job)
+    check_units(oracle, job, host, np.zeros((w.units, job.t_max), np.float32), [0, 1, units // 2, units - 2, units - 1])
