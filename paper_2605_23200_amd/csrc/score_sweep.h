@@ -495,14 +495,22 @@ __device__ __forceinline__ void stats_body(const ScoreArgs& a, Lds& sm, int unit
           for (int k = 0; k < n; ++k) acc[k] = centre;
         }
         if (!BF16 && g0 > 0) forget_terms(av);
-        tile_mma<BF16, n, HD, !centred, !MOMENTS>(av, qlds + qoff + g0 * 32 * QS, lane, acc, key_exp);
+        tile_mma<BF16, n, HD, !centred, !MOMENTS && !TAIL>(av, qlds + qoff + g0 * 32 * QS, lane, acc, key_exp);
         if (MOMENTS) {
 #pragma unroll
           for (int k = 0; k < n; ++k) col_moments(acc[k], g0 + k);
         }
 #pragma unroll
         for (int k = 0; k < n; ++k) col_stats(acc[k], g0 + k);
+        if (TAIL) __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    // The sums stay here: sunk past the store of g below they keep the logits of all column blocks (179 registers spilled with 256
+    // queries, 128 channels; with 64 channels 727 us per step with this and 759 without, 256 units of 32768, 128 queries; with up to
+    // four blocks of 128 channels 1 % more with it).
+    if constexpr (CAUSAL && MOMENTS && (kPipe<BF16, NB, TAIL> || HD == 64)) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) asm volatile("" : "+v"(z[nb]));
     }
     if constexpr (KEYS != KEYS_NONE)
       add_keys<HD, KEYS == KEYS_COS>(av, sm.ident, sm.inv_len[KEYS == KEYS_COS ? wave : 0], lane, ragged ? T - t0 : 32, ksum);
@@ -529,7 +537,10 @@ __device__ __forceinline__ void stats_body(const ScoreArgs& a, Lds& sm, int unit
     }
   };
   auto block = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0) __attribute__((always_inline)) {
-    if (t0 + 32 > T)
+    // (the plain blocks in front of a tail end at a multiple of 32: without the ragged form next to them the kernels that carry a
+    // tail take no more registers than those without.  us per step with it and without: 476 and 462 for 64 fp32 units of 16384, 128
+    // queries; 2155 and 1904 for 256 units of 32768, expected attention, 256 queries, where 23 registers spilled)
+    if (!(CAUSAL && !TAIL) && t0 + 32 > T)
       block_of(av, t0, std::true_type{}, std::true_type{});
     else
       block_of(av, t0, std::false_type{}, std::true_type{});
