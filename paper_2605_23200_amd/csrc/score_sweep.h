@@ -884,6 +884,11 @@ __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) f[nb] = a.fin[(int64_t)unit * a.n_pad + nb * 32 + c];
   }
+  [[maybe_unused]] const int log2_w = 31 - __clz(a.d.W);  // MODE_LAST_LANES: of a power of two
+  if (MODE == MODE_LAST_LANES) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) f[nb].y *= (float)a.d.W;
+  }
   float v_part = 0.f;  // this lane's share of sum(max(u,0)+eps): one term per block of 32 keys of this wave (32 blocks per chunk)
   auto block = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0) __attribute__((always_inline)) {
     float pu[16], pg[16], pm[16];
@@ -950,6 +955,7 @@ __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit
       const int seen = a.d.G * min(a.d.W, T - t);  // (head, query) pairs that see key t
       ru += (float)(a.d.N - seen) * reduce16_over32<true>(pm, c);
     }
+    if (MODE == MODE_LAST_LANES) ru = ldexpf(ru, -log2_w);
     if (MODE == MODE_MEAN) rg = ru;
     if constexpr (KEYS != KEYS_NONE) {
       const float n2 = __shfl(key_norm2(key_gram<HD>(av), c), hf * 32 + acc_row(c >> 1, hf));  // of token t

@@ -17,9 +17,10 @@ static constexpr float kNegInit = -3.0e38f;  // finite "minus infinity" for runn
 static constexpr int kThreads = 256;
 
 // MODE_LAST_LANES: last query, windows of 1, 2, 4, .. 32 queries.  The newest queries of all column blocks then sit in the same
-// lanes, with weights that are the window's length times those of u: the score is the share of these lanes in the sum that u
-// takes anyway, the same bits without a multiply-add per logit and 16 registers for a sum of its own.  us per step with the sum
-// and without: 152.4 and 149.5 (192 ragged units of up to 9001, 112 queries, 64 channels), 256.3 and 251.3 (25 of 44127, 224
+// lanes, and a share in the score is the window's length times one in u, a power of two: the shares carry the score's weight
+// 1 / (G Z), the score is what these lanes hold of the sum, and u is the sum over the length.  The bits of a sum of its own, without
+// a multiply-add per logit and 16 registers; u keeps more where a share lies below 2^-126.  (With u's weight the score would lose up
+// to five bits there.)  us per step with the sum and without: 152.4 and 149.5 (192 ragged units of up to 9001, 112 queries, 64 channels), 256.3 and 251.3 (25 of 44127, 224
 // queries), 256.6 and 252.7 (276 of up to 5547 in one launch), 36.2 and 35.0 (32 of 1715); 8 others 0.99 to 1.01.
 enum { MODE_MEAN = 0, MODE_LAST = 1, MODE_EXPECTED = 2, MODE_LAST_LANES = 3 };
 inline bool newest_share_lanes(int window) { return window <= 32 && (window & (window - 1)) == 0; }
@@ -410,13 +411,13 @@ __device__ __forceinline__ float reduce16_over32(const float (&v)[16], int c) {
   return op(w1, dpp_xor1(w1));
 }
 
-// The last-query score of token c >> 1 from the sums of u (MODE_LAST_LANES).
+// The last-query score of token c >> 1 from the sums of all queries (MODE_LAST_LANES).
 __device__ __forceinline__ float newest_lanes(const float (&pu)[16], int c, int window) {
   float v[16];
   const bool newest = (c & (window - 1)) == window - 1;
 #pragma unroll
   for (int i = 0; i < 16; ++i) v[i] = newest ? pu[i] : 0.f;
-  return reduce16_over32(v, c) * (float)window;
+  return reduce16_over32(v, c);
 }
 
 }  // namespace ams

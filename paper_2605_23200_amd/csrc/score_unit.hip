@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
     for (int w = 0; w < kUnitWaves; ++w) Z += (double)xch[w][n].y * (double)__builtin_amdgcn_exp2f(xch[w][n].x - M);
     const bool real = n < a.d.N;
     const bool newest = real && (n % a.d.W) == a.d.W - 1;
-    fin_s[n] = make_float4(M, real ? (float)(1.0 / ((double)a.d.N * Z)) : 0.f,
+    fin_s[n] = make_float4(M, real ? (float)(1.0 / ((double)(MODE == MODE_LAST_LANES ? a.d.G : a.d.N) * Z)) : 0.f,
                            newest ? (float)(1.0 / ((double)a.d.G * Z)) : 0.f, real ? 1.f : 0.f);
   }
   __syncthreads();
@@ -131,6 +131,7 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
   float4 f[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) f[nb] = fin_s[nb * 32 + c];
+  [[maybe_unused]] const int log2_w = 31 - __clz(a.d.W);  // MODE_LAST_LANES: of a power of two
   float v_part = 0.f;  // this lane's share of sum(max(u,0)+eps)
   auto usage_block = [&](const uint4 (&av)[Tr<BF16, HD>::kAVecs], int t0) __attribute__((always_inline)) {
     float pu[16], pg[16];
@@ -154,7 +155,8 @@ __global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a
       }
     }
     const int t = t0 + acc_row(c >> 1, hf);
-    const float ru = reduce16_over32(pu, c);
+    float ru = reduce16_over32(pu, c);
+    if (MODE == MODE_LAST_LANES) ru = ldexpf(ru, -log2_w);
     float rg = ru;
     if (MODE == MODE_LAST) rg = reduce16_over32(pg, c);
     if (MODE == MODE_LAST_LANES) rg = newest_lanes(pu, c, a.d.W);

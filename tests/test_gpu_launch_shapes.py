@@ -335,6 +335,32 @@ def test_last_query_in_windows_of_any_length(oracle, dtype, G, W, units, T, caus
     _run(oracle, w, scorer=B.SCORER_LAST_QUERY, units=sorted({0, units // 2, units - 1}))
 
 
+@pytest.mark.parametrize("path,T,G,W,causal", [(B.SCORE_PATH_TWO_SWEEPS, 4000, 1, 32, False), (B.SCORE_PATH_TWO_SWEEPS, 4000, 2, 32, True),
+                                               (B.SCORE_PATH_TWO_SWEEPS, 8193, 4, 32, False), (B.SCORE_PATH_TWO_SWEEPS, 8193, 14, 16, True),
+                                               (B.SCORE_PATH_ONE_LAUNCH, 4000, 1, 32, False), (B.SCORE_PATH_ONE_LAUNCH, 4000, 4, 16, False)])
+def test_last_query_shares_below_the_smallest_normal_number(path, T, G, W, causal):
+    """Exact products (two channels of queries and keys are not zero), Z = T - 32 to a relative 1e-30: a share of the newest query is
+    2^x / ((T - 32) G) with x the logit in base 2, formed in fp32 from |x| <= 126 (relative 126 * 2^-23) and rounded once below
+    2^-126 (2^-150), by one multiply-add per group's query: the zeros that it is added to change nothing."""
+    D = 64
+    Q, K = np.zeros((G, W, D), np.float32), np.zeros((T, D), np.float32)
+    Q[:, -1, :2] = 8.0
+    at = np.arange(32) * (T // 32) + np.arange(32) % 5
+    at[-8:] = T - 1 - np.arange(8)                                      # (within a causal window)
+    K[at, 0], K[at, 1] = -86.0, -np.arange(32) / 64                     # logits of -86 .. -86.5
+    bits = lambda x: (np.ascontiguousarray(x).view(np.uint32) >> 16).astype(np.uint16)
+    p = B.make_params(n_layers=1, batch=1, n_kv_heads=1, group=G, window=W, head_dim=D, kv_dtype=B.BF16, t_max=T, t_stride=T, budget=64,
+                      n_segments=4, scorer=B.SCORER_LAST_QUERY, causal=causal, score_path=path)
+    k, q = to_dev(bits(K)).view(torch.bfloat16).reshape(1, 1, 1, T, D), to_dev(bits(Q)).view(torch.bfloat16).reshape(1, 1, G, W, D)
+    u, g = torch.zeros((1, T), device=DEV), torch.zeros((1, T), device=DEV)
+    B.ams_score(p, B.dense_view(k, k), to_dev(np.array([T], np.int32)), q, u, g, workspace(p))
+    want = np.exp(K[at].astype(np.float64).sum(1)) / (T - 32)            # G equal shares of 1 / G
+    got = to_host(g)[0, at].astype(np.float64)
+    assert (want < 2.0 ** -126).all()
+    err = np.abs(got - want)
+    assert (err <= G * 2.0 ** -150 + 127 * 2.0 ** -23 * want).all(), (err / 2.0 ** -149).max()
+
+
 @pytest.mark.parametrize("vec", [True, False])
 @pytest.mark.parametrize("T,S,delta,l_min,l_max,pool,causal,must,one", [
     (2048, 24, 0.1, 16, 256, 5, True, True, True), (2049, 24, 0.1, 16, 256, 5, True, True, True),
