@@ -425,7 +425,7 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
       // Time without over time with, by rounds: fp32 one 1.02 to 1.03, two 0.98 to 0.99 (300 units of 1200, 400 of 1100, 64
       // channels); large bf16 tiles one 1.03 to 1.07, two 1.01 to 1.02 (512 of 1500 and 2048), four 0.98 (900 of 1100), six to
       // eight 0.98 to 0.99; small ones one 1.06 to 1.08, two 1.08 (832 of 1425), three 1.02 (1224 of 3000).
-      const bool small = bf16 && nb <= (d.D == 64 ? 2 : 1);
+      const bool small = unit_tile_small(bf16, nb, d.D);
       const bool few = d.units <= (small ? 3 * 512 : bf16 ? 2 * 256 : 256);
       const UnitCuts* cuts = vc && few ? vc->unit_cuts : nullptr;
       e = launch_score_unit(a, bf16, d.D, mode, cuts, s, &oneread);

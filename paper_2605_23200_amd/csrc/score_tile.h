@@ -25,6 +25,12 @@ static constexpr int kThreads = 256;
 enum { MODE_MEAN = 0, MODE_LAST = 1, MODE_EXPECTED = 2, MODE_LAST_LANES = 3 };
 inline bool newest_share_lanes(int window) { return window <= 32 && (window & (window - 1)) == 0; }
 
+// Tiles of the one-launch scorer of which a CU holds two workgroups, four waves to a SIMD: at most 128 registers.  All but one take
+// no more by themselves; the last-query score of 128 channels with a sum of its own took 129 to 132 and ran one workgroup on a CU:
+// us per step 278.8 and 269.6 (500 units of 2000, a window of 24 queries), 355 and 339 (600), 547 and 524 (1000), 664 and 627 (1500
+// of 1500); with the quotas in launches of their own 844 and 826 (2000 of 1500), 839 and 812 (3000 of 1000).
+constexpr bool unit_tile_small(bool bf16, int nb, int head_dim) { return bf16 && nb <= (head_dim == 64 ? 2 : 1); }
+
 struct ScoreArgs {
   KvDev k;
   Dims d;

@@ -21,7 +21,7 @@ constexpr int kUnitThreads = 512, kUnitWaves = kUnitThreads / 64;
 // 82.2 (192 of 4093, 64 channels), 110.3 and 101.8 (832 of 1425, 64 channels), 58.6 and 55.5 (300 of 1024, 8 queries), 407 and 398
 // (1224 of 3000, 32 queries), 119.0 and 117.0 (512 of 1500, 64 queries), 309 and 308 (600 fp32 units of 2000).
 template <bool BF16, int NB, int MODE, int HD, bool CUTS>
-__global__ __launch_bounds__(kUnitThreads, 2) void score_unit_kernel(ScoreArgs a, MsArgs ms, CutsOut out) {
+__global__ __launch_bounds__(kUnitThreads, (unit_tile_small(BF16, NB, HD) ? 4 : 2)) void score_unit_kernel(ScoreArgs a, MsArgs ms, CutsOut out) {
   constexpr int NG = (BF16 && NB % 2 == 0 && NB >= 4) ? NB / 2 : NB, QS = Tr<BF16, HD>::kQStride, NQ = NB * 32;
   constexpr bool kLast = MODE == MODE_LAST || MODE == MODE_LAST_LANES;
   extern __shared__ __align__(16) char qlds[];

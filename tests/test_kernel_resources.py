@@ -54,3 +54,11 @@ def test_tails_cost_the_first_sweep_no_registers(kernels):
     assert len(causal) >= 24
     worse = {a: (n, spills[a[:2] + (0,) + a[3:]]) for a, n in causal.items() if n > spills[a[:2] + (0,) + a[3:]]}
     assert not worse
+
+
+def test_small_tiles_of_the_one_launch_scorer_leave_a_cu_two_workgroups(kernels):
+    """512 threads each: 128 registers, half of the LDS (the query window comes on top, NB * 32 rows)."""
+    small = {a: k for n, a, k in kernels if n == "score_unit_kernel" and a[0] and a[1] <= (2 if a[3] == 64 else 1)}
+    assert len(small) == 18                                 # bf16, column blocks, mode, channels, cuts
+    for a, k in small.items():
+        assert k[".vgpr_count"] <= 128 and 2 * (k[".group_segment_fixed_size"] + a[1] * 32 * (a[3] * 2 + 16)) <= 160 * 1024, a
