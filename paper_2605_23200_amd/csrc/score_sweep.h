@@ -908,7 +908,7 @@ __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit
           const float share = sees ? f[nb].y * e : 0.f;
           pu[i] += share;
           pm[i] = fmaxf(pm[i], share);
-          if (MODE == MODE_LAST) pg[i] += sees ? f[nb].z * e : 0.f;
+          if (!BF16 && MODE == MODE_LAST) pg[i] += sees ? f[nb].z * e : 0.f;
         }
       } else {
 #pragma unroll
@@ -954,6 +954,21 @@ __device__ __forceinline__ void usage_body(const ScoreArgs& a, Lds& sm, int unit
     if (masked) {
       const int seen = a.d.G * min(a.d.W, T - t);  // (head, query) pairs that see key t
       ru += (float)(a.d.N - seen) * reduce16_over32<true>(pm, c);
+      // The products once more, instead of a third sum next to the usage and its maxima, which the bf16 kernels do not have the
+      // registers for (27 spilled at 65 to 128 queries, 8 at 256: 108.1 -> 106.9 us per step for 64 units of 8192, 318.6 -> 315.3
+      // for 128 of 16000; fp32 kernels, two waves on a SIMD, hold it: 90.4 and 95.6 with the products twice, 8 units of 8192).
+      if constexpr (BF16 && MODE == MODE_LAST) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          floatx16 acc[1];
+          tile_mma<BF16, 1, HD>(av, qlds + qoff + nb * 32 * QS, lane, acc, key_exp);
+#pragma unroll
+          for (int i = 0; i < 16; ++i)  // (the newest queries see every key)
+            pg[i] += f[nb].z != 0.f ? f[nb].z * __builtin_amdgcn_exp2f(__builtin_fmaf(acc[0][i], c2, -f[nb].x)) : 0.f;
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
     }
     if (MODE == MODE_LAST_LANES) ru = ldexpf(ru, -log2_w);
     if (MODE == MODE_MEAN) rg = ru;

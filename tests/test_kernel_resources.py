@@ -62,3 +62,12 @@ def test_small_tiles_of_the_one_launch_scorer_leave_a_cu_two_workgroups(kernels)
     assert len(small) == 18                                 # bf16, column blocks, mode, channels, cuts
     for a, k in small.items():
         assert k[".vgpr_count"] <= 128 and 2 * (k[".group_segment_fixed_size"] + a[1] * 32 * (a[3] * 2 + 16)) <= 160 * 1024, a
+
+
+def test_tails_cost_the_second_sweep_no_registers(kernels):
+    """bf16 caches: the fp32 instances of 65 to 128 queries and 128 channels fill all 256 registers without a tail."""
+    spills = _spills(kernels, "score_usage_kernel")         # bf16, column blocks, mode, causal, channels, keys, fold
+    causal = {a: n for a, n in spills.items() if a[0] and a[3]}
+    assert len(causal) >= 50
+    worse = {a: (n, spills[a[:3] + (0,) + a[4:]]) for a, n in causal.items() if n > spills[a[:3] + (0,) + a[4:]]}
+    assert not worse
