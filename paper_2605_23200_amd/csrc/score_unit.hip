@@ -50,11 +50,12 @@ __global__ __launch_bounds__(kUnitThreads, (unit_tile_small(BF16, NB, HD) ? 4 : 
   constexpr int kStep = kUnitWaves * 32;  // tokens between two blocks of one wave
   if (wave * 32 < T) load_a<BF16, HD>(a, l, b, h, wave * 32, T, lane, av0);
   const float q_top = load_q<BF16, NB, HD, kUnitThreads>(a, l, b, h, qlds);
-  // in flight during the walks
-  const bool credit = a.vc_part && a.credit;
+  // In flight during the walks, 16 bytes at a time also where only the sum is wanted (CUTS = false): us per step with 4-byte loads
+  // and with these 306.0 and 301.5 (2048 units of 1024, 64 channels), 799 and 791 (3000 of 1000), 588 and 585 (700 of 4000).
+  const bool credit = a.vc_part && a.credit, vec = CUTS ? ms.vec : (a.d.t_stride & 3) == 0 && ((uintptr_t)a.credit & 15) == 0;
 #pragma unroll
   for (int r = 0; r < kRounds; ++r)
-    load_run(a.credit + (int64_t)unit * a.d.t_stride, (r * kUnitThreads + (int)threadIdx.x) * 4, credit ? T : 0, CUTS && ms.vec, cr[r], 0.f);
+    load_run(a.credit + (int64_t)unit * a.d.t_stride, (r * kUnitThreads + (int)threadIdx.x) * 4, credit ? T : 0, vec, cr[r], 0.f);
   const int key_exp = settle_q<BF16, NB, HD, kUnitThreads>(a, l, b, h, qlds, q_top);
   const float c2 = a.c2;
 

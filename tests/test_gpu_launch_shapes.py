@@ -427,6 +427,30 @@ def test_one_launch_scorer_goes_on_to_the_quotas(oracle, T, S, dtype, G, W, D, s
     check_units(oracle, job, host, before, [0, 1, 4, 5], scorer=scorer)
 
 
+@pytest.mark.parametrize("units,T,dtype,G,W,D,scorer,follows", [
+    (256, 300, "f32", 1, 8, 64, B.SCORER_MEAN_WINDOW, None), (257, 300, "f32", 1, 8, 64, B.SCORER_MEAN_WINDOW, "unit_mass_cuts"),
+    (512, 200, "bf16", 4, 32, 128, B.SCORER_LAST_QUERY, None), (513, 200, "bf16", 4, 32, 128, B.SCORER_LAST_QUERY, "mass_ema"),
+    (1536, 130, "bf16", 1, 8, 64, B.SCORER_MEAN_WINDOW, None), (1537, 130, "bf16", 1, 8, 64, B.SCORER_MEAN_WINDOW, "mass_ema"),
+    (1536, 97, "bf16", 1, 24, 128, B.SCORER_LAST_QUERY, None), (130, 555, "f32", 3, 32, 128, B.SCORER_MEAN_WINDOW, None)])
+def test_units_up_to_which_the_scorer_goes_on_to_the_quotas(oracle, units, T, dtype, G, W, D, scorer, follows):
+    """One round of fp32 tiles, two of large bf16 ones, three of small ones; past them the scorer hands its sums of usage and credit
+    to the kernel that forms masses and cuts (up to 512 units) or to the position-wise one.  Short and empty sequences would only
+    repeat the pinned path's test."""
+    w = inputs.CONFIGS[1].scaled(L=1, B=1, H=units, G=G, W=W, D=D, T=T, T_min=T, dtype=dtype, budget=T // 4, S=5, n_spans=2,
+                                 span_len=(4, 30))
+    host = inputs.dense_cache(w, n_threads=4)
+    credit = np.random.default_rng(units).random((units, T)).astype(np.float32)
+    credit /= credit.sum(1, keepdims=True)
+    job = Job(w, host, scorer=scorer, credit=credit)
+    labels = _labels(job)
+    assert "score_unit" in labels
+    assert (follows in labels) if follows else not any("mass" in x or "cuts" in x for x in labels)
+    check_properties_all_units(job)
+    before = np.zeros((units, job.t_max), np.float32)
+    before[:, :T] = credit
+    check_units(oracle, job, host, before, [0, 1, units // 2, units - 1], scorer=scorer)
+
+
 @pytest.mark.parametrize("vec", [True, False])
 @pytest.mark.parametrize("T,S,fused", [(2048, 64, True), (2049, 5, True), (4096, 64, True), (4097, 7, True), (8192, 64, True),
                                        (8193, 16, False), (3000, 65, False), (63, 3, True)])
