@@ -646,12 +646,15 @@ __device__ __forceinline__ float4 query_weights(const ScoreArgs& a, int n, int T
                      real ? 1.f : 0.f);
 }
 
-// Latency bounds this kernel: up to eight chunks of a thread's range travel at once, more of them four at a time, and the credit
-// before them (4 units of 10126 positions, 80 chunks: 12.1 -> 10.3 us, 45.0 -> 42.9 per step; 10 of 87760 22.6 -> 20.0; sixteen at
-// once lose, 46.0; no difference where the credit's bytes bound it, 14.6 and 14.2 for 256 of 32768).
 // Chunk statistics merged per query: the 1024 threads split into (query, contiguous range of
 // chunks) pairs, the ranges are then combined in ascending order (fixed association) -> M_n and
 // the per-query weights of the column sums.
+// Latency bounds this kernel: a thread's range of up to two or up to eight chunks travels at once, a longer one four chunks at a
+// time, and the credit before them.  us of the kernel with one chunk after the other and the credit last, with eight places at once
+// in all ranges of up to eight, and as it is: 12.1, 12.8 and 12.2 (256 units of 32768, a chunk per thread), 11.0, 11.6 and 11.1 (the
+// same with the expected attention), 5.6, 6.1 and 5.8 (causal window), 9.2, 7.6 and 7.6 (4 units of 10126, 80 chunks, five per
+// thread), 11.5, 10.5 and 10.6 (10 of 87760), 23.5, 21.9 and 22.1 (112 of 131072, 224 queries).  A form for every power of two costs
+// the causal one 0.2, the larger code being read in a kernel of 5 us; sixteen places at once lose (46.0 us per step, 42.9 with eight).
 constexpr int kReduceThreads = 1024;
 __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs a) {
   __shared__ float pm[kReduceThreads];
@@ -686,14 +689,20 @@ __global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs 
     const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
     float M = kNegInit;
     double Z = 0.0;
-    if (per <= 8) {  // all entries in flight
-      float2 s[8];
+    auto all_at_once = [&](auto most) __attribute__((always_inline)) {
+      constexpr int N = decltype(most)::value;
+      float2 s[N];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) s[i] = c0 + i < c1 ? p[(int64_t)(c0 + i) * a.n_pad] : make_float2(kNegInit, 0.f);
+      for (int i = 0; i < N; ++i) s[i] = c0 + i < c1 ? p[(int64_t)(c0 + i) * a.n_pad] : make_float2(kNegInit, 0.f);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) M = fmaxf(M, s[i].x);
+      for (int i = 0; i < N; ++i) M = fmaxf(M, s[i].x);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) Z += (double)s[i].y * (double)__builtin_amdgcn_exp2f(s[i].x - M);
+      for (int i = 0; i < N; ++i) Z += (double)s[i].y * (double)__builtin_amdgcn_exp2f(s[i].x - M);
+    };
+    if (per <= 2) {
+      all_at_once(std::integral_constant<int, 2>{});
+    } else if (per <= 8) {
+      all_at_once(std::integral_constant<int, 8>{});
     } else {
 #pragma unroll 4
       for (int c = c0; c < c1; ++c) M = fmaxf(M, p[(int64_t)c * a.n_pad].x);
