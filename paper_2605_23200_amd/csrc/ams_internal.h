@@ -129,10 +129,15 @@ hipError_t launch_score_oneread(const ams_params* p, const Dims& d, const KvDev&
 // to the quotas.
 struct ScoreArgs;
 hipError_t launch_score_unit(const ScoreArgs& a, bool bf16, int head_dim, int mode, const UnitCuts* cuts, hipStream_t s, bool* ran);
-// The two sweeps under the causal window (score_causal.hip), with the last-query score (score_last.hip), and with both.
-hipError_t launch_causal_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
-hipError_t launch_last_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
-hipError_t launch_causal_last_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
+// The first sweep and the reduction of its statistics (score.hip; under the causal window score_causal.hip); the reduction alone.
+hipError_t launch_first_sweep(const ScoreArgs& a, int nb, int head_dim, bool moments, bool bf16, hipStream_t s);
+hipError_t launch_causal_first_sweep(const ScoreArgs& a, int nb, int head_dim, bool moments, bool bf16, hipStream_t s);
+hipError_t launch_score_reduce(const ScoreArgs& a, hipStream_t s);
+// The second sweep: usage alone under the causal window (score_causal.hip), usage and last-query score (score_last.hip), both
+// (score_causal_last.hip).
+hipError_t launch_causal_usage(const ScoreArgs& a, int nb, int head_dim, bool bf16, hipStream_t s);
+hipError_t launch_last_usage(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
+hipError_t launch_causal_last_usage(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s);
 // The two sweeps with the key-diversity score, or the mean cosines of the redundancy-aware one, left in a.g (bf16 caches,
 // no causal window; score_keys.hip).
 hipError_t launch_key_sweeps(const ScoreArgs& a, int nb, int head_dim, bool cosines, hipStream_t s);

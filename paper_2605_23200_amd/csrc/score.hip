@@ -329,7 +329,115 @@ hipError_t launch_redundancy(const ScoreArgs& a, char* ws, const WsLayout& wl, f
   return hipGetLastError();
 }
 
+// Chunk statistics merged per query: the 1024 threads split into (query, contiguous range of
+// chunks) pairs, the ranges are then combined in ascending order (fixed association) -> M_n and
+// the per-query weights of the column sums.
+// Latency bounds this kernel: a thread's range of up to two or up to eight chunks travels at once, a longer one four chunks at a
+// time, and the credit before them.  us of the kernel with one chunk after the other and the credit last, with eight places at once
+// in all ranges of up to eight, and as it is: 12.1, 12.8 and 12.2 (256 units of 32768, a chunk per thread), 11.0, 11.6 and 11.1 (the
+// same with the expected attention), 5.6, 6.1 and 5.8 (causal window), 9.2, 7.6 and 7.6 (4 units of 10126, 80 chunks, five per
+// thread), 11.5, 10.5 and 10.6 (10 of 87760), 23.5, 21.9 and 22.1 (112 of 131072, 224 queries).  A form for every power of two costs
+// the causal one 0.2, the larger code being read in a kernel of 5 us; sixteen places at once lose (46.0 us per step, 42.9 with eight).
+constexpr int kReduceThreads = 1024;
+__global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs a) {
+  __shared__ float pm[kReduceThreads];
+  __shared__ double pz[kReduceThreads];
+  const int unit = blockIdx.x;
+  if (unit == 0 && threadIdx.x == 0 && a.status) *a.status = 0;  // no bounded wait on this path
+  int l, b, h;
+  unit_coords(a.d, unit, l, b, h);
+  const int T = seq_len(a.d, a.seq_lens, b);
+  const int len = chunk_len(a, T), nch = (causal_t_end(a, T, a.causal) + len - 1) / len + (a.causal ? 1 : 0);
+  double credit = 0.0;  // sum of the credit before the update (for the EMA normaliser), strided partials in a fixed tree
+  if (a.csum) {         // first, so that the statistics travel meanwhile
+    const float* c_row = a.credit + (int64_t)unit * a.d.t_stride;
+    if ((a.d.t_stride & 3) == 0 && ((uintptr_t)a.credit & 15) == 0) {  // 16-byte loads, several in flight
+      const float4* c4 = (const float4*)c_row;
+      const int n4 = T >> 2;
+#pragma unroll 8
+      for (int q = threadIdx.x; q < n4; q += kReduceThreads) {
+        const float4 v = c4[q];
+        credit += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
+      }
+      for (int t = (n4 << 2) + threadIdx.x; t < T; t += kReduceThreads) credit += (double)c_row[t];
+    } else {
+      for (int t = threadIdx.x; t < T; t += kReduceThreads) credit += (double)c_row[t];
+    }
+  }
+  const int parts = kReduceThreads / a.n_pad;
+  const int n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
+  if (part < parts) {
+    const int per = (nch + parts - 1) / parts;
+    const int c0 = part * per, c1 = min(nch, c0 + per);
+    const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
+    float M = kNegInit;
+    double Z = 0.0;
+    auto all_at_once = [&](auto most) __attribute__((always_inline)) {
+      constexpr int N = decltype(most)::value;
+      float2 s[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) s[i] = c0 + i < c1 ? p[(int64_t)(c0 + i) * a.n_pad] : make_float2(kNegInit, 0.f);
+#pragma unroll
+      for (int i = 0; i < N; ++i) M = fmaxf(M, s[i].x);
+#pragma unroll
+      for (int i = 0; i < N; ++i) Z += (double)s[i].y * (double)__builtin_amdgcn_exp2f(s[i].x - M);
+    };
+    if (per <= 2) {
+      all_at_once(std::integral_constant<int, 2>{});
+    } else if (per <= 8) {
+      all_at_once(std::integral_constant<int, 8>{});
+    } else {
+#pragma unroll 4
+      for (int c = c0; c < c1; ++c) M = fmaxf(M, p[(int64_t)c * a.n_pad].x);
+#pragma unroll 4
+      for (int c = c0; c < c1; ++c) {
+        const float2 s = p[(int64_t)c * a.n_pad];
+        Z += (double)s.y * (double)__builtin_amdgcn_exp2f(s.x - M);
+      }
+    }
+    pm[threadIdx.x] = M;
+    pz[threadIdx.x] = Z;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < a.n_pad) {
+    float M = kNegInit;
+    for (int q = 0; q < parts; ++q) M = fmaxf(M, pm[q * a.n_pad + n]);
+    double Z = 0.0;
+    for (int q = 0; q < parts; ++q) Z += pz[q * a.n_pad + n] * (double)__builtin_amdgcn_exp2f(pm[q * a.n_pad + n] - M);
+    a.fin[(int64_t)unit * a.n_pad + n] = query_weights(a, n, T, M, Z, a.causal, true);
+  }
+  if (a.ksum && (int)threadIdx.x < a.d.D) {  // the unit's key sum takes the place of its first chunk's, for the second sweep
+    double* k = a.ksum + (int64_t)unit * a.n_chunks * a.d.D + threadIdx.x;
+    double t = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < nch; ++c) t += k[(int64_t)c * a.d.D];
+    *k = t;
+  }
+  if (a.csum) {
+    __shared__ double cs[kReduceThreads / 64];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) credit += __shfl_xor(credit, o);
+    if ((threadIdx.x & 63) == 0) cs[threadIdx.x >> 6] = credit;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int w = 0; w < kReduceThreads / 64; ++w) t += cs[w];
+      a.csum[unit] = t;
+    }
+  }
+}
+
 }  // namespace
+
+hipError_t launch_score_reduce(const ScoreArgs& a, hipStream_t s) {
+  prof_mark("score_reduce", s);
+  hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_first_sweep(const ScoreArgs& a, int nb, int head_dim, bool moments, bool bf16, hipStream_t s) {
+  return first_sweep<false>(a, nb, head_dim, moments, bf16, s);
+}
 
 hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, const KvDev* v,
                         const int32_t* seq_lens,
@@ -448,11 +556,15 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     vc_even = a.even;
     keys_done = true;
   } else if (!oneread) {
-    const bool last = p->scorer == AMS_SCORER_LAST_QUERY;
+    const bool last = p->scorer == AMS_SCORER_LAST_QUERY, moments = mode == MODE_EXPECTED;
+    e = causal ? launch_causal_first_sweep(a, nb, d.D, moments, bf16, s) : launch_first_sweep(a, nb, d.D, moments, bf16, s);
+    if (e != hipSuccess) return e;
+    ScoreArgs a2 = a;
+    if (moments) a2.g = nullptr;  // the moment-based score has been written by the first sweep: the second one leaves g alone
     if (causal)
-      e = last ? launch_causal_last_sweeps(a, nb, d.D, mode, bf16, s) : launch_causal_sweeps(a, nb, d.D, mode, bf16, s);
+      e = last ? launch_causal_last_usage(a2, nb, d.D, mode, bf16, s) : launch_causal_usage(a2, nb, d.D, bf16, s);
     else
-      e = last ? launch_last_sweeps(a, nb, d.D, mode, bf16, s) : launch_sweeps<false, SCORERS_MEAN>(a, nb, d.D, mode, bf16, s);
+      e = last ? launch_last_usage(a2, nb, d.D, mode, bf16, s) : second_sweep<MODE_MEAN, false>(a2, nb, d.D, bf16, s);
     vc_stride = a.n_chunks;
     vc_tokens = a.chunk;
     vc_even = a.even;

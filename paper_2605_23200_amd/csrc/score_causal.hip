@@ -4,9 +4,14 @@
 
 namespace ams {
 
-hipError_t launch_causal_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s) {
+hipError_t launch_causal_first_sweep(const ScoreArgs& a, int nb, int head_dim, bool moments, bool bf16, hipStream_t s) {
   if (!a.causal) return hipErrorInvalidValue;
-  return launch_sweeps<true, SCORERS_MEAN>(a, nb, head_dim, mode, bf16, s);
+  return first_sweep<true>(a, nb, head_dim, moments, bf16, s);
+}
+
+hipError_t launch_causal_usage(const ScoreArgs& a, int nb, int head_dim, bool bf16, hipStream_t s) {
+  if (!a.causal) return hipErrorInvalidValue;
+  return second_sweep<MODE_MEAN, true>(a, nb, head_dim, bf16, s);
 }
 
 }  // namespace ams

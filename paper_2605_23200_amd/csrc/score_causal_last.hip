@@ -3,9 +3,10 @@
 
 namespace ams {
 
-hipError_t launch_causal_last_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s) {
+hipError_t launch_causal_last_usage(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s) {
   if (!a.causal) return hipErrorInvalidValue;
-  return launch_sweeps<true, SCORERS_LAST>(a, nb, head_dim, mode, bf16, s);
+  if (mode == MODE_LAST_LANES) return second_sweep<MODE_LAST_LANES, true>(a, nb, head_dim, bf16, s);
+  return mode == MODE_LAST ? second_sweep<MODE_LAST, true>(a, nb, head_dim, bf16, s) : hipErrorInvalidValue;
 }
 
 }  // namespace ams

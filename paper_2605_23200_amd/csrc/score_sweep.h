@@ -646,104 +646,6 @@ __device__ __forceinline__ float4 query_weights(const ScoreArgs& a, int n, int T
                      real ? 1.f : 0.f);
 }
 
-// Chunk statistics merged per query: the 1024 threads split into (query, contiguous range of
-// chunks) pairs, the ranges are then combined in ascending order (fixed association) -> M_n and
-// the per-query weights of the column sums.
-// Latency bounds this kernel: a thread's range of up to two or up to eight chunks travels at once, a longer one four chunks at a
-// time, and the credit before them.  us of the kernel with one chunk after the other and the credit last, with eight places at once
-// in all ranges of up to eight, and as it is: 12.1, 12.8 and 12.2 (256 units of 32768, a chunk per thread), 11.0, 11.6 and 11.1 (the
-// same with the expected attention), 5.6, 6.1 and 5.8 (causal window), 9.2, 7.6 and 7.6 (4 units of 10126, 80 chunks, five per
-// thread), 11.5, 10.5 and 10.6 (10 of 87760), 23.5, 21.9 and 22.1 (112 of 131072, 224 queries).  A form for every power of two costs
-// the causal one 0.2, the larger code being read in a kernel of 5 us; sixteen places at once lose (46.0 us per step, 42.9 with eight).
-constexpr int kReduceThreads = 1024;
-__global__ __launch_bounds__(kReduceThreads) void score_reduce_kernel(ScoreArgs a) {
-  __shared__ float pm[kReduceThreads];
-  __shared__ double pz[kReduceThreads];
-  const int unit = blockIdx.x;
-  if (unit == 0 && threadIdx.x == 0 && a.status) *a.status = 0;  // no bounded wait on this path
-  int l, b, h;
-  unit_coords(a.d, unit, l, b, h);
-  const int T = seq_len(a.d, a.seq_lens, b);
-  const int len = chunk_len(a, T), nch = (causal_t_end(a, T, a.causal) + len - 1) / len + (a.causal ? 1 : 0);
-  double credit = 0.0;  // sum of the credit before the update (for the EMA normaliser), strided partials in a fixed tree
-  if (a.csum) {         // first, so that the statistics travel meanwhile
-    const float* c_row = a.credit + (int64_t)unit * a.d.t_stride;
-    if ((a.d.t_stride & 3) == 0 && ((uintptr_t)a.credit & 15) == 0) {  // 16-byte loads, several in flight
-      const float4* c4 = (const float4*)c_row;
-      const int n4 = T >> 2;
-#pragma unroll 8
-      for (int q = threadIdx.x; q < n4; q += kReduceThreads) {
-        const float4 v = c4[q];
-        credit += ((double)v.x + (double)v.y) + ((double)v.z + (double)v.w);
-      }
-      for (int t = (n4 << 2) + threadIdx.x; t < T; t += kReduceThreads) credit += (double)c_row[t];
-    } else {
-      for (int t = threadIdx.x; t < T; t += kReduceThreads) credit += (double)c_row[t];
-    }
-  }
-  const int parts = kReduceThreads / a.n_pad;
-  const int n = threadIdx.x % a.n_pad, part = threadIdx.x / a.n_pad;
-  if (part < parts) {
-    const int per = (nch + parts - 1) / parts;
-    const int c0 = part * per, c1 = min(nch, c0 + per);
-    const float2* p = a.part + (int64_t)unit * (a.n_chunks + 1) * a.n_pad + n;
-    float M = kNegInit;
-    double Z = 0.0;
-    auto all_at_once = [&](auto most) __attribute__((always_inline)) {
-      constexpr int N = decltype(most)::value;
-      float2 s[N];
-#pragma unroll
-      for (int i = 0; i < N; ++i) s[i] = c0 + i < c1 ? p[(int64_t)(c0 + i) * a.n_pad] : make_float2(kNegInit, 0.f);
-#pragma unroll
-      for (int i = 0; i < N; ++i) M = fmaxf(M, s[i].x);
-#pragma unroll
-      for (int i = 0; i < N; ++i) Z += (double)s[i].y * (double)__builtin_amdgcn_exp2f(s[i].x - M);
-    };
-    if (per <= 2) {
-      all_at_once(std::integral_constant<int, 2>{});
-    } else if (per <= 8) {
-      all_at_once(std::integral_constant<int, 8>{});
-    } else {
-#pragma unroll 4
-      for (int c = c0; c < c1; ++c) M = fmaxf(M, p[(int64_t)c * a.n_pad].x);
-#pragma unroll 4
-      for (int c = c0; c < c1; ++c) {
-        const float2 s = p[(int64_t)c * a.n_pad];
-        Z += (double)s.y * (double)__builtin_amdgcn_exp2f(s.x - M);
-      }
-    }
-    pm[threadIdx.x] = M;
-    pz[threadIdx.x] = Z;
-  }
-  __syncthreads();
-  if ((int)threadIdx.x < a.n_pad) {
-    float M = kNegInit;
-    for (int q = 0; q < parts; ++q) M = fmaxf(M, pm[q * a.n_pad + n]);
-    double Z = 0.0;
-    for (int q = 0; q < parts; ++q) Z += pz[q * a.n_pad + n] * (double)__builtin_amdgcn_exp2f(pm[q * a.n_pad + n] - M);
-    a.fin[(int64_t)unit * a.n_pad + n] = query_weights(a, n, T, M, Z, a.causal, true);
-  }
-  if (a.ksum && (int)threadIdx.x < a.d.D) {  // the unit's key sum takes the place of its first chunk's, for the second sweep
-    double* k = a.ksum + (int64_t)unit * a.n_chunks * a.d.D + threadIdx.x;
-    double t = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < nch; ++c) t += k[(int64_t)c * a.d.D];
-    *k = t;
-  }
-  if (a.csum) {
-    __shared__ double cs[kReduceThreads / 64];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) credit += __shfl_xor(credit, o);
-    if ((threadIdx.x & 63) == 0) cs[threadIdx.x >> 6] = credit;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      double t = 0.0;
-      for (int w = 0; w < kReduceThreads / 64; ++w) t += cs[w];
-      a.csum[unit] = t;
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Sweep 2: u[t] = sum_n exp2(x[n][t] - M_n) / (N Z_n), and g for the softmax-based scorers.
 // ---------------------------------------------------------------------------------------------
@@ -1072,23 +974,36 @@ __global__ __launch_bounds__((kSweepThreads<BF16, NB, HD>), (BF16 && NB <= 4) ? 
   usage_body<BF16, NB, MODE, CAUSAL, false, HD, KEYS, FOLD>(a, sm, unit, chunk);
 }
 
-// Scorers that a source file instantiates the sweeps for (with all of them in one code object 8 units of 32768 positions took
-// 70.2 us per step, 68.4 with the last query's in one of their own).
-enum { SCORERS_MEAN = 0, SCORERS_LAST = 1 };
+// Calls f with the tile of a launch: (bf16 cache, column blocks, channels) as types.
+template <typename F>
+hipError_t by_tile(int nb, int head_dim, bool bf16, F f) {
+  auto by_nb = [&](auto bf16_c, auto hd_c) {
+    if (nb <= 1) return f(bf16_c, std::integral_constant<int, 1>{}, hd_c);
+    if (nb <= 2) return f(bf16_c, std::integral_constant<int, 2>{}, hd_c);
+    if (nb <= 4) return f(bf16_c, std::integral_constant<int, 4>{}, hd_c);
+    if constexpr (decltype(bf16_c)::value) {
+      if (nb <= 7) return f(bf16_c, std::integral_constant<int, 7>{}, hd_c);
+      if (nb <= 8) return f(bf16_c, std::integral_constant<int, 8>{}, hd_c);
+    }
+    return hipErrorInvalidValue;
+  };
+  auto by_dtype = [&](auto hd_c) { return bf16 ? by_nb(std::true_type{}, hd_c) : by_nb(std::false_type{}, hd_c); };
+  return head_dim == 64 ? by_dtype(std::integral_constant<int, 64>{}) : by_dtype(std::integral_constant<int, 128>{});
+}
 
-template <bool BF16, int NB, bool CAUSAL, int HD, int SCORERS>
-hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hipStream_t s) {
+template <bool BF16, int NB, bool CAUSAL, int HD>
+hipError_t launch_stats(const ScoreArgs& a, bool moments, hipStream_t s) {
+  const SweepGrid sg = sweep_grid(a.d.units, a.n_chunks, CAUSAL);
   auto launch = [&](auto moments_c) {
-    constexpr int M = decltype(moments_c)::value;
+    constexpr int M = decltype(moments_c)::value, lds = NB * 32 * Tr<BF16, HD>::kQStride;
     const hipError_t e = ensure_lds<score_stats_kernel<BF16, NB, CAUSAL, M, HD>>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, CAUSAL, M, HD>), grid, dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
+    prof_mark("score_stats", s);
+    hipLaunchKernelGGL((score_stats_kernel<BF16, NB, CAUSAL, M, HD>), dim3(sg.x, sg.y), dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
     return hipGetLastError();
   };
   if (!moments) return launch(std::integral_constant<int, MOMENTS_NONE>{});
-  if constexpr (SCORERS == SCORERS_LAST) {
-    return hipErrorInvalidValue;
-  } else if constexpr (BF16 && HD == 64) {
+  if constexpr (BF16 && HD == 64) {
     return launch(std::integral_constant<int, MOMENTS_CENTRED>{});
   } else {
     if constexpr (BF16 && NB == 4)
@@ -1097,26 +1012,36 @@ hipError_t launch_stats(const ScoreArgs& a, bool moments, dim3 grid, int lds, hi
   }
 }
 
-template <bool BF16, int NB, bool CAUSAL, int HD, int SCORERS>
-hipError_t launch_usage(const ScoreArgs& a, int mode, dim3 grid, int lds, hipStream_t s) {
-  const dim3 blk(kSweepThreads<BF16, NB, HD>);
-  hipError_t e;
-  auto launch = [&](auto mode_c, auto fold_c) {
-    constexpr int M = decltype(mode_c)::value;
+template <bool BF16, int NB, int MODE, bool CAUSAL, int HD>
+hipError_t launch_usage(const ScoreArgs& a, hipStream_t s) {
+  const SweepGrid sg = sweep_grid(a.d.units, a.n_chunks, CAUSAL);
+  auto launch = [&](auto fold_c) {
     constexpr bool F = decltype(fold_c)::value;
-    if ((e = ensure_lds<score_usage_kernel<BF16, NB, M, CAUSAL, HD, KEYS_NONE, F>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((score_usage_kernel<BF16, NB, M, CAUSAL, HD, KEYS_NONE, F>), grid, blk, lds, s, a);
+    constexpr int lds = NB * 32 * Tr<BF16, HD>::kQStride;
+    const hipError_t e = ensure_lds<score_usage_kernel<BF16, NB, MODE, CAUSAL, HD, KEYS_NONE, F>>(lds);
+    if (e != hipSuccess) return e;
+    prof_mark("score_usage", s);
+    hipLaunchKernelGGL((score_usage_kernel<BF16, NB, MODE, CAUSAL, HD, KEYS_NONE, F>), dim3(sg.x, sg.y),
+                       dim3(kSweepThreads<BF16, NB, HD>), lds, s, a);
     return hipGetLastError();
   };
-  auto by_fold = [&](auto mode_c) {
-    return a.fold ? launch(mode_c, std::true_type{}) : launch(mode_c, std::false_type{});
-  };
-  if constexpr (SCORERS == SCORERS_LAST) {
-    if (mode == MODE_LAST_LANES) return by_fold(std::integral_constant<int, MODE_LAST_LANES>{});
-    return mode == MODE_LAST ? by_fold(std::integral_constant<int, MODE_LAST>{}) : hipErrorInvalidValue;
-  } else {
-    return by_fold(std::integral_constant<int, MODE_MEAN>{});
-  }
+  return a.fold ? launch(std::true_type{}) : launch(std::false_type{});
+}
+
+// The sweeps over the caches of one kind of window.  The first one and the reduction after it are the same for every scorer; a file
+// holds the kernels that it names.
+template <bool CAUSAL>
+hipError_t first_sweep(const ScoreArgs& a, int nb, int head_dim, bool moments, bool bf16, hipStream_t s) {
+  const hipError_t e = by_tile(nb, head_dim, bf16, [&](auto bf16_c, auto nb_c, auto hd_c) {
+    return launch_stats<decltype(bf16_c)::value, decltype(nb_c)::value, CAUSAL, decltype(hd_c)::value>(a, moments, s);
+  });
+  return e != hipSuccess || a.fold ? e : launch_score_reduce(a, s);
+}
+template <int MODE, bool CAUSAL>
+hipError_t second_sweep(const ScoreArgs& a, int nb, int head_dim, bool bf16, hipStream_t s) {
+  return by_tile(nb, head_dim, bf16, [&](auto bf16_c, auto nb_c, auto hd_c) {
+    return launch_usage<decltype(bf16_c)::value, decltype(nb_c)::value, MODE, CAUSAL, decltype(hd_c)::value>(a, s);
+  });
 }
 
 // The two plain sweeps with the keys riding along.
@@ -1130,51 +1055,10 @@ hipError_t run_key_sweeps(const ScoreArgs& a, hipStream_t s) {
   if ((e = ensure_lds<usage>(lds_k)) != hipSuccess) return e;
   prof_mark("score_stats", s);
   hipLaunchKernelGGL((score_stats_kernel<true, NB, false, MOMENTS_NONE, HD, KEYS>), grid, blk, lds, s, a);
-  if (!FOLD) {
-    prof_mark("score_reduce", s);
-    hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
-  }
+  if (!FOLD && (e = launch_score_reduce(a, s)) != hipSuccess) return e;
   prof_mark("score_usage", s);
   hipLaunchKernelGGL(usage, grid, blk, lds_k, s, a);
   return hipGetLastError();
-}
-
-template <bool BF16, int NB, bool CAUSAL, int HD, int SCORERS>
-hipError_t run_softmax_sweeps(const ScoreArgs& a, int mode, hipStream_t s) {
-  const int lds = NB * 32 * Tr<BF16, HD>::kQStride;
-  const SweepGrid sg = sweep_grid(a.d.units, a.n_chunks, CAUSAL);
-  const dim3 grid(sg.x, sg.y);
-  hipError_t e;
-  prof_mark("score_stats", s);
-  if ((e = launch_stats<BF16, NB, CAUSAL, HD, SCORERS>(a, mode == MODE_EXPECTED, grid, lds, s)) != hipSuccess) return e;
-  if (!a.fold) {
-    prof_mark("score_reduce", s);
-    hipLaunchKernelGGL(score_reduce_kernel, dim3(a.d.units), dim3(kReduceThreads), 0, s, a);
-  }
-  // the moment-based score has been written by the first sweep: the second one leaves g alone
-  ScoreArgs a2 = a;
-  if (mode == MODE_EXPECTED) a2.g = nullptr;
-  prof_mark("score_usage", s);
-  return launch_usage<BF16, NB, CAUSAL, HD, SCORERS>(a2, mode, grid, lds, s);
-}
-
-template <bool BF16, bool CAUSAL, int HD, int SCORERS>
-hipError_t run_by_nb(const ScoreArgs& a, int nb, int mode, hipStream_t s) {
-  if (nb <= 1) return run_softmax_sweeps<BF16, 1, CAUSAL, HD, SCORERS>(a, mode, s);
-  if (nb <= 2) return run_softmax_sweeps<BF16, 2, CAUSAL, HD, SCORERS>(a, mode, s);
-  if (nb <= 4) return run_softmax_sweeps<BF16, 4, CAUSAL, HD, SCORERS>(a, mode, s);
-  if constexpr (BF16) {
-    if (nb <= 7) return run_softmax_sweeps<BF16, 7, CAUSAL, HD, SCORERS>(a, mode, s);
-    if (nb <= 8) return run_softmax_sweeps<BF16, 8, CAUSAL, HD, SCORERS>(a, mode, s);
-  }
-  return hipErrorInvalidValue;
-}
-
-template <bool CAUSAL, int SCORERS>
-hipError_t launch_sweeps(const ScoreArgs& a, int nb, int head_dim, int mode, bool bf16, hipStream_t s) {
-  if (head_dim == 64)
-    return bf16 ? run_by_nb<true, CAUSAL, 64, SCORERS>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 64, SCORERS>(a, nb, mode, s);
-  return bf16 ? run_by_nb<true, CAUSAL, 128, SCORERS>(a, nb, mode, s) : run_by_nb<false, CAUSAL, 128, SCORERS>(a, nb, mode, s);
 }
 
 }  // namespace

@@ -71,3 +71,8 @@ def test_tails_cost_the_second_sweep_no_registers(kernels):
     assert len(causal) >= 50
     worse = {a: (n, spills[a[:3] + (0,) + a[4:]]) for a, n in causal.items() if n > spills[a[:3] + (0,) + a[4:]]}
     assert not worse
+
+
+def test_every_kernel_is_in_the_library_once(kernels):
+    names = [k[".name"] for _, _, k in kernels]
+    assert sorted({n for n in names if names.count(n) > 1}) == []
