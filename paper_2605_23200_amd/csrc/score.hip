@@ -528,13 +528,16 @@ hipError_t launch_score(const ams_params* p, const Dims& d, const KvDev& k, cons
     const bool want_unit = p->score_path == AMS_SCORE_PATH_ONE_LAUNCH ||
                            (p->score_path == AMS_SCORE_PATH_AUTO && d.units >= kUnitScorerMinUnits && !keys_ride && !thin);
     if (want_unit) {
-      // The scorer's workgroups go on to the quotas (score_unit_kernel) in the few rounds in which the 6 to 8 us at the end of each
-      // cost less than the launches: a CU holds two of them with small bf16 tiles, else one, so that nothing runs beside the end.
-      // Time without over time with, by rounds: fp32 one 1.02 to 1.03, two 0.98 to 0.99 (300 units of 1200, 400 of 1100, 64
-      // channels); large bf16 tiles one 1.03 to 1.07, two 1.01 to 1.02 (512 of 1500 and 2048), four 0.98 (900 of 1100), six to
-      // eight 0.98 to 0.99; small ones one 1.06 to 1.08, two 1.08 (832 of 1425), three 1.02 (1224 of 3000).
-      const bool small = unit_tile_small(bf16, nb, d.D);
-      const bool few = d.units <= (small ? 3 * 512 : bf16 ? 2 * 256 : 256);
+      // The scorer's workgroups go on to the quotas (score_unit_kernel) where the 6 to 8 us at their end cost less than the launch.
+      // Small bf16 tiles, of which a CU holds two that hide part of each other's end: up to three rounds; time without over time with
+      // 1.02 to 1.06 for one, 1.04 to 1.09 for two (520 to 1024 units of 400 to 3500 positions), 1.00 to 1.07 for three (1040 to
+      // 1536).  The others: one round, 1.03 to 1.08 (200 and 256 units of 400 to 3500, large bf16 tiles), 1.02 to 1.08 (130 and 256
+      // fp32 units of 300 to 3000; four blocks of 128 channels 1.04 at 300 positions, 1.01 at 1000, 0.99 to 1.01 from 2000 on).  Two
+      // rounds expose two such ends: 0.97 to 1.00 (264 to 512 units of 400 and 1500), fp32 0.98 to 0.99.  Past 2048 positions the
+      // launch that they replace needs 512 threads a unit and costs more: there 1.00 to 1.01 (2176 and 3500), but for the tile that
+      // fills the registers (128 channels, over 64 queries: 0.98 to 1.01).  Four rounds 0.98.
+      const bool small = unit_tile_small(bf16, nb, d.D), two = bf16 && d.t_max > 2048 && (nb <= 2 || d.D == 64);
+      const bool few = d.units <= (small ? 3 * 512 : two ? 2 * 256 : 256);
       const UnitCuts* cuts = vc && few ? vc->unit_cuts : nullptr;
       e = launch_score_unit(a, bf16, d.D, mode, cuts, s, &oneread);
       if (cuts && oneread) vc->cuts = true;

@@ -19,7 +19,7 @@ constexpr int kUnitThreads = 512, kUnitWaves = kUnitThreads / 64;
 // CUTS: the workgroup goes on to the masses, the cuts and the quotas (mass_cuts.h) on the usage that it holds, 4 to 9 us at its end
 // for one or two launches of 11 to 17.  us per step without and with: 170.5 and 166.1 (256 units of 2176, 128 queries), 86.9 and
 // 82.2 (192 of 4093, 64 channels), 110.3 and 101.8 (832 of 1425, 64 channels), 58.6 and 55.5 (300 of 1024, 8 queries), 407 and 398
-// (1224 of 3000, 32 queries), 119.0 and 117.0 (512 of 1500, 64 queries), 309 and 308 (600 fp32 units of 2000).
+// (1224 of 3000, 32 queries).  Only in launches of few rounds (launch_score).
 template <bool BF16, int NB, int MODE, int HD, bool CUTS>
 __global__ __launch_bounds__(kUnitThreads, (unit_tile_small(BF16, NB, HD) ? 4 : 2)) void score_unit_kernel(ScoreArgs a, MsArgs ms, CutsOut out) {
   constexpr int NG = (BF16 && NB % 2 == 0 && NB >= 4) ? NB / 2 : NB, QS = Tr<BF16, HD>::kQStride, NQ = NB * 32;

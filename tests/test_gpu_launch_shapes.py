@@ -429,13 +429,15 @@ def test_one_launch_scorer_goes_on_to_the_quotas(oracle, T, S, dtype, G, W, D, s
 
 @pytest.mark.parametrize("units,T,dtype,G,W,D,scorer,follows", [
     (256, 300, "f32", 1, 8, 64, B.SCORER_MEAN_WINDOW, None), (257, 300, "f32", 1, 8, 64, B.SCORER_MEAN_WINDOW, "unit_mass_cuts"),
-    (512, 200, "bf16", 4, 32, 128, B.SCORER_LAST_QUERY, None), (513, 200, "bf16", 4, 32, 128, B.SCORER_LAST_QUERY, "mass_ema"),
+    (256, 200, "bf16", 4, 32, 128, B.SCORER_LAST_QUERY, None), (257, 200, "bf16", 4, 32, 128, B.SCORER_LAST_QUERY, "unit_mass_cuts"),
+    (512, 200, "bf16", 4, 32, 64, B.SCORER_LAST_QUERY, "unit_mass_cuts"), (258, 2049, "bf16", 4, 32, 64, B.SCORER_MEAN_WINDOW, None),
+    (257, 2049, "bf16", 3, 32, 128, B.SCORER_MEAN_WINDOW, "unit_mass_cuts"), (513, 200, "bf16", 4, 32, 128, B.SCORER_LAST_QUERY, "mass_ema"),
     (1536, 130, "bf16", 1, 8, 64, B.SCORER_MEAN_WINDOW, None), (1537, 130, "bf16", 1, 8, 64, B.SCORER_MEAN_WINDOW, "mass_ema"),
     (1536, 97, "bf16", 1, 24, 128, B.SCORER_LAST_QUERY, None), (130, 555, "f32", 3, 32, 128, B.SCORER_MEAN_WINDOW, None)])
 def test_units_up_to_which_the_scorer_goes_on_to_the_quotas(oracle, units, T, dtype, G, W, D, scorer, follows):
-    """One round of fp32 tiles, two of large bf16 ones, three of small ones; past them the scorer hands its sums of usage and credit
-    to the kernel that forms masses and cuts (up to 512 units) or to the position-wise one.  Short and empty sequences would only
-    repeat the pinned path's test."""
+    """One round of fp32 and of large bf16 tiles (two of most of the latter past 2048 positions), three of small ones; past them the
+    scorer hands its sums of usage and credit to the kernel that forms masses and cuts (up to 512 units) or to the position-wise one.
+    Short and empty sequences would only repeat the pinned path's test."""
     w = inputs.CONFIGS[1].scaled(L=1, B=1, H=units, G=G, W=W, D=D, T=T, T_min=T, dtype=dtype, budget=T // 4, S=5, n_spans=2,
                                  span_len=(4, 30))
     host = inputs.dense_cache(w, n_threads=4)
