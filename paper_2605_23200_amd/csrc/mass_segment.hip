@@ -295,7 +295,6 @@ hipError_t launch_segment_static(const ams_params* p, const Dims& d, const int32
   return hipGetLastError();
 }
 
-// The fused step's mass / EMA / segmentation / quota stages.
 // The arguments of the stages between the scores and the selection of a fused step.
 hipError_t unit_cuts_args(const ams_params* p, const Dims& d, const int32_t* seq_lens, const float* u, float* credit, float* m_used,
                           int32_t* bounds, float* seg_mass, int32_t* quota, int32_t* idx, int32_t* n_kept, uint32_t* flags,
@@ -318,6 +317,7 @@ bool unit_scorer_cuts(const ams_params* p) {
   return p->pool_kernel <= 1 && p->seg_delta == 0.f && p->n_segments <= kStepMaxSeg;
 }
 
+// The fused step's mass / EMA / segmentation / quota stages, where the scorer has not done them.
 hipError_t launch_unit_mass(const ams_params* p, const Dims& d, const int32_t* seq_lens, const UnitCuts& uc, const VcInfo& vc,
                             hipStream_t s) {
   if (vc.cuts) return hipSuccess;  // the scorer has done it

@@ -10,8 +10,8 @@
 // in fp32; the ratio in double.  (Sums of 16 keys in fp32 first took 2 % less, 1166 against 1193 us per step and 1299 against
 // 1326, but lose a mean key far below the size of its keys.)  256 units of 32768 keys: 1734 -> 1193 us per step for the key
 // diversity, 1927 -> 1326 for the mean cosines with the softmax partials of the cosines taken where they are formed.  fp32
-// caches, the causal window (whose newest keys go through the tail kernels) and a pinned one-launch path keep the streaming
-// kernels.
+// caches, the causal window (whose sweeps give the newest keys to workgroups of their own) and a pinned one-launch path keep the
+// streaming kernels.
 #include "score_sweep.h"
 
 namespace ams {

@@ -156,10 +156,12 @@ constexpr int kSweepThreads = !BF16 && NB == 4 && HD == 128 ? 2 * kThreads : kTh
 // are seen by every query and run like those of the plain sweeps, which then stop at t_end; the few
 // blocks from t_end on go to one workgroup more per unit, the last ones of the launch, where a (query, key) pair
 // the mask hides is left out.  As launches of their own they took 7 to 16 us each; beside the others they cost nothing in
-// large launches and 1 to 4 us in small ones: us per step 1055 and 1044 (256 units of 32768), 106 and 91 (64 of 4000), 252 and
-// 229 (40 of 30000, 224 queries), 65 and 52 (6 of 1090 with the paper's options, without the reduction's launch as well).  Mixed
+// large launches and 1 to 4 us in small ones: us per step 106 and 91 (64 units of 4000), 252 and 229 (40 of 30000, 224 queries), 65
+// and 52 (6 of 1090 with the paper's options, without the reduction's launch as well), 1055 and 1044 (256 of 32768, no further apart
+// than the runs of one side).  Mixed
 // in with the units' chunks (one of them first in every unit) they break the order of the key stream: 1092, 99, 241; 100 units
 // of 20000 take 320 in two launches, 362 mixed and 298 at the end.
+//
 // Which (unit, chunk) a workgroup of the sweeps takes.  Dense caches: grid x = chunk, grid y = unit.
 // Paged caches keep the rows of a position's KV heads next to each other in a slot, so there the
 // heads of one (layer, sequence, chunk) are given to consecutive workgroups: they run at the same

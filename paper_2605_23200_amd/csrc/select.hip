@@ -190,9 +190,10 @@ __device__ __forceinline__ void top_bin(const int* h, int lane, int& rem, uint32
 }
 
 // ---- Segments longer than the registers hold: the scores are read from memory in every pass ----
-// Bound: one CU reads the scores four to six times and adds every key to its bin in LDS once or twice.  The range of the keys;
-// bins over it (2048 with 1024 threads) until the bin with the last pick holds few keys; those keys into LDS, where the bins are
-// refined down to one key; the picks in ascending order.  Every wave reads a stretch of its own with 16-byte loads, so that its
+// Bound: one CU reads the scores four times, six or seven at most, and adds keys to their bins in LDS in one of these passes or a few.
+// The range of the keys; bins over it until the bin with the last pick holds few keys (1024 threads: 2048 bins, one to three
+// passes; fewer threads: 256 bins, up to four); those keys into LDS, where the bins are refined down to one key (or, where the
+// bin is taken as a whole or its keys are equal, a count of the picks of every stretch); the picks in ascending order.  Every wave reads a stretch of its own with 16-byte loads, so that its
 // counts place its picks and no pass has a barrier inside.  A unit in one segment: 72 us for 32 units of 74913 scores (181 with
 // four radix passes of 4-byte loads and two barriers per 1024 positions of the last one), 42 for 16 of 40000 (98).
 template <int BLOCK>
